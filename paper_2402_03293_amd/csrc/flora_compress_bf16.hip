@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void compress_bf16_kernel(const MatDev* __rest
     auto gen_tile = [&](int buf, int tile) {
         const int jl = 2 * (tid & 15);
         const int q = tid >> 4;
-        const uint64_t j = (uint64_t)tile * kBK + jl;
+        const uint32_t j = (uint32_t)tile * kBK + jl;
         const Quad z0 = normal_quad(seed_lo, seed_hi, j, (uint32_t)(q0 + q), cgen);
         const Quad z1 = normal_quad(seed_lo, seed_hi, j + 1, (uint32_t)(q0 + q), cgen);
 #pragma unroll
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     const int gen_j = NQ * (tid % JG);
     const uint32_t gen_q = (uint32_t)(tid / JG);
     auto gen_tile = [&](int buf, int tile) {
-        const uint64_t j = (uint64_t)tile * kWBK + (uint64_t)gen_j;
+        const uint32_t j = (uint32_t)tile * kWBK + (uint32_t)gen_j;
         uint32_t pk[NQ / 2][4];
 #pragma unroll
         for (int e = 0; e < NQ; e += 2) {

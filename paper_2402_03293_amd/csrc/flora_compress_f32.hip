@@ -189,7 +189,7 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
             if (QT % 256 == 0 || idx < QT) {
                 const int jl = idx % kBK;
                 const int q = idx / kBK;
-                const Quad z = normal_quad(seed_lo, seed_hi, (uint64_t)(j0 + jl), (uint32_t)q, cgen);
+                const Quad z = normal_quad(seed_lo, seed_hi, (uint32_t)(j0 + jl), (uint32_t)q, cgen);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) ldsA[kg][buf][4 * q + e][jl] = z.z[e];
             }

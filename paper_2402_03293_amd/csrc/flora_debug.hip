@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void debug_mfma_kernel(float* sink, int iters)
 __global__ __launch_bounds__(256) void debug_generator_kernel(float* sink, int iters, uint32_t seed)
 {
     const float c = neg2_ln2_over(256);
-    const uint64_t j = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const uint32_t j = blockIdx.x * 256u + threadIdx.x;
     float acc = 0.f;
     for (int i = 0; i < iters; ++i) {
         const Quad z = normal_quad(seed, 17u, j, (uint32_t)i, c);

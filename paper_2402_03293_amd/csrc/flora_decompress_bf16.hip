@@ -46,8 +46,8 @@ __global__ __launch_bounds__(256) void decompress_bf16_kernel(const MatDev* __re
     bf16x8 breg[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-        const Quad z0 = normal_quad(seed_lo, seed_hi, (uint64_t)(jok ? j : 0), (uint32_t)(4 * s + 2 * g), cgen);
-        const Quad z1 = normal_quad(seed_lo, seed_hi, (uint64_t)(jok ? j : 0), (uint32_t)(4 * s + 2 * g + 1), cgen);
+        const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)(jok ? j : 0), (uint32_t)(4 * s + 2 * g), cgen);
+        const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)(jok ? j : 0), (uint32_t)(4 * s + 2 * g + 1), cgen);
         const uint4 pk = make_uint4(pack_bf16x2(z0.z[0], z0.z[1]), pack_bf16x2(z0.z[2], z0.z[3]),
                                     pack_bf16x2(z1.z[0], z1.z[1]), pack_bf16x2(z1.z[2], z1.z[3]));
         breg[s] = __builtin_bit_cast(bf16x8, pk);
@@ -184,8 +184,8 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
         if (j > m - 1) j = m - 1;      // clamped: columns past m are never stored
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            const Quad z0 = normal_quad(seed_lo, seed_hi, (uint64_t)j, (uint32_t)(8 * s + 2 * g), cgen);
-            const Quad z1 = normal_quad(seed_lo, seed_hi, (uint64_t)j, (uint32_t)(8 * s + 2 * g + 1), cgen);
+            const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)j, (uint32_t)(8 * s + 2 * g), cgen);
+            const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)j, (uint32_t)(8 * s + 2 * g + 1), cgen);
             const uint4 pk = make_uint4(pack_bf16x2(z0.z[0], z0.z[1]), pack_bf16x2(z0.z[2], z0.z[3]),
                                         pack_bf16x2(z1.z[0], z1.z[1]), pack_bf16x2(z1.z[2], z1.z[3]));
             areg[jt][s] = __builtin_bit_cast(bf16x8, pk);

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __res
     float breg[H];
 #pragma unroll
     for (int i = 0; i < R / 8; ++i) {
-        const Quad z = normal_quad(seed_lo, seed_hi, (uint64_t)(jok ? j : 0),
+        const Quad z = normal_quad(seed_lo, seed_hi, (uint32_t)(jok ? j : 0),
                                    (uint32_t)(g * (R / 8) + i), cgen);
 #pragma unroll
         for (int e = 0; e < 4; ++e) breg[4 * i + e] = z.z[e];

@@ -90,8 +90,8 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
         }
 #pragma unroll
         for (int e = 0; e < NQ; e += 2) {
-            const Quad z0 = normal_quad(seed_lo, seed_hi, (uint64_t)(j + e), gen_q, cgen);
-            const Quad z1 = normal_quad(seed_lo, seed_hi, (uint64_t)(j + e + 1), gen_q, cgen);
+            const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)(j + e), gen_q, cgen);
+            const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)(j + e + 1), gen_q, cgen);
             float w0 = (SRC == 1) ? rsqrtf(wt[e]) : 1.f, w1 = (SRC == 1) ? rsqrtf(wt[e + 1]) : 1.f;
             w0 = (j + e < t1) ? w0 : 0.f;
             w1 = (j + e + 1 < t1) ? w1 : 0.f;
@@ -280,8 +280,8 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
         uint32_t pk[NC][NQ / 2][4];
 #pragma unroll
         for (int e = 0; e < NQ; e += 2) {
-            const Quad z0 = normal_quad(seed_lo, seed_hi, (uint64_t)(j + e), gen_q, cgen);
-            const Quad z1 = normal_quad(seed_lo, seed_hi, (uint64_t)(j + e + 1), gen_q, cgen);
+            const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)(j + e), gen_q, cgen);
+            const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)(j + e + 1), gen_q, cgen);
             const float m0 = (j + e < t1) ? 1.f : 0.f, m1 = (j + e + 1 < t1) ? 1.f : 0.f;
 #pragma unroll
             for (int i = 0; i < 4; ++i) pk[0][e / 2][i] = pack_bf16x2(m0 * z0.z[i], m1 * z1.z[i]);
@@ -497,8 +497,8 @@ __global__ __launch_bounds__(64 * WAVES) void quadform_kernel(const MatDev* __re
                 } else {
                     // (all lanes generate: rows past the end take the last row's values and are masked below)
                     const long long jr = ok ? row : zn - 1;
-                    const Quad q0 = normal_quad(seed_lo, seed_hi, (uint64_t)jr, (uint32_t)(8 * s + g), cgen);
-                    const Quad q1 = normal_quad(seed_lo, seed_hi, (uint64_t)jr, (uint32_t)(8 * s + 4 + g), cgen);
+                    const Quad q0 = normal_quad(seed_lo, seed_hi, (uint32_t)jr, (uint32_t)(8 * s + g), cgen);
+                    const Quad q1 = normal_quad(seed_lo, seed_hi, (uint32_t)jr, (uint32_t)(8 * s + 4 + g), cgen);
                     const float w = ok ? 1.f : 0.f;
                     lo = v4f{w * q0.z[0], w * q0.z[1], w * q0.z[2], w * q0.z[3]};
                     hi = v4f{w * q1.z[0], w * q1.z[1], w * q1.z[2], w * q1.z[3]};
@@ -621,8 +621,8 @@ __global__ __launch_bounds__(64 * WAVES) void quadform_cols_kernel(const MatDev*
         for (int s = 0; s < S; ++s) {
             // step s = 2 beta + sl holds k1 = 32 beta + 16 sl + 4 g + (0..3) and the same + 8: quads 8 beta + 4 sl + g and + 2
             const uint32_t q0 = (uint32_t)(8 * (s >> 1) + 4 * (s & 1) + g);
-            const Quad a = normal_quad(seed_lo, seed_hi, (uint64_t)jr, q0, cgen);
-            const Quad b = normal_quad(seed_lo, seed_hi, (uint64_t)jr, q0 + 2u, cgen);
+            const Quad a = normal_quad(seed_lo, seed_hi, (uint32_t)jr, q0, cgen);
+            const Quad b = normal_quad(seed_lo, seed_hi, (uint32_t)jr, q0 + 2u, cgen);
             const v4u pk = {pack_bf16x2(w * a.z[0], w * a.z[1]), pack_bf16x2(w * a.z[2], w * a.z[3]),
                             pack_bf16x2(w * b.z[0], w * b.z[1]), pack_bf16x2(w * b.z[2], w * b.z[3])};
             zreg[s] = __builtin_bit_cast(bf16x8, pk);

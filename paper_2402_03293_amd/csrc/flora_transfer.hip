@@ -69,14 +69,14 @@ __global__ __launch_bounds__(256) void transfer_T_kernel(const MatDev* __restric
         // old projection: rows j0.., columns kb*KB1 .. +KB1
         for (int idx = tid; idx < kBJ * (KB1 / 4); idx += 256) {
             const int jl = idx % kBJ, q = idx / kBJ;
-            Quad z = normal_quad(M.seed_lo, M.seed_hi, (uint64_t)(j0 + jl), (uint32_t)(kb * (KB1 / 4) + q), cgen);
+            Quad z = normal_quad(M.seed_lo, M.seed_hi, (uint32_t)(j0 + jl), (uint32_t)(kb * (KB1 / 4) + q), cgen);
             const bool ok = j0 + jl < m;
 #pragma unroll
             for (int i = 0; i < 4; ++i) ldsOld[jl][4 * q + i] = ok ? z.z[i] : 0.f;
         }
         for (int idx = tid; idx < kBJ * (R / 4); idx += 256) {
             const int jl = idx % kBJ, q = idx / kBJ;
-            Quad z = normal_quad(M.seedn_lo, M.seedn_hi, (uint64_t)(j0 + jl), (uint32_t)q, cgen);
+            Quad z = normal_quad(M.seedn_lo, M.seedn_hi, (uint32_t)(j0 + jl), (uint32_t)q, cgen);
             const bool ok = j0 + jl < m;
 #pragma unroll
             for (int i = 0; i < 4; ++i) ldsNew[jl][4 * q + i] = ok ? z.z[i] : 0.f;
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(512) void transfer_T_big_kernel(const MatDev* __res
             const long long j = j0 + jl;
             // (one generator call with selected arguments: lanes of a wave may be on either side)
             const bool isold = q < SLAB / 4;
-            const Quad z = normal_quad(isold ? so_lo : sn_lo, isold ? so_hi : sn_hi, (uint64_t)j,
+            const Quad z = normal_quad(isold ? so_lo : sn_lo, isold ? so_hi : sn_hi, (uint32_t)j,
                                        isold ? qold0 + (uint32_t)q : (uint32_t)(q - SLAB / 4), cgen);
             const bool ok = j < jend;
             const v4f v = {ok ? z.z[0] : 0.f, ok ? z.z[1] : 0.f, ok ? z.z[2] : 0.f, ok ? z.z[3] : 0.f};
