@@ -80,6 +80,7 @@ struct Plan {
     std::vector<WorkItem> items;        // main work table
     std::vector<WorkItem> items2;       // transfer: state <- state T table
     int mt = 1;                         // bf16 compress: rows per workgroup = 128 * mt
+    int any_rows = 0;                   // bf16 compress: some rows of G do not start on 16-byte boundaries
     int vec = 0;                        // decompress: the 16-byte-per-lane bf16 kernel (256-column workgroups)
     int kc = 0;                         // fp32 compress: columns per part (0: whole rows)
     size_t ws_floats = 0;               // compress: floats of partial products (shared-column mode)
@@ -223,16 +224,23 @@ void build_compress_f32_items(Plan& p)
 void build_compress_bf16_items(Plan& p)
 {
     // The wide kernel (512, 256 or 128 rows per workgroup, rank slices of 128) regenerates A least
-    // often; it needs 16-byte aligned rows of G.  A launch should give the chip at least one
+    // often.  A launch should give the chip at least one
     // and a half workgroups per compute unit: if whole row blocks do not, the columns of a row
     // block are shared between up to a few workgroups (partial products, combined by the last
     // one to finish), then the row blocks are halved.  Sharing costs nparts * rows * r * 8
     // bytes of extra traffic per block, so parts stay at 768 columns or more.
-    // Unaligned sets take the narrow kernel with the largest rows-per-workgroup (128 * mt)
-    // that still gives the chip two workgroups per compute unit.
-    bool aligned = (p.variant & 3) == 2;      // fp32 gradients take the narrow kernel
-    for (int l = 0; l < p.count; ++l)   // 16-byte aligned rows, 32-bit byte offsets within 64 rows
-        aligned = aligned && (p.host_mats[l].m % 8) == 0 && p.host_mats[l].m <= (1LL << 23);
+    // fp32 gradients, and sets with some row of G that does not start on a 16-byte boundary, take its
+    // ANY form (512 rows only with bf16 at r = 64: its operand copies, and fp32 tiles, need the registers).
+    // Rows too long for 32-bit byte offsets within 64 rows take the narrow kernel with the largest
+    // rows-per-workgroup (128 * mt) that still gives the chip two workgroups per compute unit.
+    const bool f32 = (p.variant & 3) == 3;
+    bool fits = true, whole_rows = !f32;
+    for (int l = 0; l < p.count; ++l) {
+        fits = fits && p.host_mats[l].m <= (f32 ? 1LL << 22 : 1LL << 23);
+        whole_rows = whole_rows && (p.host_mats[l].m % 8) == 0;
+    }
+    p.any_rows = !whole_rows;
+    const bool allow512 = whole_rows || (p.r == 64 && !f32);
     const int wide_slice = (p.r == 64) ? 64 : 128;
     auto wide_wgs = [&](int rows, long long kc) {
         long long wgs = 0;
@@ -244,10 +252,11 @@ void build_compress_bf16_items(Plan& p)
     };
     int mt = 4;
     long long kc = 0;       // columns per part (0: whole rows)
-    if (g_tune.compress_bf16_mt && (aligned || g_tune.compress_bf16_mt <= 4)) {
+    if (g_tune.compress_bf16_mt && (fits || g_tune.compress_bf16_mt <= 4)) {
         mt = g_tune.compress_bf16_mt;
+        if (mt == 8 && !allow512) mt = 16;
         kc = g_tune.compress_splitk_cols;
-    } else if (aligned) {
+    } else if (fits) {
         const int rows_opt[2] = {512, 256};
         const long long kc_opt[3] = {0, 1536, 768};
         mt = 16; kc = 768;
@@ -267,7 +276,7 @@ void build_compress_bf16_items(Plan& p)
             }
             return 2 * longest <= 3 * std::max<long long>(1, total / 256);
         };
-        for (int ri = 0; ri < 2 && !found; ++ri)
+        for (int ri = allow512 ? 0 : 1; ri < 2 && !found; ++ri)
             for (int ki = 0; ki < 3 && !found; ++ki)
                 if (wide_wgs(rows_opt[ri], kc_opt[ki]) >= 384 && (kc_opt[ki] > 0 || balanced(rows_opt[ri], 0))) {
                     mt = rows_opt[ri] == 512 ? 8 : 16;
@@ -290,7 +299,6 @@ void build_compress_bf16_items(Plan& p)
             wgs += (p.host_mats[l].n + 128 * mt - 1) / (128 * mt) * (p.r / kCompressBf16Slice);
         if (wgs >= 512) break;
     }
-    if (mt >= 8 && !aligned) mt = 4;
     const bool wide = mt >= 8;
     if (!wide) kc = 0;
     p.mt = mt;
@@ -986,7 +994,7 @@ static int compress_chunk(const flora_matrix_t* mats, int count, int r, flora_dt
         uint32_t* counters = p->d_work ? reinterpret_cast<uint32_t*>(static_cast<char*>(p->d_work) +
                                                                    round_up(p->ws_floats * 4, 256))
                                        : nullptr;
-        FLORA_HIP(launch_compress_bf16_mt(dm, di, (int)p->items.size(), sa, r, p->mt, variant == 3, map, a, b,
+        FLORA_HIP(launch_compress_bf16_mt(dm, di, (int)p->items.size(), sa, r, p->mt, variant == 3, p->any_rows, map, a, b,
                                           partials, counters, s));
     }
     else {

@@ -204,8 +204,9 @@ __global__ __launch_bounds__(256) void compress_bf16_kernel(const MatDev* __rest
 
 // ---------------------------------------------------------------------------
 // Wide variant: 8 waves own 512 (or 256, 128) rows x RS rank columns (RS = 128, or 64 at
-// r = 64) and sweep m in tiles of 64 columns.  It needs rows of G that start on
-// 16-byte boundaries (m % 8 == 0); the kernel above remains for everything else.
+// r = 64) and sweep m in tiles of 64 columns.  It takes bf16 gradients whose rows start on 16-byte
+// boundaries (m % 8 == 0), bf16 gradients with rows of any length (ANY) and fp32 gradients (always
+// ANY); the kernel above remains for rows too long for 32-bit offsets.
 //
 // What bounds this kernel is, in this order, how fast G reaches the registers
 // (it is read once from HBM and r / RS - 1 more times from L2), the vector ALU
@@ -232,8 +233,9 @@ constexpr int kWBK = 64;             // columns of G per tile
 constexpr int kWLda = kWBK + 8;      // padded LDS row (bf16 elements): 144 bytes
 
 // per wave: CT 16-wide column tiles (RS = 16 CT), RT 16-row tiles; MAP 1: input squared;
-// ONCE: r = RS, a single rank slice, so the launch reads G exactly once
-template <int CT, int RT, int MAP, bool ONCE>
+// ONCE: r = RS, a single rank slice, so the launch reads G exactly once; GT: uint16_t (bf16) or float;
+// ANY: rows of G start anywhere their element size allows
+template <int CT, int RT, int MAP, bool ONCE, typename GT, bool ANY>
 __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* __restrict__ mats,
                                                                  const WorkItem* __restrict__ items,
                                                                  const SeedArgs seeds, int R, float a, float b,
@@ -248,6 +250,11 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     constexpr int LDE = RS + 4;      // padded row of the epilogue staging (floats)
     constexpr int kABytes = 2 * RS * kWLda * 2;
     constexpr int kEBytes = 8 * 16 * LDE * 4;
+    constexpr bool kF32 = sizeof(GT) == 4;
+    static_assert(ANY || !kF32, "fp32 gradients come with ANY");
+    constexpr int ES = (int)sizeof(GT);
+    constexpr int NL = kF32 ? 4 : 2;         // 16-byte loads per 16 rows x 64 columns and lane
+    constexpr bool kShift = ANY && !kF32;    // an odd row length puts every other row at half a dword
     __shared__ uint32_t lds_flag;
     __shared__ __attribute__((aligned(16))) unsigned char lds_raw[kABytes > kEBytes ? kABytes : kEBytes];
     typedef uint16_t (*lds_a_t)[RS][kWLda];
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     const MatDev& M = mats[it.mat];
     const long long n = M.n, m = M.m;
     const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
-    const uint16_t* __restrict__ G = reinterpret_cast<const uint16_t*>(M.grad);
+    const GT* __restrict__ G = reinterpret_cast<const GT*>(M.grad);
     float* __restrict__ state = M.state;
 
     const int tid = threadIdx.x;
@@ -265,20 +272,22 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
     const float cgen = neg2_ln2_over(R);
-    // this workgroup's share of the columns: tiles [tile0, ntiles)
+    // this workgroup's share of the columns: tiles [tile0, tile0 + ntiles)
     const long long col_end = (it.col1 < m) ? (long long)it.col1 : m;
     const int tile0 = it.col0 / kWBK;
-    const int ntiles = (int)((col_end + kWBK - 1) / kWBK);
+    const int ntiles = (int)((col_end + kWBK - 1) / kWBK) - tile0;
     const uint32_t q0 = (uint32_t)(it.slice * (RS / 4));   // first Philox quad of this rank slice
     const long long row_end = ((long long)it.row0 + it.rows < n) ? (long long)it.row0 + it.rows : n;
     const long long wave_row0 = (long long)it.row0 + wave * WR;
 
-    // One buffer resource for the WR rows of this wave, covering exactly its valid rows:
-    // rows past the end and (through kOob) columns past m read as zero.
+    // One buffer resource for the WR rows of this wave, covering exactly its valid rows (ANY: up to
+    // the dword that holds the last element): rows past the end and (through kOob) columns past m
+    // read as zero.
     long long valid = row_end - wave_row0;
     valid = valid < 0 ? 0 : (valid > WR ? WR : valid);
-    const rsrc_t rs = make_rsrc(G + (wave_row0 < n ? wave_row0 : 0) * m, valid * m * 2);
-    // Chunk (s, g) of a tile holds columns j0 + 32 s + 8 g .. + 7; m % 8 == 0, so a chunk is
+    const long long gbytes = valid * m * ES;
+    const rsrc_t rs = make_rsrc(G + (wave_row0 < n ? wave_row0 : 0) * m, kShift ? (gbytes + 3) / 4 * 4 : gbytes);
+    // bf16: chunk (s, g) of a tile holds columns j0 + 32 s + 8 g .. + 7; m % 8 == 0, so a chunk is
     // all in or all out.  Out-of-range chunks are pointed at kOob and fetch nothing.
     //
     // Two ways of fetching a tile.  By halves (two rank slices): lane (li, g) loads what operand
@@ -293,44 +302,118 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     // two rank slices, where every byte passes the load path twice, that costs more than the
     // whole lines gain (workload 4: 2.70 against 2.31 ms), with one it wins (workload 3: 54
     // against 64 us).
+    //
+    // fp32 gradients: the same rows with four columns per lane and load, twice the loads.  The
+    // contraction order over columns is free, so operand (rt, s) of lane (li, g) takes columns
+    // 32 s + 4 g .. + 3 and 32 s + 16 + 4 g .. + 3 (two loads of 64 contiguous bytes per row, or of whole
+    // lines as above), rounded to bf16 (nearest even) when the tile's turn comes, and A lies in LDS
+    // in that order.
+    //
+    // ANY: dword-aligned 16-byte loads.  With bf16 and m odd, odd rows start in the middle of a dword:
+    // they are fetched from the dword their chunk begins in, together with the fifth dword that holds
+    // the chunk's last element, and shifted into place (v_alignbit_b32) when the tile's turn comes.  A
+    // last tile that is not whole is taken first, dword by dword, with what lies past the last
+    // column masked: the loop then has whole tiles only.
     constexpr bool kLines = ONCE;
+    struct Tile {
+        v4u w[RT][NL];
+        uint32_t x[kShift ? RT : 1][kShift ? NL : 1];    // fifth dword of an odd row's chunk
+    };
+    const bool odd_row = kShift && (m & 1) && (li & 1);  // (row numbers within a wave differ from li by a multiple of 8)
+    const uint32_t lane_col = kLines ? (kF32 ? 4u * (uint32_t)g + 16u * (uint32_t)(li >> 3) : 8u * (uint32_t)(g + 4 * (li >> 3)))
+                                     : (kF32 ? 4u : 8u) * (uint32_t)g;
     uint32_t lane_off[2 * RT];
 #pragma unroll
-    for (int x = 0; x < 2 * RT; ++x)
-        lane_off[x] = kLines ? ((uint32_t)(8 * x + (li & 7)) * (uint32_t)m + 8u * (uint32_t)(g + 4 * (li >> 3))) * 2u
-                             : ((uint32_t)(16 * (x >> 1) + li) * (uint32_t)m + 8u * (uint32_t)g) * 2u;
-    auto load_half = [&](v4u (&dst)[RT][2], int tile, int s) {
-        const uint32_t col = (uint32_t)tile * kWBK + 32u * (uint32_t)s + 8u * (uint32_t)g;
-        const bool ok = col < (uint32_t)col_end;
-        const uint32_t coff = ((uint32_t)tile * kWBK + 32u * (uint32_t)s) * 2u;
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) dst[rt][s] = buf_load_u4<ONCE>(rs, ok ? lane_off[2 * rt] + coff : kOob);
+    for (int x = 0; x < 2 * RT; ++x) {
+        const uint32_t row = kLines ? (uint32_t)(8 * x + (li & 7)) : (uint32_t)(16 * (x >> 1) + li);
+        lane_off[x] = (row * (uint32_t)m + lane_col) * ES - (odd_row ? 2u : 0u);
+    }
+    // Load k < NL of row tile rt: its address within the rows (index into lane_off) and its first
+    // column within the tile, apart from the lane's own part of either.
+    auto load_x = [](int rt, int k) { return kLines ? 2 * rt + (kF32 ? (k & 1) : k) : 2 * rt; };
+    auto load_col = [](int k) { return kLines ? (kF32 ? 32u * (uint32_t)(k >> 1) : 0u) : (kF32 ? 16u : 32u) * (uint32_t)k; };
+    auto load_one = [&](Tile& t, int tile, int rt, int k) {
+        const uint32_t col0 = (uint32_t)tile * kWBK + load_col(k);
+        const bool ok = col0 + lane_col < (uint32_t)col_end;
+        const uint32_t off = ok ? lane_off[load_x(rt, k)] + col0 * ES : kOob;
+        t.w[rt][k] = buf_load_u4<ONCE>(rs, off);
+        if (kShift) t.x[rt][k] = __float_as_uint(buf_load_f(rs, odd_row ? off + 16u : kOob));
     };
-    auto load_tile = [&](v4u (&dst)[RT][2], int tile) {
+    auto load_half = [&](Tile& t, int tile, int s) {
+#pragma unroll
+        for (int k = s * (NL / 2); k < (s + 1) * (NL / 2); ++k)
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) load_one(t, tile, rt, k);
+    };
+    auto load_tile = [&](Tile& t, int tile) {
         if (!kLines) {
-            load_half(dst, tile, 0);
-            load_half(dst, tile, 1);
+            load_half(t, tile, 0);
+            load_half(t, tile, 1);
             return;
         }
-        const uint32_t col = (uint32_t)tile * kWBK + 8u * (uint32_t)(g + 4 * (li >> 3));
-        const bool ok = col < (uint32_t)col_end;
-        const uint32_t coff = (uint32_t)tile * kWBK * 2u;
 #pragma unroll
-        for (int x = 0; x < 2 * RT; ++x) dst[x >> 1][x & 1] = buf_load_u4<ONCE>(rs, ok ? lane_off[x] + coff : kOob);
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int k = 0; k < NL; ++k) load_one(t, tile, rt, k);
     };
-    auto settle_tile = [&](v4u (&t)[RT][2]) {
+    // The columns of dword d of load k: kPer of them from dword_col on (an odd row's first dword begins
+    // one column before its chunk, which may be column -1).
+    constexpr int kPer = kF32 ? 1 : 2;
+    const int cend = (int)col_end;
+    auto dword_col = [&](int tile, int k, int d) {
+        return tile * kWBK + (int)load_col(k) + (int)lane_col + kPer * d - (odd_row ? 1 : 0);
+    };
+    auto load_part = [&](Tile& t, int tile) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int k = 0; k < NL; ++k) {
+                const uint32_t off = lane_off[load_x(rt, k)] + ((uint32_t)tile * kWBK + load_col(k)) * ES;
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    t.w[rt][k][d] = __float_as_uint(buf_load_f(rs, dword_col(tile, k, d) < cend ? off + 4u * d : kOob));
+                if (kShift)
+                    t.x[rt][k] = __float_as_uint(buf_load_f(rs, odd_row && dword_col(tile, k, 4) < cend ? off + 16u : kOob));
+            }
+    };
+    auto mask_part = [&](Tile& t, int tile) {
+        if (!kShift) return;             // an fp32 dword is one column: in or out as a whole
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int k = 0; k < NL; ++k) {
+#pragma unroll
+                for (int d = 0; d < 4; ++d)
+                    if (dword_col(tile, k, d) + 1 >= cend) t.w[rt][k][d] &= 0xffffu;
+                if (dword_col(tile, k, 4) + 1 >= cend) t.x[rt][k] &= 0xffffu;
+            }
+    };
+    auto settle_tile = [&](Tile& t) {
+        if (kShift) {
+            const uint32_t sh = odd_row ? 16u : 0u;
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int k = 0; k < NL; ++k) {
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) t.w[rt][k][d] = __builtin_amdgcn_alignbit(t.w[rt][k][d + 1], t.w[rt][k][d], sh);
+                    t.w[rt][k][3] = __builtin_amdgcn_alignbit(t.x[rt][k], t.w[rt][k][3], sh);
+                }
+        }
         if (!kLines) return;
         constexpr int kRor8 = 0x128;          // DPP row_ror:8: lane li of a row of 16 reads lane li ^ 8
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t lo = t[rt][0][c], hi = t[rt][1][c];
-                // s = 0: lanes li >= 8 (banks 2, 3) take load 2 rt + 1's lanes li - 8
-                t[rt][0][c] = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)hi, kRor8, 0xf, 0xc, false);
-                // s = 1: lanes li < 8 (banks 0, 1) take load 2 rt's lanes li + 8
-                t[rt][1][c] = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)lo, kRor8, 0xf, 0x3, false);
-            }
+            for (int k = 0; k < NL; k += 2)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const uint32_t lo = t.w[rt][k][c], hi = t.w[rt][k + 1][c];
+                    // lanes li >= 8 (banks 2, 3) of the first take the second's lanes li - 8
+                    t.w[rt][k][c] = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)hi, kRor8, 0xf, 0xc, false);
+                    // lanes li < 8 (banks 0, 1) of the second take the first's lanes li + 8
+                    t.w[rt][k + 1][c] = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)lo, kRor8, 0xf, 0x3, false);
+                }
     };
 
     // 64 x RS normals per tile = 16 RS quads, NQ per thread: thread p takes quad index
@@ -340,6 +423,8 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     // are needed elsewhere); the scheduling barriers keep the compiler from mixing them.
     const int gen_j = NQ * (tid % JG);
     const uint32_t gen_q = (uint32_t)(tid / JG);
+    // where column gen_j lies in an LDS row: in order, or (fp32) in the order the operands contract
+    const int gen_pos = kF32 ? (gen_j & 32) + 8 * ((gen_j >> 2) & 3) + 4 * ((gen_j >> 4) & 1) + (gen_j & 3) : gen_j;
     auto gen_tile = [&](int buf, int tile) {
         const uint32_t j = (uint32_t)tile * kWBK + (uint32_t)gen_j;
         uint32_t pk[NQ / 2][4];
@@ -354,7 +439,7 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            uint16_t* dst = &ldsA[buf][4 * gen_q + i][gen_j];
+            uint16_t* dst = &ldsA[buf][4 * gen_q + i][gen_pos];
             if (NQ == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(pk[0][i], pk[NQ / 2 - 1][i]);
             else *reinterpret_cast<uint32_t*>(dst) = pk[0][i];
         }
@@ -367,20 +452,45 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // The operands of half s (32 columns) of a settled tile, as bf16; MAP 1: squared in fp32 first.
+    auto operands = [&](const Tile& t, int s, v4u (&op)[RT]) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            if constexpr (kF32) {
+                v4f f0 = __builtin_bit_cast(v4f, t.w[rt][NL / 2 * s]), f1 = __builtin_bit_cast(v4f, t.w[rt][NL / 2 * s + NL / 4]);
+                if (MAP == 1) { f0 = f0 * f0; f1 = f1 * f1; }
+                op[rt] = v4u{pack_bf16x2(f0.x, f0.y), pack_bf16x2(f0.z, f0.w), pack_bf16x2(f1.x, f1.y), pack_bf16x2(f1.z, f1.w)};
+            } else {
+                const v4u w = t.w[rt][s];
+                op[rt] = MAP == 1 ? v4u{square_bf16x2(w.x), square_bf16x2(w.y), square_bf16x2(w.z), square_bf16x2(w.w)} : w;
+            }
+        }
+    };
+
     // The tile in `gt` / LDS buffer `buf` goes through the matrix cores, one half (32
     // columns) at a time; the B operand of column tile ct + 1 is fetched from LDS while tile
     // ct multiplies.  As soon as the MFMAs of a half are issued its registers are refilled
-    // with the tile two steps ahead.
-    auto mfma_tile = [&](v4u (&gt)[RT][2], int buf, int tile) {
+    // with the tile two steps ahead.  With ANY the operands are copies (shifted, or rounded to
+    // bf16), so the refill goes out before the MFMAs.
+    auto mfma_tile = [&](Tile& gt, int buf, int next) {
         settle_tile(gt);
+        v4u op[kShift ? 2 : 1][RT];
+        if (kShift) {
+            operands(gt, 0, op[0]);
+            operands(gt, 1, op[kShift ? 1 : 0]);
+            __builtin_amdgcn_sched_barrier(0);
+            load_tile(gt, next);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            if (MAP == 1) {      // the statistic's term: G squared in fp32, rounded back to bf16
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-                    gt[rt][s] = v4u{square_bf16x2(gt[rt][s].x), square_bf16x2(gt[rt][s].y),
-                                    square_bf16x2(gt[rt][s].z), square_bf16x2(gt[rt][s].w)};
+            if (!kShift) operands(gt, s, op[0]);
+            if (kF32) {       // (loads 2 s and 2 s + 1 are half s, by lines as well)
+                __builtin_amdgcn_sched_barrier(0);
+                load_half(gt, next, s);
+                __builtin_amdgcn_sched_barrier(0);
             }
+            const v4u (&o)[RT] = op[kShift ? s : 0];
             bf16x8 bv = *reinterpret_cast<const bf16x8*>(&ldsA[buf][li][32 * s + 8 * g]);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
@@ -388,13 +498,14 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
                 if (ct + 1 < CT) bn = *reinterpret_cast<const bf16x8*>(&ldsA[buf][16 * (ct + 1) + li][32 * s + 8 * g]);
 #pragma unroll
                 for (int rt = 0; rt < RT; ++rt)
-                    acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, gt[rt][s]), bv,
-                                                                          acc[rt][ct], 0, 0, 0);
+                    acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, o[rt]), bv, acc[rt][ct], 0, 0, 0);
                 bv = bn;
             }
             __builtin_amdgcn_sched_barrier(0);
-            if (!kLines) load_half(gt, tile + 2, s);
-            else if (s == 1) load_tile(gt, tile + 2);
+            if (!ANY) {
+                if (!kLines) load_half(gt, next, s);
+                else if (s == 1) load_tile(gt, next);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -405,27 +516,33 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     // after barrier t, into the buffer tile t has just left, while the late waves already
     // multiply tile t + 1.  Either way a share of tile t + 1 is complete before barrier t and
     // overwrites a buffer whose last readers passed barrier t - 1.  The accumulators are
-    // touched by one code path only.
+    // touched by one code path only.  (Tiles are counted from the one taken first: the last one
+    // where that is not whole, see above, else tile0.)
     const bool early = wave < 4;
-    auto gen_if = [&](bool mine, int buf, int tile) {
-        if (mine && tile < ntiles) gen_tile(buf, tile);
+    const bool part_first = ANY && (col_end % kWBK) != 0;
+    const int tbase = tile0 - (part_first ? 1 : 0);           // tile number t > 0 is tbase + t
+    const int tfirst = part_first ? tile0 + ntiles - 1 : tile0;
+    auto gen_if = [&](bool mine, int buf, int t) {
+        if (mine && t < ntiles) gen_tile(buf, tbase + t);
     };
 
-    v4u gx[RT][2], gy[RT][2];
-    load_tile(gx, tile0);
-    load_tile(gy, tile0 + 1);
-    gen_tile(0, tile0);
-    gen_if(early, 1, tile0 + 1);
+    Tile gx, gy;
+    if (part_first) load_part(gx, tfirst);
+    else load_tile(gx, tfirst);
+    load_tile(gy, tbase + 1);
+    gen_tile(0, tfirst);
+    gen_if(early, 1, 1);
+    if (part_first) mask_part(gx, tfirst);
     __syncthreads();
-    for (int tile = tile0; tile < ntiles; tile += 2) {
-        mfma_tile(gx, 0, tile);
-        gen_if(!early, 1, tile + 1);
+    for (int t = 0; t < ntiles; t += 2) {
+        mfma_tile(gx, 0, tbase + t + 2);
+        gen_if(!early, 1, t + 1);
         __syncthreads();
-        gen_if(early, 0, tile + 2);
-        if (tile + 1 < ntiles) mfma_tile(gy, 1, tile + 1);     // uniform over the workgroup
-        gen_if(!early, 0, tile + 2);
+        gen_if(early, 0, t + 2);
+        if (t + 1 < ntiles) mfma_tile(gy, 1, tbase + t + 3);     // uniform over the workgroup
+        gen_if(!early, 0, t + 2);
         __syncthreads();
-        gen_if(early, 1, tile + 3);
+        gen_if(early, 1, t + 3);
     }
     __syncthreads();   // the staging area below overlays the A buffers
 
@@ -552,24 +669,35 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
 
 namespace {
 
-template <int MAP>
+template <int MAP, typename GT, bool ANY>
 hipError_t launch_wide(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, int r, int mt,
                        float a, float b, float* partials, uint32_t* counters, hipStream_t s)
 {
     const dim3 grid((unsigned)nitems), block(512);
+#define FLORA_WIDE(CT, RT, ONCE) \
+    hipLaunchKernelGGL((compress_bf16_wide_kernel<CT, RT, MAP, ONCE, GT, ANY>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters)
     if (mt == 32) {
-        if (r == 64) hipLaunchKernelGGL((compress_bf16_wide_kernel<4, 1, MAP, true>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
-        else if (r == 128) hipLaunchKernelGGL((compress_bf16_wide_kernel<8, 1, MAP, true>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
-        else hipLaunchKernelGGL((compress_bf16_wide_kernel<8, 1, MAP, false>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
-    } else if (mt == 8) {
-        if (r == 64) hipLaunchKernelGGL((compress_bf16_wide_kernel<4, 4, MAP, true>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
-        else if (r == 128) hipLaunchKernelGGL((compress_bf16_wide_kernel<8, 4, MAP, true>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
-        else hipLaunchKernelGGL((compress_bf16_wide_kernel<8, 4, MAP, false>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
+        if (r == 64) FLORA_WIDE(4, 1, true);
+        else if (r == 128) FLORA_WIDE(8, 1, true);
+        else FLORA_WIDE(8, 1, false);
+    } else if (mt == 16) {
+        if (r == 64) FLORA_WIDE(4, 2, true);
+        else if (r == 128) FLORA_WIDE(8, 2, true);
+        else FLORA_WIDE(8, 2, false);
     } else {
-        if (r == 64) hipLaunchKernelGGL((compress_bf16_wide_kernel<4, 2, MAP, true>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
-        else if (r == 128) hipLaunchKernelGGL((compress_bf16_wide_kernel<8, 2, MAP, true>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
-        else hipLaunchKernelGGL((compress_bf16_wide_kernel<8, 2, MAP, false>), grid, block, 0, s, mats, items, seeds, r, a, b, partials, counters);
+        // (with operand copies, or fp32 tiles, 512 rows fit in the registers at most at r = 64)
+        bool launched = false;
+        if constexpr (sizeof(GT) == 2)
+            if (r == 64) { FLORA_WIDE(4, 4, true); launched = true; }
+        if constexpr (!ANY)
+            if (r != 64) {
+                if (r == 128) FLORA_WIDE(8, 4, true);
+                else FLORA_WIDE(8, 4, false);
+                launched = true;
+            }
+        if (!launched) return hipErrorInvalidValue;
     }
+#undef FLORA_WIDE
     return hipGetLastError();
 }
 
@@ -599,19 +727,26 @@ hipError_t launch_narrow(const MatDev* mats, const WorkItem* items, int nitems, 
 }  // namespace
 
 // All items of one launch share one MT (rows per workgroup = 128 * MT; 8, 16 and 32 select the wide
-// kernel), chosen by the host.  partials / counters: workspace of the wide kernel's shared-column
-// mode (may be null when no item has nparts > 1).
+// kernel), chosen by the host.  any_rows: some matrix has rows of G that do not start on 16-byte
+// boundaries.  partials / counters: workspace of the wide kernel's shared-column mode (may be null
+// when no item has nparts > 1).
 hipError_t launch_compress_bf16_mt(const MatDev* mats, const WorkItem* items, int nitems,
-                                   const SeedArgs& seeds, int r, int mt, int grad_is_f32, int map, float a, float b,
+                                   const SeedArgs& seeds, int r, int mt, int grad_is_f32, int any_rows, int map, float a, float b,
                                    float* partials, uint32_t* counters, hipStream_t s)
 {
     if (nitems == 0) return hipSuccess;
     if (r != 64 && r != 128 && r != 256) return hipErrorInvalidValue;
-    if (grad_is_f32 && mt > 4) return hipErrorInvalidValue;   // fp32 gradients: first kernel only
     if (map != 0 && map != 1) return hipErrorInvalidValue;
-    if (mt == 8 || mt == 16 || mt == 32)     // wide kernel: 512 (8), 256 (16) or 128 (32) rows per workgroup, rank slices of 128 (64 at r = 64)
-        return (map == 1) ? launch_wide<1>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
-                          : launch_wide<0>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
+    if (mt == 8 || mt == 16 || mt == 32) {   // wide kernel: 512 (8), 256 (16) or 128 (32) rows per workgroup, rank slices of 128 (64 at r = 64)
+        if (grad_is_f32)
+            return (map == 1) ? launch_wide<1, float, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
+                              : launch_wide<0, float, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
+        if (any_rows)
+            return (map == 1) ? launch_wide<1, uint16_t, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
+                              : launch_wide<0, uint16_t, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
+        return (map == 1) ? launch_wide<1, uint16_t, false>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
+                          : launch_wide<0, uint16_t, false>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
+    }
     const dim3 grid((unsigned)nitems), block(256);
     return (map == 1) ? launch_narrow<1>(mats, items, nitems, seeds, r, mt, grad_is_f32, a, b, grid, block, s)
                       : launch_narrow<0>(mats, items, nitems, seeds, r, mt, grad_is_f32, a, b, grid, block, s);

@@ -188,6 +188,39 @@ def test_compress_bf16_every_launch_shape(n, m, r, mt):
     assert rows.max() < TOL_BF16, (int(rows.argmax()), float(rows.max()))
 
 
+# rows of G that start anywhere (odd widths, widths that are no multiple of 8, fp32 gradients) in the
+# wide kernel: widths around a tile of 64 columns and around the pieces of a load, row counts around a
+# wave's and a workgroup's, whole rows and shared columns.  The matrix lies between NaNs: whatever a
+# load fetches beside its row must not reach the result.  Bar: one rounded operand (A; with fp32
+# gradients G is compared as the kernel rounds it), about 2^-9 / sqrt(3) = 1.1e-3 on a large matrix;
+# the smallest have a handful of terms per entry, hence 6e-3 as for the other launch shapes.
+@pytest.mark.parametrize("mt,kc", [(8, 0), (16, 64), (32, 0), (32, 192)])
+@pytest.mark.parametrize("gdt", ["f32", "bf16"])
+@pytest.mark.parametrize("n,m,r", [(33, 1, 64), (130, 7, 128), (257, 63, 256), (97, 65, 64), (513, 127, 128), (31, 66, 256),
+                                   (300, 130, 64), (129, 333, 256), (1030, 961, 64), (64, 1283, 128)])
+def test_compress_bf16_rows_that_start_anywhere(n, m, r, gdt, mt, kc):
+    seed = 2600 + n + m + r
+    dt = torch.float32 if gdt == "f32" else torch.bfloat16
+    buf = torch.full((n * m + 128,), float("nan"), device=DEV, dtype=dt)
+    G = buf[64:64 + n * m].view(n, m)
+    G.copy_(rand((n, m), seed, dt))
+    st = torch.zeros((n, r), device=DEV)
+    mats = flora.matrices([(n, m)], grads=[G], states=[st], seeds=[seed])
+    ref = oracle.compress(to64(G.to(torch.bfloat16)), r, seed)
+    flora.set_tuning("compress_bf16_mt", mt)
+    flora.set_tuning("compress_splitk_cols", kc)
+    try:
+        for step in range(2):                     # (the arrival counters must be back at zero)
+            flora.compress(mats, r, flora.F32 if gdt == "f32" else flora.BF16, 0.0, 1.0)
+            sync()
+            assert rel_fro(to64(st), ref) < 6e-3
+            rows = np.linalg.norm(to64(st) - ref, axis=1) / np.linalg.norm(ref, axis=1)
+            assert rows.max() < TOL_BF16, (int(rows.argmax()), float(rows.max()))
+    finally:
+        flora.set_tuning("compress_bf16_mt", 0)
+        flora.set_tuning("compress_splitk_cols", 0)
+
+
 # the wide kernel with the columns of a row block shared between workgroups (partial products
 # combined by the last workgroup to arrive): several parts, ragged last part, two launches in a
 # row on the same descriptor set (the arrival counters must be back at zero), grouped matrices
