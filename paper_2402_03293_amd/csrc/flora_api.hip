@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <unordered_map>
 #include <vector>
@@ -80,6 +81,7 @@ struct Plan {
     std::vector<WorkItem> items;        // main work table
     std::vector<WorkItem> items2;       // transfer: state <- state T table
     int mt = 1;                         // bf16 compress: rows per workgroup = 128 * mt
+    int combine = 0;                    // bf16 compress: shared columns are added by a launch of their own
     int any_rows = 0;                   // bf16 compress: some rows of G do not start on 16-byte boundaries
     int vec = 0;                        // decompress: the 16-byte-per-lane bf16 kernel (256-column workgroups)
     int kc = 0;                         // fp32 compress: columns per part (0: whole rows)
@@ -134,6 +136,7 @@ struct Tuning {
     int compress_bf16_mt = 0;       // bf16 compress: rows per workgroup / 128: 1, 2 or 4; wide kernel: 8, 16, 32
     int compress_f32_mt = 0;        // fp32 compress: rows per workgroup / 64: 1 or 2
     int compress_splitk_cols = 0;   // wide bf16 compress: columns per part when a row block's columns are shared
+    int compress_combine = 0;       // wide bf16 compress, shared columns: 0 choose, 1 added by the last to arrive, 2 by a launch
     int decompress_rows = 0;        // decompress / update: rows per workgroup, a multiple of 32
     int decompress_vec = -1;        // bf16 decompress: -1 choose, 0 scalar kernel, 1 vector kernel when aligned
     int update_wpolicy = 0;         // update passes: 0 choose; 1 + (bit 0 stream reads of W, bit 1 stream writes)
@@ -221,18 +224,103 @@ void build_compress_f32_items(Plan& p)
     }
 }
 
+// Launch shape of the wide bf16 compress kernel: rows per workgroup (mt 8, 16, 32: 512, 256, 128), columns
+// per workgroup (kc; 0: whole rows) and, where the columns of a row block are shared, how the parts are
+// added (by the last workgroup to arrive, or by a launch of their own).
+struct WideShape {
+    int mt = 16;
+    long long kc = 0;
+    int combine = 0;
+};
+
+// Chosen by the time, in microseconds, that each shape is expected to take.  A workgroup sweeps its columns
+// 64 at a time; per such tile
+//   alone on its compute unit it needs 3.2 us per 64 KB of G (it waits for loads),
+//   with its compute unit full it takes 0.79 us for the generator (64 x 128 entries of A) and 1.6 us per
+//   64 KB (a second rank slice finds G in L2: 0.86 of that), plus about two tiles' worth to start and
+//   end a workgroup;
+// rows that start anywhere count their bytes 2.4 times (a second load per piece of an odd row, and pieces
+// that straddle lines).  The launch ends with the longest workgroup or with the fullest compute
+// unit.  Shared columns cost, added by the last to arrive, 1.5 us + 0.87 us per part of 128 x 128 it reads
+// + 0.14 us per MB of partial products, or, by a launch of their own, 1.3 us + 0.38 us per MB.
+// Fitted to 2772 measured launches (126 sets: 1 to 96 matrices of GPT-2, GPT-2 XL and T5-3B shapes and
+// small ones, r = 64 / 128 / 256, bf16 rows aligned and not, fp32): the shape chosen is 1.017 times the
+// best one's time in the geometric mean (1.15 at worst), where fixed thresholds on the number of
+// workgroups were at 1.21 (1.66): one 1600 x 6400 matrix at r = 128 29 -> 19 us, 12 T5-3B matrices
+// at r = 256 188 -> 122 us, 48 GPT-2 base matrices at r = 256 122 -> 90 us.
+WideShape choose_wide(const Plan& p, bool f32, bool whole_rows, bool allow512)
+{
+    const int slice = (p.r == 64) ? 64 : 128, slices = p.r / slice;
+    std::vector<int> order(p.count);
+    for (int i = 0; i < p.count; ++i) order[i] = i;
+    std::sort(order.begin(), order.end(), [&](int x, int y) { return p.host_mats[x].m > p.host_mats[y].m; });
+    WideShape best;
+    double best_us = -1.0;
+    std::vector<double> load(256);
+    long long last_parts = 0;
+    for (int mt = allow512 ? 8 : 16; mt <= 32; mt *= 2) {
+        const int rows = 4096 / mt;
+        const double kb64 = rows * 64.0 * (f32 ? 4 : 2) / 65536.0 * (f32 || whole_rows ? 1.0 : 2.4);
+        const double alone = 3.2 * kb64, full = 0.79 * slice / 128.0 + 1.6 * kb64 * (slices > 1 ? 0.86 : 1.0);
+        for (long long kc : {0, 1536, 768, 384, 192}) {
+            // workgroups, their tiles, and the products of shared columns
+            long long wgs = 0, tiles = 0, longest = 0, most_parts = 1, parts_sum = 0;
+            double part_mb = 0.0;
+            auto shares = [&](const MatDev& M, long long& parts) {      // tiles of one part
+                parts = kc > 0 ? (M.m + kc - 1) / kc : 1;
+                const long long t = ((M.m + parts - 1) / parts + 63) / 64;
+                parts = (M.m + 64 * t - 1) / (64 * t);
+                return t;
+            };
+            for (int l : order) {
+                const MatDev& M = p.host_mats[l];
+                long long parts;
+                const long long t = shares(M, parts), blocks = (M.n + rows - 1) / rows * slices;
+                wgs += blocks * parts; tiles += blocks * ((M.m + 63) / 64);
+                longest = std::max(longest, t); most_parts = std::max(most_parts, parts); parts_sum += parts;
+                if (parts > 1) part_mb += (double)blocks * parts * rows * slice * 4.0 / 1e6;
+            }
+            if (kc > 0 && parts_sum == last_parts) continue;            // the same pieces as the coarser split
+            last_parts = parts_sum;
+            double fullest = (tiles + 2.0 * wgs) / 256.0;
+            if (wgs <= 2048) {                                          // in the order of the table, each to the emptiest unit
+                std::fill(load.begin(), load.end(), 0.0);
+                for (int l : order) {
+                    const MatDev& M = p.host_mats[l];
+                    long long parts;
+                    const long long t = shares(M, parts), blocks = (M.n + rows - 1) / rows * slices;
+                    for (long long w = 0; w < blocks * parts; ++w) {
+                        std::pop_heap(load.begin(), load.end(), std::greater<double>());
+                        load.back() += (double)t + 2.0;
+                        std::push_heap(load.begin(), load.end(), std::greater<double>());
+                    }
+                }
+                fullest = *std::max_element(load.begin(), load.end());
+            } else {
+                fullest += 0.5 * (double)longest;
+            }
+            const double sweep = std::max(alone * (double)longest, full * fullest);
+            const double by_last = 1.5 + 0.87 * (double)most_parts * rows * slice / 16384.0 + 0.14 * part_mb;
+            const double by_launch = 1.3 + 0.38 * part_mb;
+            for (int combine = 0; combine < (most_parts > 1 ? 2 : 1); ++combine) {
+                const double us = sweep + (most_parts > 1 ? (combine ? by_launch : by_last) : 0.0);
+                if (best_us < 0.0 || us < best_us) {
+                    best_us = us;
+                    best.mt = mt; best.kc = kc; best.combine = combine;
+                }
+            }
+        }
+    }
+    return best;
+}
+
 void build_compress_bf16_items(Plan& p)
 {
     // The wide kernel (512, 256 or 128 rows per workgroup, rank slices of 128) regenerates A least
-    // often.  A launch should give the chip at least one
-    // and a half workgroups per compute unit: if whole row blocks do not, the columns of a row
-    // block are shared between up to a few workgroups (partial products, combined by the last
-    // one to finish), then the row blocks are halved.  Sharing costs nparts * rows * r * 8
-    // bytes of extra traffic per block, so parts stay at 768 columns or more.
-    // fp32 gradients, and sets with some row of G that does not start on a 16-byte boundary, take its
-    // ANY form (512 rows only with bf16 at r = 64: its operand copies, and fp32 tiles, need the registers).
-    // Rows too long for 32-bit byte offsets within 64 rows take the narrow kernel with the largest
-    // rows-per-workgroup (128 * mt) that still gives the chip two workgroups per compute unit.
+    // often.  fp32 gradients, and sets with some row of G that does not start on a 16-byte boundary, take
+    // its ANY form (512 rows only with bf16 at r = 64: its operand copies, and fp32 tiles, need the
+    // registers).  Rows too long for 32-bit byte offsets within 64 rows take the narrow kernel with the
+    // largest rows-per-workgroup (128 * mt) that still gives the chip two workgroups per compute unit.
     const bool f32 = (p.variant & 3) == 3;
     bool fits = true, whole_rows = !f32;
     for (int l = 0; l < p.count; ++l) {
@@ -242,57 +330,18 @@ void build_compress_bf16_items(Plan& p)
     p.any_rows = !whole_rows;
     const bool allow512 = whole_rows || (p.r == 64 && !f32);
     const int wide_slice = (p.r == 64) ? 64 : 128;
-    auto wide_wgs = [&](int rows, long long kc) {
-        long long wgs = 0;
-        for (int l = 0; l < p.count; ++l) {
-            const long long parts = kc > 0 ? (p.host_mats[l].m + kc - 1) / kc : 1;
-            wgs += (p.host_mats[l].n + rows - 1) / rows * (p.r / wide_slice) * parts;
-        }
-        return wgs;
-    };
     int mt = 4;
     long long kc = 0;       // columns per part (0: whole rows)
+    p.combine = g_tune.compress_combine == 2;
     if (g_tune.compress_bf16_mt && (fits || g_tune.compress_bf16_mt <= 4)) {
         mt = g_tune.compress_bf16_mt;
         if (mt == 8 && !allow512) mt = 16;
         kc = g_tune.compress_splitk_cols;
     } else if (fits) {
-        const int rows_opt[2] = {512, 256};
-        const long long kc_opt[3] = {0, 1536, 768};
-        mt = 16; kc = 768;
-        bool found = false;
-        // An option also has to be balanced: a workgroup sweeps its columns 64 at a time, and when
-        // the longest sweep is more than one and a half times a compute unit's even share of all
-        // tiles, that workgroup finishes long after the rest (24 matrices of T5-3B shapes with whole
-        // rows: 384 workgroups, the 16384-column ones 256 tiles long against an even share of 48,
-        // 574 us; in parts of 1536 columns 210 us).
-        auto balanced = [&](int rows, long long kc) {
-            long long total = 0, longest = 0;
-            for (int l = 0; l < p.count; ++l) {
-                const long long m = p.host_mats[l].m;
-                const long long tiles = (m + 63) / 64;
-                total += (p.host_mats[l].n + rows - 1) / rows * (p.r / wide_slice) * tiles;
-                longest = std::max(longest, kc > 0 ? std::min(tiles, (kc + 63) / 64) : tiles);
-            }
-            return 2 * longest <= 3 * std::max<long long>(1, total / 256);
-        };
-        for (int ri = allow512 ? 0 : 1; ri < 2 && !found; ++ri)
-            for (int ki = 0; ki < 3 && !found; ++ki)
-                if (wide_wgs(rows_opt[ri], kc_opt[ki]) >= 384 && (kc_opt[ki] > 0 || balanced(rows_opt[ri], 0))) {
-                    mt = rows_opt[ri] == 512 ? 8 : 16;
-                    kc = kc_opt[ki];
-                    found = true;
-                }
-        // Launches over one or two matrices cannot fill the chip either way; what counts then is
-        // how long the longest workgroup runs.  Fewer than about 130 workgroups of 256 rows: rows
-        // are taken 128 at a time, and below about 150 of those the columns in parts of 384
-        // (single matrices of GPT-2 XL and T5-3B shapes: 23-47 -> 21-37 us at r = 256, 21-38 ->
-        // 14-26 us at r = 64; taller or wider ones lose with smaller pieces and keep 256 x 768).
-        if (!found && wide_wgs(256, 768) < 130) {
-            mt = 32;
-            kc = wide_wgs(128, 768) < 150 ? 384 : 768;
-        }
-        if (g_tune.compress_splitk_cols) kc = g_tune.compress_splitk_cols;
+        const WideShape w = choose_wide(p, f32, whole_rows, allow512);
+        mt = w.mt;
+        kc = g_tune.compress_splitk_cols ? g_tune.compress_splitk_cols : w.kc;
+        if (!g_tune.compress_combine) p.combine = w.combine;
     } else for (; mt > 1; mt >>= 1) {
         long long wgs = 0;
         for (int l = 0; l < p.count; ++l)
@@ -995,7 +1044,7 @@ static int compress_chunk(const flora_matrix_t* mats, int count, int r, flora_dt
                                                                    round_up(p->ws_floats * 4, 256))
                                        : nullptr;
         FLORA_HIP(launch_compress_bf16_mt(dm, di, (int)p->items.size(), sa, r, p->mt, variant == 3, p->any_rows, map, a, b,
-                                          partials, counters, s));
+                                          p->combine && p->ws_counters > 0, partials, counters, s));
     }
     else {
         // column groups per workgroup: two for whole rows; one when the pieces are 512 columns
@@ -1550,6 +1599,9 @@ int flora_set_tuning(const char* name, int value)
     } else if (std::strcmp(name, "compress_splitk_cols") == 0) {
         if (value < 0 || (value % 64) != 0) return FLORA_ERR_INVALID;
         g_tune.compress_splitk_cols = value;
+    } else if (std::strcmp(name, "compress_combine") == 0) {
+        if (value < 0 || value > 2) return FLORA_ERR_INVALID;
+        g_tune.compress_combine = value;
     } else if (std::strcmp(name, "compress_bf16_mt") == 0) {
         if (!pow2_124 && value != 8 && value != 16 && value != 32) return FLORA_ERR_INVALID;
         g_tune.compress_bf16_mt = value;

@@ -553,9 +553,10 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     //
     // A workgroup that owns all columns of its rows updates the state directly.  When the
     // columns of a row block are shared between nparts workgroups (short launches, to fill
-    // the chip), each stores its partial product; the one that finishes last adds the
-    // partials in the order 0 .. nparts - 1, whoever it is, and updates the state, so the
-    // result does not depend on timing.
+    // the chip), each stores its partial product; the parts are added in the order 0 .. nparts - 1
+    // whichever way, so the result does not depend on timing.  Either the one that finishes last adds
+    // them and updates the state, or (counters null) combine_parts_kernel, launched next on the same
+    // stream, does.
     float* stage = reinterpret_cast<float*>(lds_raw) + wave * (16 * LDE);
     constexpr int LPR = RS / 4;           // lanes per row when reading back
     constexpr int RPI = 64 / LPR;         // rows per instruction
@@ -589,17 +590,16 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const v4f nv = *reinterpret_cast<const v4f*>(&stage[(erow + RPI * p) * LDE + 4 * echunk]);
-            if (split) {
+            if (split && counters) {
                 // written through to memory (device scope): another XCD's L2 never sees a stale copy
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, nv), st_rs, (int)goff[p], 0, 16);
-            } else {
-                buf_store_f4(st_rs, goff[p], v4f{a * oldv[p].x + b * nv.x, a * oldv[p].y + b * nv.y,
-                                                 a * oldv[p].z + b * nv.z, a * oldv[p].w + b * nv.w});
-            }
+            } else if (split) buf_store_f4(st_rs, goff[p], nv);
+            else buf_store_f4(st_rs, goff[p], v4f{a * oldv[p].x + b * nv.x, a * oldv[p].y + b * nv.y,
+                                                  a * oldv[p].z + b * nv.z, a * oldv[p].w + b * nv.w});
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);   // reads done before the next block overwrites the area
     }
-    if (!split) return;
+    if (!split || !counters) return;
 
     // ---- shared columns: count arrivals; the last one combines.  The partials are stored and
     // loaded with device scope on the accesses themselves (write-through / L2-bypassing), so
@@ -665,6 +665,43 @@ __global__ __launch_bounds__(512) void compress_bf16_wide_kernel(const MatDev* _
     if (tid == 0) counters[it.cidx] = 0u;     // every part has arrived: ready for the next launch
 }
 
+// state <- a * state + b * (sum of a shared row block's partial products, in the order 0 .. nparts - 1).
+// The launch has the wide kernel's table: the workgroup of part p of a block takes the p-th share of the
+// block's rows, so the sums run on as many workgroups as the products did (the last of a block's parts
+// to arrive adding all of them by itself took 5 to 20 us at the end of a launch over a few matrices).
+template <int RS>
+__global__ __launch_bounds__(512) void combine_parts_kernel(const MatDev* __restrict__ mats,
+                                                            const WorkItem* __restrict__ items, int R, int block_rows,
+                                                            float a, float b, const float* __restrict__ partials)
+{
+    const WorkItem it = items[blockIdx.x];
+    if (it.nparts <= 1) return;
+    const MatDev& M = mats[it.mat];
+    const int rows = (int)((long long)it.row0 + it.rows < M.n ? it.rows : M.n - it.row0);     // valid rows of the block
+    const int share = (rows + it.nparts - 1) / it.nparts;
+    const int r0 = it.part * share, r1 = r0 + share < rows ? r0 + share : rows;
+    const float* src = partials + (size_t)it.poff;
+    const size_t stride = (size_t)block_rows * RS;
+    float* dst = M.state + (long long)it.row0 * R + it.slice * RS;
+    for (int f = r0 * (RS / 4) + (int)threadIdx.x; f < r1 * (RS / 4); f += 512) {
+        const int row = f / (RS / 4), c = 4 * (f % (RS / 4));
+        float* d = dst + (size_t)row * R + c;
+        const float* s = src + (size_t)row * RS + c;
+        const v4f old = a != 0.f ? ldg4(d) : v4f{0.f, 0.f, 0.f, 0.f};
+        v4f sum = {0.f, 0.f, 0.f, 0.f};
+        int q = 0;
+        for (; q + 4 <= it.nparts; q += 4) {          // four loads in flight
+            v4f v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = ldg4(s + (size_t)(q + e) * stride);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum += v[e];
+        }
+        for (; q < it.nparts; ++q) sum += ldg4(s + (size_t)q * stride);
+        *(FLORA_GLOBAL v4f*)d = v4f{a * old.x + b * sum.x, a * old.y + b * sum.y, a * old.z + b * sum.z, a * old.w + b * sum.w};
+    }
+}
+
 }  // namespace
 
 namespace {
@@ -728,24 +765,32 @@ hipError_t launch_narrow(const MatDev* mats, const WorkItem* items, int nitems, 
 
 // All items of one launch share one MT (rows per workgroup = 128 * MT; 8, 16 and 32 select the wide
 // kernel), chosen by the host.  any_rows: some matrix has rows of G that do not start on 16-byte
-// boundaries.  partials / counters: workspace of the wide kernel's shared-column mode (may be null
-// when no item has nparts > 1).
+// boundaries.  partials / counters: workspace of the wide kernel's shared columns (null when no item
+// has nparts > 1); combine: the parts are added by a launch of their own (then no counters).
 hipError_t launch_compress_bf16_mt(const MatDev* mats, const WorkItem* items, int nitems,
                                    const SeedArgs& seeds, int r, int mt, int grad_is_f32, int any_rows, int map, float a, float b,
-                                   float* partials, uint32_t* counters, hipStream_t s)
+                                   int combine, float* partials, uint32_t* counters, hipStream_t s)
 {
     if (nitems == 0) return hipSuccess;
     if (r != 64 && r != 128 && r != 256) return hipErrorInvalidValue;
+    if (combine) counters = nullptr;
     if (map != 0 && map != 1) return hipErrorInvalidValue;
     if (mt == 8 || mt == 16 || mt == 32) {   // wide kernel: 512 (8), 256 (16) or 128 (32) rows per workgroup, rank slices of 128 (64 at r = 64)
+        hipError_t e;
         if (grad_is_f32)
-            return (map == 1) ? launch_wide<1, float, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
-                              : launch_wide<0, float, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
-        if (any_rows)
-            return (map == 1) ? launch_wide<1, uint16_t, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
-                              : launch_wide<0, uint16_t, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
-        return (map == 1) ? launch_wide<1, uint16_t, false>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
-                          : launch_wide<0, uint16_t, false>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
+            e = (map == 1) ? launch_wide<1, float, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
+                           : launch_wide<0, float, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
+        else if (any_rows)
+            e = (map == 1) ? launch_wide<1, uint16_t, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
+                           : launch_wide<0, uint16_t, true>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
+        else
+            e = (map == 1) ? launch_wide<1, uint16_t, false>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s)
+                           : launch_wide<0, uint16_t, false>(mats, items, nitems, seeds, r, mt, a, b, partials, counters, s);
+        if (e != hipSuccess || !combine) return e;
+        const int block_rows = mt == 8 ? 512 : (mt == 16 ? 256 : 128);
+        if (r == 64) hipLaunchKernelGGL((combine_parts_kernel<64>), dim3((unsigned)nitems), dim3(512), 0, s, mats, items, r, block_rows, a, b, partials);
+        else hipLaunchKernelGGL((combine_parts_kernel<128>), dim3((unsigned)nitems), dim3(512), 0, s, mats, items, r, block_rows, a, b, partials);
+        return hipGetLastError();
     }
     const dim3 grid((unsigned)nitems), block(256);
     return (map == 1) ? launch_narrow<1>(mats, items, nitems, seeds, r, mt, grad_is_f32, a, b, grid, block, s)

@@ -237,7 +237,7 @@ hipError_t launch_compress_f32(const MatDev* mats, const WorkItem* items, int ni
                                float* partials, uint32_t* counters, hipStream_t s);
 hipError_t launch_compress_bf16_mt(const MatDev* mats, const WorkItem* items, int nitems,
                                    const SeedArgs& seeds, int r, int mt, int grad_is_f32, int any_rows, int map, float a, float b,
-                                   float* partials, uint32_t* counters, hipStream_t s);
+                                   int combine, float* partials, uint32_t* counters, hipStream_t s);
 hipError_t launch_decompress_f32(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds,
                                  int r, int mode, int out_is_bf16, DecompressParams p, hipStream_t s);
 hipError_t launch_decompress_bf16(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds,

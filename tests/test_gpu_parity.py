@@ -194,11 +194,12 @@ def test_compress_bf16_every_launch_shape(n, m, r, mt):
 # load fetches beside its row must not reach the result.  Bar: one rounded operand (A; with fp32
 # gradients G is compared as the kernel rounds it), about 2^-9 / sqrt(3) = 1.1e-3 on a large matrix;
 # the smallest have a handful of terms per entry, hence 6e-3 as for the other launch shapes.
+@pytest.mark.parametrize("combine", [1, 2])       # shared columns added by the last part to arrive, or by a launch
 @pytest.mark.parametrize("mt,kc", [(8, 0), (16, 64), (32, 0), (32, 192)])
 @pytest.mark.parametrize("gdt", ["f32", "bf16"])
 @pytest.mark.parametrize("n,m,r", [(33, 1, 64), (130, 7, 128), (257, 63, 256), (97, 65, 64), (513, 127, 128), (31, 66, 256),
                                    (300, 130, 64), (129, 333, 256), (1030, 961, 64), (64, 1283, 128)])
-def test_compress_bf16_rows_that_start_anywhere(n, m, r, gdt, mt, kc):
+def test_compress_bf16_rows_that_start_anywhere(n, m, r, gdt, mt, kc, combine):
     seed = 2600 + n + m + r
     dt = torch.float32 if gdt == "f32" else torch.bfloat16
     buf = torch.full((n * m + 128,), float("nan"), device=DEV, dtype=dt)
@@ -209,6 +210,7 @@ def test_compress_bf16_rows_that_start_anywhere(n, m, r, gdt, mt, kc):
     ref = oracle.compress(to64(G.to(torch.bfloat16)), r, seed)
     flora.set_tuning("compress_bf16_mt", mt)
     flora.set_tuning("compress_splitk_cols", kc)
+    flora.set_tuning("compress_combine", combine)
     try:
         for step in range(2):                     # (the arrival counters must be back at zero)
             flora.compress(mats, r, flora.F32 if gdt == "f32" else flora.BF16, 0.0, 1.0)
@@ -219,6 +221,7 @@ def test_compress_bf16_rows_that_start_anywhere(n, m, r, gdt, mt, kc):
     finally:
         flora.set_tuning("compress_bf16_mt", 0)
         flora.set_tuning("compress_splitk_cols", 0)
+        flora.set_tuning("compress_combine", 0)
 
 
 # the wide kernel with the columns of a row block shared between workgroups (partial products
