@@ -548,8 +548,21 @@ bool choose_gram(const Plan& p)
 
 void build_gram_items(Plan& p)
 {
-    const long long gchunk = g_tune.gram_chunk ? g_tune.gram_chunk : kGramChunk;
-    auto chunks_of = [&](long long len) { return (int)((len + gchunk - 1) / gchunk); };
+    // Pieces of the long index: the largest that still give the chip 384 workgroups (the sums of a launch
+    // over a few matrices otherwise run on a workgroup per matrix: 16 GPT-2 base matrices at r = 128, the
+    // two Gram kernels 45 + 73 us in pieces of 3072; smaller pieces cost r^2 floats each, written and read).
+    auto pieces = [&](bool rows, long long most, long long least) {
+        for (long long c = most; c > least; c /= 2) {
+            long long wgs = 0;
+            for (const MatDev& M : p.host_mats) wgs += ((rows ? M.n : M.m) + c - 1) / c;
+            if (wgs >= 384) return c;
+        }
+        return least;
+    };
+    const long long chunk_m = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(false, kGramChunk, 192);
+    const long long chunk_n = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(true, kGramChunk, 192);
+    const long long cols = pieces(false, kQuadformCols, p.r >= 128 ? 512 : 256);
+    auto chunks_of = [&](long long len, long long chunk) { return (int)((len + chunk - 1) / chunk); };
     auto emit_chunks = [&](int l, long long len, int chunks) {
         const long long per = ((len + chunks - 1) / chunks + 63) / 64 * 64;
         for (int c = 0; c < chunks; ++c) {
@@ -560,8 +573,8 @@ void build_gram_items(Plan& p)
             p.items2.push_back(w);
         }
     };
-    auto emit_blocks = [&](int l, long long len) {
-        const long long nb = (len + kQuadformRows - 1) / kQuadformRows;
+    auto emit_blocks = [&](int l, long long len, long long rows) {
+        const long long nb = (len + rows - 1) / rows;
         const long long per = ((len + nb - 1) / nb + 31) / 32 * 32;
         int b = 0;
         for (long long r0 = 0; r0 < len; r0 += per, ++b) {
@@ -573,8 +586,8 @@ void build_gram_items(Plan& p)
     };
     for (int l = 0; l < p.count; ++l) {
         MatDev& M = p.host_mats[(size_t)l];
-        M.gchunks_m = chunks_of(M.m);
-        M.gchunks_n = chunks_of(M.n);
+        M.gchunks_m = chunks_of(M.m, chunk_m);
+        M.gchunks_n = chunks_of(M.n, chunk_n);
     }
     // longest first within each table
     std::vector<int> by_m(p.count), by_n(p.count);
@@ -586,9 +599,9 @@ void build_gram_items(Plan& p)
     p.n_gm = (int)(p.items2.size() - before); before = p.items2.size();
     for (int l : by_n) emit_chunks(l, p.host_mats[(size_t)l].n, p.host_mats[(size_t)l].gchunks_n);
     p.n_gn = (int)(p.items2.size() - before); before = p.items2.size();
-    for (int l : by_n) p.host_mats[(size_t)l].item0 = emit_blocks(l, p.host_mats[(size_t)l].n);
+    for (int l : by_n) p.host_mats[(size_t)l].item0 = emit_blocks(l, p.host_mats[(size_t)l].n, kQuadformRows);
     p.n_qr = (int)(p.items2.size() - before); before = p.items2.size();
-    for (int l : by_m) (void)emit_blocks(l, p.host_mats[(size_t)l].m);
+    for (int l : by_m) (void)emit_blocks(l, p.host_mats[(size_t)l].m, cols);
     p.n_qc = (int)(p.items2.size() - before);
 }
 
@@ -607,7 +620,7 @@ size_t workspace_bytes_for(const std::vector<MatDev>& mats, int kind, int r, boo
         if (kind == kKindFactored) {
             b += round_up((size_t)M.ncolchunks * M.n * 4, 256);
             b += round_up((size_t)M.nrowblocks * M.m * 4, 256);
-            b += round_up((size_t)M.nitems * 4, 256);
+            b += round_up((size_t)std::max(M.nitems, M.item0) * 4, 256);
             b += 256;
         }
         if (kind == kKindSumsq) b += (size_t)kSumsqBlocks * 4;
@@ -823,7 +836,7 @@ int get_plan(int kind, int variant, int r, const std::vector<MatDev>& mats, hipS
             if (kind == kKindFactored) {
                 M.rowpart = reinterpret_cast<float*>(w); w += round_up((size_t)M.ncolchunks * M.n * 4, 256);
                 M.colpart = reinterpret_cast<float*>(w); w += round_up((size_t)M.nrowblocks * M.m * 4, 256);
-                M.itempart = reinterpret_cast<float*>(w); w += round_up((size_t)M.nitems * 4, 256);
+                M.itempart = reinterpret_cast<float*>(w); w += round_up((size_t)std::max(M.nitems, M.item0) * 4, 256);
                 M.scal = reinterpret_cast<float*>(w); w += 256;
             }
         }
@@ -1182,8 +1195,7 @@ static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16,
             FLORA_HIP(launch_gram(dm, gn, p->n_gn, count, sa, r, 2, s));
             FLORA_HIP(launch_quadform(dm, qc, p->n_qc, sa, r, 1, u->alpha, u->beta2, u->eps1, s));
             FLORA_HIP(launch_gram(dm, gm, p->n_gm, count, sa, r, clip ? 3 : 0, s));
-            FLORA_HIP(launch_quadform(dm, qr, p->n_qr, sa, r, 0, u->alpha, u->beta2, u->eps1, s));
-            if (clip) FLORA_HIP(launch_quadform(dm, qr, p->n_qr, sa, r, 2, u->alpha, u->beta2, u->eps1, s));
+            FLORA_HIP(launch_quadform(dm, qr, p->n_qr, sa, r, clip ? 2 : 0, u->alpha, u->beta2, u->eps1, s));
         } else if (factored) {
             st = run_decompress(p, sa, r, kModeStats, 0, dp, s);
             if (st != FLORA_OK) return st;

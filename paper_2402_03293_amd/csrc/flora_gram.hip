@@ -21,13 +21,14 @@
 //   bf16), both MFMA operands come from there.  combine_gram_kernel adds the chunks' partials in
 //   chunk order and stores the result as bf16 in the arrangement the quadratic-form kernel that
 //   reads it copies into LDS.
-// quadform_kernel: q_i = Z_i B Z_i^T for a block of rows of Z (rows of S, loaded; at rank 64 also
-//   rows of A, regenerated), B a Gram matrix held in LDS.  The product is taken transposed,
+// quadform_rows_kernel: q_i = Z_i B Z_i^T for a block of rows of Z = S, B a Gram matrix that passes through
+//   LDS.  The product is taken transposed,
 //   D[k2][i] = sum_k1 B[k2][k1] Z[i][k1], so that lane (i, g) ends up with D[16 c + 4 g + v][i]; the
 //   contraction order over k1 is free, and it is chosen so that the same lane's operand
 //   registers hold exactly Z[i][16 c + 4 g + v]: q_i is then a dot product of registers the lane
-//   already has, summed over the four lanes that share a row.  quadform_cols_kernel (ranks >= 128)
-//   is the same scheme on 32 x 32 x 16 tiles for rows of A generated into the operand registers.
+//   already has, summed over the four lanes that share a row.  quadform_cols_small_kernel (rank 64) and
+//   quadform_cols_kernel (ranks >= 128, on 32 x 32 x 16 tiles) are the same scheme for rows of A generated
+//   into the operand registers.
 //   The kernels finish the statistics themselves (R_i, K_j, one partial sum of R per row block).
 #include <type_traits>
 
@@ -416,46 +417,91 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
 }
 
 // B <- sum over the chunks of their partials, in chunk order; stored as bf16 with the columns of
-// every 32-block in the order quadform_kernel contracts them.  which 0: P (chunks of m), 1: Q (chunks
-// of n), 2: P' (chunks of m; it is kept right behind Q)
+// every 32-block in the order the quadratic-form kernels contract them.  which 0: P (chunks of m), 1: Q
+// (chunks of n), 2: P' (chunks of m; it is kept right behind Q); 0 and 2 together as blockIdx.z = 0, 1
 template <int R>
-__global__ __launch_bounds__(256) void combine_gram_kernel(const MatDev* __restrict__ mats, int which)
+__global__ __launch_bounds__(256) void combine_gram_kernel(const MatDev* __restrict__ mats, int first)
 {
     const MatDev& M = mats[blockIdx.y];
+    const int which = first + 2 * (int)blockIdx.z;
     const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;       // four consecutive k1 of one row k2
     if (idx >= R * R) return;
     const int nch = which == 1 ? M.gchunks_n : M.gchunks_m;
     const int part0 = which == 0 ? 0 : (which == 1 ? M.gchunks_m : M.gchunks_m + M.gchunks_n);
+    const float* src = M.grampart + (size_t)part0 * R * R + idx;
     v4f s = {0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < nch; ++c) {
-        const v4f p = ldg4(M.grampart + (size_t)(part0 + c) * R * R + idx);
-        s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+    int c = 0;
+    for (; c + 8 <= nch; c += 8) {                              // eight loads in flight
+        v4f p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = ldg4(src + (size_t)(c + e) * R * R);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += p[e];
     }
+    for (; c < nch; ++c) s += ldg4(src + (size_t)c * R * R);
     uint16_t* B = which == 0 ? M.gramP : (which == 1 ? M.gramQ : M.gramQ + R * R);
     const int k2 = idx / R, k1 = idx % R;                       // k1 % 4 == 0: the four stay together
-    // (Q at ranks >= 128 is read by quadform_cols_kernel, everything else by quadform_kernel)
+    // (Q at ranks >= 128 is read by quadform_cols_kernel, everything else in the other order)
     const int pos = (k1 & ~31) + ((which == 1 && R >= 128) ? perm32w(k1 & 31) : perm32(k1 & 31));
     const v2u pk = {pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w)};
     *reinterpret_cast<FLORA_GLOBAL v2u*>((FLORA_GLOBAL uint16_t*)(B + k2 * R + pos)) = pk;
 }
 
-// SRC 0: Z = S (rows of the state), B = P;  SRC 1: Z = A(seed) (rows = columns of W), B = Q.
-// The statistics are finished where the sums appear (each row and column belongs to one lane):
-// OUT 0: R_i <- beta2 R_i + (1 - beta2) (alpha^2 q_i / m + eps1), and rowpart[block] <- the block's sum
-//        of the new R_i (for mean(R));
-// OUT 1: K_j <- beta2 K_j + (1 - beta2) (alpha^2 q_j / n + eps1);
-// OUT 2: itempart[block] <- alpha^2 sum_i q_i / R_i  (the clipping sum of this row block, but for
-//        the factor mean(R), which rms_finalize_kernel supplies)
-template <int R, int SRC, int OUT, int WAVES, int ZT>
-__global__ __launch_bounds__(64 * WAVES) void quadform_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items,
-                                                       const SeedArgs seeds, float alpha, float beta2, float eps1)
+// q_i = Z_i B Z_i^T for 16 ZT rows of Z held in operand registers, rows [16 CT0, 16 (CT0 + NCT)) of B in LDS:
+// D[16 ct + 4 g + v][i], then its dot product with Z[i][16 ct + 4 g + v], which is elements 4 (ct % 2) + v
+// of step ct / 2 of this lane's own operand registers.
+template <int S, int ZT, int CT0, int NCT, int LDB>
+__device__ __forceinline__ void quadform_tiles(float (&q)[ZT], const bf16x8 (&zreg)[ZT][S], const uint16_t (*ldsB)[LDB], int li, int g)
 {
-    constexpr int S = R / 32;            // contraction steps
-    constexpr int CT = R / 16;           // 16-row tiles of B
-    constexpr int LDB = R + 8;           // padded LDS row (bf16 elements)
-    // (ZT: 16-row tiles of Z per wave and round)
-    __shared__ __attribute__((aligned(16))) uint16_t ldsB[R][LDB];
-    __shared__ float lds_fin[WAVES];
+#pragma unroll
+    for (int c = 0; c < NCT; ++c) {
+        const int ct = CT0 + c;
+        f32x4 acc[ZT];
+#pragma unroll
+        for (int z = 0; z < ZT; ++z) acc[z] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&ldsB[16 * c + li][32 * s + 8 * g]);
+#pragma unroll
+            for (int z = 0; z < ZT; ++z)
+                acc[z] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, zreg[z][s], acc[z], 0, 0, 0);
+        }
+#pragma unroll
+        for (int z = 0; z < ZT; ++z) {
+            const v4u zz = __builtin_bit_cast(v4u, zreg[z][ct / 2]);
+            const uint32_t w0 = (ct & 1) ? zz.z : zz.x, w1 = (ct & 1) ? zz.w : zz.y;
+            q[z] = __builtin_fmaf(acc[z][0], __uint_as_float(w0 << 16), q[z]);
+            q[z] = __builtin_fmaf(acc[z][1], __uint_as_float(w0 & 0xffff0000u), q[z]);
+            q[z] = __builtin_fmaf(acc[z][2], __uint_as_float(w1 << 16), q[z]);
+            q[z] = __builtin_fmaf(acc[z][3], __uint_as_float(w1 & 0xffff0000u), q[z]);
+        }
+        // (keeps the compiler from hoisting every column tile's LDS reads to the top: the
+        // registers are the operand tiles' and must not spill)
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The row statistics and the clipping sum from ONE read of S (a pass each
+// took 0.61 ms on 384 T5-3B matrices at r = 256, together they take 0.55; on 16 GPT-2 base matrices at
+// r = 128, 22 + 20 us against 11):
+//   R_i <- beta2 R_i + (1 - beta2) (alpha^2 S_i P S_i^T / m + eps1), rowpart[block] <- the block's sum of the
+//          new R_i (for mean(R));
+//   CLIP: itempart[block] <- alpha^2 sum_i (S_i P' S_i^T) / R_i (the clipping sum of this row block, but for
+//         the factor mean(R), which rms_finalize_kernel supplies).
+// A workgroup's 256 rows of S stay in operand registers (32 to a wave) while P and then P' pass through LDS, at
+// r = 256 by halves: 68 KB instead of 135, so that two workgroups share a compute unit and one loads while
+// the other multiplies.
+template <int R, bool CLIP>
+__global__ __launch_bounds__(512, R >= 256 ? 4 : 2) void quadform_rows_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items,
+                                                            float alpha, float beta2, float eps1)
+{
+    constexpr int S = R / 32;                      // contraction steps
+    constexpr int ZT = 2;                          // 16-row tiles of S per wave
+    constexpr int KB = R < 128 ? R : 128;          // rows of B in LDS at a time
+    constexpr int LDB = R + 8;                     // padded LDS row (bf16 elements)
+    static_assert(8 * 16 * ZT == kQuadformRows, "one round of rows per workgroup");
+    __shared__ __attribute__((aligned(16))) uint16_t ldsB[KB][LDB];
+    __shared__ float lds_fin[2][8];
 
     const WorkItem it = items[blockIdx.x];
     const MatDev& M = mats[it.mat];
@@ -463,123 +509,155 @@ __global__ __launch_bounds__(64 * WAVES) void quadform_kernel(const MatDev* __re
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
-    const long long zn = SRC == 0 ? M.n : M.m;            // rows of Z
+    const long long row_end = ((long long)it.row0 + it.rows < M.n) ? (long long)it.row0 + it.rows : M.n;
+
+    // this wave's rows: row0 + wave * 16 ZT + 16 z + li
+    const long long wrow = (long long)it.row0 + wave * (16 * ZT);
+    long long valid = row_end - wrow;
+    valid = valid < 0 ? 0 : (valid > 16 * ZT ? 16 * ZT : valid);
+    const rsrc_t srs = make_rsrc(M.state + (wrow < M.n ? wrow : 0) * R, valid * R * 4);      // rows past the end read as zero
+    bf16x8 zreg[ZT][S];
+#pragma unroll
+    for (int z = 0; z < ZT; ++z)
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const uint32_t off = (uint32_t)((16 * z + li) * R + 32 * s + 4 * g) * 4u;
+            const v4f lo = buf_load_f4(srs, off), hi = buf_load_f4(srs, off + 64u);
+            const v4u pk = {pack_bf16x2(lo.x, lo.y), pack_bf16x2(lo.z, lo.w), pack_bf16x2(hi.x, hi.y), pack_bf16x2(hi.z, hi.w)};
+            zreg[z][s] = __builtin_bit_cast(bf16x8, pk);
+        }
+
+    auto stage_B = [&](const uint16_t* B) {
+#pragma unroll
+        for (int f0 = 0; f0 < KB * (R / 8); f0 += 512) {
+            const int f = f0 + tid;
+            *reinterpret_cast<v4u*>(&ldsB[f / (R / 8)][8 * (f % (R / 8))]) = ldg4(B + (f / (R / 8)) * R + 8 * (f % (R / 8)));
+        }
+    };
+    auto form = [&](float (&q)[ZT], const uint16_t* B) {
+#pragma unroll
+        for (int z = 0; z < ZT; ++z) q[z] = 0.f;
+        __syncthreads();                           // the readers of what LDS held before are done
+        stage_B(B);
+        __syncthreads();
+        quadform_tiles<S, ZT, 0, KB / 16, LDB>(q, zreg, ldsB, li, g);
+        if constexpr (R > KB) {
+            static_assert(R <= 2 * KB, "two halves");
+            __syncthreads();
+            stage_B(B + KB * R);
+            __syncthreads();
+            quadform_tiles<S, ZT, KB / 16, KB / 16, LDB>(q, zreg, ldsB, li, g);
+        }
+#pragma unroll
+        for (int z = 0; z < ZT; ++z) {             // all four lanes of row li then hold q_i
+            q[z] += __shfl_xor(q[z], 16);
+            q[z] += __shfl_xor(q[z], 32);
+        }
+    };
+
+    float q[ZT], rn[ZT], total_r = 0.f, total_u = 0.f;
+    form(q, M.gramP);
+#pragma unroll
+    for (int z = 0; z < ZT; ++z) {
+        const long long row = wrow + 16 * z + li;
+        rn[z] = 1.f;
+        if (row < row_end) {
+            rn[z] = beta2 * ldg(M.row_stat + row) + (1.f - beta2) * (alpha * alpha * q[z] / (float)M.m + eps1);
+            if (g == 0) {
+                stg(M.row_stat + row, rn[z]);
+                total_r += rn[z];
+            }
+        }
+    }
+    if (CLIP) {
+        form(q, M.gramQ + R * R);
+#pragma unroll
+        for (int z = 0; z < ZT; ++z)
+            if (wrow + 16 * z + li < row_end && g == 0) total_u += q[z] / rn[z];
+    }
+    auto wave_sum = [](float t) {                  // (only the lanes g == 0 hold anything)
+        t += __shfl_xor(t, 8);
+        t += __shfl_xor(t, 4);
+        t += __shfl_xor(t, 2);
+        t += __shfl_xor(t, 1);
+        return t;
+    };
+    total_r = wave_sum(total_r);
+    if (CLIP) total_u = wave_sum(total_u);
+    if (lane == 0) { lds_fin[0][wave] = total_r; lds_fin[1][wave] = total_u; }
+    __syncthreads();
+    if (tid == 0) {
+        float fr = 0.f, fu = 0.f;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) { fr += lds_fin[0][w]; fu += lds_fin[1][w]; }
+        M.rowpart[it.part] = fr;
+        if (CLIP) M.itempart[it.part] = alpha * alpha * fu;
+    }
+}
+
+// The column statistics at rank 64: K_j <- beta2 K_j + (1 - beta2) (alpha^2 A_j Q A_j^T / n + eps1), rows A_j
+// regenerated straight into the operand registers.
+template <int R, int ZT>
+__global__ __launch_bounds__(512) void quadform_cols_small_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items,
+                                                                  const SeedArgs seeds, float alpha, float beta2, float eps1)
+{
+    constexpr int S = R / 32;            // contraction steps
+    constexpr int LDB = R + 8;           // padded LDS row (bf16 elements)
+    __shared__ __attribute__((aligned(16))) uint16_t ldsB[R][LDB];
+
+    const WorkItem it = items[blockIdx.x];
+    const MatDev& M = mats[it.mat];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, g = lane >> 4;
+    const long long zn = M.m;
     const long long row_end = ((long long)it.row0 + it.rows < zn) ? (long long)it.row0 + it.rows : zn;
     const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
     const float cgen = neg2_ln2_over(R);
 
-    // B into LDS: R rows of R bf16, 16 bytes per thread and step
-    {
-        const uint16_t* B = SRC == 1 ? M.gramQ : (OUT == 2 ? M.gramQ + R * R : M.gramP);
-        for (int f = tid; f < R * (R / 8); f += 64 * WAVES) {
-            const int k2 = f / (R / 8), c8 = f % (R / 8);
-            *reinterpret_cast<v4u*>(&ldsB[k2][8 * c8]) = ldg4(B + k2 * R + 8 * c8);
-        }
+    for (int f = tid; f < R * (R / 8); f += 512) {
+        const int k2 = f / (R / 8), c8 = f % (R / 8);
+        *reinterpret_cast<v4u*>(&ldsB[k2][8 * c8]) = ldg4(M.gramQ + k2 * R + 8 * c8);
     }
     __syncthreads();
 
-    float total = 0.f;
-    for (long long rb = it.row0; rb < row_end; rb += WAVES * 16 * ZT) {
+    for (long long rb = it.row0; rb < row_end; rb += 8 * 16 * ZT) {
         // this wave's rows: rb + wave * 16 ZT + 16 z + li
         bf16x8 zreg[ZT][S];
 #pragma unroll
         for (int z = 0; z < ZT; ++z) {
             const long long row = rb + (wave * ZT + z) * 16 + li;
-            const bool ok = row < row_end;
+            // (all lanes generate: rows past the end take the last row's values and are not stored)
+            const uint32_t jr = (uint32_t)(row < row_end ? row : zn - 1);
 #pragma unroll
             for (int s = 0; s < S; ++s) {
-                v4f lo = {0.f, 0.f, 0.f, 0.f}, hi = {0.f, 0.f, 0.f, 0.f};
-                if (SRC == 0) {
-                    if (ok) {
-                        lo = ldg4(M.state + row * R + 32 * s + 4 * g);
-                        hi = ldg4(M.state + row * R + 32 * s + 16 + 4 * g);
-                    }
-                } else {
-                    // (all lanes generate: rows past the end take the last row's values and are masked below)
-                    const long long jr = ok ? row : zn - 1;
-                    const Quad q0 = normal_quad(seed_lo, seed_hi, (uint32_t)jr, (uint32_t)(8 * s + g), cgen);
-                    const Quad q1 = normal_quad(seed_lo, seed_hi, (uint32_t)jr, (uint32_t)(8 * s + 4 + g), cgen);
-                    const float w = ok ? 1.f : 0.f;
-                    lo = v4f{w * q0.z[0], w * q0.z[1], w * q0.z[2], w * q0.z[3]};
-                    hi = v4f{w * q1.z[0], w * q1.z[1], w * q1.z[2], w * q1.z[3]};
-                }
-                const v4u pk = {pack_bf16x2(lo.x, lo.y), pack_bf16x2(lo.z, lo.w), pack_bf16x2(hi.x, hi.y), pack_bf16x2(hi.z, hi.w)};
+                const Quad q0 = normal_quad(seed_lo, seed_hi, jr, (uint32_t)(8 * s + g), cgen);
+                const Quad q1 = normal_quad(seed_lo, seed_hi, jr, (uint32_t)(8 * s + 4 + g), cgen);
+                const v4u pk = {pack_bf16x2(q0.z[0], q0.z[1]), pack_bf16x2(q0.z[2], q0.z[3]),
+                                pack_bf16x2(q1.z[0], q1.z[1]), pack_bf16x2(q1.z[2], q1.z[3])};
                 zreg[z][s] = __builtin_bit_cast(bf16x8, pk);
             }
         }
         float q[ZT];
 #pragma unroll
         for (int z = 0; z < ZT; ++z) q[z] = 0.f;
-        // two column tiles of D at a time: D[16 ct + 4 g + v][i], then its dot product with Z[i][16 ct + 4 g + v],
-        // which is elements 4 (ct % 2) + v of step ct / 2 of this lane's own operand registers
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            f32x4 acc[ZT];
-#pragma unroll
-            for (int z = 0; z < ZT; ++z) acc[z] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < S; ++s) {
-                const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&ldsB[16 * ct + li][32 * s + 8 * g]);
-#pragma unroll
-                for (int z = 0; z < ZT; ++z)
-                    acc[z] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bv, zreg[z][s], acc[z], 0, 0, 0);
-            }
-#pragma unroll
-            for (int z = 0; z < ZT; ++z) {
-                const v4u zz = __builtin_bit_cast(v4u, zreg[z][ct / 2]);
-                const uint32_t w0 = (ct & 1) ? zz.z : zz.x, w1 = (ct & 1) ? zz.w : zz.y;
-                q[z] = __builtin_fmaf(acc[z][0], __uint_as_float(w0 << 16), q[z]);
-                q[z] = __builtin_fmaf(acc[z][1], __uint_as_float(w0 & 0xffff0000u), q[z]);
-                q[z] = __builtin_fmaf(acc[z][2], __uint_as_float(w1 << 16), q[z]);
-                q[z] = __builtin_fmaf(acc[z][3], __uint_as_float(w1 & 0xffff0000u), q[z]);
-            }
-            // (keeps the compiler from hoisting every column tile's LDS reads to the top: the
-            // registers are the operand tiles' and must not spill)
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        quadform_tiles<S, ZT, 0, R / 16, LDB>(q, zreg, ldsB, li, g);
 #pragma unroll
         for (int z = 0; z < ZT; ++z) {
             float v = q[z];
             v += __shfl_xor(v, 16);
             v += __shfl_xor(v, 32);             // all four lanes of row li now hold q_i
             const long long row = rb + (wave * ZT + z) * 16 + li;
-            if (row < row_end) {
-                if (OUT == 0) {
-                    if (g == 0) {
-                        const float rn = beta2 * ldg(M.row_stat + row) + (1.f - beta2) * (alpha * alpha * v / (float)M.m + eps1);
-                        stg(M.row_stat + row, rn);
-                        total += rn;
-                    }
-                } else if (OUT == 1) {
-                    if (g == 0)
-                        stg(M.col_stat + row, beta2 * ldg(M.col_stat + row) + (1.f - beta2) * (alpha * alpha * v / (float)M.n + eps1));
-                } else if (g == 0) {
-                    total += v / ldg(M.row_stat + row);
-                }
-            }
-        }
-    }
-    if (OUT != 1) {
-        float t = total;
-        t += __shfl_xor(t, 8);
-        t += __shfl_xor(t, 4);
-        t += __shfl_xor(t, 2);
-        t += __shfl_xor(t, 1);
-        if (lane == 0) lds_fin[wave] = t;
-        __syncthreads();
-        if (tid == 0) {
-            float fin = 0.f;
-#pragma unroll
-            for (int w = 0; w < WAVES; ++w) fin += lds_fin[w];
-            if (OUT == 0) M.rowpart[it.part] = fin;
-            else M.itempart[it.part] = alpha * alpha * fin;
+            if (row < row_end && g == 0)
+                stg(M.col_stat + row, beta2 * ldg(M.col_stat + row) + (1.f - beta2) * (alpha * alpha * v / (float)M.n + eps1));
         }
     }
 }
 
 // The column statistics at ranks >= 128: K_j <- beta2 K_j + (1 - beta2) (alpha^2 A_j Q A_j^T / n + eps1),
 // rows A_j regenerated straight into matrix-core operand registers, Q in LDS.  The scheme of
-// quadform_kernel on v_mfma_f32_32x32x16_bf16: a wave owns 32 rows per round, D[k2][j] =
+// quadform_rows_kernel on v_mfma_f32_32x32x16_bf16: a wave owns 32 rows per round, D[k2][j] =
 // sum_k1 Q[k2][k1] A[j][k1] comes out with lane (j, g) holding k2 = 32 c + 8 a + 4 g + v, and the
 // contraction order is chosen (perm32w) so that the lane's own operand registers hold exactly
 // A[j][32 c + 8 a + 4 g + v].  Twice the rows per LDS read of Q and the faster tile shape.
@@ -674,9 +752,8 @@ hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, 
         if (src == 2) { hipLaunchKernelGGL((gram_kernel<R, 2>), grid, block, 0, s, mats, items, seeds); q = true; }
     }
     if (!p && !q && !p2) return hipErrorInvalidValue;
-    if (p) hipLaunchKernelGGL((combine_gram_kernel<R>), cgrid, dim3(256), 0, s, mats, 0);
+    if (p) hipLaunchKernelGGL((combine_gram_kernel<R>), dim3(cgrid.x, cgrid.y, p2 ? 2 : 1), dim3(256), 0, s, mats, 0);
     if (q) hipLaunchKernelGGL((combine_gram_kernel<R>), cgrid, dim3(256), 0, s, mats, 1);
-    if (p2) hipLaunchKernelGGL((combine_gram_kernel<R>), cgrid, dim3(256), 0, s, mats, 2);
     return hipGetLastError();
 }
 
@@ -684,20 +761,16 @@ template <int R>
 hipError_t launch_quadform_r(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, int out,
                              float alpha, float beta2, float eps1, hipStream_t s)
 {
-    // r = 256: the operand registers of a row tile are a quarter of a 128-register budget, so 16
-    // waves with one row tile each; below that 8 waves with two
-    constexpr int W = R >= 256 ? 16 : 8, ZT = R >= 256 ? 1 : 2;
-    const dim3 grid((unsigned)nitems), block(64 * W);
-    if constexpr (R >= 128) {
-        if (out == 1) {
-            hipLaunchKernelGGL((quadform_cols_kernel<R, 16>), grid, dim3(1024), 0, s, mats, items, seeds, alpha, beta2, eps1);
-            return hipGetLastError();
-        }
-    }
+    const dim3 grid((unsigned)nitems);
     switch (out) {
-    case 0: hipLaunchKernelGGL((quadform_kernel<R, 0, 0, W, ZT>), grid, block, 0, s, mats, items, seeds, alpha, beta2, eps1); break;
-    case 1: hipLaunchKernelGGL((quadform_kernel<R, 1, 1, W, ZT>), grid, block, 0, s, mats, items, seeds, alpha, beta2, eps1); break;
-    case 2: hipLaunchKernelGGL((quadform_kernel<R, 0, 2, W, ZT>), grid, block, 0, s, mats, items, seeds, alpha, beta2, eps1); break;
+    case 0: hipLaunchKernelGGL((quadform_rows_kernel<R, false>), grid, dim3(512), 0, s, mats, items, alpha, beta2, eps1); break;
+    case 2: hipLaunchKernelGGL((quadform_rows_kernel<R, true>), grid, dim3(512), 0, s, mats, items, alpha, beta2, eps1); break;
+    case 1:
+        if constexpr (R >= 128)
+            hipLaunchKernelGGL((quadform_cols_kernel<R, 16>), grid, dim3(1024), 0, s, mats, items, seeds, alpha, beta2, eps1);
+        else
+            hipLaunchKernelGGL((quadform_cols_small_kernel<R, 2>), grid, dim3(512), 0, s, mats, items, seeds, alpha, beta2, eps1);
+        break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -720,8 +793,8 @@ hipError_t launch_gram(const MatDev* mats, const WorkItem* items, int nitems, in
     }
 }
 
-// out 0: row sums of Gt^2 (Z = S, B = P) into the row statistics, 1: column sums (Z = A, B = Q) into the
-// column statistics, 2: the clipping sum (Z = S, B = P')
+// out 0: row sums of Gt^2 (Z = S, B = P) into the row statistics, 2: the same and the clipping sum (B = P'),
+// 1: column sums (Z = A, B = Q) into the column statistics
 hipError_t launch_quadform(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, int r, int out,
                            float alpha, float beta2, float eps1, hipStream_t s)
 {

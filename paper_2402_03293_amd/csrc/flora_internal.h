@@ -266,7 +266,8 @@ constexpr int kApplyTRows = 32;          // rows per workgroup, state <- state T
 constexpr int kApplyTRowsBig = 64;       // ... ranks 64 and above
 constexpr int kTransferChunk = 1024;     // columns per workgroup of the T kernel, ranks 64 and above
 constexpr int kSumsqBlocks = 256;        // workgroups per matrix, sum of W^2
-constexpr int kGramChunk = 3072;         // long-index entries per workgroup of the Gram sums
-constexpr int kQuadformRows = 1024;      // rows of Z per workgroup of the quadratic forms
+constexpr int kGramChunk = 3072;         // long-index entries per workgroup of the Gram sums, at most
+constexpr int kQuadformRows = 256;       // rows of S per workgroup of the quadratic forms
+constexpr int kQuadformCols = 1024;      // rows of A per workgroup of the column statistics, at most
 
 }  // namespace flora
