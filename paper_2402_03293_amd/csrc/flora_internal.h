@@ -245,7 +245,7 @@ hipError_t launch_decompress_bf16(const MatDev* mats, const WorkItem* items, int
 hipError_t launch_transfer_T(const MatDev* mats, const WorkItem* items, int nitems, int count, int r, hipStream_t s);
 hipError_t launch_apply_T(const MatDev* mats, const WorkItem* items, int nitems, int r, float ca, float cb,
                           hipStream_t s);
-hipError_t launch_stats_finalize(const MatDev* mats, int count, float beta2, float eps1, int gram, hipStream_t s);
+hipError_t launch_stats_finalize(const MatDev* mats, int count, float beta2, float eps1, hipStream_t s);
 hipError_t launch_rms_finalize(const MatDev* mats, int count, float clip_d, int scale_parameter, float eps2, int gram,
                                hipStream_t s);
 hipError_t launch_gram(const MatDev* mats, const WorkItem* items, int nitems, int count, const SeedArgs& seeds, int r,
