@@ -45,8 +45,8 @@
  *     hands the library a buffer with flora_set_workspace(): from then on everything above is
  *     carved from the caller's buffer and the library calls neither hipMalloc nor hipHostMalloc.
  *     Either way a call whose pointers have been seen before uploads nothing; one with new
- *     pointers (another buffer of a ring, a freshly allocated gradient) costs one small
- *     asynchronous copy and no allocation or synchronisation, so calling once per matrix from a
+ *     pointers (another buffer of a ring, a freshly allocated gradient) costs one small upload
+ *     on the stream and no allocation or synchronisation, so calling once per matrix from a
  *     training loop stays cheap.  No per-matrix state (seed, step, epoch) is kept between calls:
  *     that lives with the caller.
  *   - HIP graphs.  A call whose shapes and pointers have been seen on its stream is kernel
@@ -55,8 +55,8 @@
  *     tables and descriptor images, so these must stay where they are for as long as the graph is
  *     replayed: between capture and the last replay do not call flora_set_tuning,
  *     flora_set_workspace or flora_shutdown, do not let calls with other pointer sets on the same
- *     shapes push the captured image out (the library keeps the 16 most recently used images
- *     per plan for sets of more than 32 matrices, 64 for sets of 5 to 32, 512 for smaller ones;
+ *     shapes push the captured image out (the library keeps the 64 most recently used images
+ *     per plan for sets of more than 4 matrices, 512 for smaller ones;
  *     8 with a caller-owned workspace), and stay below 1024 distinct (shape set, stream, entry
  *     point) combinations.
  *   - Calls on one stream execute in order.  Calls issued concurrently from

@@ -56,8 +56,8 @@ struct Image {
     uint64_t hash = 0;
     MatDev* d_mats = nullptr;    // device copy (inside one of the plan's slabs)
     char* h_stage = nullptr;     // pinned staging of the same size
-    hipEvent_t ev = nullptr;     // recorded after the upload
-    bool ev_pending = false;
+    uint32_t* done = nullptr;    // pinned: the upload kernel leaves `gen` here once it has read the staging
+    uint32_t gen = 0;            // number of this slot's uploads
     uint64_t tick = 0;
 };
 
@@ -128,6 +128,7 @@ struct Arena {
     size_t used = 0;
 };
 Arena g_ws;
+constexpr size_t kDoneBytes = 64;       // an image's upload mark in pinned memory, a line of its own
 constexpr int kArenaImages = 8;         // descriptor images per plan in the caller's workspace
 
 // Launch-shape knobs, settable through flora_set_tuning (0 = let the library choose).
@@ -152,15 +153,13 @@ uint64_t g_tick = 0;
 
 void free_plan(Plan* p)
 {
-    for (Image& im : p->images) {
-        if (im.ev_pending) (void)hipEventSynchronize(im.ev);
-        if (im.ev) (void)hipEventDestroy(im.ev);
-    }
     if (!p->in_arena) {
-        // hipFree waits for the device, so kernels still reading these buffers have finished
+        // hipFree waits for the device, so kernels still reading these buffers (the pinned staging
+        // too, freed last) have finished
         if (p->d_tables) (void)hipFree(p->d_tables);
         if (p->d_work) (void)hipFree(p->d_work);
         for (void* d : p->dev_slabs) (void)hipFree(d);
+        if (!p->d_tables && !p->d_work && p->dev_slabs.empty()) (void)hipDeviceSynchronize();
         for (void* h : p->pin_slabs) (void)hipHostFree(h);
         if (p->h_tables) (void)hipHostFree(p->h_tables);
     }
@@ -694,9 +693,10 @@ void build_host_plan(Plan* p, const std::vector<MatDev>& mats)
     if (kind == kKindCompress) p->wbytes = round_up(p->ws_floats * 4, 256) + p->ws_counters * 4;
     p->mats_bytes = round_up(sizeof(MatDev) * (size_t)count, 256);
     // descriptor images kept per plan: many for calls on a few matrices (a training loop that
-    // steps one layer per call cycles through hundreds of pointer sets), a few for large sets
-    p->image_cap = count <= 4 ? 512 : (count <= 32 ? 64 : 16);
-    p->images_per_slab = (int)std::max<size_t>(1, std::min<size_t>(64, (64 * 1024) / p->mats_bytes));
+    // steps one layer per call cycles through hundreds of pointer sets), 64 for others (a cycle of 8 or 16
+    // micro-batches with a gradient buffer each, several times over)
+    p->image_cap = count <= 4 ? 512 : 64;
+    p->images_per_slab = (int)std::max<size_t>(8, std::min<size_t>(64, (64 * 1024) / p->mats_bytes));
 }
 
 // Device part: tables uploaded, work area ready.  In library-allocated memory, or (in_arena) at
@@ -869,14 +869,16 @@ int get_plan(int kind, int variant, int r, const std::vector<MatDev>& mats, hipS
             void* hp = nullptr;
             FLORA_HIP(hipMalloc(&d, p->mats_bytes * (size_t)p->images_per_slab));
             p->dev_slabs.push_back(d);
-            FLORA_HIP(hipHostMalloc(&hp, p->mats_bytes * (size_t)p->images_per_slab, hipHostMallocDefault));
+            FLORA_HIP(hipHostMalloc(&hp, (p->mats_bytes + kDoneBytes) * (size_t)p->images_per_slab, hipHostMallocDefault));
             p->pin_slabs.push_back(hp);
         }
         Image im;
         im.d_mats = reinterpret_cast<MatDev*>(static_cast<char*>(p->dev_slabs[(size_t)slab]) + p->mats_bytes * (size_t)within);
         if (!p->in_arena) {
-            im.h_stage = static_cast<char*>(p->pin_slabs[(size_t)slab]) + p->mats_bytes * (size_t)within;
-            FLORA_HIP(hipEventCreateWithFlags(&im.ev, hipEventDisableTiming));
+            char* hp = static_cast<char*>(p->pin_slabs[(size_t)slab]);
+            im.h_stage = hp + p->mats_bytes * (size_t)within;
+            im.done = reinterpret_cast<uint32_t*>(hp + p->mats_bytes * (size_t)p->images_per_slab + kDoneBytes * (size_t)within);
+            *im.done = 0;
         }
         p->images.push_back(std::move(im));
     } else {
@@ -893,7 +895,8 @@ int get_plan(int kind, int variant, int r, const std::vector<MatDev>& mats, hipS
                 p->index.erase(it);
                 break;
             }
-        if (old.ev_pending) { FLORA_HIP(hipEventSynchronize(old.ev)); old.ev_pending = false; }
+        // (long done as a rule: image_cap calls ago; otherwise the stream is waited for)
+        if (old.done && __atomic_load_n(old.done, __ATOMIC_ACQUIRE) != old.gen) FLORA_HIP(hipStreamSynchronize(stream));
     }
     Image& im = p->images[(size_t)slot];
     im.img = img;
@@ -904,9 +907,7 @@ int get_plan(int kind, int variant, int r, const std::vector<MatDev>& mats, hipS
         FLORA_HIP(hipMemcpyAsync(im.d_mats, im.img.data(), ibytes, hipMemcpyHostToDevice, stream));
     } else {
         std::memcpy(im.h_stage, img.data(), ibytes);
-        FLORA_HIP(hipMemcpyAsync(im.d_mats, im.h_stage, ibytes, hipMemcpyHostToDevice, stream));
-        FLORA_HIP(hipEventRecord(im.ev, stream));
-        im.ev_pending = true;
+        FLORA_HIP(launch_upload_image(im.h_stage, im.d_mats, p->mats_bytes, im.done, ++im.gen, stream));
     }
     p->index.emplace(h, slot);
     p->cur_mats = im.d_mats;

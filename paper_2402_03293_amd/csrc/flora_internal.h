@@ -254,6 +254,7 @@ hipError_t launch_quadform(const MatDev* mats, const WorkItem* items, int nitems
                            float alpha, float beta2, float eps1, hipStream_t s);
 hipError_t launch_wsumsq_finalize(const MatDev* mats, int count, hipStream_t s);
 hipError_t launch_weight_sumsq(const MatDev* mats, int count, int weight_is_bf16, float* partials, hipStream_t s);
+hipError_t launch_upload_image(const void* src, void* dst, size_t bytes, uint32_t* done, uint32_t gen, hipStream_t s);
 hipError_t launch_zero_state(const MatDev* mats, int count, int r, hipStream_t s);
 
 // Tiling constants the host needs to build work tables.
