@@ -1,8 +1,8 @@
 // Momentum transfer (Algorithm 2, resample branch):
 //     M <- M A_old^T A_new
 // computed in the re-associated order T = A_old^T A_new (r x r), M <- M T, so
-// that no n x m intermediate exists.  Everything stays fp32 (fp32 matrix
-// cores): an error made here would be carried by every later step.
+// that no n x m intermediate exists.  Everything keeps fp32 precision: an error made here would
+// be carried by every later step.
 //
 // Ranks 8 / 16 / 32 (T is tiny):
 // transfer_T: one workgroup owns up to 32 rows k1 of T and all r columns,
@@ -13,15 +13,12 @@
 // apply_T: one workgroup owns 32 rows of M, keeps them in LDS, multiplies by
 //   T (read through the caches) and writes the rows back in place.
 //
-// Ranks 64 / 128 / 256 (2 m r^2 + 2 n r^2 flops per matrix, all fp32):
-// transfer_T_big: one workgroup (8 waves) owns a slab of up to 128 rows of T,
-//   all r columns and a chunk of 1024 of the m columns j, so the work of a
-//   launch is many equal pieces and the new projection is regenerated only
-//   r / 128 times; the generator's tiles are double buffered in LDS.  Chunk
+// Ranks 64 / 128 / 256 (2 m r^2 + 2 n r^2 flops per matrix): fp32 products as sums of products of bf16
+//   parts, see below.
+// transfer_T_split: one workgroup owns all of T (or half of it) and a chunk of 1024 of the m columns j, so
+//   the work of a launch is many equal pieces; the generator's tiles are double buffered in LDS.  Chunk
 //   partials are added in chunk order by combine_T (fixed order, no atomics).
-// apply_T_big: one workgroup owns 64 rows of M; a wave keeps its 16 rows in
-//   registers as the A operand (16 rows x 64 contiguous bytes per load), T
-//   streams through LDS in chunks of 16 rows shared by the four waves.
+// apply_T_split: one workgroup owns 64 rows of M.
 #include "flora_gen.hip.h"
 #include "flora_internal.h"
 
@@ -186,180 +183,322 @@ __global__ __launch_bounds__(256) void apply_T_kernel(const MatDev* __restrict__
 }
 
 
-template <int R>
-__global__ __launch_bounds__(512) void transfer_T_big_kernel(const MatDev* __restrict__ mats,
-                                                             const WorkItem* __restrict__ items)
-{
-    constexpr int SLAB = (R < 128) ? R : 128;     // rows of T per workgroup
-    constexpr int NTR = SLAB / 16;                // 16-row tiles of the slab: one per wave (or per pair)
-    constexpr int NH = 8 / NTR;                   // waves that share a row tile split the columns
-    constexpr int NT2W = (R / 16) / NH;           // column tiles per wave
-    constexpr int P1 = SLAB + 16, P2 = R + 16;    // row strides = 16 mod 32 banks: the four j of an
-                                                  // MFMA step land in different halves of the banks
-    constexpr int NQ = (SLAB + R) / 4;            // quads per column j (old slab, then new)
-    constexpr int QPT = 32 * NQ / 512;            // quads per thread and tile
-    __shared__ __attribute__((aligned(16))) float ldsOld[2][kBJ][P1];
-    __shared__ __attribute__((aligned(16))) float ldsNew[2][kBJ][P2];
+// ---------------------------------------------------------------------------
+// Ranks 64 and above: fp32 products on the bf16 matrix cores.  An fp32 value is the exact sum of three bf16
+// values, hi + mid + lo (8 significand bits each), and a product of two of them is the sum of nine
+// products of parts, of which the six below 2^-24 of the whole are kept: lo hi, hi lo, mid mid, mid hi,
+// hi mid, hi hi.  v_mfma_f32_32x32x16_bf16 does six of those in 0.4 of the time that
+// v_mfma_f32_16x16x4_f32 takes for the product (2200 / 6 against 140 TFLOP/s).  In the long sums over
+// columns every 16 contracted indexes are summed from zero, smallest parts first, and added to the
+// accumulator once: a quarter of the roundings at the accumulator's size that the fp32 instruction
+// makes.  Error of state A^T A' against 64 bits on the GPT-2 XL set at r = 256: 4.7e-7 with fp32
+// instructions, 2.5e-7 so.
+constexpr int kKT = 16;            // contracted indexes per tile
+constexpr int kLdk = kKT + 8;      // padded LDS row (bf16 elements): 48 bytes, conflict-free 16-byte reads
 
-    const WorkItem it = items[blockIdx.x];
+// x0, x1 -> packed hi, mid, lo parts.  hi is cut off, not rounded, so that no finite value becomes
+// infinite; infinities and NaNs stay in hi alone.
+template <bool FINITE>
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo)
+{
+    uint32_t h0 = __float_as_uint(x0) & 0xffff0000u, h1 = __float_as_uint(x1) & 0xffff0000u;
+    float r0 = x0 - __uint_as_float(h0), r1 = x1 - __uint_as_float(h1);
+    if (!FINITE) {
+        h0 = __builtin_amdgcn_classf(x0, 0x003) ? 0x7fc00000u : h0;       // NaN
+        h1 = __builtin_amdgcn_classf(x1, 0x003) ? 0x7fc00000u : h1;
+        r0 = __builtin_amdgcn_classf(x0, 0x207) ? 0.f : r0;               // NaN or infinite
+        r1 = __builtin_amdgcn_classf(x1, 0x207) ? 0.f : r1;
+    }
+    hi = (h0 >> 16) | h1;
+    mid = pack_bf16x2(r0, r1);
+    lo = pack_bf16x2(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u));
+}
+
+// Rows of 32 bytes: the two halves of every other eight rows change places, which makes 16-byte reads of 16
+// rows at one k conflict-free (k ^ half_swap(row)).
+__device__ __forceinline__ int half_swap(int row) { return row & 8; }
+
+// acc += a b over 16 contracted indexes, both given as their three parts (hi, mid, lo)
+__device__ __forceinline__ void mfma_split(f32x16& acc, const bf16x8 (&a)[3], const bf16x8 (&b)[3])
+{
+    f32x16 t;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t[v] = 0.f;
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], t, 0, 0, 0);
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], t, 0, 0, 0);
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], t, 0, 0, 0);
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], t, 0, 0, 0);
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], t, 0, 0, 0);
+    t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], t, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] += t[v];
+    asm volatile("" : "+v"(acc));      // (the additions stay here: put off, every tile's t would be alive at once)
+}
+
+// The same added to the accumulator part by part: more roundings, but no additions on the vector ALU
+__device__ __forceinline__ void mfma_split_direct(f32x16& acc, const bf16x8 (&a)[3], const bf16x8 (&b)[3])
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
+}
+
+// Partial T = A_old^T A_new over a chunk of columns: SLAB rows of T (all of them, so that A_new is
+// regenerated once, or, in launches of few chunks, half), R columns.  Tiles of 16 columns of both
+// projections are regenerated, split and stored to LDS by rank row ([part][k][j], double buffered); half
+// of the waves produce the next tile before they multiply the current one, the others after.
+// RG x CG waves of WR x WC tiles of 32 x 32.
+template <int R, int SLAB, int WR, int WC>
+__global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64) void transfer_T_split_kernel(const MatDev* __restrict__ mats,
+                                                                                              const WorkItem* __restrict__ items,
+                                                                                              int item_step)
+{
+    constexpr int RG = SLAB / 32 / WR, NW = RG * (R / 32 / WC), T = 64 * NW;
+    constexpr int ROWS = SLAB + R;                 // rank rows in LDS: SLAB of the old projection, then R of the new
+    constexpr int NU = 8 * (ROWS / 4);             // units of a tile: (pair of columns, quad)
+    __shared__ __attribute__((aligned(16))) uint16_t lds[2][3][ROWS][kLdk];
+
+    const WorkItem it = items[blockIdx.x * item_step];
     const MatDev& M = mats[it.mat];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 15, jg = lane >> 4;
-    const int tr = wave % NTR, th = wave / NTR;
+    const int ln = lane & 31, g = lane >> 5;
+    const int rt0 = (wave % RG) * WR, ct0 = (wave / RG) * WC;
     const float cgen = neg2_ln2_over(R);
     const uint32_t so_lo = M.seed_lo, so_hi = M.seed_hi, sn_lo = M.seedn_lo, sn_hi = M.seedn_hi;
-    const long long jbeg = it.col0, jend = it.col1;           // this chunk's columns
-    const int ntiles = (int)((jend - jbeg + kBJ - 1) / kBJ);
+    const uint32_t jbeg = (uint32_t)it.col0, jend = (uint32_t)it.col1;       // this chunk's columns
+    const int ntiles = (int)((jend - jbeg + kKT - 1) / kKT);
     const uint32_t qold0 = (uint32_t)(it.slice * (SLAB / 4));
 
-    auto gen_tile = [&](int buf, int tile) {
-        const long long j0 = jbeg + (long long)tile * kBJ;
+    auto produce = [&](int buf, int tile) {
 #pragma unroll
-        for (int i = 0; i < QPT; ++i) {
-            const int idx = tid + 512 * i;
-            const int q = idx % NQ, jl = idx / NQ;
-            const long long j = j0 + jl;
-            // (one generator call with selected arguments: lanes of a wave may be on either side)
-            const bool isold = q < SLAB / 4;
-            const Quad z = normal_quad(isold ? so_lo : sn_lo, isold ? so_hi : sn_hi, (uint32_t)j,
-                                       isold ? qold0 + (uint32_t)q : (uint32_t)(q - SLAB / 4), cgen);
-            const bool ok = j < jend;
-            const v4f v = {ok ? z.z[0] : 0.f, ok ? z.z[1] : 0.f, ok ? z.z[2] : 0.f, ok ? z.z[3] : 0.f};
-            if (isold) *reinterpret_cast<v4f*>(&ldsOld[buf][jl][4 * q]) = v;
-            else *reinterpret_cast<v4f*>(&ldsNew[buf][jl][4 * (q - SLAB / 4)]) = v;
+        for (int u0 = 0; u0 < NU; u0 += T) {
+            const int u = u0 + tid;
+            if (NU % T != 0 && u >= NU) break;
+            const int q = u >> 3, jp = 2 * (u & 7);
+            const uint32_t j = jbeg + (uint32_t)tile * kKT + (uint32_t)jp;
+            // (the 64 units of a wave are on one side)
+            const bool isold = __builtin_amdgcn_readfirstlane(q) < SLAB / 4;
+            const uint32_t s_lo = isold ? so_lo : sn_lo, s_hi = isold ? so_hi : sn_hi;
+            const uint32_t qq = isold ? qold0 + (uint32_t)q : (uint32_t)(q - SLAB / 4);
+            const Quad z0 = normal_quad(s_lo, s_hi, j, qq, cgen);
+            __builtin_amdgcn_sched_barrier(0);      // (one quad at a time: the registers are the accumulators')
+            const Quad z1 = normal_quad(s_lo, s_hi, j + 1, qq, cgen);
+            __builtin_amdgcn_sched_barrier(0);
+            const bool ok0 = j < jend, ok1 = j + 1 < jend;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                uint32_t h, m, l;
+                split3<true>(ok0 ? z0.z[i] : 0.f, ok1 ? z1.z[i] : 0.f, h, m, l);
+                *reinterpret_cast<uint32_t*>(&lds[buf][0][4 * q + i][jp]) = h;
+                *reinterpret_cast<uint32_t*>(&lds[buf][1][4 * q + i][jp]) = m;
+                *reinterpret_cast<uint32_t*>(&lds[buf][2][4 * q + i][jp]) = l;
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
 
-    f32x4 acc[NT2W];
+    f32x16 acc[WR][WC];
 #pragma unroll
-    for (int b = 0; b < NT2W; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int r = 0; r < WR; ++r)
+#pragma unroll
+        for (int c = 0; c < WC; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
 
-    gen_tile(0, 0);
+    const bool produce_first = ((wave >> 2) & 1) == 0;       // (waves w, w + 4, ... share a SIMD)
+    produce(0, 0);
     __syncthreads();
     for (int tile = 0; tile < ntiles; ++tile) {
         const int buf = tile & 1;
-        if (tile + 1 < ntiles) gen_tile(buf ^ 1, tile + 1);
+        if (produce_first && tile + 1 < ntiles) produce(buf ^ 1, tile + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        bf16x8 av[WR][3];
 #pragma unroll
-        for (int c = 0; c < kBJ / 4; ++c) {
-            const float av = ldsOld[buf][4 * c + jg][tr * 16 + li];
+        for (int r = 0; r < WR; ++r)
 #pragma unroll
-            for (int b = 0; b < NT2W; ++b) {
-                const float bv = ldsNew[buf][4 * c + jg][(th * NT2W + b) * 16 + li];
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[b], 0, 0, 0);
-            }
+            for (int p = 0; p < 3; ++p) av[r][p] = *reinterpret_cast<const bf16x8*>(&lds[buf][p][32 * (rt0 + r) + ln][8 * g]);
+#pragma unroll
+        for (int c = 0; c < WC; ++c) {
+            bf16x8 bv[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) bv[p] = *reinterpret_cast<const bf16x8*>(&lds[buf][p][SLAB + 32 * (ct0 + c) + ln][8 * g]);
+#pragma unroll
+            for (int r = 0; r < WR; ++r) mfma_split(acc[r][c], av[r], bv);
+            __builtin_amdgcn_sched_barrier(0);      // (or every column tile's operands are fetched first, and spill)
         }
+        if (!produce_first && tile + 1 < ntiles) produce(buf ^ 1, tile + 1);
         __syncthreads();
     }
 
-    // partial T of this chunk: rows it.slice * SLAB + tr * 16 + 4 jg + v, column (th NT2W + b) 16 + li
+    // D layout of a 32 x 32 tile: lane holds column ln and rows 8 (v / 4) + 4 g + v % 4
     float* part = M.rowpart + (size_t)it.part * R * R;
 #pragma unroll
-    for (int b = 0; b < NT2W; ++b)
+    for (int r = 0; r < WR; ++r)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int k1 = it.slice * SLAB + tr * 16 + 4 * jg + v;
-            const int k2 = (th * NT2W + b) * 16 + li;
-            stg(part + k1 * R + k2, acc[b][v]);
-        }
+        for (int c = 0; c < WC; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int k1 = it.slice * SLAB + 32 * (rt0 + r) + 8 * (v / 4) + 4 * g + (v % 4);
+                stg(part + k1 * R + 32 * (ct0 + c) + ln, acc[r][c][v]);
+            }
 }
 
-// T <- sum over the chunks of their partials, in chunk order
+// T <- sum over the chunks of their partials, in chunk order, left in three parts for the kernel below in the
+// order it copies them to LDS: per 16 rows k1 of T (one workgroup) [part][k2][16 k1] bf16, hi and mid where
+// T lies, lo over the same rows of the first chunk's partial, which nobody else reads.
 template <int R>
-__global__ __launch_bounds__(256) void combine_T_kernel(const MatDev* __restrict__ mats)
+__global__ __launch_bounds__(4 * R) void combine_T_kernel(const MatDev* __restrict__ mats)
 {
     const MatDev& M = mats[blockIdx.y];
-    const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;
-    if (idx >= R * R) return;
-    v4f s = {0.f, 0.f, 0.f, 0.f};
-    for (int c = 0; c < M.ncolchunks; ++c) {
-        const v4f p = ldg4(M.rowpart + (size_t)c * R * R + idx);
-        s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+    const int b = blockIdx.x, k2 = threadIdx.x % R, sub = threadIdx.x / R;       // rows 16 b + 4 sub .. + 3
+    const float* src = M.rowpart + (size_t)(kKT * b + 4 * sub) * R + k2;
+    const int nch = M.ncolchunks;
+    float s[4] = {0.f, 0.f, 0.f, 0.f};
+    int c = 0;
+    for (; c + 2 <= nch; c += 2) {                 // eight loads in flight
+        float v[2][4];
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[e][i] = ldg(src + (size_t)(c + e) * R * R + i * R);
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] += v[e][i];
     }
-    *reinterpret_cast<FLORA_GLOBAL v4f*>((FLORA_GLOBAL float*)(M.T + idx)) = s;
+    if (c < nch)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s[i] += ldg(src + (size_t)c * R * R + i * R);
+    uint32_t h[2], m[2], l2[2];
+    split3<true>(s[0], s[1], h[0], m[0], l2[0]);
+    split3<true>(s[2], s[3], h[1], m[1], l2[1]);
+    __syncthreads();                               // these rows of the first partial have been read
+    FLORA_GLOBAL v2u* t = (FLORA_GLOBAL v2u*)(M.T + (size_t)(kKT * b) * R);
+    FLORA_GLOBAL v2u* l = (FLORA_GLOBAL v2u*)(M.rowpart + (size_t)(kKT * b) * R);
+    t[4 * k2 + sub] = v2u{h[0], h[1]};
+    t[4 * R + 4 * k2 + sub] = v2u{m[0], m[1]};
+    l[4 * k2 + sub] = v2u{l2[0], l2[1]};
 }
 
-template <int R>
-__global__ __launch_bounds__(256) void apply_T_big_kernel(const MatDev* __restrict__ mats,
-                                                          const WorkItem* __restrict__ items, float ca, float cb)
+// 64 rows of the state times T.  A wave owns WC tiles of 32 columns and all the rows.  Per 16 indexes k1 the
+// rows are split into LDS (double buffered, fetched a step ahead); T's parts lie in memory as the operands
+// want them and go straight to registers, a step ahead too.  All rows are read before any is stored,
+// so the destination may be the state itself.
+// On the GPT-2 XL set at r = 256: 1.03 ms with fp32 instructions, 0.65 with T's parts passed through LDS, 0.59
+// so; the products alone take 0.39 and the states' traffic alone 0.27, which three workgroups per compute
+// unit overlap in part (128 or 256 rows per workgroup, for less traffic of T: 0.63 and 0.68).
+template <int R, int WC>
+__global__ __launch_bounds__((R / 32 / WC) * 64, 3) void apply_T_split_kernel(const MatDev* __restrict__ mats,
+                                                                               const WorkItem* __restrict__ items, float ca, float cb)
 {
-    constexpr int NT2 = R / 16;
-    constexpr int KC = R / 16;          // chunks of 16 rows of T
-    constexpr int P = R + 4;            // row stride = 4 mod 32 banks
-    constexpr int F4 = 16 * R / 4 / 256;   // float4 loads per thread and chunk
-    __shared__ __attribute__((aligned(16))) float ldsT[2][16][P];
+    constexpr int TH = (R / 32 / WC) * 64, WR = 2;
+    constexpr int ROWS = 64, STEPS = R / kKT;
+    constexpr int FA = ROWS * kKT / 2 / TH;        // pairs of state entries per thread and step
+    static_assert((ROWS * kKT / 2) % TH == 0, "whole pairs per thread");
+    __shared__ __attribute__((aligned(16))) uint16_t ldsA[2][3][ROWS][kKT];
 
     const WorkItem it = items[blockIdx.x];
     const MatDev& M = mats[it.mat];
-    const long long n = M.n;
-    const float* state = M.state;
-    float* dst = M.out ? reinterpret_cast<float*>(M.out) : M.state;
-    const float* __restrict__ T = M.T;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int li = lane & 15, jg = lane >> 4;
+    const int ln = lane & 31, g = lane >> 5;
+    const int ct0 = wave * WC;
+    const long long row0 = it.row0;
+    const long long row_end = row0 + it.rows < M.n ? row0 + it.rows : M.n;
+    const float* T = M.T;
+    const float* Tlo = M.rowpart;
+    float* dst = M.out ? reinterpret_cast<float*>(M.out) : M.state;
 
-    // A operand: row li of this wave's 16 rows, columns 16 c + 4 jg .. + 3 for every chunk c.
-    // MFMA step (c, t) contracts the index set { 16 c + 4 jg + t : jg < 4 }; the B operand
-    // below follows the same order.  Everything is loaded before anything is stored, so the
-    // destination may be the state itself.
-    long long arow = (long long)it.row0 + wave * 16 + li;
-    if (arow > n - 1) arow = n - 1;
-    v4f areg[KC];
+    v2f sa[FA];
+    auto fetch_A = [&](int step) {
 #pragma unroll
-    for (int c = 0; c < KC; ++c) areg[c] = ldg4(state + arow * R + 16 * c + 4 * jg);
-
-    auto fetch_T = [&](v4f (&stage)[F4], int c) {
-#pragma unroll
-        for (int i = 0; i < F4; ++i) {
-            const int f = tid + 256 * i;            // float4 number within the 16 x R chunk
-            stage[i] = ldg4(T + (size_t)(16 * c + f / (R / 4)) * R + 4 * (f % (R / 4)));
+        for (int i = 0; i < FA; ++i) {
+            const int f = tid + TH * i, rr = f >> 3, k = 2 * (f & 7);
+            const long long row = row0 + rr < row_end ? row0 + rr : row_end - 1;
+            sa[i] = ldg2(M.state + row * R + kKT * step + k);
         }
     };
-    auto stash_T = [&](const v4f (&stage)[F4], int buf) {
+    auto stash_A = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < F4; ++i) {
-            const int f = tid + 256 * i;
-            *reinterpret_cast<v4f*>(&ldsT[buf][f / (R / 4)][4 * (f % (R / 4))]) = stage[i];
+        for (int i = 0; i < FA; ++i) {
+            const int f = tid + TH * i, rr = f >> 3, k = (2 * (f & 7)) ^ half_swap(rr);
+            uint32_t h, m, l;
+            split3<false>(sa[i].x, sa[i].y, h, m, l);
+            *reinterpret_cast<uint32_t*>(&ldsA[buf][0][rr][k]) = h;
+            *reinterpret_cast<uint32_t*>(&ldsA[buf][1][rr][k]) = m;
+            *reinterpret_cast<uint32_t*>(&ldsA[buf][2][rr][k]) = l;
         }
     };
-
-    f32x4 acc[NT2];
+    v4u tb[2][WC][3];
+    auto fetch_T = [&](int step) {
 #pragma unroll
-    for (int b = 0; b < NT2; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < WC; ++c)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                tb[step & 1][c][p] = ldg4(reinterpret_cast<const uint16_t*>((p == 2 ? Tlo : T) + (size_t)(kKT * step) * R) +
+                                          (p == 1 ? kKT * R : 0) + kKT * (32 * (ct0 + c) + ln) + 8 * g);
+    };
 
-    v4f stage[F4];
-    fetch_T(stage, 0);
-    stash_T(stage, 0);
+    f32x16 acc[WR][WC];
+#pragma unroll
+    for (int r = 0; r < WR; ++r)
+#pragma unroll
+        for (int c = 0; c < WC; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
+
+    fetch_A(0);
+    fetch_T(0);
+    stash_A(0);
+    fetch_A(1);
     __syncthreads();
+    // (unrolled: with branches around the fetches every wait is for all of them)
 #pragma unroll
-    for (int c = 0; c < KC; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < KC) fetch_T(stage, c + 1);
+    for (int step = 0; step < STEPS; ++step) {
+        const int buf = step & 1;
+        const int k = (8 * g) ^ half_swap(ln);
+        if (step + 1 < STEPS) fetch_T(step + 1);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const float av = areg[c][t];
+        for (int r = 0; r < WR; ++r) {
+            bf16x8 av[3];
 #pragma unroll
-            for (int b = 0; b < NT2; ++b)
-                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, ldsT[buf][4 * jg + t][b * 16 + li], acc[b], 0, 0, 0);
+            for (int p = 0; p < 3; ++p) av[p] = *reinterpret_cast<const bf16x8*>(&ldsA[buf][p][32 * r + ln][k]);
+#pragma unroll
+            for (int c = 0; c < WC; ++c) {
+                const bf16x8 bv[3] = {__builtin_bit_cast(bf16x8, tb[buf][c][0]), __builtin_bit_cast(bf16x8, tb[buf][c][1]),
+                                      __builtin_bit_cast(bf16x8, tb[buf][c][2])};
+                mfma_split_direct(acc[r][c], av, bv);
+            }
         }
-        if (c + 1 < KC) stash_T(stage, buf ^ 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if (step + 1 < STEPS) stash_A(buf ^ 1);
+        if (step + 2 < STEPS) fetch_A(step + 2);
         __syncthreads();
     }
 
+    // (old values of a row of tiles first: few round trips)
 #pragma unroll
-    for (int b = 0; b < NT2; ++b)
+    for (int r = 0; r < WR; ++r) {
+        auto at = [&](int v) { return row0 + 32 * r + 8 * (v / 4) + 4 * g + (v % 4); };
+        float old[WC][16];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const long long row = (long long)it.row0 + wave * 16 + 4 * jg + v;
-            if (row < n && row < (long long)it.row0 + it.rows) {
-                float* o = dst + row * R + b * 16 + li;
-                const float old = (ca != 0.f) ? ldg(o) : 0.f;
-                stg(o, ca * old + cb * acc[b][v]);
-            }
-        }
+        for (int c = 0; c < WC; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                old[c][v] = (ca != 0.f && at(v) < row_end) ? ldg(dst + at(v) * R + 32 * (ct0 + c) + ln) : 0.f;
+#pragma unroll
+        for (int c = 0; c < WC; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (at(v) < row_end) stg(dst + at(v) * R + 32 * (ct0 + c) + ln, ca * old[c][v] + cb * acc[r][c][v]);
+    }
 }
 
 }  // namespace
@@ -368,20 +507,26 @@ hipError_t launch_transfer_T(const MatDev* mats, const WorkItem* items, int nite
 {
     if (count == 0) return hipSuccess;
     if (r >= 64) {
-        // items: (matrix, chunk of columns, slab of rows of T); then the chunks are summed
+        // items: (matrix, chunk of columns, slab of up to 128 rows of T), the slabs of a chunk in a row;
+        // then the chunks are summed
         const dim3 grid((unsigned)nitems);
         switch (r) {
         case 64:
-            hipLaunchKernelGGL((transfer_T_big_kernel<64>), grid, dim3(512), 0, s, mats, items);
-            hipLaunchKernelGGL((combine_T_kernel<64>), dim3(64 * 64 / 1024, (unsigned)count), dim3(256), 0, s, mats);
+            hipLaunchKernelGGL((transfer_T_split_kernel<64, 64, 1, 1>), grid, dim3(256), 0, s, mats, items, 1);
+            hipLaunchKernelGGL((combine_T_kernel<64>), dim3(64 / kKT, (unsigned)count), dim3(4 * 64), 0, s, mats);
             break;
         case 128:
-            hipLaunchKernelGGL((transfer_T_big_kernel<128>), grid, dim3(512), 0, s, mats, items);
-            hipLaunchKernelGGL((combine_T_kernel<128>), dim3(128 * 128 / 1024, (unsigned)count), dim3(256), 0, s, mats);
+            hipLaunchKernelGGL((transfer_T_split_kernel<128, 128, 2, 1>), grid, dim3(512), 0, s, mats, items, 1);
+            hipLaunchKernelGGL((combine_T_kernel<128>), dim3(128 / kKT, (unsigned)count), dim3(4 * 128), 0, s, mats);
             break;
         case 256:
-            hipLaunchKernelGGL((transfer_T_big_kernel<256>), grid, dim3(512), 0, s, mats, items);
-            hipLaunchKernelGGL((combine_T_kernel<256>), dim3(256 * 256 / 1024, (unsigned)count), dim3(256), 0, s, mats);
+            // both slabs of a chunk by one workgroup, which then regenerates the new projection once; where
+            // that gives the chip fewer than a workgroup per compute unit, a workgroup each
+            if (nitems / 2 >= 256)
+                hipLaunchKernelGGL((transfer_T_split_kernel<256, 256, 1, 4>), dim3((unsigned)(nitems / 2)), dim3(1024), 0, s, mats, items, 2);
+            else
+                hipLaunchKernelGGL((transfer_T_split_kernel<256, 128, 2, 2>), grid, dim3(512), 0, s, mats, items, 1);
+            hipLaunchKernelGGL((combine_T_kernel<256>), dim3(256 / kKT, (unsigned)count), dim3(4 * 256), 0, s, mats);
             break;
         default: return hipErrorInvalidValue;
         }
@@ -411,9 +556,9 @@ hipError_t launch_apply_T(const MatDev* mats, const WorkItem* items, int nitems,
     case 8: hipLaunchKernelGGL((apply_T_kernel<8>), grid, block, 0, s, mats, items, ca, cb); break;
     case 16: hipLaunchKernelGGL((apply_T_kernel<16>), grid, block, 0, s, mats, items, ca, cb); break;
     case 32: hipLaunchKernelGGL((apply_T_kernel<32>), grid, block, 0, s, mats, items, ca, cb); break;
-    case 64: hipLaunchKernelGGL((apply_T_big_kernel<64>), grid, block, 0, s, mats, items, ca, cb); break;
-    case 128: hipLaunchKernelGGL((apply_T_big_kernel<128>), grid, block, 0, s, mats, items, ca, cb); break;
-    case 256: hipLaunchKernelGGL((apply_T_big_kernel<256>), grid, block, 0, s, mats, items, ca, cb); break;
+    case 64: hipLaunchKernelGGL((apply_T_split_kernel<64, 1>), grid, dim3(128), 0, s, mats, items, ca, cb); break;
+    case 128: hipLaunchKernelGGL((apply_T_split_kernel<128, 1>), grid, dim3(256), 0, s, mats, items, ca, cb); break;
+    case 256: hipLaunchKernelGGL((apply_T_split_kernel<256, 2>), grid, dim3(256), 0, s, mats, items, ca, cb); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -429,6 +429,42 @@ def test_transfer_accumulate(n, m, r, a, b):
     assert torch.equal(C, Cc)                     # the source is only read
 
 
+# The transfer's split products at the edges of its pieces: chunks of 1024 columns, tiles of 16 columns, blocks
+# of 64 rows, r = 256 with many chunks (a workgroup per chunk) and few (one per slab of T).  Bar: no larger
+# than the fp32 error of sums of this length, 2^-24 sqrt(m + r) at worst, plus the generator's 1e-7.
+@pytest.mark.parametrize("n,m,r,count", [(1, 1, 64, 1), (63, 15, 128, 2), (65, 17, 256, 1), (64, 1024, 64, 1), (130, 1025, 128, 1),
+                                         (129, 2047, 256, 1), (70, 1041, 256, 130), (5, 3000, 64, 3)])
+def test_transfer_split_products_at_edges(n, m, r, count):
+    S0 = [rand((n, r), 700 + l) for l in range(count)]
+    st = [x.clone() for x in S0]
+    so, sn = [31 + l for l in range(count)], [9031 + l for l in range(count)]
+    flora.momentum_transfer(flora.matrices([(n, m)] * count, states=st, seeds=so, seeds_next=sn), r)
+    sync()
+    for l in sorted({0, count // 2, count - 1}):
+        ref = oracle.transfer(to64(S0[l]), m, so[l], sn[l])
+        assert rel_fro(to64(st[l]), ref) < 2.0 ** -24 * (m + r) ** 0.5 + 4e-7, l
+
+
+# infinities and NaNs in a state stay in their rows, and what the fp32 product gives for them is what comes out
+@pytest.mark.parametrize("r", [64, 256])
+def test_transfer_of_states_that_are_not_finite(r):
+    n, m = 70, 300
+    S = rand((n, r), 77)
+    S[3, 5], S[40, 0], S[64, r - 1] = float("inf"), float("nan"), 3.3e38
+    M = S.clone()
+    flora.momentum_transfer(flora.matrices([(n, m)], states=[M], seeds=[5], seeds_next=[6]), r)
+    sync()
+    clean = rand((n, r), 77)
+    ref = oracle.transfer(to64(clean), m, 5, 6)
+    ok = [i for i in range(n) if i not in (3, 40, 64)]
+    assert rel_fro(to64(M)[ok], ref[ok]) < TOL_F32
+    assert not torch.isfinite(M[3]).any() and torch.isnan(M[40]).all()
+    T = oracle.transfer(np.eye(r), m, 5, 6)
+    big = 3.3e38 * T[r - 1]
+    fits = np.abs(big) < 3e38
+    assert fits.any() and np.abs(to64(M)[64][fits] / big[fits] - 1).max() < 1e-4
+
+
 def test_transfer_accumulate_grouped_and_errors():
     shapes = [(70, 90), (33, 200), (128, 64), (5, 7)]
     r = 16
