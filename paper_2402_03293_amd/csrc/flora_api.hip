@@ -413,15 +413,18 @@ void build_compress_bf16_items(Plan& p)
 // A workgroup regenerates its slice of A once and reuses it for every row it owns, so the
 // generator's work is n m r / rows: 1024 rows make it a few percent of the kernel.  More
 // would only make workgroups long and unequal (the last ones to start then run alone);
-// fewer are chosen when the launch would otherwise not fill the chip: at ranks up to 64, where
-// the pass is bound by the weights' traffic, until there are 2048 workgroups (but not below
-// 256 rows); at r = 256, where regenerating A is a large part of a workgroup's time, 140 are
+// fewer are chosen when the launch would otherwise not fill the chip: at r = 64, where the pass is
+// bound by the weights' traffic, until there are 4096 workgroups (but not below 64 rows: 48 GPT-2 base
+// matrices 256 rows 192 us a step, 64 rows 180; 24 ragged ones 114 and 105), at smaller ranks, whose
+// workgroups own half as many columns, 2048 (not below 128 rows); at r = 256, where regenerating A is a
+// large part of a workgroup's time, 140 are
 // enough, and at r = 128 about 1000 (launches over the matrices of one to eight transformer
 // blocks of GPT-2 XL and T5-3B shapes, r = 256: update 84-453 -> 63-407 us).  A launch over one
 // or two matrices cannot fill the chip whatever the rows; there the fewest workgroups per
 // compute unit in a row finish first, and rows go down (to 32 at least) until there are about
 // 140 workgroups (single matrices of those shapes: update 27-31 -> 18-27 us at r = 256, 17-20 ->
-// 10-17 us at r = 64).
+// 10-17 us at r = 64), and at r >= 128 on to the least that keeps them to one per compute unit (one 1600 x
+// 6400 matrix at r = 256: 175 workgroups of 256 rows 22 us, 250 of 160 19, 325 of 128 29).
 int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r)
 {
     if (g_tune.decompress_rows) return g_tune.decompress_rows;
@@ -430,11 +433,14 @@ int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r)
         for (const MatDev& M : mats) w += ((M.n + rows - 1) / rows) * ((M.m + cols - 1) / cols);
         return w;
     };
-    const long long enough = r >= 256 ? 140 : (r >= 128 ? 1000 : 2048);
+    const long long enough = r >= 256 ? 140 : (r >= 128 ? 1000 : (r >= 64 ? 4096 : 2048));
+    const int least = r >= 128 ? kDecompressRows : (r >= 64 ? 64 : 128);
     int rows = 1024;
-    for (; rows > kDecompressRows; rows /= 2)
+    for (; rows > least; rows /= 2)
         if (wgs(rows) >= enough) break;
     for (; rows > 32 && wgs(rows) < 140; rows /= 2) {}
+    if (r >= 128)
+        while (rows > 32 && wgs(rows - 32) <= 256) rows -= 32;
     return rows;
 }
 

@@ -134,17 +134,33 @@ __global__ __launch_bounds__(256) void decompress_bf16_kernel(const MatDev* __re
 // state is converted to bf16 once per workgroup and shared through LDS (double
 // buffered).  The old weights of the next two blocks are in flight while the
 // current block multiplies.
-template <int MODE>
+template <int MODE, typename OT>
 struct VecPre {
-    v4f w[(MODE == kModeSgd || MODE == kModeFactored || MODE == kModeFull2) ? 4 : 1];   // rows lane / 8 + 8 p, p < 4
+    // four rows of this lane's four columns; fp32 or packed bf16
+    typename std::conditional<sizeof(OT) == 4, v4f, v2u>::type w[(MODE == kModeSgd || MODE == kModeFactored || MODE == kModeFull2) ? 4 : 1];
     v4f v[(MODE == kModeFull1 || MODE == kModeFull2) ? 4 : 1];    // unfactored second moment, same rows
     // row statistics: of those four rows (kModeFactored), or of rows li and 16 + li (kModeRms,
     // which works on the accumulator layout)
     float rs[MODE == kModeFactored ? 4 : (MODE == kModeRms ? 2 : 1)];
 };
 
+// Two workgroups per compute unit (128 registers) where the pass gets by with that.
 template <int R, int MODE, typename OT>
-__global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* __restrict__ mats,
+constexpr int vec_waves()
+{
+    const bool light = MODE == kModeOut || MODE == kModeSgd;
+    if (R == 64) return MODE == kModeFull2 ? 2 : 4;
+    if (R == 128) return light || (MODE == kModeFactored && sizeof(OT) == 2) ? 4 : 2;
+    return MODE == kModeOut ? 4 : 2;
+}
+
+// WP: cache policy of the n x m arrays (DecompressParams::wpolicy), a template argument because a branch
+// around every load and store of the row loop makes the waits between them conservative.
+// (384 T5-3B matrices, factored update at r = 256: 6.28 -> 6.17 ms; GPT-2 XL with bf16 weights, which also stay
+// packed in flight: update 1.85 -> 1.70 ms.  Whole rows of bf16 per wave through a staging tile of the
+// workgroup, and 128 registers for two workgroups per compute unit at r = 256, were slower: 1.72 and 2.41.)
+template <int R, int MODE, typename OT, int WP>
+__global__ __launch_bounds__(512, (vec_waves<R, MODE, OT>())) void decompress_bf16_vec_kernel(const MatDev* __restrict__ mats,
                                                                   const WorkItem* __restrict__ items,
                                                                   const SeedArgs seeds, DecompressParams p)
 {
@@ -158,6 +174,7 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
     constexpr bool kTotals = (MODE == kModeRms || MODE == kModeFactored || MODE == kModeFull1 || MODE == kModeFull2);
     // the two reduction passes move no weights: they work on the accumulators where they are
     constexpr bool kReduce = (MODE == kModeStats || MODE == kModeRms);
+    constexpr int PD = 3;                        // blocks of old weights in flight or in use
     __shared__ __attribute__((aligned(16))) uint16_t ldsS[2][32][LDS_ROW];
     __shared__ __attribute__((aligned(16))) float ldsT[kReduce ? 1 : 8][kReduce ? 1 : 32][TROW];
     __shared__ float lds_row[2][8][32];   // kModeStats: per-wave row sums of a block, double buffered
@@ -171,7 +188,8 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
-    const int er = lane >> 3, ec = lane & 7;     // epilogue: row er + 8 p, columns 4 ec .. 4 ec + 3
+    const int ec = lane & 7;                     // epilogue: rows erow(p), p < 4, of a block, columns 4 ec .. 4 ec + 3
+    auto erow = [&](int pp) { return (lane >> 3) + 8 * pp; };
     const float cgen = neg2_ln2_over(R);
     const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
     const long long row_end = ((long long)it.row0 + it.rows < n) ? (long long)it.row0 + it.rows : n;
@@ -194,8 +212,8 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
 
     // The accumulator of a 16 x 16 tile holds, per lane, four consecutive columns of one row;
     // the wave's 32 x 32 block then goes through its own staging tile in LDS and comes back
-    // with eight lanes along each row: lane (er, ec) holds columns 4 ec .. 4 ec + 3 of rows
-    // er + 8 p.  A row of the block is one 128-byte line of W, so every load and store
+    // with eight lanes along each row: lane 8 e + ec holds columns 4 ec .. 4 ec + 3 of rows
+    // e + 8 p.  A row of the block is one 128-byte line of W, so every load and store
     // instruction moves whole lines (8 rows x 128 bytes), the cheapest pattern for the
     // texture path.  m % 4 == 0: the four columns are all in or all out.
     const uint32_t c0 = (uint32_t)it.col0 + 32u * wave + 4u * ec;
@@ -283,22 +301,23 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
     // second moment), chosen by the host from their size: a set that fits the last-level cache
     // stays there for the next step (plain accesses); a larger one is written, and a much larger
     // one also read, with the non-temporal hint so that it does not push out what is reused.
-    const bool ld_stream = (p.wpolicy & 1) != 0, st_stream = (p.wpolicy & 2) != 0;
-    auto load_w4 = [&](rsrc_t rw, uint32_t off) -> v4f {
-        if (sizeof(OT) == 4) return ld_stream ? buf_load_f4<true>(rw, off) : buf_load_f4<false>(rw, off);
-        const v2u pk = ld_stream ? buf_load_u2<true>(rw, off) : buf_load_u2<false>(rw, off);
-        return v4f{bf16_bits_to_f32(pk.x & 0xffffu), bf16_bits_to_f32(pk.x >> 16),
-                   bf16_bits_to_f32(pk.y & 0xffffu), bf16_bits_to_f32(pk.y >> 16)};
+    constexpr bool ld_stream = (WP & 1) != 0, st_stream = (WP & 2) != 0;
+    auto load_w4 = [&](rsrc_t rw, uint32_t off) {
+        if constexpr (sizeof(OT) == 4) return buf_load_f4<ld_stream>(rw, off);
+        else return buf_load_u2<ld_stream>(rw, off);
+    };
+    auto old_w = [&](const VecPre<MODE, OT>& pre, int pp) -> v4f {
+        if constexpr (sizeof(OT) == 4) return pre.w[pp];
+        else return v4f{__uint_as_float(pre.w[pp].x << 16), __uint_as_float(pre.w[pp].x & 0xffff0000u),
+                        __uint_as_float(pre.w[pp].y << 16), __uint_as_float(pre.w[pp].y & 0xffff0000u)};
     };
     auto store_w4 = [&](rsrc_t rw, uint32_t off, v4f v) -> v4f {
         if (sizeof(OT) == 4) {
-            if (st_stream) buf_store_f4<true>(rw, off, v);
-            else buf_store_f4<false>(rw, off, v);
+            buf_store_f4<st_stream>(rw, off, v);
             return v;
         }
         const v2u pk = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
-        if (st_stream) buf_store_u2<true>(rw, off, pk);
-        else buf_store_u2<false>(rw, off, pk);
+        buf_store_u2<st_stream>(rw, off, pk);
         return v4f{bf16_bits_to_f32(pk.x & 0xffffu), bf16_bits_to_f32(pk.x >> 16),
                    bf16_bits_to_f32(pk.y & 0xffffu), bf16_bits_to_f32(pk.y >> 16)};
     };
@@ -309,12 +328,12 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
         return make_rsrc(M.vfull + base * m, rows * m * 4);
     };
     auto woff = [&](int pp) -> uint32_t {
-        return cok ? ((uint32_t)(er + 8 * pp) * (uint32_t)m + c0) * (uint32_t)sizeof(OT) : kOob;
+        return cok ? ((uint32_t)erow(pp) * (uint32_t)m + c0) * (uint32_t)sizeof(OT) : kOob;
     };
     auto voff = [&](int pp) -> uint32_t {     // the second moment is always fp32
-        return cok ? ((uint32_t)(er + 8 * pp) * (uint32_t)m + c0) * 4u : kOob;
+        return cok ? ((uint32_t)erow(pp) * (uint32_t)m + c0) * 4u : kOob;
     };
-    auto pre_fetch = [&](VecPre<MODE>& pre, long long rb) {
+    auto pre_fetch = [&](VecPre<MODE, OT>& pre, long long rb) {
         if (kUsesW) {
             const rsrc_t rw = wrsrc(rb);
 #pragma unroll
@@ -323,12 +342,12 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
         if (kUsesV) {
             const rsrc_t rv = vrsrc(rb);
 #pragma unroll
-            for (int pp = 0; pp < 4; ++pp) pre.v[pp] = ld_stream ? buf_load_f4<true>(rv, voff(pp)) : buf_load_f4<false>(rv, voff(pp));
+            for (int pp = 0; pp < 4; ++pp) pre.v[pp] = buf_load_f4<ld_stream>(rv, voff(pp));
         }
         if (MODE == kModeFactored) {
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) {
-                long long row = rb + er + 8 * pp;
+                long long row = rb + erow(pp);
                 if (row > n - 1) row = n - 1;
                 pre.rs[pp] = ldg(M.row_stat + row);
             }
@@ -344,10 +363,10 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
     };
 
     v4f stage[F4];
-    VecPre<MODE> pre0, pre1, pre2;     // blocks rb, rb + 32, rb + 64
+    VecPre<MODE, OT> pre[PD];          // blocks rb, rb + 32, ...
     fetch(stage, it.row0);
-    pre_fetch(pre0, it.row0);
-    pre_fetch(pre1, (long long)it.row0 + 32);
+#pragma unroll
+    for (int d = 0; d + 1 < PD; ++d) pre_fetch(pre[d], (long long)it.row0 + 32 * d);
     stash(stage, 0);
     __syncthreads();
 
@@ -355,7 +374,7 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
     for (long long rb = it.row0; rb < row_end; rb += 32) {
         const bool more = rb + 32 < row_end;
         if (more) fetch(stage, rb + 32);
-        pre_fetch(pre2, rb + 64);      // past the end: empty resource, nothing is fetched
+        pre_fetch(pre[PD - 1], rb + 32 * (PD - 1));      // past the end: empty resource, nothing is fetched
 
         f32x4 acc[2][2];               // [i-tile][j-tile]
 #pragma unroll
@@ -375,7 +394,7 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
 
         // ---- accumulators -> row-contiguous layout through this wave's staging tile
         // (acc[itile][jt][v] = (state A^T)[rb + 16 itile + li, 32 wave + 16 jt + 4 g + v])
-        v4f gt[4];                     // gt[pp] = (state A^T)[rb + er + 8 pp, c0 .. c0 + 3]
+        v4f gt[4];                     // gt[pp] = (state A^T)[rb + erow(pp), c0 .. c0 + 3]
         if (!kReduce) {
 #pragma unroll
             for (int itile = 0; itile < 2; ++itile)
@@ -383,7 +402,7 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
                 for (int jt = 0; jt < 2; ++jt)
                     *reinterpret_cast<f32x4*>(&ldsT[wave][16 * itile + li][16 * jt + 4 * g]) = acc[itile][jt];
 #pragma unroll
-            for (int pp = 0; pp < 4; ++pp) gt[pp] = *reinterpret_cast<const v4f*>(&ldsT[wave][er + 8 * pp][4 * ec]);
+            for (int pp = 0; pp < 4; ++pp) gt[pp] = *reinterpret_cast<const v4f*>(&ldsT[wave][erow(pp)][4 * ec]);
         }
 
         if (MODE == kModeOut) {
@@ -402,7 +421,7 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
             const rsrc_t rw = wrsrc(rb);
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) {
-                const v4f a4 = gt[pp], w = pre0.w[pp];
+                const v4f a4 = gt[pp], w = old_w(pre[0], pp);
                 store_w4(rw, woff(pp), v4f{w.x - p.coef * a4.x, w.y - p.coef * a4.y,
                                            w.z - p.coef * a4.z, w.w - p.coef * a4.w});
             }
@@ -410,8 +429,8 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
             const rsrc_t rw = wrsrc(rb);
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) {
-                const float ri = rsqrtf(pre0.rs[pp]);
-                const v4f a4 = gt[pp], w = pre0.w[pp];
+                const float ri = rsqrtf(pre[0].rs[pp]);
+                const v4f a4 = gt[pp], w = old_w(pre[0], pp);
                 const v4f wn = store_w4(rw, woff(pp), v4f{w.x - kfac[0] * ri * a4.x, w.y - kfac[1] * ri * a4.y,
                                                           w.z - kfac[2] * ri * a4.z, w.w - kfac[3] * ri * a4.w});
                 // sum of the new W^2 (rows past the end and columns past m contribute exact zeros:
@@ -429,13 +448,12 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
             const float a2 = p.alpha * p.alpha, omb = 1.f - p.beta2;
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) {
-                const bool ok = cok && (rb + er + 8 * pp < row_end);
-                const v4f a4 = gt[pp], v = pre0.v[pp];
+                const bool ok = cok && (rb + erow(pp) < row_end);
+                const v4f a4 = gt[pp], v = pre[0].v[pp];
                 const v4f g2 = {a2 * a4.x * a4.x, a2 * a4.y * a4.y, a2 * a4.z * a4.z, a2 * a4.w * a4.w};
                 const v4f vn = {p.beta2 * v.x + omb * (g2.x + p.eps1), p.beta2 * v.y + omb * (g2.y + p.eps1),
                                 p.beta2 * v.z + omb * (g2.z + p.eps1), p.beta2 * v.w + omb * (g2.w + p.eps1)};
-                if (st_stream) buf_store_f4<true>(rv, voff(pp), vn);
-                else buf_store_f4<false>(rv, voff(pp), vn);
+                buf_store_f4<st_stream>(rv, voff(pp), vn);
                 const float u2 = ((g2.x / vn.x + g2.y / vn.y) + (g2.z / vn.z + g2.w / vn.w));
                 total += ok ? u2 : 0.f;
             }
@@ -443,8 +461,8 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
             const rsrc_t rw = wrsrc(rb);
 #pragma unroll
             for (int pp = 0; pp < 4; ++pp) {
-                const bool ok = cok && (rb + er + 8 * pp < row_end);
-                const v4f a4 = gt[pp], w = pre0.w[pp], v = pre0.v[pp];
+                const bool ok = cok && (rb + erow(pp) < row_end);
+                const v4f a4 = gt[pp], w = old_w(pre[0], pp), v = pre[0].v[pp];
                 const v4f wn = store_w4(rw, woff(pp), v4f{w.x - kfull * rsqrtf(v.x) * a4.x, w.y - kfull * rsqrtf(v.y) * a4.y,
                                                           w.z - kfull * rsqrtf(v.z) * a4.z, w.w - kfull * rsqrtf(v.w) * a4.w});
                 const float w2 = ((wn.x * wn.x + wn.y * wn.y) + (wn.z * wn.z + wn.w * wn.w));
@@ -480,13 +498,13 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
                 for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) t = __builtin_fmaf(acc[itile][jt][v] * acc[itile][jt][v], kfacd[jt][v], t);
-                total = __builtin_fmaf(t, 1.f / pre0.rs[itile], total);
+                total = __builtin_fmaf(t, 1.f / pre[0].rs[itile], total);
             }
         }
 
         if (more) stash(stage, buf ^ 1);
-        pre0 = pre1;
-        pre1 = pre2;
+#pragma unroll
+        for (int d = 0; d + 1 < PD; ++d) pre[d] = pre[d + 1];
         __syncthreads();
         if (MODE == kModeStats && tid < 32) {
             // the eight waves' row sums of the block just finished (written before the barrier;
@@ -530,37 +548,39 @@ __global__ __launch_bounds__(512) void decompress_bf16_vec_kernel(const MatDev* 
     }
 }
 
+template <int R, int MODE, typename OT>
+hipError_t launch_vec(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, DecompressParams p,
+                      hipStream_t s)
+{
+    const dim3 grid((unsigned)nitems), block(512);
+    constexpr bool kPolicy = MODE == kModeSgd || MODE == kModeFactored || MODE == kModeFull1 || MODE == kModeFull2;
+#define FLORA_VEC(WP) hipLaunchKernelGGL((decompress_bf16_vec_kernel<R, MODE, OT, WP>), grid, block, 0, s, mats, items, seeds, p)
+    if constexpr (kPolicy) {
+        switch (p.wpolicy & 3) {
+        case 1: FLORA_VEC(1); break;
+        case 2: FLORA_VEC(2); break;
+        case 3: FLORA_VEC(3); break;
+        default: FLORA_VEC(0); break;
+        }
+    } else FLORA_VEC(0);
+#undef FLORA_VEC
+    return hipGetLastError();
+}
+
 template <int R, typename OT>
 hipError_t launch_mode_vec(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds,
                            int mode, DecompressParams p, hipStream_t s)
 {
-    const dim3 grid((unsigned)nitems), block(512);
     switch (mode) {
-    case kModeOut:
-        hipLaunchKernelGGL((decompress_bf16_vec_kernel<R, kModeOut, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeSgd:
-        hipLaunchKernelGGL((decompress_bf16_vec_kernel<R, kModeSgd, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeStats:
-        hipLaunchKernelGGL((decompress_bf16_vec_kernel<R, kModeStats, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeRms:
-        hipLaunchKernelGGL((decompress_bf16_vec_kernel<R, kModeRms, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFactored:
-        hipLaunchKernelGGL((decompress_bf16_vec_kernel<R, kModeFactored, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFull1:
-        hipLaunchKernelGGL((decompress_bf16_vec_kernel<R, kModeFull1, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFull2:
-        hipLaunchKernelGGL((decompress_bf16_vec_kernel<R, kModeFull2, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    default:
-        return hipErrorInvalidValue;
+    case kModeOut: return launch_vec<R, kModeOut, OT>(mats, items, nitems, seeds, p, s);
+    case kModeSgd: return launch_vec<R, kModeSgd, OT>(mats, items, nitems, seeds, p, s);
+    case kModeStats: return launch_vec<R, kModeStats, float>(mats, items, nitems, seeds, p, s);
+    case kModeRms: return launch_vec<R, kModeRms, float>(mats, items, nitems, seeds, p, s);
+    case kModeFactored: return launch_vec<R, kModeFactored, OT>(mats, items, nitems, seeds, p, s);
+    case kModeFull1: return launch_vec<R, kModeFull1, float>(mats, items, nitems, seeds, p, s);
+    case kModeFull2: return launch_vec<R, kModeFull2, OT>(mats, items, nitems, seeds, p, s);
+    default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 template <int R, typename OT>
