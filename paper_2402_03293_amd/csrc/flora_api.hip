@@ -85,6 +85,7 @@ struct Plan {
     int any_rows = 0;                   // bf16 compress: some rows of G do not start on 16-byte boundaries
     int vec = 0;                        // decompress: the 16-byte-per-lane bf16 kernel (256-column workgroups)
     int kc = 0;                         // fp32 compress: columns per part (0: whole rows)
+    int kg = 2;                         // fp32 compress: column groups per workgroup
     size_t ws_floats = 0;               // compress: floats of partial products (shared-column mode)
     size_t ws_counters = 0;             // ... and arrival counters
     void* d_tables = nullptr;           // items + items2 (uploaded once)
@@ -185,13 +186,30 @@ void build_compress_f32_items(Plan& p)
     // A workgroup streams through one compute unit's load path, which carries about an eighth
     // of a percent of the chip's bandwidth: in a launch of a few thousand row blocks the
     // long ones would finish last and alone.  Their columns are then shared between
-    // workgroups of about 512 columns (partial products combined by the last one to finish;
-    // nparts * rows * r * 8 bytes of extra traffic per block, little at these ranks).
+    // workgroups (partial products combined by the last one to finish;
+    // nparts * rows * r * 8 bytes of extra traffic per block, little at these ranks): of about 2048
+    // or 1024 columns where the set fills 600 such workgroups, else 512, and in launches of no more than a
+    // workgroup per compute unit 256, swept by two column groups.  (Filled ones are counted: 17 matrices of
+    // 5888 x 64 are 1564 workgroups of any size, but 9 of 940 x 2048 beside them take 39 us in pieces of
+    // 2048 and 23 in pieces of 512.)  r = 16, fp32, pieces of 512 / as chosen:
+    // one 1024 x 1024 matrix 11.7 / 7.4 us, eight of T5-small 12.1 / 8.3, all 96 36.9 / 34.3, 32 of GPT-2 XL
+    // 197 / 173.
     long long kc = g_tune.compress_splitk_cols;
+    p.kg = kc ? 1 : 2;
     if (kc == 0) {
-        long long blocks = 0;
-        for (int l = 0; l < p.count; ++l) blocks += (p.host_mats[l].n + rows_per_wg - 1) / rows_per_wg;
-        if (blocks < 8192) kc = 512;
+        auto wgs = [&](long long cols) {
+            long long w = 0;
+            for (int l = 0; l < p.count; ++l)
+                w += (p.host_mats[l].n + rows_per_wg - 1) / rows_per_wg * ((p.host_mats[l].m + cols - 1) / cols);
+            return w;
+        };
+        double area = 0.0;
+        for (int l = 0; l < p.count; ++l) area += (double)p.host_mats[l].n * (double)p.host_mats[l].m;
+        if (wgs(1ll << 40) < 8192) {
+            kc = area >= 600.0 * 64 * 2048 ? 2048 : (area >= 600.0 * 64 * 1024 ? 1024 : 512);
+            p.kg = 1;
+            if (wgs(512) <= 256) { kc = 256; p.kg = 2; }
+        }
     }
     p.kc = (int)kc;
     p.ws_floats = 0;
@@ -1072,8 +1090,7 @@ static int compress_chunk(const flora_matrix_t* mats, int count, int r, flora_dt
                                           p->combine && p->ws_counters > 0, partials, counters, s));
     }
     else {
-        // column groups per workgroup: two for whole rows; one when the pieces are 512 columns
-        const int kg = g_tune.compress_f32_kgroups ? g_tune.compress_f32_kgroups : (p->kc > 0 ? 1 : 2);
+        const int kg = g_tune.compress_f32_kgroups ? g_tune.compress_f32_kgroups : p->kg;
         float* partials = static_cast<float*>(p->d_work);
         uint32_t* counters = p->d_work ? reinterpret_cast<uint32_t*>(static_cast<char*>(p->d_work) +
                                                                    round_up(p->ws_floats * 4, 256))

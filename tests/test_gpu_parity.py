@@ -188,6 +188,24 @@ def test_compress_bf16_every_launch_shape(n, m, r, mt):
     assert rows.max() < TOL_BF16, (int(rows.argmax()), float(rows.max()))
 
 
+# the fp32 kernel with the pieces and column groups it chooses: a launch of few workgroups (pieces of 256
+# columns, two column groups), one of more (512), and sets large enough for 1024 and 2048.  Products and
+# sums are fp32: about sqrt(m) 2^-24 = 3e-6 at the widest, TOL_F32 as for the other shapes.
+@pytest.mark.parametrize("count,n,m", [(1, 33, 1), (1, 70, 257), (2, 65, 515), (130, 64, 1027), (620, 63, 1030), (1300, 31, 2053)])
+@pytest.mark.parametrize("r", [8, 32])
+def test_compress_f32_pieces(r, count, n, m):
+    G = rand((count, n, m + 4 - m % 4), 2500 + n + m, torch.float32)
+    Gs = [G[l].view(-1)[:n * m].view(n, m) for l in range(count)]
+    states = [torch.zeros((n, r), device=DEV) for _ in range(count)]
+    seeds = [2500 + l for l in range(count)]
+    mats = flora.matrices([(n, m)] * count, grads=Gs, states=states, seeds=seeds)
+    for _ in range(2):                            # (the arrival counters must be back at zero)
+        flora.compress(mats, r, flora.F32, 0.0, 1.0)
+        sync()
+        for l in sorted({0, count // 2, count - 1}):
+            assert rel_fro(to64(states[l]), oracle.compress(to64(Gs[l]), r, seeds[l])) < TOL_F32
+
+
 # rows of G that start anywhere (odd widths, widths that are no multiple of 8, fp32 gradients) in the
 # wide kernel: widths around a tile of 64 columns and around the pieces of a load, row counts around a
 # wave's and a workgroup's, whole rows and shared columns.  The matrix lies between NaNs: whatever a
