@@ -427,23 +427,27 @@ void build_compress_bf16_items(Plan& p)
     }
 }
 
-// Rows per decompress workgroup (an upper limit; each matrix splits its rows evenly below it).
-// A workgroup regenerates its slice of A once and reuses it for every row it owns, so the
-// generator's work is n m r / rows: 1024 rows make it a few percent of the kernel.  More
-// would only make workgroups long and unequal (the last ones to start then run alone);
-// fewer are chosen when the launch would otherwise not fill the chip: at r = 64, where the pass is
-// bound by the weights' traffic, until there are 4096 workgroups (but not below 64 rows: 48 GPT-2 base
-// matrices 256 rows 192 us a step, 64 rows 180; 24 ragged ones 114 and 105), at smaller ranks, whose
-// workgroups own half as many columns, 2048 (not below 128 rows); at r = 256, where regenerating A is a
-// large part of a workgroup's time, 140 are
-// enough, and at r = 128 about 1000 (launches over the matrices of one to eight transformer
-// blocks of GPT-2 XL and T5-3B shapes, r = 256: update 84-453 -> 63-407 us).  A launch over one
-// or two matrices cannot fill the chip whatever the rows; there the fewest workgroups per
-// compute unit in a row finish first, and rows go down (to 32 at least) until there are about
-// 140 workgroups (single matrices of those shapes: update 27-31 -> 18-27 us at r = 256, 17-20 ->
-// 10-17 us at r = 64), and at r >= 128 on to the least that keeps them to one per compute unit (one 1600 x
-// 6400 matrix at r = 256: 175 workgroups of 256 rows 22 us, 250 of 160 19, 325 of 128 29).
-int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r)
+// Rows per decompress workgroup (an upper limit; each matrix splits its rows evenly below it). A
+// workgroup regenerates its slice of A once and reuses it for every row it owns, so the generator's
+// work is n m r / rows: 1024 rows make it a few percent of the kernel.  More would only make workgroups
+// long and unequal (the last ones to start then run alone); fewer are chosen when the launch would
+// otherwise not fill the chip: at r = 256, where regenerating A is a large part of a workgroup's time,
+// 140 workgroups are enough, and at r = 128 about 1000 (launches over the matrices of one to eight
+// transformer blocks of GPT-2 XL and T5-3B shapes, r = 256: update 84-453 -> 63-407 us).  At r = 64 256
+// rows; where the plain update then has no 300 workgroups, 128; and in launches over many full
+// workgroups (rows wide enough for all columns of one), which the weights' traffic bounds, 64 in the
+// plain update and 128 under the Adafactor rules, whose kernels hold more.  us at 256 / 128 / 64 rows:
+// 16 matrices of 768 x 768 16.1 / 15.6 / 16.8 (unfactored 47 / 50 / 53), 24 of 768 x 3072 88.8 / 89.6 /
+// 90.8 (223 / 211 / 229), all 48 of GPT-2 base 135 / 126 / 114 (342 / 315 / 331), 52 of 6656 x 64 53 /
+// 59 / 77 (179 / 202 / 271).  At smaller ranks 128 rows, and 64 in such large launches (not at r = 32
+// under the Adafactor rules): r = 16, GPT-2 base 143 / 138 / 131 (364 / 348 / 339), T5-small 63 / 58 /
+// 60 (160 / 151 / 150).  A launch over one or two matrices cannot fill the chip whatever the rows;
+// there the fewest workgroups per compute unit in a row finish first, and rows go down (to 32 at least)
+// until there are about 140 workgroups (200 at small ranks: four 768 x 768 matrices at r = 8 8.9 -> 6.7
+// us; single matrices of those shapes: update 27-31 -> 18-27 us at r = 256, 17-20 -> 10-17 us at r =
+// 64), and at r >= 128 on to the least that keeps them to one per compute unit (one 1600 x 6400 matrix
+// at r = 256: 175 workgroups of 256 rows 22 us, 250 of 160 19, 325 of 128 29).
+int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r, bool adafactor)
 {
     if (g_tune.decompress_rows) return g_tune.decompress_rows;
     auto wgs = [&](int rows) {
@@ -451,12 +455,23 @@ int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r)
         for (const MatDev& M : mats) w += ((M.n + rows - 1) / rows) * ((M.m + cols - 1) / cols);
         return w;
     };
-    const long long enough = r >= 256 ? 140 : (r >= 128 ? 1000 : (r >= 64 ? 4096 : 2048));
-    const int least = r >= 128 ? kDecompressRows : (r >= 64 ? 64 : 128);
+    // workgroups of 256 rows that the set would fill
+    double full = 0.0;
+    for (const MatDev& M : mats) full += (double)M.n * (double)M.m / (256.0 * cols);
     int rows = 1024;
-    for (; rows > least; rows /= 2)
-        if (wgs(rows) >= enough) break;
-    for (; rows > 32 && wgs(rows) < 140; rows /= 2) {}
+    if (r >= 128) {
+        const long long enough = r >= 256 ? 140 : 1000;
+        for (; rows > kDecompressRows; rows /= 2)
+            if (wgs(rows) >= enough) break;
+    } else if (r == 64) {
+        for (; rows > kDecompressRows; rows /= 2)
+            if (wgs(rows) >= 2048) break;
+        if (full >= 850.0) rows = (adafactor || full < 1024.0) ? 128 : 64;
+        else if (!adafactor && wgs(kDecompressRows) < 300) rows = 128;
+    } else {
+        rows = (full >= 1024.0 && !(adafactor && r == 32)) ? 64 : 128;
+    }
+    for (; rows > 32 && wgs(rows) < (r <= 32 ? 200 : 140); rows /= 2) {}
     if (r >= 128)
         while (rows > 32 && wgs(rows - 32) <= 256) rows -= 32;
     return rows;
@@ -471,7 +486,7 @@ void build_decompress_items(Plan& p)
     p.vec = vec;
     const int cols = vec ? kDecompressColsVec : kDecompressCols;
     // (the vector kernel addresses a workgroup's state rows with 32-bit byte offsets)
-    const int rows_per_wg = std::min(choose_decompress_rows(p.host_mats, cols, p.r), vec ? (1 << 20) : 0x7fffffe0);
+    const int rows_per_wg = std::min(choose_decompress_rows(p.host_mats, cols, p.r, p.kind == kKindFactored), vec ? (1 << 20) : 0x7fffffe0);
     struct Group { int mat, rb, row0, rows, nchunks; };
     std::vector<Group> groups;
     for (int l = 0; l < p.count; ++l) {
