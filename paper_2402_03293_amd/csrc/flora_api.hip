@@ -1174,10 +1174,10 @@ static int transfer_chunk(const flora_matrix_t* mats, int count, int r, float* c
 // and a half times the cache, and the compress launches stream their gradients past the cache
 // (one rank slice: every rank but 256), part of it is still found there at the next step, so the
 // reads stay plain.  Anything larger is read with the hint as well: nothing of it survives.
-// Whole steps, same box (plain / streamed writes / both): GPT-2 base, r = 64, 324 MiB: 0.193 /
-// 0.171 / 0.190 ms; GPT-2 XL shapes: r = 64, 234 MiB 0.145 / 0.144 / 0.152, 469 MiB 0.308 / 0.300 /
-// 0.292, 1875 MiB 1.124 / 1.119 / 1.072; r = 256, 117 MiB 0.148 / 0.150 / 0.154, 234 MiB 0.272 /
-// 0.272 / 0.264, 5.6 GiB 3.70 / 3.69 / 3.58.
+// Whole steps (plain / streamed writes / both), us: GPT-2 base, r = 64, 324 MiB: 168 / 168 / 159; GPT-2
+// XL shapes: r = 64, 117 MiB 70 / 68 / 76, 234 MiB 123 / 120 / 124, 352 MiB 192 / 191 / 179, 469 MiB 252 /
+// 248 / 228; r = 128, 234 MiB 164 / 158 / 161, 352 MiB 248 / 231 / 237, 938 MiB 617 / 601 / 573; r = 256,
+// 234 MiB 234 / 232 / 218, 938 MiB 671 / 667 / 654; the same under all of them at r = 16.
 static int choose_wpolicy(const flora_matrix_t* mats, int count, int r, const flora_update_t* u, int wbf16)
 {
     if (g_tune.update_wpolicy) return g_tune.update_wpolicy - 1;
@@ -1191,7 +1191,7 @@ static int choose_wpolicy(const flora_matrix_t* mats, int count, int r, const fl
     // a caller that spreads one optimizer step over several calls says how large the whole set is
     const double mib = std::max(bytes / (1024.0 * 1024.0), (double)u->step_weight_mib);
     if (mib <= 192.0) return 0;
-    if (mib <= 400.0 && r != 256) return 2;
+    if (mib <= (r == 128 ? 400.0 : 300.0) && r != 256) return 2;
     return 3;
 }
 
