@@ -161,7 +161,8 @@ int flora_decompress(const flora_matrix_t* mats, int count, int r, float alpha,
 /* Momentum transfer (Algorithm 2, resample branch), computed as
  * T = A(seed)^T A(seed_next) (r x r, in the workspace) and then
  *     state <- state T        ( = state A(seed)^T A(seed_next) )
- * entirely in fp32.  Uses state, n, m, seed, seed_next.  The caller replaces
+ * at fp32 precision (at ranks >= 64 as six products of bf16 parts per fp32 product, whose error is no
+ * larger than that of fp32 sums).  Uses state, n, m, seed, seed_next.  The caller replaces
  * seed by seed_next afterwards. */
 int flora_momentum_transfer(const flora_matrix_t* mats, int count, int r, void* hip_stream);
 
@@ -189,7 +190,7 @@ int flora_momentum_transfer_static(const flora_matrix_t* mats, int count, int r,
  * Section 2.4), with no n x m pass:
  *     dst[l] <- a * dst[l] + b * state A(seed)^T A(seed_next)
  * equal to compressing the decompressed state, computed as T = A(seed)^T A(seed_next) and
- * state T entirely in fp32.  `dst` is a HOST array of `count` DEVICE pointers to n x r fp32
+ * state T at fp32 precision.  `dst` is a HOST array of `count` DEVICE pointers to n x r fp32
  * buffers, none of which may be the matrix's own state.  Uses state, n, m, seed, seed_next. */
 int flora_transfer_accumulate(const flora_matrix_t* mats, int count, int r, float a, float b,
                               float* const* dst, void* hip_stream);

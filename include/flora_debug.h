@@ -59,9 +59,11 @@ int flora_debug_compute_loop(int kind, int iters, void* sink, double* work_out, 
  * (value 0 restores the default).  Names: "compress_f32_kgroups" (1, 2, 4: column groups per
  * workgroup in the fp32 compress kernel), "compress_f32_mt" (1, 2: rows per workgroup / 64 in
  * the same kernel), "compress_bf16_mt" (1, 2, 4: rows per workgroup / 128
- * in the bf16 compress kernel; 8 / 16 / 32: its wide variant with 512 / 256 / 128 rows, used only when
- * every m is a multiple of 8), "compress_splitk_cols" (a multiple of 64: in the wide variant,
- * share the columns of a row block between workgroups of about this many columns each), "decompress_rows" (a multiple of 32: rows per workgroup in the
+ * in the bf16 compress kernel; 8 / 16 / 32: its wide variant with 512 / 256 / 128 rows),
+ * "compress_splitk_cols" (a multiple of 64: in the wide variant and the fp32 kernel,
+ * share the columns of a row block between workgroups of about this many columns each),
+ * "compress_combine" (shared columns in the wide variant: 1 added by the last workgroup to arrive, 2 by a
+ * launch of their own), "decompress_rows" (a multiple of 32: rows per workgroup in the
  * decompress / update kernels), "decompress_vec" (1: always the 4-byte-per-lane kernel at
  * ranks >= 64, 2: the 16-byte-per-lane kernel whenever every m is a multiple of 4, which is
  * also the default), "factored_gram" (the factored rule at ranks >= 64: 1 reduction passes over the decompressed

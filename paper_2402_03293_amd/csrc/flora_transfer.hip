@@ -5,11 +5,13 @@
 // be carried by every later step.
 //
 // Ranks 8 / 16 / 32 (T is tiny):
-// transfer_T: one workgroup owns up to 32 rows k1 of T and all r columns,
-//   sweeps j = 0..m-1 in tiles of 32, regenerating both projections' tiles
-//   into LDS ([j][k] layout) and contracting over j with
-//   v_mfma_f32_16x16x4_f32.  The reduction order is fixed, so T is
-//   reproducible bit for bit.
+// transfer_T: one workgroup owns all of T and sweeps j = 0..m-1 in tiles of 32, dealt in turn to 4, 8 or 16
+//   groups of waves (r = 32, 16, 8), which regenerate both projections' tiles into LDS ([j][k] layout) and
+//   contract over j with v_mfma_f32_16x16x4_f32.  Generator and barriers are a serial chain along j, and
+//   a matrix has one workgroup: with all four waves of it on one tile at a time, 4 matrices of 768 x 3072
+//   took 84 / 93 / 131 us (transfer, r = 8 / 16 / 32), so dealt 14 / 23 / 54; one of 264 x 8192 214 / 238 /
+//   337 and 30 / 52 / 132; 200 of 768 x 1024, which fill the chip, 37 / 42 / 66 and 38 / 37 / 43.
+//   The reduction order is fixed, so T is reproducible bit for bit.
 // apply_T: one workgroup owns 32 rows of M, keeps them in LDS, multiplies by
 //   T (read through the caches) and writes the rows back in place.
 //
@@ -29,90 +31,76 @@ namespace {
 constexpr int kBJ = 32;   // rows of A per tile
 
 template <int R>
-__global__ __launch_bounds__(256) void transfer_T_kernel(const MatDev* __restrict__ mats)
+__global__ __launch_bounds__(1024) void transfer_T_kernel(const MatDev* __restrict__ mats)
 {
-    constexpr int KB1 = (R < 32) ? R : 32;          // rows of T per workgroup
-    constexpr int NT1 = (KB1 + 15) / 16;
-    constexpr int NT2 = (R + 15) / 16;
-    constexpr int NT2W = (NT2 + 3) / 4;             // column tiles of T per wave
-    constexpr int P1 = NT1 * 16 + 4, P2 = NT2 * 16 + 4;
-    __shared__ float ldsOld[kBJ][P1];
-    __shared__ float ldsNew[kBJ][P2];
+    constexpr int GT = kBJ * R / 4;                 // threads of a group: a quad of each projection each
+    constexpr int KG = 1024 / GT;                   // groups, each with its own tiles
+    constexpr int NT = (R + 15) / 16;               // 16 x 16 tiles of T each way
+    constexpr int P = R + 4;
+    static_assert(2 * kBJ * P >= NT * NT * 256, "a group's sums take the place of its tiles");
+    __shared__ __attribute__((aligned(16))) float lds[KG][2 * kBJ * P];
 
-    constexpr int blocks_per_mat = (R + KB1 - 1) / KB1;
-    const int mat = blockIdx.x / blocks_per_mat;
-    const int kb = blockIdx.x - mat * blocks_per_mat;
-    const MatDev& M = mats[mat];
+    const MatDev& M = mats[blockIdx.x];
     const long long m = M.m;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x % GT;
+    const int kg = __builtin_amdgcn_readfirstlane(threadIdx.x / GT);
     const int lane = tid & 63, wave = tid >> 6;
     const int li = lane & 15, jg = lane >> 4;
+    const int lk = li & (R - 1);                    // (r = 8: rows and columns 8 .. 15 of the tile are not kept)
     const float cgen = neg2_ln2_over(R);
+    float* const ldsOld = lds[kg];
+    float* const ldsNew = ldsOld + kBJ * P;
 
-    // zero the padding columns once (ranks below 16)
-    for (int idx = tid; idx < kBJ * P1; idx += 256) ldsOld[idx / P1][idx % P1] = 0.f;
-    for (int idx = tid; idx < kBJ * P2; idx += 256) ldsNew[idx / P2][idx % P2] = 0.f;
-    __syncthreads();
-
-    f32x4 acc[NT1][NT2W];
+    // wave w: column tile w of T
+    f32x4 acc[NT];
 #pragma unroll
-    for (int a = 0; a < NT1; ++a)
-#pragma unroll
-        for (int b = 0; b < NT2W; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int a = 0; a < NT; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const int ntiles = (int)((m + kBJ - 1) / kBJ);
-    for (int tile = 0; tile < ntiles; ++tile) {
-        const long long j0 = (long long)tile * kBJ;
-        // old projection: rows j0.., columns kb*KB1 .. +KB1
-        for (int idx = tid; idx < kBJ * (KB1 / 4); idx += 256) {
-            const int jl = idx % kBJ, q = idx / kBJ;
-            Quad z = normal_quad(M.seed_lo, M.seed_hi, (uint32_t)(j0 + jl), (uint32_t)(kb * (KB1 / 4) + q), cgen);
+    for (int tile0 = 0; tile0 < ntiles; tile0 += KG) {
+        const long long j0 = (long long)(tile0 + kg) * kBJ;        // (zeros beyond the last tile)
+        {
+            const int jl = tid % kBJ, q = tid / kBJ;
             const bool ok = j0 + jl < m;
+            const Quad zo = normal_quad(M.seed_lo, M.seed_hi, (uint32_t)(j0 + jl), (uint32_t)q, cgen);
+            const Quad zn = normal_quad(M.seedn_lo, M.seedn_hi, (uint32_t)(j0 + jl), (uint32_t)q, cgen);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ldsOld[jl][4 * q + i] = ok ? z.z[i] : 0.f;
-        }
-        for (int idx = tid; idx < kBJ * (R / 4); idx += 256) {
-            const int jl = idx % kBJ, q = idx / kBJ;
-            Quad z = normal_quad(M.seedn_lo, M.seedn_hi, (uint32_t)(j0 + jl), (uint32_t)q, cgen);
-            const bool ok = j0 + jl < m;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) ldsNew[jl][4 * q + i] = ok ? z.z[i] : 0.f;
+            for (int i = 0; i < 4; ++i) {
+                ldsOld[jl * P + 4 * q + i] = ok ? zo.z[i] : 0.f;
+                ldsNew[jl * P + 4 * q + i] = ok ? zn.z[i] : 0.f;
+            }
         }
         __syncthreads();
+        if (wave < NT) {
 #pragma unroll
-        for (int c = 0; c < kBJ / 4; ++c) {
-            float av[NT1];
+            for (int c = 0; c < kBJ / 4; ++c) {
+                const float bv = ldsNew[(4 * c + jg) * P + wave * 16 + lk];
 #pragma unroll
-            for (int a = 0; a < NT1; ++a) av[a] = ldsOld[4 * c + jg][a * 16 + li];
-#pragma unroll
-            for (int b = 0; b < NT2W; ++b) {
-                const int t2 = wave + 4 * b;
-                if (t2 < NT2) {
-                    const float bv = ldsNew[4 * c + jg][t2 * 16 + li];
-#pragma unroll
-                    for (int a = 0; a < NT1; ++a)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[a], bv, acc[a][b], 0, 0, 0);
-                }
+                for (int a = 0; a < NT; ++a)
+                    acc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(ldsOld[(4 * c + jg) * P + a * 16 + lk], bv, acc[a], 0, 0, 0);
             }
         }
         __syncthreads();
     }
 
-    // D layout of the 16x16 tile: lane holds column lane % 16, rows 4 * (lane / 16) + v.
+    // the groups' sums, added in their order by the first
+    if (kg > 0 && wave < NT) {
 #pragma unroll
-    for (int a = 0; a < NT1; ++a)
+        for (int a = 0; a < NT; ++a) *reinterpret_cast<f32x4*>(&lds[kg][((a * NT + wave) * 64 + lane) * 4]) = acc[a];
+    }
+    __syncthreads();
+    if (kg > 0 || wave >= NT) return;
 #pragma unroll
-        for (int b = 0; b < NT2W; ++b) {
-            const int t2 = wave + 4 * b;
-            if (t2 < NT2) {
+    for (int a = 0; a < NT; ++a) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int k1 = kb * KB1 + a * 16 + 4 * jg + v;
-                    const int k2 = t2 * 16 + li;
-                    if (a * 16 + 4 * jg + v < KB1 && k2 < R) M.T[k1 * R + k2] = acc[a][b][v];
-                }
-            }
+        for (int k = 1; k < KG; ++k) acc[a] += *reinterpret_cast<const f32x4*>(&lds[k][((a * NT + wave) * 64 + lane) * 4]);
+        // D layout of the 16x16 tile: lane holds column lane % 16, rows 4 * (lane / 16) + v.
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int k1 = a * 16 + 4 * jg + v, k2 = wave * 16 + li;
+            if (k1 < R && k2 < R) M.T[k1 * R + k2] = acc[a][v];
         }
+    }
 }
 
 template <int R>
@@ -250,28 +238,35 @@ __device__ __forceinline__ void mfma_split_direct(f32x16& acc, const bf16x8 (&a)
 // regenerated once, or, in launches of few chunks, half), R columns.  Tiles of 16 columns of both
 // projections are regenerated, split and stored to LDS by rank row ([part][k][j], double buffered); half
 // of the waves produce the next tile before they multiply the current one, the others after.
-// RG x CG waves of WR x WC tiles of 32 x 32.
-template <int R, int SLAB, int WR, int WC>
-__global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64) void transfer_T_split_kernel(const MatDev* __restrict__ mats,
-                                                                                              const WorkItem* __restrict__ items,
-                                                                                              int item_step)
+// RG x CG waves of WR x WC tiles of 32 x 32; with KG > 1 KG groups of them take every KG-th tile each, with
+// buffers of their own, and their sums are added in the groups' order.  (For launches that leave compute units
+// idle: one workgroup then holds as many waves as several would, and the chain along a chunk is KG times
+// shorter.  Transfers, one group / KG: r = 64, 4 matrices of 768 x 3072 60 / 38 us, 8 of 80 x 448 33 / 24;
+// above a workgroup per compute unit the tiles of several workgroups overlap as well, and LDS then holds
+// no more waves with them.)
+template <int R, int SLAB, int WR, int WC, int KG>
+__global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64 * KG) void transfer_T_split_kernel(
+    const MatDev* __restrict__ mats, const WorkItem* __restrict__ items, int item_step)
 {
     constexpr int RG = SLAB / 32 / WR, NW = RG * (R / 32 / WC), T = 64 * NW;
     constexpr int ROWS = SLAB + R;                 // rank rows in LDS: SLAB of the old projection, then R of the new
     constexpr int NU = 8 * (ROWS / 4);             // units of a tile: (pair of columns, quad)
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2][3][ROWS][kLdk];
+    static_assert(KG == 1 || (KG - 1) * SLAB * R * 4 <= KG * 2 * 3 * ROWS * kLdk * 2, "the sums take the place of the tiles");
+    __shared__ __attribute__((aligned(16))) uint16_t lds_all[KG][2][3][ROWS][kLdk];
 
     const WorkItem it = items[blockIdx.x * item_step];
     const MatDev& M = mats[it.mat];
-    const int tid = threadIdx.x;
+    const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / T);
+    const int tid = (int)threadIdx.x - kg * T;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto& lds = lds_all[kg];
     const int ln = lane & 31, g = lane >> 5;
     const int rt0 = (wave % RG) * WR, ct0 = (wave / RG) * WC;
     const float cgen = neg2_ln2_over(R);
     const uint32_t so_lo = M.seed_lo, so_hi = M.seed_hi, sn_lo = M.seedn_lo, sn_hi = M.seedn_hi;
     const uint32_t jbeg = (uint32_t)it.col0, jend = (uint32_t)it.col1;       // this chunk's columns
-    const int ntiles = (int)((jend - jbeg + kKT - 1) / kKT);
+    const int ntiles = (int)((jend - jbeg + KG * kKT - 1) / (KG * kKT));      // of each group (zeros beyond the chunk)
     const uint32_t qold0 = (uint32_t)(it.slice * (SLAB / 4));
 
     auto produce = [&](int buf, int tile) {
@@ -280,7 +275,7 @@ __global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64) void transfe
             const int u = u0 + tid;
             if (NU % T != 0 && u >= NU) break;
             const int q = u >> 3, jp = 2 * (u & 7);
-            const uint32_t j = jbeg + (uint32_t)tile * kKT + (uint32_t)jp;
+            const uint32_t j = jbeg + (uint32_t)(tile * KG + kg) * kKT + (uint32_t)jp;
             // (the 64 units of a wave are on one side)
             const bool isold = __builtin_amdgcn_readfirstlane(q) < SLAB / 4;
             const uint32_t s_lo = isold ? so_lo : sn_lo, s_hi = isold ? so_hi : sn_hi;
@@ -310,7 +305,7 @@ __global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64) void transfe
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[r][c][v] = 0.f;
 
-    const bool produce_first = ((wave >> 2) & 1) == 0;       // (waves w, w + 4, ... share a SIMD)
+    const bool produce_first = (((wave + kg * NW) >> 2) & 1) == 0;       // (waves w, w + 4, ... share a SIMD)
     produce(0, 0);
     __syncthreads();
     for (int tile = 0; tile < ntiles; ++tile) {
@@ -333,6 +328,31 @@ __global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64) void transfe
         }
         if (!produce_first && tile + 1 < ntiles) produce(buf ^ 1, tile + 1);
         __syncthreads();
+    }
+
+    if (KG > 1) {
+        float* sums = reinterpret_cast<float*>(lds_all);
+        constexpr int per_wave = WR * WC * 16 * 64;
+        if (kg > 0) {
+#pragma unroll
+            for (int r = 0; r < WR; ++r)
+#pragma unroll
+                for (int c = 0; c < WC; ++c)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        sums[((kg - 1) * NW + wave) * per_wave + ((r * WC + c) * 16 + v) * 64 + lane] = acc[r][c][v];
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int k = 1; k < KG; ++k)
+#pragma unroll
+            for (int r = 0; r < WR; ++r)
+#pragma unroll
+                for (int c = 0; c < WC; ++c)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        acc[r][c][v] += sums[((k - 1) * NW + wave) * per_wave + ((r * WC + c) * 16 + v) * 64 + lane];
     }
 
     // D layout of a 32 x 32 tile: lane holds column ln and rows 8 (v / 4) + 4 g + v % 4
@@ -512,33 +532,34 @@ hipError_t launch_transfer_T(const MatDev* mats, const WorkItem* items, int nite
         const dim3 grid((unsigned)nitems);
         switch (r) {
         case 64:
-            hipLaunchKernelGGL((transfer_T_split_kernel<64, 64, 1, 1>), grid, dim3(256), 0, s, mats, items, 1);
+            if (nitems <= 256)
+                hipLaunchKernelGGL((transfer_T_split_kernel<64, 64, 1, 1, 4>), grid, dim3(1024), 0, s, mats, items, 1);
+            else
+                hipLaunchKernelGGL((transfer_T_split_kernel<64, 64, 1, 1, 1>), grid, dim3(256), 0, s, mats, items, 1);
             hipLaunchKernelGGL((combine_T_kernel<64>), dim3(64 / kKT, (unsigned)count), dim3(4 * 64), 0, s, mats);
             break;
         case 128:
-            hipLaunchKernelGGL((transfer_T_split_kernel<128, 128, 2, 1>), grid, dim3(512), 0, s, mats, items, 1);
+            if (nitems <= 256)
+                hipLaunchKernelGGL((transfer_T_split_kernel<128, 128, 2, 1, 2>), grid, dim3(1024), 0, s, mats, items, 1);
+            else
+                hipLaunchKernelGGL((transfer_T_split_kernel<128, 128, 2, 1, 1>), grid, dim3(512), 0, s, mats, items, 1);
             hipLaunchKernelGGL((combine_T_kernel<128>), dim3(128 / kKT, (unsigned)count), dim3(4 * 128), 0, s, mats);
             break;
         case 256:
             // both slabs of a chunk by one workgroup, which then regenerates the new projection once; where
             // that gives the chip fewer than a workgroup per compute unit, a workgroup each
             if (nitems / 2 >= 256)
-                hipLaunchKernelGGL((transfer_T_split_kernel<256, 256, 1, 4>), dim3((unsigned)(nitems / 2)), dim3(1024), 0, s, mats, items, 2);
+                hipLaunchKernelGGL((transfer_T_split_kernel<256, 256, 1, 4, 1>), dim3((unsigned)(nitems / 2)), dim3(1024), 0, s, mats, items, 2);
             else
-                hipLaunchKernelGGL((transfer_T_split_kernel<256, 128, 2, 2>), grid, dim3(512), 0, s, mats, items, 1);
+                hipLaunchKernelGGL((transfer_T_split_kernel<256, 128, 2, 2, 1>), grid, dim3(512), 0, s, mats, items, 1);
             hipLaunchKernelGGL((combine_T_kernel<256>), dim3(256 / kKT, (unsigned)count), dim3(4 * 256), 0, s, mats);
             break;
         default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
     }
-    const dim3 block(256);
 #define FLORA_T(RR)                                                                              \
-    case RR: {                                                                                   \
-        constexpr int kb1 = (RR < 32) ? RR : 32;                                                 \
-        hipLaunchKernelGGL((transfer_T_kernel<RR>), dim3((unsigned)(count * ((RR + kb1 - 1) / kb1))), \
-                           block, 0, s, mats);                                                   \
-    } break;
+    case RR: hipLaunchKernelGGL((transfer_T_kernel<RR>), dim3((unsigned)count), dim3(1024), 0, s, mats); break;
     switch (r) {
         FLORA_T(8) FLORA_T(16) FLORA_T(32)
     default: return hipErrorInvalidValue;

@@ -463,6 +463,14 @@ def test_transfer_split_products_at_edges(n, m, r, count):
         assert rel_fro(to64(st[l]), ref) < 2.0 ** -24 * (m + r) ** 0.5 + 4e-7, l
 
 
+# T's tiles dealt to groups of waves: sets around 256 pieces (r = 64 and 128: four and two groups up to there),
+# columns around the 64 / 32 of a round there and the 512 / 256 / 128 at r = 8 / 16 / 32.  Same bar.
+@pytest.mark.parametrize("n,m,r,count", [(3, 31, 8, 2), (70, 513, 8, 1), (33, 511, 8, 3), (40, 255, 16, 2), (65, 289, 16, 1), (64, 127, 32, 2),
+                                         (31, 1154, 32, 1), (20, 63, 64, 256), (20, 65, 64, 257), (9, 31, 128, 256), (9, 33, 128, 257)])
+def test_transfer_tiles_in_groups(n, m, r, count):
+    test_transfer_split_products_at_edges(n, m, r, count)
+
+
 # infinities and NaNs in a state stay in their rows, and what the fp32 product gives for them is what comes out
 @pytest.mark.parametrize("r", [64, 256])
 def test_transfer_of_states_that_are_not_finite(r):
