@@ -187,13 +187,13 @@ void build_compress_f32_items(Plan& p)
     // of a percent of the chip's bandwidth: in a launch of a few thousand row blocks the
     // long ones would finish last and alone.  Their columns are then shared between
     // workgroups (partial products combined by the last one to finish;
-    // nparts * rows * r * 8 bytes of extra traffic per block, little at these ranks): of about 2048
-    // or 1024 columns where the set fills 600 such workgroups, else 512, and in launches of no more than a
+    // nparts * rows * r * 8 bytes of extra traffic per block, little at these ranks): of about 1024
+    // columns where the set fills 600 such workgroups, else 512, and in launches of no more than a
     // workgroup per compute unit 256, swept by two column groups.  (Filled ones are counted: 17 matrices of
-    // 5888 x 64 are 1564 workgroups of any size, but 9 of 940 x 2048 beside them take 39 us in pieces of
-    // 2048 and 23 in pieces of 512.)  r = 16, fp32, pieces of 512 / as chosen:
-    // one 1024 x 1024 matrix 11.7 / 7.4 us, eight of T5-small 12.1 / 8.3, all 96 36.9 / 34.3, 32 of GPT-2 XL
-    // 197 / 173.
+    // 5888 x 64 are 1564 workgroups of any size, but 9 of 940 x 2048 beside them take 28 us in pieces of
+    // 1024 and 24 in pieces of 512.)  r = 16, fp32, pieces of 512 / as chosen: one 1024 x 1024 matrix 11.7 /
+    // 7.4 us, eight of T5-small 12.1 / 8.3, all 96 36.9 / 34.3.  (2048 is faster yet where the set fills that,
+    // but one chain of additions along it rounds more.)
     long long kc = g_tune.compress_splitk_cols;
     p.kg = kc ? 1 : 2;
     if (kc == 0) {
@@ -206,7 +206,7 @@ void build_compress_f32_items(Plan& p)
         double area = 0.0;
         for (int l = 0; l < p.count; ++l) area += (double)p.host_mats[l].n * (double)p.host_mats[l].m;
         if (wgs(1ll << 40) < 8192) {
-            kc = area >= 600.0 * 64 * 2048 ? 2048 : (area >= 600.0 * 64 * 1024 ? 1024 : 512);
+            kc = area >= 600.0 * 64 * 1024 ? 1024 : 512;
             p.kg = 1;
             if (wgs(512) <= 256) { kc = 256; p.kg = 2; }
         }

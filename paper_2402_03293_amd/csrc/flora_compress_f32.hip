@@ -196,11 +196,13 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
         }
     };
 
-    f32x4 acc[MT][NT];
+    // (the two halves of a tile add up apart: sums over 1024 columns then round no more than those over 512
+    // in one chain)
+    f32x4 acc[MT][NT], acc2[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = acc2[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // A workgroup that owns its rows outright fetches the old state now, so that the read is
     // long finished when the epilogue needs it (clamped addresses; unused lanes read row n-1).
@@ -234,8 +236,8 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         const float x = gt[mt][c][t];
-                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(MAP == 1 ? x * x : x, bv[nt][t],
-                                                                           acc[mt][nt], 0, 0, 0);
+                        f32x4& sum = c < 2 ? acc[mt][nt] : acc2[mt][nt];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x4f32(MAP == 1 ? x * x : x, bv[nt][t], sum, 0, 0, 0);
                     }
         }
     };
@@ -281,6 +283,11 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
         if (active) mfma_tile(gt, 0, false);
         __syncthreads();
     }
+
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] += acc2[mt][nt];
 
     // D layout of the 16x16 tile: lane holds column lane % 16, rows 4 * (lane / 16) + v.
     // Column groups 1 .. KG-1 hand their partial sums to group 0 through LDS; group 0 adds

@@ -189,7 +189,7 @@ def test_compress_bf16_every_launch_shape(n, m, r, mt):
 
 
 # the fp32 kernel with the pieces and column groups it chooses: a launch of few workgroups (pieces of 256
-# columns, two column groups), one of more (512), and sets large enough for 1024 and 2048.  Products and
+# columns, two column groups), one of more (512), and sets large enough for 1024.  Products and
 # sums are fp32: about sqrt(m) 2^-24 = 3e-6 at the widest, TOL_F32 as for the other shapes.
 @pytest.mark.parametrize("count,n,m", [(1, 33, 1), (1, 70, 257), (2, 65, 515), (130, 64, 1027), (620, 63, 1030), (1300, 31, 2053)])
 @pytest.mark.parametrize("r", [8, 32])
