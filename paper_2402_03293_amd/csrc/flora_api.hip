@@ -570,23 +570,21 @@ void build_transfer_T_items(Plan& p)
 
 // The factored rule's reduction passes as quadratic forms in Gram matrices (flora_gram.hip): chosen
 // when that is clearly less arithmetic than two passes over the n x m product, 6 (m + n) r^2 against
-// 4 n m r flops per matrix, and expected to be shorter: the sums of r x r matrices take twice the launches.
-// Microseconds per GFLOP and the difference of the launches, from 1, 4 and 16 matrices of 128 x 128 ..
-// 1600 x 6400, e.g. (passes / Gram sums) 16 of 1024 x 1024 at r = 64 54 / 62 us, 16 of 768 x 3072 101 / 89,
-// 4 of 2048 x 2048 at r = 256 82 / 140, 16 of 1600 x 6400 593 / 524, 384 of T5-3B shapes 4.5 / 2.1 ms.
+// 4 n m r flops per matrix (with a margin: kernels with r x r outputs and split sums run the
+// matrix cores less efficiently than the long sweeps of the decompression).  The two routes round at
+// different places, so their statistics differ by 2e-4 to 7e-4: the rule compares work per matrix and
+// never the number of matrices in the call, or a matrix stepped alone and one stepped with others of its
+// shape would get different statistics.
 bool choose_gram(const Plan& p)
 {
     if (!rank_bf16(p.r)) return false;
     if (g_tune.factored_gram) return g_tune.factored_gram == 2;
     double pass = 0.0, gram = 0.0;
     for (const MatDev& M : p.host_mats) {
-        pass += 4e-9 * (double)M.n * (double)M.m * p.r;
-        gram += 6e-9 * ((double)M.n + (double)M.m) * p.r * p.r;
+        pass += 4.0 * (double)M.n * (double)M.m * p.r;
+        gram += 6.0 * ((double)M.n + (double)M.m) * p.r * p.r;
     }
-    if (1.5 * gram >= pass) return false;
-    if (p.r == 64) return 14.0 + 2.0 * gram < 2.4 * pass;
-    if (p.r == 128) return 22.0 + 3.0 * gram < 2.2 * pass;
-    return 62.0 + 3.2 * gram < 1.73 * pass;
+    return 1.5 * gram < pass;
 }
 
 void build_gram_items(Plan& p)

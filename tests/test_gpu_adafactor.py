@@ -425,3 +425,26 @@ def test_factored_rule_through_gram_matrices(r, clip_d, beta2):
         assert rel_fro(to64(res[2][2][l]), to64(res[1][2][l])) < 2e-3
         e = rel_fro(to64(res[2][1][l]), Rr)
         print("gram route r=%d %s: R err %.2e K err %.2e" % (r, shapes[l], e, rel_fro(to64(res[2][2][l]), Kr)))
+
+
+# The route (Gram matrices or passes) may not depend on how many matrices share the call: the statistics of one
+# matrix stepped alone, with 3 and with 15 others of its shape.  Between calls only the pieces of the fp32 sums
+# differ (1e-6), which turns a few bf16 roundings of Gram entries (2^-9 each, on a share of about 1e-3 of the
+# r^2 terms of a quadratic form: 2^-9 sqrt(1e-3) / r < 1e-6); the two routes are 2e-4 apart at least.
+@pytest.mark.parametrize("n,m,r", [(768, 3072, 128), (512, 2048, 64), (1600, 2048, 256)])
+def test_factored_statistics_do_not_depend_on_the_number_of_matrices(n, m, r):
+    g = torch.Generator(device="cpu").manual_seed(r)
+    S = torch.randn(n, r, generator=g).to(DEV)
+    W0 = torch.randn(n, m, generator=g).to(DEV)
+    got = []
+    for count in (1, 4, 16):
+        Ws, Ss = [W0.clone() for _ in range(count)], [S.clone() for _ in range(count)]
+        R = [torch.full((n,), 0.5, device=DEV) for _ in range(count)]
+        K = [torch.full((m,), 0.5, device=DEV) for _ in range(count)]
+        mats = flora.matrices([(n, m)] * count, weights=Ws, states=Ss, row_stats=R, col_stats=K, seeds=[9] * count)
+        flora.apply_update(mats, r, flora.F32, flora.factored_update(1e-2, 1.0, 0.2, 1e-30, 1.0))
+        sync()
+        got.append((to64(R[0]), to64(K[0]), to64(Ws[0]) - to64(W0)))
+    for one in got[1:]:
+        for a, b in zip(one, got[0]):
+            assert rel_fro(a, b) < 2e-5
