@@ -161,8 +161,8 @@ int flora_decompress(const flora_matrix_t* mats, int count, int r, float alpha,
 /* Momentum transfer (Algorithm 2, resample branch), computed as
  * T = A(seed)^T A(seed_next) (r x r, in the workspace) and then
  *     state <- state T        ( = state A(seed)^T A(seed_next) )
- * at fp32 precision (at ranks >= 64 as six products of bf16 parts per fp32 product, whose error is no
- * larger than that of fp32 sums).  Uses state, n, m, seed, seed_next.  The caller replaces
+ * at fp32 precision (at ranks >= 64 as six products of bf16 parts per fp32 product: what is left out is
+ * at most 2^-24 of it, as much as one fp32 rounding, and the sums round less often).  Uses state, n, m, seed, seed_next.  The caller replaces
  * seed by seed_next afterwards. */
 int flora_momentum_transfer(const flora_matrix_t* mats, int count, int r, void* hip_stream);
 

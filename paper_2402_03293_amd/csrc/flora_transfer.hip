@@ -174,30 +174,35 @@ __global__ __launch_bounds__(256) void apply_T_kernel(const MatDev* __restrict__
 // ---------------------------------------------------------------------------
 // Ranks 64 and above: fp32 products on the bf16 matrix cores.  An fp32 value is the exact sum of three bf16
 // values, hi + mid + lo (8 significand bits each), and a product of two of them is the sum of nine
-// products of parts, of which the six below 2^-24 of the whole are kept: lo hi, hi lo, mid mid, mid hi,
-// hi mid, hi hi.  v_mfma_f32_32x32x16_bf16 does six of those in 0.4 of the time that
-// v_mfma_f32_16x16x4_f32 takes for the product (2200 / 6 against 140 TFLOP/s).  In the long sums over
-// columns every 16 contracted indexes are summed from zero, smallest parts first, and added to the
-// accumulator once: a quarter of the roundings at the accumulator's size that the fp32 instruction
-// makes.  Error of state A^T A' against 64 bits on the GPT-2 XL set at r = 256: 4.7e-7 with fp32
-// instructions, 2.5e-7 so.
+// products of parts, of which six are kept: lo hi, hi lo, mid mid, mid hi, hi mid, hi hi.  The three left out
+// are 2^-24 of the product at most and 6e-9 of it in the root mean square.  v_mfma_f32_32x32x16_bf16 does six
+// of those in 0.4 of the time that v_mfma_f32_16x16x4_f32 takes for the product (2200 / 6 against 140
+// TFLOP/s).  In the long sums over columns every 16 contracted indexes are summed from zero, smallest parts
+// first, and added to the accumulator once: a quarter of the roundings at the accumulator's size that
+// the fp32 instruction makes.  Errors against 64 bits (T alone is what a unit state gets): T of 1 / 2 / 3 / 16 /
+// 200 / 5000 columns 3.4 / 3.3 / 3.3 / 3.3 / 7.4 / 19e-8 (fp32 instructions 2.5 / 3.1 / 3.6 / 7.4 / 26 / 57e-8:
+// smaller only for one product or two); a dense state times T at r = 64 / 128 / 256, 1 to 5000 columns, 11
+// to 22 / 17 to 25 / 25 to 32e-8 (14 to 59 / 21 to 60 / 30 to 63e-8).
 constexpr int kKT = 16;            // contracted indexes per tile
 constexpr int kLdk = kKT + 8;      // padded LDS row (bf16 elements): 48 bytes, conflict-free 16-byte reads
 
-// x0, x1 -> packed hi, mid, lo parts.  hi is cut off, not rounded, so that no finite value becomes
-// infinite; infinities and NaNs stay in hi alone.
+// x0, x1 -> packed hi, mid, lo parts, each rounded to nearest: mid is at most 2^-8 and lo 2^-17 of x, which is
+// what bounds the products left out.  (Where x would round beyond the largest bf16 value hi is that value; infinities
+// and NaNs stay in hi alone.)
 template <bool FINITE>
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo)
 {
-    uint32_t h0 = __float_as_uint(x0) & 0xffff0000u, h1 = __float_as_uint(x1) & 0xffff0000u;
-    float r0 = x0 - __uint_as_float(h0), r1 = x1 - __uint_as_float(h1);
+    constexpr float kMax = 0x1.fep127f;
+    if (FINITE) hi = pack_bf16x2(x0, x1);
+    else hi = pack_bf16x2(__builtin_amdgcn_fmed3f(x0, -kMax, kMax), __builtin_amdgcn_fmed3f(x1, -kMax, kMax));
+    float r0 = x0 - __uint_as_float(hi << 16), r1 = x1 - __uint_as_float(hi & 0xffff0000u);
     if (!FINITE) {
-        h0 = __builtin_amdgcn_classf(x0, 0x003) ? 0x7fc00000u : h0;       // NaN
-        h1 = __builtin_amdgcn_classf(x1, 0x003) ? 0x7fc00000u : h1;
-        r0 = __builtin_amdgcn_classf(x0, 0x207) ? 0.f : r0;               // NaN or infinite
-        r1 = __builtin_amdgcn_classf(x1, 0x207) ? 0.f : r1;
+        const bool n0 = __builtin_amdgcn_classf(x0, 0x207), n1 = __builtin_amdgcn_classf(x1, 0x207);      // NaN or infinite
+        const uint32_t h = pack_bf16x2(x0, x1);
+        hi = (n0 ? h & 0xffffu : hi & 0xffffu) | (n1 ? h & 0xffff0000u : hi & 0xffff0000u);
+        r0 = n0 ? 0.f : r0;
+        r1 = n1 ? 0.f : r1;
     }
-    hi = (h0 >> 16) | h1;
     mid = pack_bf16x2(r0, r1);
     lo = pack_bf16x2(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u));
 }

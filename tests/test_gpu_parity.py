@@ -448,8 +448,8 @@ def test_transfer_accumulate(n, m, r, a, b):
 
 
 # The transfer's split products at the edges of its pieces: chunks of 1024 columns, tiles of 16 columns, blocks
-# of 64 rows, r = 256 with many chunks (a workgroup per chunk) and few (one per slab of T).  Bar: no larger
-# than the fp32 error of sums of this length, 2^-24 sqrt(m + r) at worst, plus the generator's 1e-7.
+# of 64 rows, r = 256 with many chunks (a workgroup per chunk) and few (one per slab of T).  Bar: what fp32
+# sums of this length may be off, 2^-24 sqrt(m + r), plus the generator's share.
 @pytest.mark.parametrize("n,m,r,count", [(1, 1, 64, 1), (63, 15, 128, 2), (65, 17, 256, 1), (64, 1024, 64, 1), (130, 1025, 128, 1),
                                          (129, 2047, 256, 1), (70, 1041, 256, 130), (5, 3000, 64, 3)])
 def test_transfer_split_products_at_edges(n, m, r, count):
@@ -461,6 +461,36 @@ def test_transfer_split_products_at_edges(n, m, r, count):
     for l in sorted({0, count // 2, count - 1}):
         ref = oracle.transfer(to64(S0[l]), m, so[l], sn[l])
         assert rel_fro(to64(st[l]), ref) < 2.0 ** -24 * (m + r) ** 0.5 + 4e-7, l
+
+
+# One product of two fp32 values as products of parts: a unit state times T = a b^T (one column).  What is left
+# out is at most 2^-24 of the product, the last addition rounds by 2^-24, the five before it by less than that
+# together; with parts cut off instead of rounded what is left out reaches 2^-22.  Then sums of a few
+# columns, against the same sums of fp32 products in numpy.
+@pytest.mark.parametrize("r", [64, 128, 256])
+def test_transfer_split_products_round_like_fp32(r):
+    def A(seed, m):
+        a = torch.empty(m, r, device=DEV)
+        assert flora.lib().flora_debug_generate(seed, m, r, a.data_ptr(), None, None) == flora.OK
+        sync()
+        return a.cpu().numpy()
+
+    def T_of(m, s0, s1):
+        unit = torch.eye(r, device=DEV)
+        flora.momentum_transfer(flora.matrices([(r, m)], states=[unit], seeds=[s0], seeds_next=[s1]), r)
+        sync()
+        return to64(unit)
+
+    for s in range(8):
+        ref = np.outer(A(5 + s, 1)[0].astype(np.float64), A(99 + s, 1)[0].astype(np.float64))
+        assert np.abs(T_of(1, 5 + s, 99 + s) / ref - 1.0).max() < 3 * 2.0 ** -24
+    for m in (5, 16, 40, 300):
+        a, b = A(7, m), A(8, m)
+        ref = a.astype(np.float64).T @ b.astype(np.float64)
+        fp32 = np.zeros((r, r), np.float32)
+        for j in range(m):
+            fp32 += np.outer(a[j], b[j])
+        assert rel_fro(T_of(m, 7, 8), ref) < rel_fro(fp32, ref), m
 
 
 # T's tiles dealt to groups of waves: sets around 256 pieces (r = 64 and 128: four and two groups up to there),
