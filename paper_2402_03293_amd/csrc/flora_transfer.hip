@@ -187,22 +187,12 @@ constexpr int kKT = 16;            // contracted indexes per tile
 constexpr int kLdk = kKT + 8;      // padded LDS row (bf16 elements): 48 bytes, conflict-free 16-byte reads
 
 // x0, x1 -> packed hi, mid, lo parts, each rounded to nearest: mid is at most 2^-8 and lo 2^-17 of x, which is
-// what bounds the products left out.  (Where x would round beyond the largest bf16 value hi is that value; infinities
-// and NaNs stay in hi alone.)
-template <bool FINITE>
+// what bounds the products left out.  Where hi is infinite or a NaN (so is x, or it rounds beyond the largest bf16
+// value) the parts do not stand for x.
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo)
 {
-    constexpr float kMax = 0x1.fep127f;
-    if (FINITE) hi = pack_bf16x2(x0, x1);
-    else hi = pack_bf16x2(__builtin_amdgcn_fmed3f(x0, -kMax, kMax), __builtin_amdgcn_fmed3f(x1, -kMax, kMax));
-    float r0 = x0 - __uint_as_float(hi << 16), r1 = x1 - __uint_as_float(hi & 0xffff0000u);
-    if (!FINITE) {
-        const bool n0 = __builtin_amdgcn_classf(x0, 0x207), n1 = __builtin_amdgcn_classf(x1, 0x207);      // NaN or infinite
-        const uint32_t h = pack_bf16x2(x0, x1);
-        hi = (n0 ? h & 0xffffu : hi & 0xffffu) | (n1 ? h & 0xffff0000u : hi & 0xffff0000u);
-        r0 = n0 ? 0.f : r0;
-        r1 = n1 ? 0.f : r1;
-    }
+    hi = pack_bf16x2(x0, x1);
+    const float r0 = x0 - __uint_as_float(hi << 16), r1 = x1 - __uint_as_float(hi & 0xffff0000u);
     mid = pack_bf16x2(r0, r1);
     lo = pack_bf16x2(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u));
 }
@@ -293,7 +283,7 @@ __global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64 * KG) void tr
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 uint32_t h, m, l;
-                split3<true>(ok0 ? z0.z[i] : 0.f, ok1 ? z1.z[i] : 0.f, h, m, l);
+                split3(ok0 ? z0.z[i] : 0.f, ok1 ? z1.z[i] : 0.f, h, m, l);
                 *reinterpret_cast<uint32_t*>(&lds[buf][0][4 * q + i][jp]) = h;
                 *reinterpret_cast<uint32_t*>(&lds[buf][1][4 * q + i][jp]) = m;
                 *reinterpret_cast<uint32_t*>(&lds[buf][2][4 * q + i][jp]) = l;
@@ -400,8 +390,8 @@ __global__ __launch_bounds__(4 * R) void combine_T_kernel(const MatDev* __restri
 #pragma unroll
         for (int i = 0; i < 4; ++i) s[i] += ldg(src + (size_t)c * R * R + i * R);
     uint32_t h[2], m[2], l2[2];
-    split3<true>(s[0], s[1], h[0], m[0], l2[0]);
-    split3<true>(s[2], s[3], h[1], m[1], l2[1]);
+    split3(s[0], s[1], h[0], m[0], l2[0]);
+    split3(s[2], s[3], h[1], m[1], l2[1]);
     __syncthreads();                               // these rows of the first partial have been read
     FLORA_GLOBAL v2u* t = (FLORA_GLOBAL v2u*)(M.T + (size_t)(kKT * b) * R);
     FLORA_GLOBAL v2u* l = (FLORA_GLOBAL v2u*)(M.rowpart + (size_t)(kKT * b) * R);
@@ -414,6 +404,9 @@ __global__ __launch_bounds__(4 * R) void combine_T_kernel(const MatDev* __restri
 // rows are split into LDS (double buffered, fetched a step ahead); T's parts lie in memory as the operands
 // want them and go straight to registers, a step ahead too.  All rows are read before any is stored,
 // so the destination may be the state itself.
+// The parts of an infinite entry, times parts of T that may have either sign, would add up to a NaN: rows with an
+// entry that is not finite (or too large for bf16) are noted while they are split, left out of the stores and
+// multiplied in fp32 at the end.
 // On the GPT-2 XL set at r = 256: 1.03 ms with fp32 instructions, 0.65 with T's parts passed through LDS, 0.59
 // so; the products alone take 0.39 and the states' traffic alone 0.27, which three workgroups per compute
 // unit overlap in part (128 or 256 rows per workgroup, for less traffic of T: 0.63 and 0.68).
@@ -426,6 +419,7 @@ __global__ __launch_bounds__((R / 32 / WC) * 64, 3) void apply_T_split_kernel(co
     constexpr int FA = ROWS * kKT / 2 / TH;        // pairs of state entries per thread and step
     static_assert((ROWS * kKT / 2) % TH == 0, "whole pairs per thread");
     __shared__ __attribute__((aligned(16))) uint16_t ldsA[2][3][ROWS][kKT];
+    __shared__ uint32_t lds_odd[ROWS / 32];        // rows with an entry that has no parts
 
     const WorkItem it = items[blockIdx.x];
     const MatDev& M = mats[it.mat];
@@ -434,6 +428,7 @@ __global__ __launch_bounds__((R / 32 / WC) * 64, 3) void apply_T_split_kernel(co
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ln = lane & 31, g = lane >> 5;
     const int ct0 = wave * WC;
+    if (tid < ROWS / 32) lds_odd[tid] = 0u;
     const long long row0 = it.row0;
     const long long row_end = row0 + it.rows < M.n ? row0 + it.rows : M.n;
     const float* T = M.T;
@@ -441,6 +436,10 @@ __global__ __launch_bounds__((R / 32 / WC) * 64, 3) void apply_T_split_kernel(co
     float* dst = M.out ? reinterpret_cast<float*>(M.out) : M.state;
 
     v2f sa[FA];
+    typedef uint16_t v2h __attribute__((ext_vector_type(2)));
+    v2h most[FA];                                  // largest hi parts of this thread's share of row (tid + TH i) / 8
+#pragma unroll
+    for (int i = 0; i < FA; ++i) most[i] = v2h{0, 0};
     auto fetch_A = [&](int step) {
 #pragma unroll
         for (int i = 0; i < FA; ++i) {
@@ -454,7 +453,8 @@ __global__ __launch_bounds__((R / 32 / WC) * 64, 3) void apply_T_split_kernel(co
         for (int i = 0; i < FA; ++i) {
             const int f = tid + TH * i, rr = f >> 3, k = (2 * (f & 7)) ^ half_swap(rr);
             uint32_t h, m, l;
-            split3<false>(sa[i].x, sa[i].y, h, m, l);
+            split3(sa[i].x, sa[i].y, h, m, l);
+            most[i] = __builtin_elementwise_max(most[i], __builtin_bit_cast(v2h, h & 0x7fff7fffu));
             *reinterpret_cast<uint32_t*>(&ldsA[buf][0][rr][k]) = h;
             *reinterpret_cast<uint32_t*>(&ldsA[buf][1][rr][k]) = m;
             *reinterpret_cast<uint32_t*>(&ldsA[buf][2][rr][k]) = l;
@@ -505,24 +505,66 @@ __global__ __launch_bounds__((R / 32 / WC) * 64, 3) void apply_T_split_kernel(co
         __builtin_amdgcn_sched_barrier(0);
         if (step + 1 < STEPS) stash_A(buf ^ 1);
         if (step + 2 < STEPS) fetch_A(step + 2);
+        if (step + 1 == STEPS)
+#pragma unroll
+            for (int i = 0; i < FA; ++i)
+                if (most[i].x >= 0x7f80 || most[i].y >= 0x7f80) atomicOr(&lds_odd[(tid + TH * i) >> 8], 1u << (((tid + TH * i) >> 3) & 31));
         __syncthreads();
     }
 
     // (old values of a row of tiles first: few round trips)
+    const int nvalid = (int)(row_end - row0);
 #pragma unroll
     for (int r = 0; r < WR; ++r) {
-        auto at = [&](int v) { return row0 + 32 * r + 8 * (v / 4) + 4 * g + (v % 4); };
+        const uint32_t valid = nvalid >= 32 * (r + 1) ? ~0u : (nvalid > 32 * r ? (1u << (nvalid - 32 * r)) - 1u : 0u);
+        const uint32_t live = (valid & ~lds_odd[r]) >> (4 * g);        // this lane's rows: bits 8 (v / 4) + v % 4
+        float* at = dst + (row0 + 32 * r + 4 * g) * R + 32 * ct0 + ln;
         float old[WC][16];
 #pragma unroll
         for (int c = 0; c < WC; ++c)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                old[c][v] = (ca != 0.f && at(v) < row_end) ? ldg(dst + at(v) * R + 32 * (ct0 + c) + ln) : 0.f;
+                old[c][v] = (ca != 0.f && (live >> (8 * (v / 4) + v % 4) & 1u)) ? ldg(at + (8 * (v / 4) + v % 4) * R + 32 * c) : 0.f;
 #pragma unroll
         for (int c = 0; c < WC; ++c)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                if (at(v) < row_end) stg(dst + at(v) * R + 32 * (ct0 + c) + ln, ca * old[c][v] + cb * acc[r][c][v]);
+                if (live >> (8 * (v / 4) + v % 4) & 1u) stg(at + (8 * (v / 4) + v % 4) * R + 32 * c, ca * old[c][v] + cb * acc[r][c][v]);
+    }
+
+    // Rows with an entry that has no parts: in fp32, by every wave for its own columns
+#pragma unroll 1
+    for (int q = 0; q < ROWS / 32; ++q) {
+        uint32_t rows = lds_odd[q];
+#pragma unroll 1
+        for (; rows != 0u; rows &= rows - 1u) {
+            const int rr = 32 * q + __builtin_ctz(rows);
+            if (rr >= nvalid) break;               // (rows past the end are copies of the last)
+            const float* x = M.state + (row0 + rr) * R;
+            float sum[WC];
+#pragma unroll
+            for (int c = 0; c < WC; ++c) sum[c] = 0.f;
+#pragma unroll 1
+            for (int k = 0; k < R; ++k) {
+                const float xk = ldg(x + k);
+                const size_t blk = (size_t)(k & ~(kKT - 1)) * R;
+                const uint16_t* th = reinterpret_cast<const uint16_t*>(T + blk);
+                const uint16_t* tl = reinterpret_cast<const uint16_t*>(Tlo + blk);
+#pragma unroll
+                for (int c = 0; c < WC; ++c) {
+                    const int at = kKT * (32 * (ct0 + c) + ln) + (k & (kKT - 1));
+                    const float t = bf16_bits_to_f32(ldg(th + at)) + (bf16_bits_to_f32(ldg(th + kKT * R + at)) + bf16_bits_to_f32(ldg(tl + at)));
+                    sum[c] = __builtin_fmaf(xk, t, sum[c]);
+                }
+            }
+            __syncthreads();                       // every wave has read the row
+            if (g == 0)
+#pragma unroll
+                for (int c = 0; c < WC; ++c) {
+                    float* d = dst + (row0 + rr) * R + 32 * (ct0 + c) + ln;
+                    stg(d, (ca != 0.f ? ca * ldg(d) : 0.f) + cb * sum[c]);
+                }
+        }
     }
 }
 

@@ -501,24 +501,47 @@ def test_transfer_tiles_in_groups(n, m, r, count):
     test_transfer_split_products_at_edges(n, m, r, count)
 
 
-# infinities and NaNs in a state stay in their rows, and what the fp32 product gives for them is what comes out
-@pytest.mark.parametrize("r", [64, 256])
-def test_transfer_of_states_that_are_not_finite(r):
-    n, m = 70, 300
-    S = rand((n, r), 77)
-    S[3, 5], S[40, 0], S[64, r - 1] = float("inf"), float("nan"), 3.3e38
-    M = S.clone()
-    flora.momentum_transfer(flora.matrices([(n, m)], states=[M], seeds=[5], seeds_next=[6]), r)
-    sync()
+# What is not finite in a state stays in its row and comes out as the fp32 product gives it: inf times T's entry
+# has that entry's sign, two infinities of opposite signs in one sum are a NaN, a NaN is one in the whole row.
+@pytest.mark.parametrize("n,accumulate", [(70, False), (129, True), (64, False), (1, False)])
+@pytest.mark.parametrize("r", [8, 64, 128, 256])
+def test_transfer_of_states_that_are_not_finite(r, n, accumulate):
+    m, inf = 300, float("inf")
     clean = rand((n, r), 77)
-    ref = oracle.transfer(to64(clean), m, 5, 6)
-    ok = [i for i in range(n) if i not in (3, 40, 64)]
-    assert rel_fro(to64(M)[ok], ref[ok]) < TOL_F32
-    assert not torch.isfinite(M[3]).any() and torch.isnan(M[40]).all()
+    S = clean.clone()
+    put = {0: [(3, inf)], 3: [(5, inf)], 31: [(0, -inf)], 33: [(r - 1, inf), (2, 1e30)], 40: [(0, float("nan"))],
+           63: [(1, inf), (r - 2, -inf)], 64: [(r - 1, 3.3e38)], n - 1: [(r // 2, -inf)]}
+    put = {i: v for i, v in put.items() if i < n}
+    for i, entries in put.items():
+        for k, v in entries:
+            S[i, k] = v
+    M, out = S.clone(), torch.zeros((n, r), device=DEV)
+    mats = flora.matrices([(n, m)], states=[M], seeds=[5], seeds_next=[6])
+    if accumulate:
+        flora.transfer_accumulate(mats, r, 0.0, 1.0, [out])
+    else:
+        flora.momentum_transfer(mats, r)
+        out = M
+    sync()
+    got = to64(out)
+    finite = [i for i in range(n) if i not in put]
+    if finite:
+        assert rel_fro(got[finite], oracle.transfer(to64(clean), m, 5, 6)[finite]) < TOL_F32
     T = oracle.transfer(np.eye(r), m, 5, 6)
-    big = 3.3e38 * T[r - 1]
-    fits = np.abs(big) < 3e38
-    assert fits.any() and np.abs(to64(M)[64][fits] / big[fits] - 1).max() < 1e-4
+    big = np.abs(T) > 1e-5 * np.abs(T).max()          # (the sign of an entry nearer to zero is a matter of rounding)
+    for i, entries in put.items():
+        infs = [(k, v) for k, v in entries if np.isinf(v)]
+        if any(np.isnan(v) for _, v in entries):
+            assert np.isnan(got[i]).all(), i
+        elif infs:
+            signs = np.stack([np.sign(v) * np.sign(T[k]) for k, v in infs])
+            sure = np.stack([big[k] for k, _ in infs]).all(axis=0)
+            want = np.where((signs == signs[0]).all(axis=0), signs[0] * inf, np.nan)
+            assert np.array_equal(got[i][sure], want[sure], equal_nan=True), i
+        else:                                         # huge but finite
+            want = entries[0][1] * T[entries[0][0]]
+            fits = np.abs(want) < 3e38
+            assert fits.any() and np.abs(got[i][fits] / want[fits] - 1).max() < 1e-4
 
 
 def test_transfer_accumulate_grouped_and_errors():
