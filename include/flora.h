@@ -46,8 +46,9 @@
  *     carved from the caller's buffer and the library calls neither hipMalloc nor hipHostMalloc.
  *     Either way a call whose pointers have been seen before uploads nothing; one with new
  *     pointers (another buffer of a ring, a freshly allocated gradient) costs one small upload
- *     on the stream and no allocation or synchronisation, so calling once per matrix from a
- *     training loop stays cheap.  No per-matrix state (seed, step, epoch) is kept between calls:
+ *     on the stream and no allocation or synchronisation (a host that is more new pointer sets
+ *     ahead of the stream than the images kept, see below, waits for the oldest upload, never for
+ *     the stream), so calling once per matrix from a training loop stays cheap.  No per-matrix state (seed, step, epoch) is kept between calls:
  *     that lives with the caller.
  *   - HIP graphs.  A call whose shapes and pointers have been seen on its stream is kernel
  *     launches only and may be recorded into a HIP graph (seeds are kernel arguments: a resample

@@ -13,6 +13,7 @@
 #include <cstring>
 #include <functional>
 #include <mutex>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -786,6 +787,19 @@ int place_plan(Plan* p, hipStream_t stream)
     return FLORA_OK;
 }
 
+// Waits until a slot's last upload has read the staging.  As a rule that was image_cap uploads ago; a host
+// further ahead of the stream than that waits for this upload alone, not for what was enqueued after it.
+int wait_uploaded(const Image& im, hipStream_t stream)
+{
+    while (im.done && __atomic_load_n(im.done, __ATOMIC_ACQUIRE) != im.gen) {
+        const hipError_t e = hipStreamQuery(stream);
+        if (e == hipSuccess) break;                // nothing is left that could read it
+        if (e != hipErrorNotReady) FLORA_HIP(e);
+        std::this_thread::yield();
+    }
+    return FLORA_OK;
+}
+
 // Plans the call being prepared needs (caller's workspace only).
 std::vector<Plan*> g_pending;
 
@@ -932,8 +946,8 @@ int get_plan(int kind, int variant, int r, const std::vector<MatDev>& mats, hipS
                 p->index.erase(it);
                 break;
             }
-        // (long done as a rule: image_cap calls ago; otherwise the stream is waited for)
-        if (old.done && __atomic_load_n(old.done, __ATOMIC_ACQUIRE) != old.gen) FLORA_HIP(hipStreamSynchronize(stream));
+        const int st = wait_uploaded(old, stream);
+        if (st != FLORA_OK) return st;
     }
     Image& im = p->images[(size_t)slot];
     im.img = img;

@@ -758,3 +758,49 @@ def test_micro_batches_accumulated_straight_into_the_momentum(r, gdt):
     mean = sum(to64(g) for g in G) / tau
     ref = oracle.compress(mean, r, seed, state=to64(M0), a=beta, b=1.0 - beta)
     assert rel_fro(to64(M) - beta * to64(M0), ref - beta * to64(M0)) < tol_for(r)
+
+
+# More pointer sets than a plan keeps descriptor images of (64 above four matrices, 512 up to there): slots are used
+# again while earlier calls are still queued, twice over, and every call must have seen its own pointers.
+@pytest.mark.parametrize("count,sets", [(5, 150), (1, 1100)])
+def test_more_pointer_sets_than_descriptor_images(count, sets):
+    n, m, r = 17, 40, 8
+    G = rand((sets, count, n, m), 41)
+    st = torch.zeros((sets, count, n, r), device=DEV)
+    seeds = [3 + l for l in range(count)]
+    mats = [flora.matrices([(n, m)] * count, grads=[G[i, l] for l in range(count)], states=[st[i, l] for l in range(count)], seeds=seeds)
+            for i in range(sets)]
+    busy = torch.randn(4096, 4096, device=DEV)
+    sync()
+    for _ in range(2):
+        for _ in range(3):
+            busy @ busy
+        for i in range(sets):
+            flora.compress(mats[i], r, flora.F32, 0.5, 1.0)
+    sync()
+    for i in sorted({0, 1, 63, 64, 65, 127, 128, 149, 511, 512, 513, 1024, sets - 1} & set(range(sets))):
+        for l in range(count):
+            assert rel_fro(to64(st[i, l]), 1.5 * oracle.compress(to64(G[i, l]), r, seeds[l])) < TOL_F32, (i, l)
+
+
+def test_a_new_pointer_set_waits_for_an_old_upload_not_for_the_stream():
+    count, n, m, r = 5, 16, 32, 8
+    G, st = rand((65, count, n, m), 42), torch.zeros((65, count, n, r), device=DEV)
+    mats = [flora.matrices([(n, m)] * count, grads=list(G[i]), states=list(st[i]), seeds=list(range(count))) for i in range(65)]
+    busy = torch.randn(8192, 8192, device=DEV)
+    busy @ busy
+    flora.set_tuning("compress_f32_mt", 0)            # plans start anew
+    sync()
+    for _ in range(3):
+        busy @ busy                                   # 1.1 TFLOP each: the uploads below wait for these
+    for i in range(64):
+        flora.compress(mats[i], r, flora.F32, 0.0, 1.0)
+    for _ in range(40):
+        busy @ busy
+    after = torch.cuda.Event()
+    after.record()
+    flora.compress(mats[64], r, flora.F32, 0.0, 1.0)  # takes the first one's slot
+    assert not after.query()
+    sync()
+    for i in (0, 63, 64):
+        assert rel_fro(to64(st[i, 0]), oracle.compress(to64(G[i, 0]), r, 0)) < TOL_F32
