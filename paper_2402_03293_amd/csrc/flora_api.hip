@@ -111,9 +111,11 @@ struct Plan {
     size_t tbytes = 0;                  // bytes of the tables
     size_t wbytes = 0;                  // bytes of the work area
     bool pending = false;               // needed by the call being prepared (caller's workspace)
-    // factored rule through Gram matrices: items2 = [Gram sums over m | over n | quadratic forms over the
-    // rows of S | over the rows of A]
-    bool gram = false;
+    // where the factored rule's sums come from: passes over the n x m product, which leave partial sums of rows and
+    // columns, or Gram matrices: items2 = [Gram sums over m | over n | quadratic forms over the rows of S |
+    // over the rows of A]
+    enum Route { kNoSums, kPasses, kGram };
+    Route route = kNoSums;
     int n_gm = 0, n_gn = 0, n_qr = 0, n_qc = 0;
 };
 
@@ -448,7 +450,10 @@ void build_compress_bf16_items(Plan& p)
 // us; single matrices of those shapes: update 27-31 -> 18-27 us at r = 256, 17-20 -> 10-17 us at r =
 // 64), and at r >= 128 on to the least that keeps them to one per compute unit (one 1600 x 6400 matrix
 // at r = 256: 175 workgroups of 256 rows 22 us, 250 of 160 19, 325 of 128 29).
-int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r, bool adafactor)
+// colsums: the factored rule's passes, which leave a partial sum of every column per row block (4 m bytes each:
+// 128 rows instead of 256 would hold 177 instead of 96 MiB for T5-3B at r = 32, whose state is 165): never
+// below 256 rows except to reach 140 workgroups.
+int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r, bool adafactor, bool colsums)
 {
     if (g_tune.decompress_rows) return g_tune.decompress_rows;
     auto wgs = [&](int rows) {
@@ -460,20 +465,17 @@ int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r, boo
     double full = 0.0;
     for (const MatDev& M : mats) full += (double)M.n * (double)M.m / (256.0 * cols);
     int rows = 1024;
-    if (r >= 128) {
-        const long long enough = r >= 256 ? 140 : 1000;
-        for (; rows > kDecompressRows; rows /= 2)
-            if (wgs(rows) >= enough) break;
-    } else if (r == 64) {
-        for (; rows > kDecompressRows; rows /= 2)
-            if (wgs(rows) >= 2048) break;
+    const long long enough = r >= 256 ? 140 : (r >= 128 ? 1000 : 2048);
+    for (; rows > kDecompressRows; rows /= 2)
+        if (wgs(rows) >= enough) break;
+    if (!colsums && r == 64) {
         if (full >= 850.0) rows = (adafactor || full < 1024.0) ? 128 : 64;
         else if (!adafactor && wgs(kDecompressRows) < 300) rows = 128;
-    } else {
+    } else if (!colsums && r <= 32) {
         rows = (full >= 1024.0 && !(adafactor && r == 32)) ? 64 : 128;
     }
-    for (; rows > 32 && wgs(rows) < (r <= 32 ? 200 : 140); rows /= 2) {}
-    if (r >= 128)
+    for (; rows > 32 && wgs(rows) < (r <= 32 && !colsums ? 200 : 140); rows /= 2) {}
+    if (r >= 128 && !colsums)
         while (rows > 32 && wgs(rows - 32) <= 256) rows -= 32;
     return rows;
 }
@@ -487,7 +489,7 @@ void build_decompress_items(Plan& p)
     p.vec = vec;
     const int cols = vec ? kDecompressColsVec : kDecompressCols;
     // (the vector kernel addresses a workgroup's state rows with 32-bit byte offsets)
-    const int rows_per_wg = std::min(choose_decompress_rows(p.host_mats, cols, p.r, p.kind == kKindFactored), vec ? (1 << 20) : 0x7fffffe0);
+    const int rows_per_wg = std::min(choose_decompress_rows(p.host_mats, cols, p.r, p.kind == kKindFactored, p.route == Plan::kPasses), vec ? (1 << 20) : 0x7fffffe0);
     struct Group { int mat, rb, row0, rows, nchunks; };
     std::vector<Group> groups;
     for (int l = 0; l < p.count; ++l) {
@@ -592,7 +594,9 @@ void build_gram_items(Plan& p)
 {
     // Pieces of the long index: the largest that still give the chip 384 workgroups (the sums of a launch
     // over a few matrices otherwise run on a workgroup per matrix: 16 GPT-2 base matrices at r = 128, the
-    // two Gram kernels 45 + 73 us in pieces of 3072; smaller pieces cost r^2 floats each, written and read).
+    // two Gram kernels 45 + 73 us in pieces of 3072), as far as memory allows: a piece holds r^2 floats,
+    // and all of them no more than pieces of 3072 and the partial sums that the passes would leave
+    // (24 matrices of T5-3B at r = 256, whose state is 96 MiB: 52 MiB; without the limit 473).
     auto pieces = [&](bool rows, long long most, long long least) {
         for (long long c = most; c > least; c /= 2) {
             long long wgs = 0;
@@ -601,9 +605,30 @@ void build_gram_items(Plan& p)
         }
         return least;
     };
-    const long long chunk_m = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(false, kGramChunk, 192);
-    const long long chunk_n = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(true, kGramChunk, 192);
+    long long chunk_m = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(false, kGramChunk, 192);
+    long long chunk_n = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(true, kGramChunk, 192);
     const long long cols = pieces(false, kQuadformCols, p.r >= 128 ? 512 : 256);
+    // (work tables included: smaller pieces, and workgroups of fewer rows in the update, are more entries)
+    const size_t rr = (size_t)p.r * p.r * 4;
+    auto pieces_of = [](long long len, long long chunk) { return (size_t)((len + chunk - 1) / chunk); };
+    size_t limit = 0;
+    for (const MatDev& M : p.host_mats) {
+        const size_t gm = pieces_of(M.m, kGramChunk), gn = pieces_of(M.n, kGramChunk), nb = pieces_of(M.n, 1024);
+        limit += (2 * gm + gn) * rr + (size_t)M.ncolchunks * M.n * 4 + nb * M.m * 4 +
+                 sizeof(WorkItem) * (gm + gn + nb + pieces_of(M.m, 1024) + nb * M.ncolchunks);
+    }
+    while (!g_tune.gram_chunk && (chunk_m < kGramChunk || chunk_n < kGramChunk)) {
+        size_t need = sizeof(WorkItem) * p.items.size(), by_m = 0, by_n = 0;
+        for (const MatDev& M : p.host_mats) {
+            const size_t gm = pieces_of(M.m, chunk_m), gn = pieces_of(M.n, chunk_n);
+            need += std::max(2 * gm, gn) * rr + sizeof(WorkItem) * (gm + gn + pieces_of(M.n, kQuadformRows) + pieces_of(M.m, cols));
+            by_m += 2 * gm; by_n += gn;
+        }
+        if (need <= limit) break;
+        // (the sums over m and over n take turns in the same memory)
+        if (chunk_n == kGramChunk || (chunk_m < kGramChunk && by_m >= by_n)) chunk_m *= 2;
+        else chunk_n *= 2;
+    }
     auto chunks_of = [&](long long len, long long chunk) { return (int)((len + chunk - 1) / chunk); };
     auto emit_chunks = [&](int l, long long len, int chunks) {
         const long long per = ((len + chunks - 1) / chunks + 63) / 64 * 64;
@@ -647,24 +672,36 @@ void build_gram_items(Plan& p)
     p.n_qc = (int)(p.items2.size() - before);
 }
 
-size_t workspace_bytes_for(const std::vector<MatDev>& mats, int kind, int r, bool gram = false)
+// One matrix's share of an Adafactor plan's work area, in bytes: Gram matrices (P, Q, P' as bf16) and their pieces,
+// partial sums of rows (Gram route: of a row block's R), of columns, of workgroups, and four scalars.
+struct AdafactorShare {
+    size_t bf16 = 0, pieces = 0, row = 0, col = 0, item = 0, scal = 256;
+    size_t total() const { return 3 * bf16 + pieces + row + col + item + scal; }
+};
+AdafactorShare adafactor_share(const MatDev& M, Plan::Route route, int r)
+{
+    AdafactorShare a;
+    a.item = round_up((size_t)std::max(M.nitems, M.item0) * 4, 256);
+    if (route == Plan::kGram) {
+        a.bf16 = round_up((size_t)r * r * 2, 256);
+        a.pieces = round_up((size_t)std::max(2 * M.gchunks_m, M.gchunks_n) * r * r * 4, 256);
+        a.row = round_up((size_t)M.item0 * 4, 256);
+    } else if (route == Plan::kPasses) {
+        a.row = round_up((size_t)M.ncolchunks * M.n * 4, 256);
+        a.col = round_up((size_t)M.nrowblocks * M.m * 4, 256);
+    }
+    return a;
+}
+
+size_t workspace_bytes_for(const std::vector<MatDev>& mats, int kind, int r, Plan::Route route)
 {
     size_t b = 0;
     for (const MatDev& M : mats) {
-        if (kind == kKindFactored && gram) {
-            b += 3 * round_up((size_t)r * r * 2, 256);
-            b += round_up((size_t)(2 * M.gchunks_m + M.gchunks_n) * r * r * 4, 256);
-        }
         if (kind == kKindTransfer) {
             b += round_up((size_t)r * r * 4, 256);
             if (r >= 64) b += round_up((size_t)M.ncolchunks * r * r * 4, 256);
         }
-        if (kind == kKindFactored) {
-            b += round_up((size_t)M.ncolchunks * M.n * 4, 256);
-            b += round_up((size_t)M.nrowblocks * M.m * 4, 256);
-            b += round_up((size_t)std::max(M.nitems, M.item0) * 4, 256);
-            b += 256;
-        }
+        if (kind == kKindFactored) b += adafactor_share(M, route, r).total();
         if (kind == kKindSumsq) b += (size_t)kSumsqBlocks * 4;
     }
     return b;
@@ -719,15 +756,14 @@ void build_host_plan(Plan* p, const std::vector<MatDev>& mats)
         build_transfer_T_items(*p);
         build_apply_T_items(*p);
     } else if (kind != kKindSumsq) {
+        if (kind == kKindFactored && (p->variant & 3) == 2)       // the factored rule (not the unfactored one)
+            p->route = choose_gram(*p) ? Plan::kGram : Plan::kPasses;
         build_decompress_items(*p);
-        if (kind == kKindFactored && (p->variant & 3) == 2) {     // the factored rule (not the unfactored one)
-            p->gram = choose_gram(*p);
-            if (p->gram) build_gram_items(*p);
-        }
+        if (p->route == Plan::kGram) build_gram_items(*p);
     }
     p->off2 = round_up(sizeof(WorkItem) * p->items.size(), 256);
     p->tbytes = p->off2 + round_up(sizeof(WorkItem) * p->items2.size(), 256);
-    p->wbytes = workspace_bytes_for(p->host_mats, kind, r, p->gram);
+    p->wbytes = workspace_bytes_for(p->host_mats, kind, r, p->route);
     if (kind == kKindCompress) p->wbytes = round_up(p->ws_floats * 4, 256) + p->ws_counters * 4;
     p->mats_bytes = round_up(sizeof(MatDev) * (size_t)count, 256);
     // descriptor images kept per plan: many for calls on a few matrices (a training loop that
@@ -879,21 +915,19 @@ int get_plan(int kind, int variant, int r, const std::vector<MatDev>& mats, hipS
             const MatDev& t = p->host_mats[(size_t)l];
             M.ncolchunks = t.ncolchunks; M.nrowblocks = t.nrowblocks; M.item0 = t.item0; M.nitems = t.nitems;
             M.gchunks_m = t.gchunks_m; M.gchunks_n = t.gchunks_n;
-            if (kind == kKindFactored && p->gram) {
-                M.gramP = reinterpret_cast<uint16_t*>(w); w += round_up((size_t)r * r * 2, 256);
-                M.gramQ = reinterpret_cast<uint16_t*>(w); w += 2 * round_up((size_t)r * r * 2, 256);   // Q, then P'
-                M.grampart = reinterpret_cast<float*>(w);
-                w += round_up((size_t)(2 * M.gchunks_m + M.gchunks_n) * r * r * 4, 256);
-            }
             if (kind == kKindTransfer) {
                 M.T = reinterpret_cast<float*>(w); w += round_up((size_t)r * r * 4, 256);
                 if (r >= 64) { M.rowpart = reinterpret_cast<float*>(w); w += round_up((size_t)M.ncolchunks * r * r * 4, 256); }
             }
             if (kind == kKindFactored) {
-                M.rowpart = reinterpret_cast<float*>(w); w += round_up((size_t)M.ncolchunks * M.n * 4, 256);
-                M.colpart = reinterpret_cast<float*>(w); w += round_up((size_t)M.nrowblocks * M.m * 4, 256);
-                M.itempart = reinterpret_cast<float*>(w); w += round_up((size_t)std::max(M.nitems, M.item0) * 4, 256);
-                M.scal = reinterpret_cast<float*>(w); w += 256;
+                const AdafactorShare a = adafactor_share(t, p->route, r);
+                M.gramP = reinterpret_cast<uint16_t*>(w); w += a.bf16;
+                M.gramQ = reinterpret_cast<uint16_t*>(w); w += 2 * a.bf16;     // Q, then P'
+                M.grampart = reinterpret_cast<float*>(w); w += a.pieces;
+                M.rowpart = reinterpret_cast<float*>(w); w += a.row;
+                M.colpart = reinterpret_cast<float*>(w); w += a.col;
+                M.itempart = reinterpret_cast<float*>(w); w += a.item;
+                M.scal = reinterpret_cast<float*>(w); w += a.scal;
             }
         }
     }
@@ -1237,7 +1271,7 @@ static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16,
         if (st != FLORA_OK) return st;
     } else {
         DecompressParams dp{u->alpha, u->lr, u->beta2, u->eps1, wpolicy};
-        const int gram = (factored && p->gram) ? 1 : 0;
+        const int gram = p->route == Plan::kGram ? 1 : 0;
         if (gram) {
             // row and column sums of Gt^2 as quadratic forms in A^T A and S^T S, then the clipping
             // sum as one in A^T diag(1 / K) A: no pass over the n x m product before the update
@@ -1616,7 +1650,9 @@ size_t flora_workspace_bytes(const flora_matrix_t* mats, int count, int r)
         size_t comp = 0;
         if (rank_bf16(r)) comp = std::max(plan_need(kKindCompress, 2, r, mats + c0, cn), plan_need(kKindCompress, 3, r, mats + c0, cn));
         else comp = plan_need(kKindCompress, 0, r, mats + c0, cn);
-        step += comp + plan_need(kKindFactored, 2, r, mats + c0, cn) + plan_need(kKindTransfer, 0, r, mats + c0, cn);
+        const size_t update = std::max({plan_need(kKindFactored, 2, r, mats + c0, cn), plan_need(kKindFactored, 3, r, mats + c0, cn),
+                                        plan_need(kKindDecompress, 0, r, mats + c0, cn)});
+        step += comp + update + plan_need(kKindTransfer, 0, r, mats + c0, cn);
         sumsq += plan_need(kKindSumsq, 0, 0, mats + c0, cn);
     }
     return std::max(step, sumsq);

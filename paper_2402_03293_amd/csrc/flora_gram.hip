@@ -188,8 +188,8 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
     }
 
     // partial of this chunk: D layout, lane holds column 16 ct + li and rows 4 g + v of each tile
-    // (partials: those of P over chunks of m, then those of Q over chunks of n, then those of P')
-    const int part0 = SRC == 0 ? 0 : (SRC == 2 ? M.gchunks_m : M.gchunks_m + M.gchunks_n);
+    // (partials: those of P over chunks of m, then those of P'; or those of Q over chunks of n, combined before)
+    const int part0 = SRC == 1 ? M.gchunks_m : 0;
     float* part = M.grampart + (size_t)(part0 + it.part) * R * R;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -392,8 +392,8 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
     float* turn = reinterpret_cast<float*>(lds_raw) + wave * (32 * 33);     // (only waves that own tiles touch it)
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        // (partials: those of P over chunks of m, then those of Q over chunks of n, then those of P')
-        const int part0 = MODE == 2 ? M.gchunks_m : (c ? M.gchunks_m + M.gchunks_n : 0);
+        // (partials: those of P over chunks of m, then those of P'; or those of Q over chunks of n, combined before)
+        const int part0 = c ? M.gchunks_m : 0;
         float* part = M.grampart + (size_t)(part0 + it.part) * R * R;
 #pragma unroll
         for (int w = 0; w < TW; ++w) {
@@ -427,7 +427,7 @@ __global__ __launch_bounds__(256) void combine_gram_kernel(const MatDev* __restr
     const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;       // four consecutive k1 of one row k2
     if (idx >= R * R) return;
     const int nch = which == 1 ? M.gchunks_n : M.gchunks_m;
-    const int part0 = which == 0 ? 0 : (which == 1 ? M.gchunks_m : M.gchunks_m + M.gchunks_n);
+    const int part0 = which == 2 ? M.gchunks_m : 0;
     const float* src = M.grampart + (size_t)part0 * R * R + idx;
     v4f s = {0.f, 0.f, 0.f, 0.f};
     int c = 0;

@@ -16,13 +16,14 @@ struct MatDev {
     float* wsumsq;      // 1 float: sum of W^2, read for the parameter scale and refreshed by the update
     void* out;          // flora_decompress destination; flora_transfer_accumulate destination (n x r fp32)
     float* T;           // r x r transfer matrix (workspace)
-    float* rowpart;     // [ncolchunks][n] partial row sums of Gt^2; transfer: [chunks][r][r] partials of T (workspace)
+    float* rowpart;     // [ncolchunks][n] partial row sums of Gt^2, Gram route [item0] sums of R; transfer:
+                        // [chunks][r][r] partials of T (workspace)
     float* colpart;     // [nrowblocks][m] partial column sums of Gt^2 (workspace)
     float* itempart;    // [nitems] per-workgroup partial sums of U^2, later of the new W^2 (workspace)
     float* scal;        // [4]: mean(R), clip scale, parameter scale max(eps2, RMS(W)) or 1, spare (workspace)
     uint16_t* gramP;    // r x r bf16: A^T A, later A^T diag(1/K) A (factored rule through Gram matrices; workspace)
     uint16_t* gramQ;    // r x r bf16: S^T S (workspace)
-    float* grampart;    // [chunks][r][r] partial Gram matrices of the chunks of m or of n (workspace)
+    float* grampart;    // [chunks][r][r] partial Gram matrices of the chunks of n, then of m twice (workspace)
     long long n, m;
     uint32_t seed_lo, seed_hi, seedn_lo, seedn_hi;   // used by the transfer kernels only
     int ncolchunks, nrowblocks;   // decompress tiling of this matrix

@@ -204,6 +204,48 @@ def test_workspace_bytes_is_the_sum_of_the_fused_steps_plans(index, r):
                                                     + twork + 8 * image)
 
 
+def _adafactor_bytes_in_large_pieces(shapes, r):
+    """An Adafactor plan whose row blocks are of 256 rows at least (where that gives enough workgroups), with Gram
+    sums in pieces of 3072 beside each other and the passes' partial sums of rows and columns."""
+    vec = r >= 64 and all(m % 4 == 0 for _, m in shapes)
+    cols = 256 if vec else 128
+    up = lambda a, b: -(-a // b)
+    wgs = lambda rows: sum(up(n, rows) * up(m, cols) for n, m in shapes)
+    rows, enough = 1024, 140 if r >= 256 else 1000 if r >= 128 else 2048
+    while rows > 256 and wgs(rows) < enough:
+        rows //= 2
+    while rows > 32 and wgs(rows) < 140:
+        rows //= 2
+    gram = r >= 64 and 9 * sum((n + m) * r * r for n, m in shapes) < 4 * sum(n * m * r for n, m in shapes)
+    items = items2 = work = 0
+    for n, m in shapes:
+        per = up(up(n, up(n, rows)), 32) * 32
+        nb, nc = up(n, per), up(m, cols)
+        items += nb * nc
+        work += _round256(4 * nc * n) + _round256(4 * nb * m) + 256
+        if gram:
+            gm, gn, qr, qc = up(m, 3072), up(n, 3072), up(n, 1024), up(m, 1024)
+            items2 += gm + gn + qr + qc
+            work += 3 * _round256(2 * r * r) + _round256(4 * (2 * gm + gn) * r * r) + _round256(4 * max(nb * nc, qr))
+        else:
+            work += _round256(4 * nb * nc)
+    return _round256(48 * items) + _round256(48 * items2) + _round256(work) + 8 * _round256(184 * len(shapes))
+
+
+# Smaller pieces and row blocks for short launches may not cost memory: the method's point is what a step holds.
+@pytest.mark.parametrize("r", [8, 16, 32, 64, 128, 256])
+def test_adafactor_plans_hold_no_more_than_large_pieces_would(r):
+    t5s, gpt, t53b, xl = (workloads.workload(i).shapes for i in (2, 3, 4, 5))
+    sets = [t5s, gpt, gpt[:16], t53b, t53b[:24], t53b[:32], xl, xl[:16], [(1600, 6400)], [(1600, 6400)] * 16, [(768, 50257)],
+            [(4096, 16384)], [(256, 256)], [(1100, 1003)] * 6 + [(257, 2051)] * 6 + [(770, 3001)] * 6 + [(2000, 777)] * 6,
+            [(33, 1)], [(65, 515)] * 300, [(1023, 999)] * 4, [(8192, 64)] * 9]
+    for shapes in sets:
+        most = _adafactor_bytes_in_large_pieces(shapes, r)
+        assert flora.debug_plan_bytes(3, shapes, r) <= most, (shapes[:2], len(shapes), r)
+        # the rules without column sums fit wherever the factored one does
+        assert flora.debug_plan_bytes(1, shapes, r) <= flora.workspace_bytes(flora.matrices(shapes), r)
+
+
 def test_workspace_bytes_rejects_bad_sets():
     assert flora.workspace_bytes(flora.matrices([(0, 4)]), 16) == 0
     assert flora.workspace_bytes(flora.matrices([(4, 4)]), 12) == 0
