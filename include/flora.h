@@ -261,8 +261,11 @@ void flora_derive_seeds(uint64_t global_seed, uint64_t first_matrix_id, int coun
  * flora_workspace_bytes: the smallest workspace with which every entry point accepts this set of
  * matrices at rank r, i.e. what the most demanding call occupies: flora_fused_step with a
  * transfer and an Adafactor rule (its transfer, compress and update plans are resident together).
- * Exact, not a bound: with one 256-byte unit less that call returns FLORA_ERR_INVALID.  Only n and
- * m of the descriptors are read.  Host only.  0 for an invalid set or rank.
+ * Exact, not a bound: with one 256-byte unit less that call returns FLORA_ERR_INVALID, unless its
+ * compress launch has a shape that holds less (fp32 gradients and rows of G that do not start on
+ * 16-byte boundaries at ranks >= 64, small launches at the other ranks): then the call takes that
+ * shape, which is slower and adds its sums in another order.  Only n and m of the descriptors are
+ * read.  Host only.  0 for an invalid set or rank.
  *
  * flora_set_workspace: dev_ptr is DEVICE memory, 256-byte aligned, of `bytes` bytes, owned by the
  * caller and kept alive until the workspace is replaced, cleared (dev_ptr NULL and bytes 0:
@@ -275,7 +278,7 @@ void flora_derive_seeds(uint64_t global_seed, uint64_t first_matrix_id, int coun
  * give the workspace the sum of what its calls need to avoid that; flora_workspace_bytes is
  * enough for one fused step).  Calls that use the workspace must be ordered by the caller (one
  * stream, or events between streams): the refill relies on it.  Results are bit for bit those
- * of the library-allocated mode.  Drops every cached plan.  Not to be called while kernels of
+ * of the library-allocated mode (given flora_workspace_bytes of each set at least).  Drops every cached plan.  Not to be called while kernels of
  * earlier calls may still run, or between a graph capture and its replays. */
 size_t flora_workspace_bytes(const flora_matrix_t* mats, int count, int r);
 int flora_set_workspace(void* dev_ptr, size_t bytes);

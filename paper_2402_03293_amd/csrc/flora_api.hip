@@ -87,6 +87,7 @@ struct Plan {
     int vec = 0;                        // decompress: the 16-byte-per-lane bf16 kernel (256-column workgroups)
     int kc = 0;                         // fp32 compress: columns per part (0: whole rows)
     int kg = 2;                         // fp32 compress: column groups per workgroup
+    int lean = 0;                       // 1, 2: launch shapes of less and of least memory (see Arena)
     size_t ws_floats = 0;               // compress: floats of partial products (shared-column mode)
     size_t ws_counters = 0;             // ... and arrival counters
     void* d_tables = nullptr;           // items + items2 (uploaded once)
@@ -126,10 +127,15 @@ struct Plan {
 // beside those already placed, all placed plans are dropped and the workspace is refilled: the
 // caller keeps the calls that use it ordered (one stream, or events), so kernels of earlier calls
 // have consumed their tables before the refill's copies land.
+// A workspace smaller than flora_workspace_bytes of a set takes that set all the same if lean plans make it fit:
+// slower, and sums in another order.  (Compress with fp32 gradients or rows of G on no 16-byte boundary at
+// ranks >= 64: 1 no columns shared, 2 the narrow kernel, whose work table is the shortest; compress at ranks up to
+// 32: pieces of 512 columns at least; the factored rule's passes: row blocks of 256 in filled launches.)
 struct Arena {
     char* base = nullptr;
     size_t size = 0;
     size_t used = 0;
+    int lean = 0;               // calls have only fitted with lean plans
 };
 Arena g_ws;
 constexpr size_t kDoneBytes = 64;       // an image's upload mark in pinned memory, a line of its own
@@ -211,7 +217,7 @@ void build_compress_f32_items(Plan& p)
         if (wgs(1ll << 40) < 8192) {
             kc = area >= 600.0 * 64 * 1024 ? 1024 : 512;
             p.kg = 1;
-            if (wgs(512) <= 256) { kc = 256; p.kg = 2; }
+            if (wgs(512) <= 256 && !p.lean) { kc = 256; p.kg = 2; }
         }
     }
     p.kc = (int)kc;
@@ -244,6 +250,21 @@ void build_compress_f32_items(Plan& p)
     }
 }
 
+// Bytes of work table, partial products and counters of a wide launch.
+size_t wide_bytes(const Plan& p, int mt, long long kc)
+{
+    const int slice = (p.r == 64) ? 64 : 128, rows = 4096 / mt;
+    size_t b = 0;
+    for (const MatDev& M : p.host_mats) {
+        long long parts = kc > 0 ? (M.m + kc - 1) / kc : 1;
+        const long long per = ((M.m + parts - 1) / parts + 63) / 64 * 64;
+        parts = (M.m + per - 1) / per;
+        const size_t blocks = (size_t)((M.n + rows - 1) / rows) * (p.r / slice);
+        b += blocks * parts * sizeof(WorkItem) + (parts > 1 ? blocks * (parts * rows * slice + 1) * 4 : 0);
+    }
+    return b;
+}
+
 // Launch shape of the wide bf16 compress kernel: rows per workgroup (mt 8, 16, 32: 512, 256, 128), columns
 // per workgroup (kc; 0: whole rows) and, where the columns of a row block are shared, how the parts are
 // added (by the last workgroup to arrive, or by a launch of their own).
@@ -252,6 +273,44 @@ struct WideShape {
     long long kc = 0;
     int combine = 0;
 };
+
+// The coarsest shape that gives the chip enough to do: 512 or 256 rows with whole rows or columns in parts of 1536 or
+// 768 until there are 384 workgroups (whole rows only where the longest is no more than one and a half times a
+// compute unit's even share); launches of fewer than 130 by 128 rows, and below 150 of those by parts of 384.
+// What it holds is the most that the chosen shape may: short launches may not cost memory (384 T5-3B
+// matrices at r = 128 in parts of 1536, which would take 3 % less time, hold 589 MiB of partial
+// products; 120 of 7680 x 64 at r = 256 in parts of 192 720).
+WideShape coarse_wide(const Plan& p)
+{
+    const int slices = p.r == 64 ? 1 : p.r / 128;
+    auto wgs = [&](int rows, long long kc) {
+        long long w = 0;
+        for (const MatDev& M : p.host_mats) w += (M.n + rows - 1) / rows * slices * (kc > 0 ? (M.m + kc - 1) / kc : 1);
+        return w;
+    };
+    auto balanced = [&](int rows) {
+        long long total = 0, longest = 0;
+        for (const MatDev& M : p.host_mats) {
+            const long long tiles = (M.m + 63) / 64;
+            total += (M.n + rows - 1) / rows * slices * tiles;
+            longest = std::max(longest, tiles);
+        }
+        return 2 * longest <= 3 * std::max<long long>(1, total / 256);
+    };
+    WideShape w;
+    for (int mt = 8; mt <= 16; mt *= 2)
+        for (long long kc : {0, 1536, 768})
+            if (wgs(4096 / mt, kc) >= 384 && (kc > 0 || balanced(4096 / mt))) {
+                w.mt = mt; w.kc = kc;
+                return w;
+            }
+    w.mt = 16; w.kc = 768;
+    if (wgs(256, 768) < 130) {
+        w.mt = 32;
+        w.kc = wgs(128, 768) < 150 ? 384 : 768;
+    }
+    return w;
+}
 
 // Chosen by the time, in microseconds, that each shape is expected to take.  A workgroup sweeps its columns
 // 64 at a time; per such tile
@@ -271,6 +330,16 @@ struct WideShape {
 WideShape choose_wide(const Plan& p, bool f32, bool whole_rows, bool allow512)
 {
     const int slice = (p.r == 64) ? 64 : 128, slices = p.r / slice;
+    const WideShape coarse = coarse_wide(p);
+    size_t most = wide_bytes(p, coarse.mt, coarse.kc);
+    // fp32 gradients cannot take 512 rows.  Rows on no 16-byte boundary are worth more memory (one 1600 x 6401
+    // matrix at r = 64: 15 us with shared columns, 93 without), and a plan that holds none of it is there for a
+    // workspace without room (lean); in sets above some 30 M elements 128 whole rows keep up.
+    bool odd = false;
+    for (const MatDev& M : p.host_mats) odd = odd || (M.m % 8) != 0;
+    if (odd) most = (size_t)32 << 20;
+    else if (f32) most = std::min(most, (size_t)32 << 20);
+    if (f32 || odd) most = std::max(most, wide_bytes(p, 16, 0));
     std::vector<int> order(p.count);
     for (int i = 0; i < p.count; ++i) order[i] = i;
     std::sort(order.begin(), order.end(), [&](int x, int y) { return p.host_mats[x].m > p.host_mats[y].m; });
@@ -283,6 +352,7 @@ WideShape choose_wide(const Plan& p, bool f32, bool whole_rows, bool allow512)
         const double kb64 = rows * 64.0 * (f32 ? 4 : 2) / 65536.0 * (f32 || whole_rows ? 1.0 : 2.4);
         const double alone = 3.2 * kb64, full = 0.79 * slice / 128.0 + 1.6 * kb64 * (slices > 1 ? 0.86 : 1.0);
         for (long long kc : {0, 1536, 768, 384, 192}) {
+            if (p.lean && !(whole_rows && !f32) ? kc > 0 : wide_bytes(p, mt, kc) > most) continue;
             // workgroups, their tiles, and the products of shared columns
             long long wgs = 0, tiles = 0, longest = 0, most_parts = 1, parts_sum = 0;
             double part_mb = 0.0;
@@ -348,6 +418,7 @@ void build_compress_bf16_items(Plan& p)
         whole_rows = whole_rows && (p.host_mats[l].m % 8) == 0;
     }
     p.any_rows = !whole_rows;
+    if (p.any_rows && p.lean == 2) fits = false;
     const bool allow512 = whole_rows || (p.r == 64 && !f32);
     const int wide_slice = (p.r == 64) ? 64 : 128;
     int mt = 4;
@@ -450,10 +521,10 @@ void build_compress_bf16_items(Plan& p)
 // us; single matrices of those shapes: update 27-31 -> 18-27 us at r = 256, 17-20 -> 10-17 us at r =
 // 64), and at r >= 128 on to the least that keeps them to one per compute unit (one 1600 x 6400 matrix
 // at r = 256: 175 workgroups of 256 rows 22 us, 250 of 160 19, 325 of 128 29).
-// colsums: the factored rule's passes, which leave a partial sum of every column per row block (4 m bytes each:
-// 128 rows instead of 256 would hold 177 instead of 96 MiB for T5-3B at r = 32, whose state is 165): never
-// below 256 rows except to reach 140 workgroups.
-int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r, bool adafactor, bool colsums)
+// colsums: the factored rule's passes leave a partial sum of every column per row block (4 m bytes each: 128 rows
+// instead of 256 would hold 177 instead of 96 MiB for T5-3B at r = 32, whose state is 165): fewer rows than
+// fill the chip only up to 32 MiB of them, and not in a lean plan (see Arena).
+int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r, bool adafactor, bool colsums, bool lean)
 {
     if (g_tune.decompress_rows) return g_tune.decompress_rows;
     auto wgs = [&](int rows) {
@@ -461,22 +532,29 @@ int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r, boo
         for (const MatDev& M : mats) w += ((M.n + rows - 1) / rows) * ((M.m + cols - 1) / cols);
         return w;
     };
-    // workgroups of 256 rows that the set would fill
-    double full = 0.0;
-    for (const MatDev& M : mats) full += (double)M.n * (double)M.m / (256.0 * cols);
     int rows = 1024;
     const long long enough = r >= 256 ? 140 : (r >= 128 ? 1000 : 2048);
     for (; rows > kDecompressRows; rows /= 2)
         if (wgs(rows) >= enough) break;
-    if (!colsums && r == 64) {
+    int most = rows;                       // rows where column sums may not cost memory
+    for (; most > 32 && wgs(most) < 140; most /= 2) {}
+    // workgroups of 256 rows that the set would fill
+    double full = 0.0;
+    for (const MatDev& M : mats) full += (double)M.n * (double)M.m / (256.0 * cols);
+    if (r == 64) {
         if (full >= 850.0) rows = (adafactor || full < 1024.0) ? 128 : 64;
         else if (!adafactor && wgs(kDecompressRows) < 300) rows = 128;
-    } else if (!colsums && r <= 32) {
+    } else if (r <= 32) {
         rows = (full >= 1024.0 && !(adafactor && r == 32)) ? 64 : 128;
     }
-    for (; rows > 32 && wgs(rows) < (r <= 32 && !colsums ? 200 : 140); rows /= 2) {}
-    if (r >= 128 && !colsums)
+    for (; rows > 32 && wgs(rows) < (r <= 32 ? 200 : 140); rows /= 2) {}
+    if (r >= 128)
         while (rows > 32 && wgs(rows - 32) <= 256) rows -= 32;
+    if (colsums && rows < most) {
+        size_t held = 0;
+        for (const MatDev& M : mats) held += (size_t)((M.n + rows - 1) / rows) * M.m * 4;
+        if (lean || r >= 128 || held > (size_t)32 << 20) rows = most;
+    }
     return rows;
 }
 
@@ -489,7 +567,7 @@ void build_decompress_items(Plan& p)
     p.vec = vec;
     const int cols = vec ? kDecompressColsVec : kDecompressCols;
     // (the vector kernel addresses a workgroup's state rows with 32-bit byte offsets)
-    const int rows_per_wg = std::min(choose_decompress_rows(p.host_mats, cols, p.r, p.kind == kKindFactored, p.route == Plan::kPasses), vec ? (1 << 20) : 0x7fffffe0);
+    const int rows_per_wg = std::min(choose_decompress_rows(p.host_mats, cols, p.r, p.kind == kKindFactored, p.route == Plan::kPasses, p.lean > 0), vec ? (1 << 20) : 0x7fffffe0);
     struct Group { int mat, rb, row0, rows, nchunks; };
     std::vector<Group> groups;
     for (int l = 0; l < p.count; ++l) {
@@ -596,7 +674,8 @@ void build_gram_items(Plan& p)
     // over a few matrices otherwise run on a workgroup per matrix: 16 GPT-2 base matrices at r = 128, the
     // two Gram kernels 45 + 73 us in pieces of 3072), as far as memory allows: a piece holds r^2 floats,
     // and all of them no more than pieces of 3072 and the partial sums that the passes would leave
-    // (24 matrices of T5-3B at r = 256, whose state is 96 MiB: 52 MiB; without the limit 473).
+    // (24 matrices of T5-3B at r = 256, whose state is 96 MiB: 52 MiB; without the limit 473), or than the
+    // state itself up to 32 MiB (not in a lean plan, see Arena).
     auto pieces = [&](bool rows, long long most, long long least) {
         for (long long c = most; c > least; c /= 2) {
             long long wgs = 0;
@@ -608,7 +687,8 @@ void build_gram_items(Plan& p)
     long long chunk_m = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(false, kGramChunk, 192);
     long long chunk_n = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(true, kGramChunk, 192);
     const long long cols = pieces(false, kQuadformCols, p.r >= 128 ? 512 : 256);
-    // (work tables included: smaller pieces, and workgroups of fewer rows in the update, are more entries)
+    // (work tables included: smaller pieces, and workgroups of fewer rows here and in the compress launch, are more
+    // entries)
     const size_t rr = (size_t)p.r * p.r * 4;
     auto pieces_of = [](long long len, long long chunk) { return (size_t)((len + chunk - 1) / chunk); };
     size_t limit = 0;
@@ -617,11 +697,15 @@ void build_gram_items(Plan& p)
         limit += (2 * gm + gn) * rr + (size_t)M.ncolchunks * M.n * 4 + nb * M.m * 4 +
                  sizeof(WorkItem) * (gm + gn + nb + pieces_of(M.m, 1024) + nb * M.ncolchunks);
     }
+    size_t state = 0;
+    for (const MatDev& M : p.host_mats) state += (size_t)M.n * p.r * 4;
+    if (!p.lean) limit = std::max(limit, std::min(state, (size_t)32 << 20));
     while (!g_tune.gram_chunk && (chunk_m < kGramChunk || chunk_n < kGramChunk)) {
         size_t need = sizeof(WorkItem) * p.items.size(), by_m = 0, by_n = 0;
         for (const MatDev& M : p.host_mats) {
             const size_t gm = pieces_of(M.m, chunk_m), gn = pieces_of(M.n, chunk_n);
-            need += std::max(2 * gm, gn) * rr + sizeof(WorkItem) * (gm + gn + pieces_of(M.n, kQuadformRows) + pieces_of(M.m, cols));
+            need += std::max(2 * gm, gn) * rr + 1024 +         // (1024: padding, and partial sums of workgroups)
+                    sizeof(WorkItem) * (gm + gn + pieces_of(M.n, kQuadformRows) + pieces_of(M.m, cols) + 2 * pieces_of(M.n, 128));
             by_m += 2 * gm; by_n += gn;
         }
         if (need <= limit) break;
@@ -836,6 +920,29 @@ int wait_uploaded(const Image& im, hipStream_t stream)
     return FLORA_OK;
 }
 
+bool has_lean(int kind) { return kind == kKindCompress || kind == kKindFactored; }
+
+// Bytes of a caller-owned workspace one plan of this kind would occupy (host work only).
+size_t plan_need(int kind, int variant, int r, const std::vector<MatDev>& mats, int lean = 0)
+{
+    Plan p;
+    p.kind = kind; p.variant = variant; p.r = r; p.count = (int)mats.size(); p.lean = lean;
+    build_host_plan(&p, mats);
+    return arena_need(p);
+}
+
+// ... and the plans of the most demanding call on a set, flora_fused_step with a transfer and an Adafactor rule:
+// its transfer, compress and update plans are resident together.
+size_t step_bytes(const std::vector<MatDev>& mats, int r, int lean = 0)
+{
+    size_t comp = 0;
+    if (rank_bf16(r)) comp = std::max(plan_need(kKindCompress, 2, r, mats, lean), plan_need(kKindCompress, 3, r, mats, lean));
+    else comp = plan_need(kKindCompress, 0, r, mats, lean);
+    const size_t update = std::max({plan_need(kKindFactored, 2, r, mats, lean), plan_need(kKindFactored, 3, r, mats, lean),
+                                    plan_need(kKindDecompress, 0, r, mats)});
+    return comp + update + plan_need(kKindTransfer, 0, r, mats);
+}
+
 // Plans the call being prepared needs (caller's workspace only).
 std::vector<Plan*> g_pending;
 
@@ -884,6 +991,8 @@ int get_plan(int kind, int variant, int r, const std::vector<MatDev>& mats, hipS
         p->device = device; p->stream = stream; p->kind = kind; p->variant = variant; p->count = count; p->r = r;
         p->shape_hash = sh;
         p->in_arena = arena;
+        if (arena && has_lean(kind))
+            for (p->lean = g_ws.lean; p->lean < 2 && step_bytes(mats, r, p->lean) > g_ws.size;) ++p->lean;
         build_host_plan(p, mats);
         if (!arena) {
             const int st = place_plan(p, stream);
@@ -1016,6 +1125,24 @@ int arena_commit(hipStream_t stream)
         if (!p->placed) need_new += arena_need(*p);
     }
     if (need_new > g_ws.size - g_ws.used) {
+        if (need_all > g_ws.size) {
+            // with lean plans, then, in the place of the others (the refill below forgets those)
+            for (int lean = 1; lean <= 2 && need_all > g_ws.size; ++lean) {
+                size_t need = 0;
+                for (Plan* p : g_pending)
+                    need += has_lean(p->kind) ? plan_need(p->kind, p->variant, p->r, p->host_mats, std::max(lean, p->lean)) : arena_need(*p);
+                if (need > g_ws.size) continue;
+                g_ws.lean = std::max(g_ws.lean, lean);
+                for (Plan* p : g_pending)
+                    if (has_lean(p->kind) && p->lean < lean) {
+                        p->lean = lean;
+                        p->items.clear();
+                        p->items2.clear();
+                        build_host_plan(p, std::vector<MatDev>(p->host_mats));
+                    }
+                need_all = need;
+            }
+        }
         if (need_all > g_ws.size) {
             // also forget the host halves built for this call: they could never be placed
             for (size_t i = g_plans.size(); i-- > 0;)
@@ -1625,15 +1752,11 @@ void flora_derive_seeds(uint64_t global_seed, uint64_t first_matrix_id, int coun
     for (int i = 0; i < count; ++i) seeds_out[i] = flora_derive_seed(global_seed, first_matrix_id + (uint64_t)i, epoch);
 }
 
-// Bytes of a caller-owned workspace one plan of this kind would occupy (host work only).
-static size_t plan_need(int kind, int variant, int r, const flora_matrix_t* mats, int count)
+static std::vector<MatDev> shapes_of(const flora_matrix_t* mats, int count)
 {
-    Plan p;
-    p.kind = kind; p.variant = variant; p.r = r; p.count = count;
     std::vector<MatDev> md((size_t)count);
     for (int l = 0; l < count; ++l) { md[(size_t)l].n = mats[l].n; md[(size_t)l].m = mats[l].m; }
-    build_host_plan(&p, md);
-    return arena_need(p);
+    return md;
 }
 
 size_t flora_workspace_bytes(const flora_matrix_t* mats, int count, int r)
@@ -1643,17 +1766,11 @@ size_t flora_workspace_bytes(const flora_matrix_t* mats, int count, int r)
     for (int l = 0; l < count; ++l)
         if (mats[l].n < 1 || mats[l].m < 1 || mats[l].n > 0x7fffffffLL - 1024 || mats[l].m > (1LL << 24)) return 0;
     std::lock_guard<std::mutex> guard(g_lock);      // reads the tuning knobs
-    // The most demanding call is flora_fused_step with a transfer and an Adafactor rule: its
-    // transfer, compress and update plans are resident together, for every chunk of the call.
-    size_t step = 0, sumsq = 0;
+    size_t step = 0, sumsq = 0;         // (every chunk of a call is resident)
     FLORA_FOR_CHUNKS(count, c0, cn) {
-        size_t comp = 0;
-        if (rank_bf16(r)) comp = std::max(plan_need(kKindCompress, 2, r, mats + c0, cn), plan_need(kKindCompress, 3, r, mats + c0, cn));
-        else comp = plan_need(kKindCompress, 0, r, mats + c0, cn);
-        const size_t update = std::max({plan_need(kKindFactored, 2, r, mats + c0, cn), plan_need(kKindFactored, 3, r, mats + c0, cn),
-                                        plan_need(kKindDecompress, 0, r, mats + c0, cn)});
-        step += comp + update + plan_need(kKindTransfer, 0, r, mats + c0, cn);
-        sumsq += plan_need(kKindSumsq, 0, 0, mats + c0, cn);
+        const std::vector<MatDev> md = shapes_of(mats + c0, cn);
+        step += step_bytes(md, r);
+        sumsq += plan_need(kKindSumsq, 0, 0, md);
     }
     return std::max(step, sumsq);
 }
@@ -1680,12 +1797,13 @@ int64_t flora_debug_plan_bytes(int plan_kind, const flora_matrix_t* mats, int co
         if (mats[l].n < 1 || mats[l].m < 1 || mats[l].n > 0x7fffffffLL - 1024 || mats[l].m > (1LL << 24))
             return FLORA_ERR_INVALID;
     std::lock_guard<std::mutex> guard(g_lock);
+    const std::vector<MatDev> md = shapes_of(mats, count);
     switch (plan_kind) {
-    case 0: return (int64_t)plan_need(kKindCompress, rank_bf16(r) ? (grad_dtype == FLORA_BF16 ? 2 : 3) : 0, r, mats, count);
-    case 1: return (int64_t)plan_need(kKindDecompress, 0, r, mats, count);
-    case 2: return (int64_t)plan_need(kKindTransfer, 0, r, mats, count);
-    case 3: return (int64_t)plan_need(kKindFactored, 2, r, mats, count);
-    default: return (int64_t)plan_need(kKindSumsq, 0, 0, mats, count);
+    case 0: return (int64_t)plan_need(kKindCompress, rank_bf16(r) ? (grad_dtype == FLORA_BF16 ? 2 : 3) : 0, r, md);
+    case 1: return (int64_t)plan_need(kKindDecompress, 0, r, md);
+    case 2: return (int64_t)plan_need(kKindTransfer, 0, r, md);
+    case 3: return (int64_t)plan_need(kKindFactored, 2, r, md);
+    default: return (int64_t)plan_need(kKindSumsq, 0, 0, md);
     }
 }
 
@@ -1730,6 +1848,7 @@ int flora_set_tuning(const char* name, int value)
     // cached work tables were built for the old shapes
     drop_all_plans();
     g_ws.used = 0;
+    g_ws.lean = 0;
     return FLORA_OK;
 }
 

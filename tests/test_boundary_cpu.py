@@ -204,9 +204,10 @@ def test_workspace_bytes_is_the_sum_of_the_fused_steps_plans(index, r):
                                                     + twork + 8 * image)
 
 
-def _adafactor_bytes_in_large_pieces(shapes, r):
+def _adafactor_bytes_in_large_pieces(shapes, r, least_rows=256):
     """An Adafactor plan whose row blocks are of 256 rows at least (where that gives enough workgroups), with Gram
-    sums in pieces of 3072 beside each other and the passes' partial sums of rows and columns."""
+    sums in pieces of 3072 beside each other and the passes' partial sums of rows and columns.  least_rows 32: the
+    most that blocks of 32 rows or more take whose column sums stay within 32 MiB."""
     vec = r >= 64 and all(m % 4 == 0 for _, m in shapes)
     cols = 256 if vec else 128
     up = lambda a, b: -(-a // b)
@@ -216,6 +217,10 @@ def _adafactor_bytes_in_large_pieces(shapes, r):
         rows //= 2
     while rows > 32 and wgs(rows) < 140:
         rows //= 2
+    for fewer in (32, 64, 128) if least_rows == 32 else ():
+        if fewer < rows and 4 * sum(up(n, fewer) * m for n, m in shapes) <= 32 << 20:
+            rows = fewer
+            break
     gram = r >= 64 and 9 * sum((n + m) * r * r for n, m in shapes) < 4 * sum(n * m * r for n, m in shapes)
     items = items2 = work = 0
     for n, m in shapes:
@@ -241,9 +246,52 @@ def test_adafactor_plans_hold_no_more_than_large_pieces_would(r):
             [(33, 1)], [(65, 515)] * 300, [(1023, 999)] * 4, [(8192, 64)] * 9]
     for shapes in sets:
         most = _adafactor_bytes_in_large_pieces(shapes, r)
+        if r <= 64:       # (fewer rows than that where the column sums of the row blocks are small)
+            most = max(most, _adafactor_bytes_in_large_pieces(shapes, r, least_rows=32))
+        # (or the state itself, up to 32 MiB, for the pieces of the Gram sums)
+        most = max(most, min(sum(4 * n * r for n, _ in shapes), 32 << 20) + sum(6 * r * r + 4096 for _ in shapes) + 8 * _round256(184 * len(shapes)))
         assert flora.debug_plan_bytes(3, shapes, r) <= most, (shapes[:2], len(shapes), r)
         # the rules without column sums fit wherever the factored one does
         assert flora.debug_plan_bytes(1, shapes, r) <= flora.workspace_bytes(flora.matrices(shapes), r)
+
+
+def _compress_bytes_in_coarse_pieces(shapes, r):
+    """A wide compress plan of 512 or 256 rows and whole rows or parts of 1536 or 768 columns, the first of which
+    there are 384 (whole rows only where balanced); launches of few workgroups 128 rows, parts of 384."""
+    up = lambda a, b: -(-a // b)
+    slices, width = (1, 64) if r == 64 else (r // 128, 128)
+    wgs = lambda rows, kc: sum(up(n, rows) * slices * (up(m, kc) if kc else 1) for n, m in shapes)
+
+    def balanced(rows):
+        total = sum(up(n, rows) * slices * up(m, 64) for n, m in shapes)
+        return 2 * max(up(m, 64) for _, m in shapes) <= 3 * max(1, total // 256)
+
+    rows, kc = next(((R, k) for R in (512, 256) for k in (0, 1536, 768) if wgs(R, k) >= 384 and (k or balanced(R))), (256, 768))
+    if wgs(256, 768) < 130:
+        rows, kc = 128, 384 if wgs(128, 768) < 150 else 768
+    b = 0
+    for n, m in shapes:
+        parts = up(m, kc) if kc else 1
+        parts = up(m, up(up(m, parts), 64) * 64)
+        b += up(n, rows) * slices * (48 * parts + ((parts * rows * width + 1) * 4 if parts > 1 else 0))
+    return b + 768 + 8 * _round256(184 * len(shapes))
+
+
+@pytest.mark.parametrize("r", [64, 128, 256])
+def test_compress_plans_hold_no_more_than_coarse_pieces_would(r):
+    gpt, t53b, xl = (workloads.workload(i).shapes for i in (3, 4, 5))
+    for shapes in [gpt, gpt[:16], t53b, t53b[:24], t53b[:32], xl, xl[:16], [(1600, 6400)], [(1600, 6400)] * 16, [(4096, 16384)], [(256, 256)],
+                   [(7680, 64)] * 120, [(272, 7136)], [(64, 4416)] * 147]:
+        most = _compress_bytes_in_coarse_pieces(shapes, r)
+        assert flora.debug_plan_bytes(0, shapes, r, flora.BF16) <= most, (shapes[:2], len(shapes), r)
+        # fp32 gradients: the same, or 256 whole rows, and 32 MiB of partial products at most
+        whole = sum(48 * -(-n // 256) * max(1, r // 128) for n, _ in shapes) + 768 + 8 * _round256(184 * len(shapes))
+        assert flora.debug_plan_bytes(0, shapes, r, flora.F32) <= max(whole, min(most, (32 << 20) + whole)), (shapes[:2], len(shapes), r)
+    # rows on no 16-byte boundary: 32 MiB at most, or 256 whole rows
+    for shapes in [[(1600, 6401)], [(1600, 6401)] * 32, [(n, m - 1) for n, m in xl], [(768, 50257)], [(3211, 15823)] * 9]:
+        whole = sum(48 * -(-n // 256) * max(1, r // 128) for n, _ in shapes) + 768 + 8 * _round256(184 * len(shapes))
+        for gdt in (flora.F32, flora.BF16):
+            assert flora.debug_plan_bytes(0, shapes, r, gdt) <= (32 << 20) + whole, (shapes[:2], len(shapes), r, gdt)
 
 
 def test_workspace_bytes_rejects_bad_sets():

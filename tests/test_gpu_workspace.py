@@ -205,3 +205,51 @@ def test_more_matrices_than_one_launch_takes_with_a_workspace():
         assert torch.equal(out["library"][l], out["workspace"][l])
     for l in (0, 447, 448, 459):
         assert rel_fro(to64(out["workspace"][l]), oracle.compress(to64(G[l]), r, seeds[l])) < tol_for(r)
+
+
+@pytest.mark.parametrize("shapes,r,gdt,size", [
+    # smaller than flora_workspace_bytes by the partial products of shared columns: rows of whole columns then, and
+    ([(1100, 1003)] * 2 + [(770, 3001)] * 2, 64, "bf16", 887296),
+    ([(1100, 1003)] * 2 + [(770, 3001)] * 2, 128, "f32", 2363392),
+    ([(1100, 1003)] * 2 + [(770, 3001)] * 2, 256, "bf16", 8194304),
+    ([(768, 5025)], 64, "bf16", 469504),
+    # by the length of the wide kernel's work table: the narrow kernel
+    ([(4480, 9)] * 64, 64, "f32", 3909632),
+    # ranks up to 32: pieces of 512 columns; row blocks of 256 under the factored rule
+    ([(1024, 1024)], 16, "f32", 318976),
+    ([(1319, 2496)] + [(320, 768)] * 18, 8, "bf16", 1723904),
+])
+def test_a_workspace_below_the_stated_size_takes_what_it_can_hold(shapes, r, gdt, size):
+    """Launch shapes that hold more memory than the smallest possible are no reason to refuse a call."""
+    count = len(shapes)
+    x = _inputs(shapes, r, gdt == "bf16", 11)
+    fd = flora.BF16 if gdt == "bf16" else flora.F32
+    s0, s1 = [3 + l for l in range(count)], [70 + l for l in range(count)]
+    need = flora.workspace_bytes(flora.matrices(shapes), r)
+    assert size < need
+    out = {}
+    ws = torch.empty(size, dtype=torch.uint8, device=DEV)
+    for mode in ("library", "workspace"):
+        W, M, R, K = ([v.clone() for v in x[k]] for k in "WMRK")
+        mats = flora.matrices(shapes, grads=x["G"], weights=W, states=M, row_stats=R, col_stats=K, seeds=s0, seeds_next=s1)
+        flora.set_workspace(ws if mode == "workspace" else None)
+        fac = flora.factored_update(1e-2, 1.0, 0.5, 1e-30, 1.0)
+        for _ in range(2):
+            flora.fused_step(mats, r, fd, flora.F32, 0.9, 0.1, True, fac)
+        # and the calls on their own
+        for _ in range(2):
+            flora.compress(mats, r, fd, 0.5, 1.0)
+            flora.apply_update(mats, r, flora.F32, fac)
+        torch.cuda.synchronize()
+        out[mode] = (W, M, R, K)
+    for a, b in zip(out["library"], out["workspace"]):
+        for u, v in zip(a, b):
+            assert rel_fro(to64(v), to64(u)) < 1e-4       # (sums in another order; what bf16 rounds the other way for it)
+    l, (n, m) = count - 1, shapes[-1]
+    G = to64(x["G"][l])
+    ref = to64(x["M"][l])
+    for _ in range(2):
+        ref = oracle.compress(G, r, s1[l], state=oracle.transfer(ref, m, s0[l], s1[l]), a=0.9, b=0.1)
+    for _ in range(2):
+        ref = oracle.compress(G, r, s0[l], state=ref, a=0.5, b=1.0)
+    assert rel_fro(to64(out["workspace"][1][l]), ref) < tol_for(r)
