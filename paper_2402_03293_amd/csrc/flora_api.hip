@@ -510,12 +510,13 @@ void build_compress_bf16_items(Plan& p)
 // transformer blocks of GPT-2 XL and T5-3B shapes, r = 256: update 84-453 -> 63-407 us).  At r = 64 256
 // rows; where the plain update then has no 300 workgroups, 128; and in launches over many full
 // workgroups (rows wide enough for all columns of one), which the weights' traffic bounds, 64 in the
-// plain update and 128 under the Adafactor rules, whose kernels hold more.  us at 256 / 128 / 64 rows:
-// 16 matrices of 768 x 768 16.1 / 15.6 / 16.8 (unfactored 47 / 50 / 53), 24 of 768 x 3072 88.8 / 89.6 /
-// 90.8 (223 / 211 / 229), all 48 of GPT-2 base 135 / 126 / 114 (342 / 315 / 331), 52 of 6656 x 64 53 /
-// 59 / 77 (179 / 202 / 271).  At smaller ranks 128 rows, and 64 in such large launches (not at r = 32
-// under the Adafactor rules): r = 16, GPT-2 base 143 / 138 / 131 (364 / 348 / 339), T5-small 63 / 58 /
-// 60 (160 / 151 / 150).  A launch over one or two matrices cannot fill the chip whatever the rows;
+// plain update and 128 under the Adafactor rules, whose kernels hold more.  Plain update, us at 256 / 128 / 64
+// rows: T5-small (672 such workgroups) 55.0 / 55.9 / 57.6, 24 of 768 x 3072 (864) 79 / 75 / 72, 28 (1008) 95 / 90 / 88,
+// 30 (1080) 102 / 96 / 94, GPT-2 base (1296) 132 / 124 / 116, but 36 of 1024 x 2048 (1152) 97 / 93 / 101; unfactored,
+// the same: 164 / 162 / 182, 222 / 211 / 233, 245 / 243 / 270, 277 / 264 / 284, 335 / 318 / 337, 259 / 253 / 294.
+// At smaller ranks 128 rows: r = 16, 256 / 128 / 64 rows, T5-small 58 / 55 / 59, GPT-2 base 128 / 126 / 124, 24 of
+// 768 x 3072 78 / 68 / 71, 36 of 1024 x 2048 104 / 101 / 103; unfactored 179 / 175 / 176, 364 / 350 / 345, 234 / 230 /
+// 227, 303 / 293 / 295.  A launch over one or two matrices cannot fill the chip whatever the rows;
 // there the fewest workgroups per compute unit in a row finish first, and rows go down (to 32 at least)
 // until there are about 140 workgroups (200 at small ranks: four 768 x 768 matrices at r = 8 8.9 -> 6.7
 // us; single matrices of those shapes: update 27-31 -> 18-27 us at r = 256, 17-20 -> 10-17 us at r =
@@ -545,7 +546,7 @@ int choose_decompress_rows(const std::vector<MatDev>& mats, int cols, int r, boo
         if (full >= 850.0) rows = (adafactor || full < 1024.0) ? 128 : 64;
         else if (!adafactor && wgs(kDecompressRows) < 300) rows = 128;
     } else if (r <= 32) {
-        rows = (full >= 1024.0 && !(adafactor && r == 32)) ? 64 : 128;
+        rows = 128;
     }
     for (; rows > 32 && wgs(rows) < (r <= 32 ? 200 : 140); rows /= 2) {}
     if (r >= 128)

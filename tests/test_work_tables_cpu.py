@@ -177,3 +177,12 @@ def test_hook_rejects_bad_arguments():
     assert L.flora_debug_work_items(7, mats, 1, 16, 0, None, 0, None) == flora.ERR_INVALID
     assert L.flora_debug_work_items(0, flora.matrices([(0, 4)]), 1, 16, 0, None, 0, None) == flora.ERR_INVALID
     assert L.flora_debug_work_items(0, mats, 1, 16, 0, None, 0, None) == 1
+
+
+def test_filled_updates_at_small_ranks_take_128_rows():
+    """The rows per workgroup that launches filling the chip were measured to be fastest with, at every such size."""
+    t5s, gpt = (workloads.workload(i).shapes for i in (2, 3))
+    for shapes in (t5s, gpt, [(768, 3072)] * 24, [(1024, 2048)] * 36, [(2048, 2048)] * 8):
+        for r in (8, 16, 32):
+            items, _ = check_decompress(shapes, r)
+            assert max(it[COLS["rows"]] for it in items) == 128, (shapes[0], len(shapes), r)
