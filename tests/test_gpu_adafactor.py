@@ -387,8 +387,9 @@ def test_update_cache_policies_give_the_same_bits(n, m, r, wdt, rule):
 # ------------------------------------------- the factored rule through Gram matrices
 # Row sums, column sums and the clipping sum of the rule as quadratic forms in A^T A, S^T S and
 # A^T diag(1/K) A (ranks >= 64), against the oracle, and against the passes over the decompressed
-# gradient that they replace: ragged shapes, several chunks of the Gram sums (m or n above 3072),
-# several row blocks of the quadratic forms (above 1024), grouped matrices, with and without clipping.
+# gradient that they replace: ragged shapes, many pieces of the Gram sums (a few tiles of 64 each, as in any short
+# launch), several blocks of rows and columns of the quadratic forms (256, and 256 or 512), grouped
+# matrices, with and without clipping.  The next two tests take the long loops.
 @pytest.mark.parametrize("r", [64, 128, 256])
 @pytest.mark.parametrize("clip_d,beta2", [(1.0, 0.0), (0.0, 0.6), (0.3, 0.8)])
 def test_factored_rule_through_gram_matrices(r, clip_d, beta2):
@@ -448,3 +449,37 @@ def test_factored_statistics_do_not_depend_on_the_number_of_matrices(n, m, r):
     for one in got[1:]:
         for a, b in zip(one, got[0]):
             assert rel_fro(a, b) < 2e-5
+
+
+# Gram sums in pieces of 3072 (the loops over tiles at their longest, and a last piece that is short)
+@pytest.mark.parametrize("r", [64, 128, 256])
+@pytest.mark.parametrize("clip_d,beta2", [(1.0, 0.0), (0.0, 0.6)])
+def test_factored_rule_through_gram_matrices_in_large_pieces(r, clip_d, beta2):
+    flora.set_tuning("gram_chunk", 3072)
+    try:
+        test_factored_rule_through_gram_matrices(r, clip_d, beta2)
+    finally:
+        flora.set_tuning("gram_chunk", 0)
+
+
+# Column statistics in blocks of 1024 columns: a set with 384 such blocks (several rounds of rows of A per workgroup,
+# the last of a matrix short)
+@pytest.mark.parametrize("r", [64, 128, 256])
+def test_factored_rule_through_gram_matrices_with_large_column_blocks(r):
+    n, m, count = 40, 4000, 100
+    g = torch.Generator(device="cpu").manual_seed(950 + r)
+    S, W0 = torch.randn(count, n, r, generator=g).to(DEV), torch.randn(count, n, m, generator=g).to(DEV)
+    W, R, K = W0.clone(), torch.full((count, n), 0.7, device=DEV), torch.full((count, m), 0.6, device=DEV)
+    seeds = [int(flora.derive_seed(78, l, r)) for l in range(count)]
+    flora.set_tuning("factored_gram", 2)
+    try:
+        mats = flora.matrices([(n, m)] * count, weights=list(W), states=list(S), row_stats=list(R), col_stats=list(K), seeds=seeds)
+        flora.apply_update(mats, r, flora.F32, flora.factored_update(0.01, 0.5, 0.4, 1e-30, 1.0))
+        sync()
+    finally:
+        flora.set_tuning("factored_gram", 0)
+    for l in (0, 57, count - 1):
+        Gt = oracle.decompress(to64(S[l]), m, seeds[l], alpha=0.5)
+        Wr, Rr, Kr = oracle.factored_update(to64(W0[l]), Gt, np.full(n, 0.7), np.full(m, 0.6), 0.4, 1e-30, 1.0, 0.01)
+        assert rel_fro(to64(R[l]), Rr) < TOL_BF16 and rel_fro(to64(K[l]), Kr) < TOL_BF16, l
+        assert rel_fro(to64(W[l]) - to64(W0[l]), Wr - to64(W0[l])) < TOL_BF16, l

@@ -242,6 +242,32 @@ def test_compress_bf16_rows_that_start_anywhere(n, m, r, gdt, mt, kc, combine):
         flora.set_tuning("compress_combine", 0)
 
 
+# Shared columns added to an old state (a != 0), by the last part to arrive and by a launch of their own: aligned
+# and odd rows, row blocks that are not full, parts that differ in number between the matrices.
+@pytest.mark.parametrize("combine", [1, 2])
+@pytest.mark.parametrize("r,mt,kc", [(64, 32, 128), (128, 16, 192), (256, 8, 384)])
+@pytest.mark.parametrize("gdt", ["f32", "bf16"])
+def test_compress_shared_columns_with_an_old_state(r, mt, kc, gdt, combine):
+    dt = torch.float32 if gdt == "f32" else torch.bfloat16
+    for shapes in ([(300, 1160), (70, 200), (129, 64)], [(300, 1161), (70, 199), (513, 1030)]):
+        G = [rand(s, 2700 + r + l, dt) for l, s in enumerate(shapes)]
+        st = [rand((n, r), 2800 + l) for l, (n, _) in enumerate(shapes)]
+        ref = [oracle.compress(to64(G[l].to(torch.bfloat16)), r, 60 + l, state=to64(st[l]), a=0.9, b=0.1) for l in range(len(shapes))]
+        mats = flora.matrices(shapes, grads=G, states=st, seeds=[60 + l for l in range(len(shapes))])
+        flora.set_tuning("compress_bf16_mt", mt)
+        flora.set_tuning("compress_splitk_cols", kc)
+        flora.set_tuning("compress_combine", combine)
+        try:
+            flora.compress(mats, r, flora.F32 if gdt == "f32" else flora.BF16, 0.9, 0.1)
+            sync()
+        finally:
+            flora.set_tuning("compress_bf16_mt", 0)
+            flora.set_tuning("compress_splitk_cols", 0)
+            flora.set_tuning("compress_combine", 0)
+        for l in range(len(shapes)):
+            assert rel_fro(to64(st[l]), ref[l]) < 6e-3, shapes[l]
+
+
 # the wide kernel with the columns of a row block shared between workgroups (partial products
 # combined by the last workgroup to arrive): several parts, ragged last part, two launches in a
 # row on the same descriptor set (the arrival counters must be back at zero), grouped matrices
@@ -282,7 +308,10 @@ def test_compress_bf16_shared_columns(r, kc, mt):
 @pytest.mark.parametrize("gdt", ["f32", "bf16"])
 @pytest.mark.parametrize("n,m,r,mt", [(70, 200, 8, 0), (130, 1001, 16, 2), (257, 520, 32, 0), (300, 520, 64, 0),
                                       (257, 1001, 128, 2), (700, 264, 256, 4), (513, 31, 64, 1),
-                                      (700, 264, 256, 8), (1100, 520, 128, 16), (530, 1160, 64, 8)])
+                                      (700, 264, 256, 8), (1100, 520, 128, 16), (530, 1160, 64, 8),
+                                      # rows that start anywhere (odd widths, even ones off 16 bytes) in the wide kernel
+                                      (257, 1001, 128, 16), (530, 333, 64, 8), (97, 1283, 256, 32), (140, 522, 64, 0),
+                                      (257, 1001, 256, 0), (65, 66, 128, 0)])
 def test_compress_mapped_square(n, m, r, mt, gdt):
     dt = torch.float32 if gdt == "f32" else torch.bfloat16
     fd = flora.F32 if gdt == "f32" else flora.BF16
