@@ -164,12 +164,11 @@ uint64_t g_tick = 0;
 void free_plan(Plan* p)
 {
     if (!p->in_arena) {
-        // hipFree waits for the device, so kernels still reading these buffers (the pinned staging
-        // too, freed last) have finished
+        // hipFree waits for the device, so kernels still reading these buffers, and the pinned memory freed
+        // after them (which exists only beside device memory), have finished
         if (p->d_tables) (void)hipFree(p->d_tables);
         if (p->d_work) (void)hipFree(p->d_work);
         for (void* d : p->dev_slabs) (void)hipFree(d);
-        if (!p->d_tables && !p->d_work && p->dev_slabs.empty()) (void)hipDeviceSynchronize();
         for (void* h : p->pin_slabs) (void)hipHostFree(h);
         if (p->h_tables) (void)hipHostFree(p->h_tables);
     }

@@ -1,11 +1,13 @@
 // Compression on the bf16 matrix cores, ranks 64 / 128 / 256:
 //     state <- a * state + b * (G A(seed))
 // (Algorithm 1, compression line; Algorithm 2, EMA line).  A is rounded to
-// bf16 as it is generated; products are exact in fp32 and accumulated in fp32
-// (v_mfma_f32_32x32x16_bf16).  G is bf16, or fp32 rounded to bf16 (nearest even)
-// in registers on its way to the matrix cores (first kernel below only).  Both
-// kernels also take the elementwise square of G as their input (MAP = 1: squared in
-// fp32, then rounded to bf16), for the compressed EMA of the second moment.
+// bf16 as it is generated; products are exact in fp32 and accumulated in fp32.
+// G is bf16, or fp32 rounded to bf16 (nearest even) in registers on its way to the
+// matrix cores.  Both kernels also take the elementwise square of G as their input
+// (MAP = 1: squared in fp32, then rounded to bf16), for the compressed EMA of the
+// second moment.  The second, wide kernel is the one that launches take; the first,
+// narrow one (v_mfma_f32_32x32x16_bf16) remains for rows too long for 32-bit byte offsets
+// within 64 of them, and for plans that may hold no more than its work table.
 //
 // The cost that matters here is regenerating A, not the contraction: every
 // workgroup that sweeps the m columns of G must rebuild all the A rows it

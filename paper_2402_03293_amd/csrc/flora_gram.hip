@@ -13,7 +13,7 @@
 // What the kernels cost is regenerating A (the vector ALU), so the sums are ordered to sweep A
 // twice, not three times: Q from one read of S and the column statistics K from a sweep over
 // generated rows of A; then ONE further sweep over A yields both P and P'; then the row statistics
-// R and the clipping sum from a read of S each.
+// R and the clipping sum from one read of S.
 //
 // gram_sym_kernel (ranks >= 128) / gram_kernel (rank 64): one workgroup sums X_t X_t^T over a chunk
 //   of the long index t (X_t = row t of A, regenerated, plain and scaled with 1 / K_t; or row t of

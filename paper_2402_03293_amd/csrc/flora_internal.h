@@ -259,7 +259,6 @@ hipError_t launch_upload_image(const void* src, void* dst, size_t bytes, uint32_
 hipError_t launch_zero_state(const MatDev* mats, int count, int r, hipStream_t s);
 
 // Tiling constants the host needs to build work tables.
-constexpr int kCompressBf16Rows = 512;   // rows per workgroup, bf16 matrix-core compress
 constexpr int kCompressBf16Slice = 64;   // rank columns per workgroup, bf16 compress
 constexpr int kDecompressCols = 128;     // columns per workgroup, 4-byte-per-lane decompress kernels
 constexpr int kDecompressColsVec = 256;  // columns per workgroup, 16-byte-per-lane bf16 decompress kernel
