@@ -695,10 +695,13 @@ __global__ __launch_bounds__(64 * WAVES) void quadform_cols_kernel(const MatDev*
         const long long jr = ok ? row : zn - 1;
         const float w = ok ? 1.f : 0.f;
         bf16x8 zreg[S];
+        // (opaque, or the parts of every quad that depend on its number alone are kept over the loop, and spill)
+        uint32_t gq = (uint32_t)g;
+        asm volatile("" : "+v"(gq));
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             // step s = 2 beta + sl holds k1 = 32 beta + 16 sl + 4 g + (0..3) and the same + 8: quads 8 beta + 4 sl + g and + 2
-            const uint32_t q0 = (uint32_t)(8 * (s >> 1) + 4 * (s & 1) + g);
+            const uint32_t q0 = (uint32_t)(8 * (s >> 1) + 4 * (s & 1)) + gq;
             const Quad a = normal_quad(seed_lo, seed_hi, (uint32_t)jr, q0, cgen);
             const Quad b = normal_quad(seed_lo, seed_hi, (uint32_t)jr, q0 + 2u, cgen);
             const v4u pk = {pack_bf16x2(w * a.z[0], w * a.z[1]), pack_bf16x2(w * a.z[2], w * a.z[3]),
