@@ -195,13 +195,15 @@ void build_compress_f32_items(Plan& p)
     // of a percent of the chip's bandwidth: in a launch of a few thousand row blocks the
     // long ones would finish last and alone.  Their columns are then shared between
     // workgroups (partial products combined by the last one to finish;
-    // nparts * rows * r * 8 bytes of extra traffic per block, little at these ranks): of about 1024
-    // columns where the set fills 600 such workgroups, else 512, and in launches of no more than a
-    // workgroup per compute unit 256, swept by two column groups.  (Filled ones are counted: 17 matrices of
-    // 5888 x 64 are 1564 workgroups of any size, but 9 of 940 x 2048 beside them take 28 us in pieces of
-    // 1024 and 24 in pieces of 512.)  r = 16, fp32, pieces of 512 / as chosen: one 1024 x 1024 matrix 11.7 /
-    // 7.4 us, eight of T5-small 12.1 / 8.3, all 96 36.9 / 34.3.  (2048 is faster yet where the set fills that,
-    // but one chain of additions along it rounds more.)
+    // nparts * rows * r * 8 bytes of extra traffic per block, little at these ranks): of about 512 columns; of 1024
+    // in sets that fill 600 such workgroups, if most of it lies in matrices that these do not cut, or 1800; and in
+    // launches of no more than a workgroup per compute unit 256, swept by two column groups unless all columns are
+    // one or two tiles (256 columns at r = 32).  us in pieces of 512 / 1024: T5-small fp32 r = 16 36.9 / 34.3, 96 of
+    // 768 x 768 bf16 r = 16 24 / 22, but 9 of 2340 x 3032 bf16 r = 8 82 / 103, 20 of 1024 x 4096 fp32 r = 8 66 / 78 (over
+    // 216 sets the rule takes 0.989 of the time of 512 alone, 1.03 at worst; 600 workgroups alone 0.986, 1.25 at
+    // worst).  Short launches, 512 / 256 in one group / in two: one 1024 x 1024 matrix r = 16 10.8 / 7.7 / 7.0, 64 x 48
+    // 4.4 / 4.1 / 4.4, r = 32 4.5 / 4.3 / 6.0.  (2048 is faster yet where the set fills that, but one chain of
+    // additions along it rounds more.)
     long long kc = g_tune.compress_splitk_cols;
     p.kg = kc ? 1 : 2;
     if (kc == 0) {
@@ -211,12 +213,21 @@ void build_compress_f32_items(Plan& p)
                 w += (p.host_mats[l].n + rows_per_wg - 1) / rows_per_wg * ((p.host_mats[l].m + cols - 1) / cols);
             return w;
         };
-        double area = 0.0;
-        for (int l = 0; l < p.count; ++l) area += (double)p.host_mats[l].n * (double)p.host_mats[l].m;
+        double area = 0.0, uncut = 0.0;     // in workgroups of 64 x 1024
+        long long widest = 0;
+        for (const MatDev& M : p.host_mats) {
+            const double x = (double)M.n * (double)M.m / (64.0 * 1024.0);
+            area += x;
+            uncut += M.m <= 1024 ? x : 0.0;
+            widest = std::max(widest, M.m);
+        }
         if (wgs(1ll << 40) < 8192) {
-            kc = area >= 600.0 * 64 * 1024 ? 1024 : 512;
+            kc = area >= 1800.0 || (area >= 600.0 && 2.0 * uncut >= area) ? 1024 : 512;
             p.kg = 1;
-            if (wgs(512) <= 256 && !p.lean) { kc = 256; p.kg = 2; }
+            if (wgs(512) <= 256 && !p.lean) {
+                kc = 256;
+                p.kg = widest > (p.r == 32 ? 256 : 128) ? 2 : 1;
+            }
         }
     }
     p.kc = (int)kc;

@@ -186,3 +186,14 @@ def test_filled_updates_at_small_ranks_take_128_rows():
         for r in (8, 16, 32):
             items, _ = check_decompress(shapes, r)
             assert max(it[COLS["rows"]] for it in items) == 128, (shapes[0], len(shapes), r)
+
+
+def test_fp32_compress_pieces_by_how_much_they_would_cut():
+    """Pieces of 1024 columns only where they were measured to be no slower than 512: large sets, and sets of matrices
+    that they mostly do not cut."""
+    t5s, gpt = (workloads.workload(i).shapes for i in (2, 3))
+    for shapes, kc in ((t5s, 1024), ([(768, 768)] * 96, 1024), ([(1600, 6400)] * 12, 1024), ([(2340, 3032)] * 9, 512),
+                       ([(1600, 6400)] * 8, 512), ([(4096, 4096)] * 6, 512), (gpt, 512), ([(1024, 1024)], 256), ([(64, 48)], 256)):
+        for r in (8, 16, 32):
+            _, info = check_compress(shapes, r, flora.BF16)
+            assert int(info[2]) == kc, (shapes[0], len(shapes), r)
