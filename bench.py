@@ -31,7 +31,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0           # MI355X HBM3E, published
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # dense bf16 matrix cores, published
-GEN_RATE_MEASURED = 1.88e12     # normals/s of the generator alone on the whole chip (measured)
+GEN_RATE_MEASURED = 2.56e12     # normals/s of the generator alone on the whole chip (measured, profiles/ceilings.txt)
 HEADLINE = 4
 DEFAULT_STEPS = {1: 500, 2: 200, 3: 300, 4: 20, 5: 40}
 DEFAULT_WARM = {1: 20, 2: 10, 3: 10, 4: 2, 5: 3}
