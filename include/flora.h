@@ -262,10 +262,10 @@ void flora_derive_seeds(uint64_t global_seed, uint64_t first_matrix_id, int coun
  * matrices at rank r, i.e. what the most demanding call occupies: flora_fused_step with a
  * transfer and an Adafactor rule (its transfer, compress and update plans are resident together).
  * Exact, not a bound: with one 256-byte unit less that call returns FLORA_ERR_INVALID, unless its
- * compress launch has a shape that holds less (fp32 gradients and rows of G that do not start on
- * 16-byte boundaries at ranks >= 64, small launches at the other ranks): then the call takes that
- * shape, which is slower and adds its sums in another order.  Only n and m of the descriptors are
- * read.  Host only.  0 for an invalid set or rank.
+ * launches have shapes that hold less (as with fp32 gradients, and rows of G that do not start on
+ * 16-byte boundaries, at ranks >= 64): then the call takes those, which are slower and add their
+ * sums in another order.  Only n and m of the descriptors are read.  Host only.  0 for an invalid
+ * set or rank.
  *
  * flora_set_workspace: dev_ptr is DEVICE memory, 256-byte aligned, of `bytes` bytes, owned by the
  * caller and kept alive until the workspace is replaced, cleared (dev_ptr NULL and bytes 0:

@@ -342,6 +342,13 @@ WideShape choose_wide(const Plan& p, bool f32, bool whole_rows, bool allow512)
     const int slice = (p.r == 64) ? 64 : 128, slices = p.r / slice;
     const WideShape coarse = coarse_wide(p);
     size_t most = wide_bytes(p, coarse.mt, coarse.kc);
+    // (where that shares no columns at all, as much as the state, up to 32 MiB: five matrices of 3352 x 112 and 14 of
+    // 224 x 728 at r = 128 21 -> 13 us; a lean plan holds nothing)
+    if (!p.lean && most == wide_bytes(p, coarse.mt, 0)) {
+        size_t state = 0;
+        for (const MatDev& M : p.host_mats) state += (size_t)M.n * p.r * 4;
+        most += std::min(state, (size_t)32 << 20);
+    }
     // fp32 gradients cannot take 512 rows.  Rows on no 16-byte boundary are worth more memory (one 1600 x 6401
     // matrix at r = 64: 15 us with shared columns, 93 without), and a plan that holds none of it is there for a
     // workspace without room (lean); in sets above some 30 M elements 128 whole rows keep up.

@@ -257,7 +257,8 @@ def test_adafactor_plans_hold_no_more_than_large_pieces_would(r):
 
 def _compress_bytes_in_coarse_pieces(shapes, r):
     """A wide compress plan of 512 or 256 rows and whole rows or parts of 1536 or 768 columns, the first of which
-    there are 384 (whole rows only where balanced); launches of few workgroups 128 rows, parts of 384."""
+    there are 384 (whole rows only where balanced); launches of few workgroups 128 rows, parts of 384.  Where that shares
+    no columns, as much as the state may be held, up to 32 MiB."""
     up = lambda a, b: -(-a // b)
     slices, width = (1, 64) if r == 64 else (r // 128, 128)
     wgs = lambda rows, kc: sum(up(n, rows) * slices * (up(m, kc) if kc else 1) for n, m in shapes)
@@ -269,11 +270,14 @@ def _compress_bytes_in_coarse_pieces(shapes, r):
     rows, kc = next(((R, k) for R in (512, 256) for k in (0, 1536, 768) if wgs(R, k) >= 384 and (k or balanced(R))), (256, 768))
     if wgs(256, 768) < 130:
         rows, kc = 128, 384 if wgs(128, 768) < 150 else 768
-    b = 0
+    b = shared = 0
     for n, m in shapes:
         parts = up(m, kc) if kc else 1
         parts = up(m, up(up(m, parts), 64) * 64)
         b += up(n, rows) * slices * (48 * parts + ((parts * rows * width + 1) * 4 if parts > 1 else 0))
+        shared += parts > 1
+    if not shared:
+        b += min(sum(4 * n * r for n, _ in shapes), 32 << 20)
     return b + 768 + 8 * _round256(184 * len(shapes))
 
 
