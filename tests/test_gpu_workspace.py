@@ -213,6 +213,8 @@ def test_more_matrices_than_one_launch_takes_with_a_workspace():
     ([(1100, 1003)] * 2 + [(770, 3001)] * 2, 128, "f32", 2363392),
     ([(1100, 1003)] * 2 + [(770, 3001)] * 2, 256, "bf16", 8194304),
     ([(768, 5025)], 64, "bf16", 469504),
+    # the same with whole 16-byte rows, where the coarsest shape shares no columns
+    ([(3352, 112)] * 5 + [(224, 728)] * 14, 128, "bf16", 2880512),
     # by the length of the wide kernel's work table: the narrow kernel
     ([(4480, 9)] * 64, 64, "f32", 3909632),
     # ranks up to 32: pieces of 512 columns; row blocks of 256 under the factored rule
