@@ -17,9 +17,9 @@
 //
 // Ranks 64 / 128 / 256 (2 m r^2 + 2 n r^2 flops per matrix): fp32 products as sums of products of bf16
 //   parts, see below.
-// transfer_T_split: one workgroup owns all of T (or half of it) and a chunk of 1024 of the m columns j, so
-//   the work of a launch is many equal pieces; the generator's tiles are double buffered in LDS.  Chunk
-//   partials are added in chunk order by combine_T (fixed order, no atomics).
+// transfer_T_split: one workgroup owns a block of T (all of it in large launches) and a chunk of 1024 of the m
+//   columns j, so the work of a launch is many equal pieces; the generator's tiles are double buffered in LDS.
+//   Chunk partials are added in chunk order by combine_T (fixed order, no atomics).
 // apply_T_split: one workgroup owns 64 rows of M.
 #include "flora_gen.hip.h"
 #include "flora_internal.h"
@@ -229,27 +229,39 @@ __device__ __forceinline__ void mfma_split_direct(f32x16& acc, const bf16x8 (&a)
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
 }
 
-// Partial T = A_old^T A_new over a chunk of columns: SLAB rows of T (all of them, so that A_new is
-// regenerated once, or, in launches of few chunks, half), R columns.  Tiles of 16 columns of both
-// projections are regenerated, split and stored to LDS by rank row ([part][k][j], double buffered); half
-// of the waves produce the next tile before they multiply the current one, the others after.
+// Partial T = A_old^T A_new over a chunk of columns, an SR x SC block of it per workgroup.  Tiles of 16 columns of
+// both projections (SR and SC ranks of them) are regenerated, split and stored to LDS by rank row ([part][k][j], double
+// buffered); half of the waves produce the next tile before they multiply the current one, the others after.
 // RG x CG waves of WR x WC tiles of 32 x 32; with KG > 1 KG groups of them take every KG-th tile each, with
-// buffers of their own, and their sums are added in the groups' order.  (For launches that leave compute units
-// idle: one workgroup then holds as many waves as several would, and the chain along a chunk is KG times
-// shorter.  Transfers, one group / KG: r = 64, 4 matrices of 768 x 3072 60 / 38 us, 8 of 80 x 448 33 / 24;
-// above a workgroup per compute unit the tiles of several workgroups overlap as well, and LDS then holds
-// no more waves with them.)
-template <int R, int SLAB, int WR, int WC, int KG>
-__global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64 * KG) void transfer_T_split_kernel(
-    const MatDev* __restrict__ mats, const WorkItem* __restrict__ items, int item_step)
+// buffers of their own, and their sums are added in the groups' order.
+// What bounds it is the vector ALU: the generator, splitting, and the additions of mfma_split.  All of T in one
+// workgroup generates each entry once, but then one compute unit makes all entries of a chunk in a chain of 64 tiles;
+// smaller blocks generate the ranks of their rows and columns again, on compute units that would be idle.  (They take
+// no memory; shorter chunks would, r^2 floats each.)  T kernel alone, us, chunks of 1024 columns, blocks / KG:
+//   r = 256                 1 chunk   4    16    32    64   128   192   256   512
+//     32 x 32 / 8              17    17
+//     64 x 64 / 4              28    29    33    63   122   222
+//     128 x 128 / 2            59    59    61    63    70   135   200   265   529
+//     128 x 256 / 1           108   109   109   109   111   121   226   238   471
+//     256 x 256 / 1           152   151   153   153   153   154   165   199   393
+//   r = 128: 32 x 32 / 8 17 to 16 chunks; 64 x 64 / 4 28 at 1, 32 at 64, 60 at 96; 128 x 128 / 2 59, 60, 61, and 69 at
+//   256; / 1 69, 71, 71, 75, and 133 against 135 at 512.
+//   r = 64: 32 x 32 / 8 16 at 1, 18 at 64, 33 at 96; 64 x 64 / 4 27, 28, 29, and 30 at 256, 55 at 320; / 1 53, 53, 54, 54, 68
+//   (and 70 against 58 at 512, but several small workgroups of other launches fit beside it).
+template <int R, int SR, int SC, int WR, int WC, int KG>
+__global__ __launch_bounds__((SR / 32 / WR) * (SC / 32 / WC) * 64 * KG) void transfer_T_split_kernel(
+    const MatDev* __restrict__ mats, const WorkItem* __restrict__ items)
 {
-    constexpr int RG = SLAB / 32 / WR, NW = RG * (R / 32 / WC), T = 64 * NW;
-    constexpr int ROWS = SLAB + R;                 // rank rows in LDS: SLAB of the old projection, then R of the new
+    constexpr int RG = SR / 32 / WR, NW = RG * (SC / 32 / WC), T = 64 * NW;
+    constexpr int ROWS = SR + SC;                  // rank rows in LDS: SR of the old projection, then SC of the new
     constexpr int NU = 8 * (ROWS / 4);             // units of a tile: (pair of columns, quad)
-    static_assert(KG == 1 || (KG - 1) * SLAB * R * 4 <= KG * 2 * 3 * ROWS * kLdk * 2, "the sums take the place of the tiles");
+    constexpr int NB = (R / SR) * (R / SC);        // blocks of T, consecutive workgroups of a chunk
+    constexpr int SLABS = R > 128 ? R / 128 : 1;   // entries of the table per chunk
+    static_assert(KG == 1 || (KG - 1) * SR * SC * 4 <= KG * 2 * 3 * ROWS * kLdk * 2, "the sums take the place of the tiles");
     __shared__ __attribute__((aligned(16))) uint16_t lds_all[KG][2][3][ROWS][kLdk];
 
-    const WorkItem it = items[blockIdx.x * item_step];
+    const WorkItem it = items[blockIdx.x / NB * SLABS];
+    const int rank_row0 = (int)(blockIdx.x % NB) / (R / SC) * SR, rank_col0 = (int)(blockIdx.x % NB) % (R / SC) * SC;
     const MatDev& M = mats[it.mat];
     const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / T);
     const int tid = (int)threadIdx.x - kg * T;
@@ -262,9 +274,10 @@ __global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64 * KG) void tr
     const uint32_t so_lo = M.seed_lo, so_hi = M.seed_hi, sn_lo = M.seedn_lo, sn_hi = M.seedn_hi;
     const uint32_t jbeg = (uint32_t)it.col0, jend = (uint32_t)it.col1;       // this chunk's columns
     const int ntiles = (int)((jend - jbeg + KG * kKT - 1) / (KG * kKT));      // of each group (zeros beyond the chunk)
-    const uint32_t qold0 = (uint32_t)(it.slice * (SLAB / 4));
+    const uint32_t qold0 = (uint32_t)(rank_row0 / 4), qnew0 = (uint32_t)(rank_col0 / 4);
 
     auto produce = [&](int buf, int tile) {
+        const bool whole = jbeg + (uint32_t)(tile * KG + kg + 1) * kKT <= jend;
 #pragma unroll
         for (int u0 = 0; u0 < NU; u0 += T) {
             const int u = u0 + tid;
@@ -272,18 +285,24 @@ __global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64 * KG) void tr
             const int q = u >> 3, jp = 2 * (u & 7);
             const uint32_t j = jbeg + (uint32_t)(tile * KG + kg) * kKT + (uint32_t)jp;
             // (the 64 units of a wave are on one side)
-            const bool isold = __builtin_amdgcn_readfirstlane(q) < SLAB / 4;
+            const bool isold = __builtin_amdgcn_readfirstlane(q) < SR / 4;
             const uint32_t s_lo = isold ? so_lo : sn_lo, s_hi = isold ? so_hi : sn_hi;
-            const uint32_t qq = isold ? qold0 + (uint32_t)q : (uint32_t)(q - SLAB / 4);
-            const Quad z0 = normal_quad(s_lo, s_hi, j, qq, cgen);
+            const uint32_t qq = isold ? qold0 + (uint32_t)q : qnew0 + (uint32_t)(q - SR / 4);
+            Quad z0 = normal_quad(s_lo, s_hi, j, qq, cgen);
             __builtin_amdgcn_sched_barrier(0);      // (one quad at a time: the registers are the accumulators')
-            const Quad z1 = normal_quad(s_lo, s_hi, j + 1, qq, cgen);
+            Quad z1 = normal_quad(s_lo, s_hi, j + 1, qq, cgen);
             __builtin_amdgcn_sched_barrier(0);
-            const bool ok0 = j < jend, ok1 = j + 1 < jend;
+            if (!whole) {                           // (uniform: the masks cost a launch's last tiles only)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    z0.z[i] = j < jend ? z0.z[i] : 0.f;
+                    z1.z[i] = j + 1 < jend ? z1.z[i] : 0.f;
+                }
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 uint32_t h, m, l;
-                split3(ok0 ? z0.z[i] : 0.f, ok1 ? z1.z[i] : 0.f, h, m, l);
+                split3(z0.z[i], z1.z[i], h, m, l);
                 *reinterpret_cast<uint32_t*>(&lds[buf][0][4 * q + i][jp]) = h;
                 *reinterpret_cast<uint32_t*>(&lds[buf][1][4 * q + i][jp]) = m;
                 *reinterpret_cast<uint32_t*>(&lds[buf][2][4 * q + i][jp]) = l;
@@ -316,7 +335,7 @@ __global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64 * KG) void tr
         for (int c = 0; c < WC; ++c) {
             bf16x8 bv[3];
 #pragma unroll
-            for (int p = 0; p < 3; ++p) bv[p] = *reinterpret_cast<const bf16x8*>(&lds[buf][p][SLAB + 32 * (ct0 + c) + ln][8 * g]);
+            for (int p = 0; p < 3; ++p) bv[p] = *reinterpret_cast<const bf16x8*>(&lds[buf][p][SR + 32 * (ct0 + c) + ln][8 * g]);
 #pragma unroll
             for (int r = 0; r < WR; ++r) mfma_split(acc[r][c], av[r], bv);
             __builtin_amdgcn_sched_barrier(0);      // (or every column tile's operands are fetched first, and spill)
@@ -358,8 +377,8 @@ __global__ __launch_bounds__((SLAB / 32 / WR) * (R / 32 / WC) * 64 * KG) void tr
         for (int c = 0; c < WC; ++c)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int k1 = it.slice * SLAB + 32 * (rt0 + r) + 8 * (v / 4) + 4 * g + (v % 4);
-                stg(part + k1 * R + 32 * (ct0 + c) + ln, acc[r][c][v]);
+                const int k1 = rank_row0 + 32 * (rt0 + r) + 8 * (v / 4) + 4 * g + (v % 4);
+                stg(part + k1 * R + rank_col0 + 32 * (ct0 + c) + ln, acc[r][c][v]);
             }
 }
 
@@ -374,21 +393,17 @@ __global__ __launch_bounds__(4 * R) void combine_T_kernel(const MatDev* __restri
     const float* src = M.rowpart + (size_t)(kKT * b + 4 * sub) * R + k2;
     const int nch = M.ncolchunks;
     float s[4] = {0.f, 0.f, 0.f, 0.f};
-    int c = 0;
-    for (; c + 2 <= nch; c += 2) {                 // eight loads in flight
-        float v[2][4];
+    for (int c = 0; c < nch; c += 4) {             // sixteen loads in flight
+        float v[4][4];
 #pragma unroll
-        for (int e = 0; e < 2; ++e)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[e][i] = ldg(src + (size_t)(c + e) * R * R + i * R);
+            for (int i = 0; i < 4; ++i) v[e][i] = c + e < nch ? ldg(src + (size_t)(c + e) * R * R + i * R) : 0.f;
 #pragma unroll
-        for (int e = 0; e < 2; ++e)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
             for (int i = 0; i < 4; ++i) s[i] += v[e][i];
     }
-    if (c < nch)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) s[i] += ldg(src + (size_t)c * R * R + i * R);
     uint32_t h[2], m[2], l2[2];
     split3(s[0], s[1], h[0], m[0], l2[0]);
     split3(s[2], s[3], h[1], m[1], l2[1]);
@@ -574,35 +589,37 @@ hipError_t launch_transfer_T(const MatDev* mats, const WorkItem* items, int nite
 {
     if (count == 0) return hipSuccess;
     if (r >= 64) {
-        // items: (matrix, chunk of columns, slab of up to 128 rows of T), the slabs of a chunk in a row;
-        // then the chunks are summed
-        const dim3 grid((unsigned)nitems);
+        // items: (matrix, chunk of columns, slab of up to 128 rows of T), the slabs of a chunk in a row; a launch
+        // takes a chunk as a whole or in blocks of T; then the chunks are summed
+        const int chunks = nitems / (r > 128 ? r / 128 : 1);
+#define FLORA_SPLIT(R, SR, SC, WR, WC, KG)                                                                                     \
+    hipLaunchKernelGGL((transfer_T_split_kernel<R, SR, SC, WR, WC, KG>), dim3((unsigned)(chunks * (R / SR) * (R / SC))),       \
+                       dim3((SR / 32 / WR) * (SC / 32 / WC) * 64 * KG), 0, s, mats, items)
         switch (r) {
         case 64:
-            if (nitems <= 256)
-                hipLaunchKernelGGL((transfer_T_split_kernel<64, 64, 1, 1, 4>), grid, dim3(1024), 0, s, mats, items, 1);
-            else
-                hipLaunchKernelGGL((transfer_T_split_kernel<64, 64, 1, 1, 1>), grid, dim3(256), 0, s, mats, items, 1);
+            if (chunks <= 64) FLORA_SPLIT(64, 32, 32, 1, 1, 8);
+            else if (chunks <= 256) FLORA_SPLIT(64, 64, 64, 1, 1, 4);
+            else FLORA_SPLIT(64, 64, 64, 1, 1, 1);
             hipLaunchKernelGGL((combine_T_kernel<64>), dim3(64 / kKT, (unsigned)count), dim3(4 * 64), 0, s, mats);
             break;
         case 128:
-            if (nitems <= 256)
-                hipLaunchKernelGGL((transfer_T_split_kernel<128, 128, 2, 1, 2>), grid, dim3(1024), 0, s, mats, items, 1);
-            else
-                hipLaunchKernelGGL((transfer_T_split_kernel<128, 128, 2, 1, 1>), grid, dim3(512), 0, s, mats, items, 1);
+            if (chunks <= 16) FLORA_SPLIT(128, 32, 32, 1, 1, 8);
+            else if (chunks <= 64) FLORA_SPLIT(128, 64, 64, 1, 1, 4);
+            else if (chunks <= 256) FLORA_SPLIT(128, 128, 128, 2, 1, 2);
+            else FLORA_SPLIT(128, 128, 128, 2, 1, 1);
             hipLaunchKernelGGL((combine_T_kernel<128>), dim3(128 / kKT, (unsigned)count), dim3(4 * 128), 0, s, mats);
             break;
         case 256:
-            // both slabs of a chunk by one workgroup, which then regenerates the new projection once; where
-            // that gives the chip fewer than a workgroup per compute unit, a workgroup each
-            if (nitems / 2 >= 256)
-                hipLaunchKernelGGL((transfer_T_split_kernel<256, 256, 1, 4, 1>), dim3((unsigned)(nitems / 2)), dim3(1024), 0, s, mats, items, 2);
-            else
-                hipLaunchKernelGGL((transfer_T_split_kernel<256, 128, 2, 2, 1>), grid, dim3(512), 0, s, mats, items, 1);
+            if (chunks <= 4) FLORA_SPLIT(256, 32, 32, 1, 1, 8);
+            else if (chunks <= 16) FLORA_SPLIT(256, 64, 64, 1, 1, 4);
+            else if (chunks <= 64) FLORA_SPLIT(256, 128, 128, 2, 1, 2);
+            else if (chunks <= 128) FLORA_SPLIT(256, 128, 256, 2, 2, 1);
+            else FLORA_SPLIT(256, 256, 256, 1, 4, 1);
             hipLaunchKernelGGL((combine_T_kernel<256>), dim3(256 / kKT, (unsigned)count), dim3(4 * 256), 0, s, mats);
             break;
         default: return hipErrorInvalidValue;
         }
+#undef FLORA_SPLIT
         return hipGetLastError();
     }
 #define FLORA_T(RR)                                                                              \

@@ -530,6 +530,15 @@ def test_transfer_tiles_in_groups(n, m, r, count):
     test_transfer_split_products_at_edges(n, m, r, count)
 
 
+# T in blocks, by how many pieces a launch has: either side of every change of block, columns around the 16 of a
+# tile and the 128 / 64 of a round of eight / four groups, two pieces per matrix.  Same bar.
+@pytest.mark.parametrize("n,m,r,count", [(70, 127, 64, 64), (3, 129, 64, 65), (65, 1040, 128, 8), (20, 65, 128, 17), (9, 63, 128, 65),
+                                         (64, 129, 256, 4), (33, 1025, 256, 2), (5, 65, 256, 5), (20, 17, 256, 16), (9, 31, 256, 17),
+                                         (1, 33, 256, 64), (7, 16, 256, 65), (2, 15, 256, 129)])
+def test_transfer_in_blocks_of_T(n, m, r, count):
+    test_transfer_split_products_at_edges(n, m, r, count)
+
+
 # What is not finite in a state stays in its row and comes out as the fp32 product gives it: inf times T's entry
 # has that entry's sign, two infinities of opposite signs in one sum are a NaN, a NaN is one in the whole row.
 @pytest.mark.parametrize("n,accumulate", [(70, False), (129, True), (64, False), (1, False)])
