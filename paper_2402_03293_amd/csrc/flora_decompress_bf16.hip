@@ -20,7 +20,7 @@ namespace flora {
 
 namespace {
 
-template <int R, int MODE, typename OT>
+template <int R, int MODE, typename OT, int WP>
 __global__ __launch_bounds__(256) void decompress_bf16_kernel(const MatDev* __restrict__ mats,
                                                               const WorkItem* __restrict__ items,
                                                               const SeedArgs seeds, DecompressParams p)
@@ -34,7 +34,6 @@ __global__ __launch_bounds__(256) void decompress_bf16_kernel(const MatDev* __re
     const WorkItem it = items[blockIdx.x];
     const MatDev& M = mats[it.mat];
     const long long n = M.n, m = M.m;
-    const float* __restrict__ state = M.state;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int ln = lane & 31, g = lane >> 5;
@@ -43,30 +42,14 @@ __global__ __launch_bounds__(256) void decompress_bf16_kernel(const MatDev* __re
     const float cgen = neg2_ln2_over(R);
     const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
 
-    bf16x8 breg[S];
-#pragma unroll
-    for (int s = 0; s < S; ++s) {
-        const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)(jok ? j : 0), (uint32_t)(4 * s + 2 * g), cgen);
-        const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)(jok ? j : 0), (uint32_t)(4 * s + 2 * g + 1), cgen);
-        const uint4 pk = make_uint4(pack_bf16x2(z0.z[0], z0.z[1]), pack_bf16x2(z0.z[2], z0.z[3]),
-                                    pack_bf16x2(z1.z[0], z1.z[1]), pack_bf16x2(z1.z[2], z1.z[3]));
-        breg[s] = __builtin_bit_cast(bf16x8, pk);
-    }
-
-    EpilogueLane ep = epilogue_begin<MODE>(M, p, j, jok);
-
     const long long row_end = ((long long)it.row0 + it.rows < n) ? (long long)it.row0 + it.rows : n;
 
     // cooperative fetch of a 32 x R block of the state: float4 number f = tid + 256 i
-    // covers row f / (R/4), columns 4 (f % (R/4)) .. +3
+    // covers row f / (R/4), columns 4 (f % (R/4)) .. +3; rows past the end read as zero
     auto fetch = [&](v4f (&dst)[F4], long long rb) {
+        const rsrc_t r = tile_rsrc(M.state, R, rb, row_end);
 #pragma unroll
-        for (int i = 0; i < F4; ++i) {
-            const int f = tid + 256 * i;
-            long long row = rb + f / (R / 4);
-            if (row > n - 1) row = n - 1;
-            dst[i] = ldg4(state + row * R + 4 * (f % (R / 4)));
-        }
+        for (int i = 0; i < F4; ++i) dst[i] = buf_load_f4(r, 16u * (uint32_t)(tid + 256 * i));
     };
     auto stash = [&](const v4f (&src)[F4], int buf) {
 #pragma unroll
@@ -80,17 +63,28 @@ __global__ __launch_bounds__(256) void decompress_bf16_kernel(const MatDev* __re
     v4f stage[F4];
     fetch(stage, it.row0);
     TilePre<MODE> pre_cur, pre_nxt;
-    epilogue_fetch<MODE, OT>(pre_cur, M, p, it.row0, row_end, j, jok);
+    epilogue_fetch<MODE, OT, WP>(pre_cur, M, it.row0, row_end, j, jok);
+    __builtin_amdgcn_sched_barrier(0);
+
+    bf16x8 breg[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)(jok ? j : 0), (uint32_t)(4 * s + 2 * g), cgen);
+        const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)(jok ? j : 0), (uint32_t)(4 * s + 2 * g + 1), cgen);
+        const uint4 pk = make_uint4(pack_bf16x2(z0.z[0], z0.z[1]), pack_bf16x2(z0.z[2], z0.z[3]),
+                                    pack_bf16x2(z1.z[0], z1.z[1]), pack_bf16x2(z1.z[2], z1.z[3]));
+        breg[s] = __builtin_bit_cast(bf16x8, pk);
+    }
+
+    EpilogueLane ep = epilogue_begin<MODE>(M, p, j, jok);
     stash(stage, 0);
     __syncthreads();
 
     int buf = 0;
     for (long long rb = it.row0; rb < row_end; rb += 32) {
-        const bool more = rb + 32 < row_end;
-        if (more) {
-            fetch(stage, rb + 32);
-            epilogue_fetch<MODE, OT>(pre_nxt, M, p, rb + 32, row_end, j, jok);
-        }
+        fetch(stage, rb + 32);
+        epilogue_fetch<MODE, OT, WP>(pre_nxt, M, rb + 32, row_end, j, jok);
+        __builtin_amdgcn_sched_barrier(0);
 
         f32x16 acc;
 #pragma unroll
@@ -101,12 +95,10 @@ __global__ __launch_bounds__(256) void decompress_bf16_kernel(const MatDev* __re
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, breg[s], acc, 0, 0, 0);
         }
 
-        epilogue_tile<MODE, OT>(acc, pre_cur, M, it, p, rb, row_end, j, jok, ep, lds_red);
+        epilogue_tile<MODE, OT, WP>(acc, pre_cur, M, it, p, rb, row_end, j, jok, ep, lds_red);
 
-        if (more) {
-            stash(stage, buf ^ 1);
-            pre_cur = pre_nxt;
-        }
+        stash(stage, buf ^ 1);
+        pre_cur = pre_nxt;
         __syncthreads();
         buf ^= 1;
     }
@@ -583,37 +575,37 @@ hipError_t launch_mode_vec(const MatDev* mats, const WorkItem* items, int nitems
     }
 }
 
+template <int R, int MODE, typename OT>
+hipError_t launch_one(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, DecompressParams p, hipStream_t s)
+{
+    const dim3 grid((unsigned)nitems), block(256);
+#define FLORA_DEC(WP) hipLaunchKernelGGL((decompress_bf16_kernel<R, MODE, OT, WP>), grid, block, 0, s, mats, items, seeds, p)
+    if constexpr (Moves<MODE>::w || Moves<MODE>::v) {
+        switch (p.wpolicy & 3) {
+        case 1: FLORA_DEC(1); break;
+        case 2: FLORA_DEC(2); break;
+        case 3: FLORA_DEC(3); break;
+        default: FLORA_DEC(0); break;
+        }
+    } else FLORA_DEC(0);
+#undef FLORA_DEC
+    return hipGetLastError();
+}
+
 template <int R, typename OT>
 hipError_t launch_mode(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds,
                        int mode, DecompressParams p, hipStream_t s)
 {
-    const dim3 grid((unsigned)nitems), block(256);
     switch (mode) {
-    case kModeOut:
-        hipLaunchKernelGGL((decompress_bf16_kernel<R, kModeOut, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeSgd:
-        hipLaunchKernelGGL((decompress_bf16_kernel<R, kModeSgd, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeStats:
-        hipLaunchKernelGGL((decompress_bf16_kernel<R, kModeStats, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeRms:
-        hipLaunchKernelGGL((decompress_bf16_kernel<R, kModeRms, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFactored:
-        hipLaunchKernelGGL((decompress_bf16_kernel<R, kModeFactored, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFull1:
-        hipLaunchKernelGGL((decompress_bf16_kernel<R, kModeFull1, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFull2:
-        hipLaunchKernelGGL((decompress_bf16_kernel<R, kModeFull2, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    default:
-        return hipErrorInvalidValue;
+    case kModeOut: return launch_one<R, kModeOut, OT>(mats, items, nitems, seeds, p, s);
+    case kModeSgd: return launch_one<R, kModeSgd, OT>(mats, items, nitems, seeds, p, s);
+    case kModeStats: return launch_one<R, kModeStats, float>(mats, items, nitems, seeds, p, s);
+    case kModeRms: return launch_one<R, kModeRms, float>(mats, items, nitems, seeds, p, s);
+    case kModeFactored: return launch_one<R, kModeFactored, OT>(mats, items, nitems, seeds, p, s);
+    case kModeFull1: return launch_one<R, kModeFull1, float>(mats, items, nitems, seeds, p, s);
+    case kModeFull2: return launch_one<R, kModeFull2, OT>(mats, items, nitems, seeds, p, s);
+    default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 template <int R>

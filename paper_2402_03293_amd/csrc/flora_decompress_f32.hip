@@ -21,7 +21,8 @@ namespace flora {
 
 namespace {
 
-template <int R, int MODE, typename OT>
+// WP: cache policy of the n x m arrays the pass moves (DecompressParams::wpolicy), see flora_epilogue.hip.h.
+template <int R, int MODE, typename OT, int WP>
 __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __restrict__ mats,
                                                              const WorkItem* __restrict__ items,
                                                              const SeedArgs seeds, DecompressParams p)
@@ -32,7 +33,6 @@ __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __res
     const WorkItem it = items[blockIdx.x];
     const MatDev& M = mats[it.mat];
     const long long n = M.n, m = M.m;
-    const float* __restrict__ state = M.state;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int ln = lane & 31, g = lane >> 5;
@@ -40,6 +40,23 @@ __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __res
     const bool jok = j < m;
     const float cgen = neg2_ln2_over(R);
     const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
+    const long long row_end = ((long long)it.row0 + it.rows < n) ? (long long)it.row0 + it.rows : n;
+
+    // state rows of a tile: lane = row, this lane's half of the rank axis; rows past the end read as zero
+    auto load_state = [&](v4f (&dst)[H / 4], long long rb) {
+        const rsrc_t r = tile_rsrc(M.state, R, rb, row_end);
+#pragma unroll
+        for (int i = 0; i < H / 4; ++i) dst[i] = buf_load_f4(r, (uint32_t)(ln * R + g * H + 4 * i) * 4u);
+    };
+
+    // software pipeline: the next tile's state rows and old weights are in flight while the
+    // current tile goes through the matrix cores and is written back (the first tile's while A is
+    // regenerated)
+    v4f a_cur[H / 4], a_nxt[H / 4];
+    TilePre<MODE> pre_cur, pre_nxt;
+    load_state(a_cur, it.row0);
+    epilogue_fetch<MODE, OT, WP>(pre_cur, M, it.row0, row_end, j, jok);
+    __builtin_amdgcn_sched_barrier(0);
 
     float breg[H];
 #pragma unroll
@@ -52,29 +69,10 @@ __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __res
 
     EpilogueLane ep = epilogue_begin<MODE>(M, p, j, jok);
 
-    const long long row_end = ((long long)it.row0 + it.rows < n) ? (long long)it.row0 + it.rows : n;
-
-    // state rows of a tile: lane = row, this lane's half of the rank axis
-    auto load_state = [&](v4f (&dst)[H / 4], long long rb) {
-        long long arow = rb + ln;
-        if (arow > n - 1) arow = n - 1;
-        const float* sp = state + arow * R + g * H;
-#pragma unroll
-        for (int i = 0; i < H / 4; ++i) dst[i] = ldg4(sp + 4 * i);
-    };
-
-    // software pipeline: the next tile's state rows and old weights are in flight while the
-    // current tile goes through the matrix cores and is written back
-    v4f a_cur[H / 4], a_nxt[H / 4];
-    TilePre<MODE> pre_cur, pre_nxt;
-    load_state(a_cur, it.row0);
-    epilogue_fetch<MODE, OT>(pre_cur, M, p, it.row0, row_end, j, jok);
     for (long long rb = it.row0; rb < row_end; rb += 32) {
-        const bool more = rb + 32 < row_end;
-        if (more) {
-            load_state(a_nxt, rb + 32);
-            epilogue_fetch<MODE, OT>(pre_nxt, M, p, rb + 32, row_end, j, jok);
-        }
+        load_state(a_nxt, rb + 32);
+        epilogue_fetch<MODE, OT, WP>(pre_nxt, M, rb + 32, row_end, j, jok);
+        __builtin_amdgcn_sched_barrier(0);
         f32x16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -82,47 +80,45 @@ __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __res
         for (int s = 0; s < H; ++s)
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[s / 4][s % 4], breg[s], acc, 0, 0, 0);
 
-        epilogue_tile<MODE, OT>(acc, pre_cur, M, it, p, rb, row_end, j, jok, ep, lds_red);
-        if (more) {
+        epilogue_tile<MODE, OT, WP>(acc, pre_cur, M, it, p, rb, row_end, j, jok, ep, lds_red);
 #pragma unroll
-            for (int i = 0; i < H / 4; ++i) a_cur[i] = a_nxt[i];
-            pre_cur = pre_nxt;
-        }
+        for (int i = 0; i < H / 4; ++i) a_cur[i] = a_nxt[i];
+        pre_cur = pre_nxt;
     }
     epilogue_end<MODE>(M, it, j, jok, ep, lds_red);
+}
+
+template <int R, int MODE, typename OT>
+hipError_t launch_one(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, DecompressParams p, hipStream_t s)
+{
+    const dim3 grid((unsigned)nitems), block(256);
+#define FLORA_DEC(WP) hipLaunchKernelGGL((decompress_f32_kernel<R, MODE, OT, WP>), grid, block, 0, s, mats, items, seeds, p)
+    if constexpr (Moves<MODE>::w || Moves<MODE>::v) {
+        switch (p.wpolicy & 3) {
+        case 1: FLORA_DEC(1); break;
+        case 2: FLORA_DEC(2); break;
+        case 3: FLORA_DEC(3); break;
+        default: FLORA_DEC(0); break;
+        }
+    } else FLORA_DEC(0);
+#undef FLORA_DEC
+    return hipGetLastError();
 }
 
 template <int R, typename OT>
 hipError_t launch_mode(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds,
                        int mode, DecompressParams p, hipStream_t s)
 {
-    const dim3 grid((unsigned)nitems), block(256);
     switch (mode) {
-    case kModeOut:
-        hipLaunchKernelGGL((decompress_f32_kernel<R, kModeOut, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeSgd:
-        hipLaunchKernelGGL((decompress_f32_kernel<R, kModeSgd, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeStats:
-        hipLaunchKernelGGL((decompress_f32_kernel<R, kModeStats, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeRms:
-        hipLaunchKernelGGL((decompress_f32_kernel<R, kModeRms, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFactored:
-        hipLaunchKernelGGL((decompress_f32_kernel<R, kModeFactored, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFull1:
-        hipLaunchKernelGGL((decompress_f32_kernel<R, kModeFull1, float>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    case kModeFull2:
-        hipLaunchKernelGGL((decompress_f32_kernel<R, kModeFull2, OT>), grid, block, 0, s, mats, items, seeds, p);
-        break;
-    default:
-        return hipErrorInvalidValue;
+    case kModeOut: return launch_one<R, kModeOut, OT>(mats, items, nitems, seeds, p, s);
+    case kModeSgd: return launch_one<R, kModeSgd, OT>(mats, items, nitems, seeds, p, s);
+    case kModeStats: return launch_one<R, kModeStats, float>(mats, items, nitems, seeds, p, s);
+    case kModeRms: return launch_one<R, kModeRms, float>(mats, items, nitems, seeds, p, s);
+    case kModeFactored: return launch_one<R, kModeFactored, OT>(mats, items, nitems, seeds, p, s);
+    case kModeFull1: return launch_one<R, kModeFull1, float>(mats, items, nitems, seeds, p, s);
+    case kModeFull2: return launch_one<R, kModeFull2, OT>(mats, items, nitems, seeds, p, s);
+    default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 template <int R>

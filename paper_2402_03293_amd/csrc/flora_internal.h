@@ -97,15 +97,15 @@ __device__ __forceinline__ void stg(uint16_t* p, uint16_t v) { *(FLORA_GLOBAL ui
 
 // Buffer addressing: a wave-uniform resource (base pointer + size in bytes) plus a 32-bit
 // per-lane byte offset.  The hardware checks the offset against the size: a load beyond it
-// returns zero and a store beyond it is dropped, with no memory traffic.  Sizes are kept
-// below 2^31 so that kOob is out of range for every resource; the host guarantees that by
+// returns zero and a store beyond it is dropped, with no memory traffic.  Sizes are at most
+// 2^31 so that kOob is out of range for every resource; the host guarantees that by
 // limiting m to 2^24 columns.  Pipelined loops use this to prefetch unconditionally (a
 // prefetch past the end is pointed at kOob) and to mask ragged edges without branches.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr uint32_t kOob = 0x80000000u;
 __device__ __forceinline__ rsrc_t make_rsrc(const void* base, long long bytes)
 {
-    const uint32_t nb = bytes <= 0 ? 0u : (bytes > 0x7fffffffLL ? 0x7fffffffu : (uint32_t)bytes);
+    const uint32_t nb = bytes <= 0 ? 0u : (bytes > (long long)kOob ? kOob : (uint32_t)bytes);
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)nb, 0x00020000);
 }
 __device__ __forceinline__ v4f buf_load_f4(rsrc_t r, uint32_t off)
@@ -171,9 +171,18 @@ __device__ __forceinline__ void buf_store_u2(rsrc_t r, uint32_t off, v2u v)
 {
     __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, 0);
 }
-__device__ __forceinline__ void buf_store_h(rsrc_t r, uint32_t off, uint16_t v)
+// One element of fp32 or bf16 as its bits.
+template <typename T, bool STREAM>
+__device__ __forceinline__ uint32_t buf_load_bits(rsrc_t r, uint32_t off)
 {
-    __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)off, 0, 0);
+    if constexpr (sizeof(T) == 4) return __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, STREAM ? 2 : 0);
+    else return (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, STREAM ? 2 : 0);
+}
+template <typename T, bool STREAM>
+__device__ __forceinline__ void buf_store_bits(rsrc_t r, uint32_t off, uint32_t v)
+{
+    if constexpr (sizeof(T) == 4) __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)off, 0, STREAM ? 2 : 0);
+    else __builtin_amdgcn_raw_buffer_store_b16((uint16_t)v, r, (int)off, 0, STREAM ? 2 : 0);
 }
 
 // fp32 -> bf16, round to nearest even (finite inputs).
@@ -197,34 +206,11 @@ __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b)
 // One element of an n x m array of fp32 or bf16 (weights), as fp32.
 __device__ __forceinline__ float load_elem(const float* p) { return *(const FLORA_GLOBAL float*)p; }
 __device__ __forceinline__ float load_elem(const uint16_t* p) { return bf16_bits_to_f32(*(const FLORA_GLOBAL uint16_t*)p); }
-// Loads and stores with the non-temporal hint when STREAM is set (cache policy of the update
-// passes); stores round to nearest even and return the value that was stored.
-template <bool STREAM>
-__device__ __forceinline__ float load_elem(const float* p)
-{
-    return STREAM ? __builtin_nontemporal_load((const FLORA_GLOBAL float*)p) : *(const FLORA_GLOBAL float*)p;
-}
-template <bool STREAM>
-__device__ __forceinline__ float load_elem(const uint16_t* p)
-{
-    return bf16_bits_to_f32(STREAM ? __builtin_nontemporal_load((const FLORA_GLOBAL uint16_t*)p)
-                                   : *(const FLORA_GLOBAL uint16_t*)p);
-}
-template <bool STREAM>
-__device__ __forceinline__ float store_elem(float* p, float v)
-{
-    if (STREAM) __builtin_nontemporal_store(v, (FLORA_GLOBAL float*)p);
-    else *(FLORA_GLOBAL float*)p = v;
-    return v;
-}
-template <bool STREAM>
-__device__ __forceinline__ float store_elem(uint16_t* p, float v)
-{
-    const uint32_t b = f32_to_bf16_bits(v);
-    if (STREAM) __builtin_nontemporal_store((uint16_t)b, (FLORA_GLOBAL uint16_t*)p);
-    else *(FLORA_GLOBAL uint16_t*)p = (uint16_t)b;
-    return bf16_bits_to_f32(b);
-}
+// One element of fp32 or bf16 from its bits, and to them (round to nearest even).
+template <typename T>
+__device__ __forceinline__ float from_bits(uint32_t b) { return sizeof(T) == 4 ? __uint_as_float(b) : bf16_bits_to_f32(b); }
+template <typename T>
+__device__ __forceinline__ uint32_t to_bits(float v) { return sizeof(T) == 4 ? __float_as_uint(v) : f32_to_bf16_bits(v); }
 
 // ---- launchers implemented in the kernel translation units ----------------
 hipError_t launch_debug_generate(uint64_t seed, long long m, int r, float* A_out, uint32_t* raw_out,
