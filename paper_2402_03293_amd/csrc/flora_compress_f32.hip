@@ -251,6 +251,10 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
 #pragma unroll
         for (int u = 0; u < kPF - 1; ++u) load_tile_fast(st[u], u);
         gen_tile(0, 0);
+        // (the round after a single one is multiplied too, by zeros: finite values in the other buffer then, not
+        // whatever LDS held before, which may be NaN)
+        if (fast_rounds == 1)
+            for (int idx = tg; idx < RP * kLda; idx += 256) ldsA[kg][1][idx / kLda][idx % kLda] = 0.f;
         __syncthreads();
         // The body is free of branches around memory operations (a round past the end loads
         // nothing, multiplies zeros and skips only the generator): the compiler can then

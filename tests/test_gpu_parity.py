@@ -212,6 +212,20 @@ def test_compress_f32_pieces(r, count, n, m):
 # load fetches beside its row must not reach the result.  Bar: one rounded operand (A; with fp32
 # gradients G is compared as the kernel rounds it), about 2^-9 / sqrt(3) = 1.1e-3 on a large matrix;
 # the smallest have a handful of terms per entry, hence 6e-3 as for the other launch shapes.
+# matrices of one tile of columns: the round after it multiplies zeros, and whatever the other LDS buffer holds must
+# not turn them into NaN (a decompression of NaNs leaves its operands in every compute unit's LDS)
+@pytest.mark.parametrize("gdt", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,m,r", [(130, 64, 8), (130, 40, 16), (70, 64, 32), (65, 64, 16)])
+def test_compress_f32_one_tile_after_nans(n, m, r, gdt):
+    S, big = torch.full((4096, 256), float("nan"), device=DEV), torch.empty(4096, 4096, device=DEV)
+    G, C = rand((n, m), 77).to(gdt).contiguous(), torch.zeros(n, r, device=DEV)
+    for _ in range(3):
+        flora.decompress(flora.matrices([(4096, 4096)], states=[S], seeds=[1]), 256, 1.0, [big], flora.F32)
+        flora.compress(flora.matrices([(n, m)], grads=[G], states=[C], seeds=[3]), r, flora.F32 if gdt == torch.float32 else flora.BF16, 0.0, 1.0)
+        sync()
+        assert rel_fro(to64(C), oracle.compress(to64(G), r, 3)) < TOL_F32
+
+
 @pytest.mark.parametrize("combine", [1, 2])       # shared columns added by the last part to arrive, or by a launch
 @pytest.mark.parametrize("mt,kc", [(8, 0), (16, 64), (32, 0), (32, 192)])
 @pytest.mark.parametrize("gdt", ["f32", "bf16"])
