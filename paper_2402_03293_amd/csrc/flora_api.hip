@@ -1331,7 +1331,7 @@ static int decompress_chunk(const flora_matrix_t* mats, int count, int r, float 
     Plan* p = nullptr;
     int st = get_plan(kKindDecompress, out_dtype == FLORA_BF16 ? 1 : 0, r, md, s, &p, dry);
     if (st != FLORA_OK || dry) return st;
-    DecompressParams dp{alpha, 0.f, 0.f, 0.f, 0};
+    DecompressParams dp{alpha, 0.f, 0.f, 0.f, 0, 0};
     return run_decompress(p, sa, r, kModeOut, out_dtype == FLORA_BF16, dp, s);
 }
 
@@ -1369,25 +1369,48 @@ static int transfer_chunk(const flora_matrix_t* mats, int count, int r, float* c
 // XL shapes: r = 64, 117 MiB 70 / 68 / 76, 234 MiB 123 / 120 / 124, 352 MiB 192 / 191 / 179, 469 MiB 252 /
 // 248 / 228; r = 128, 234 MiB 164 / 158 / 161, 352 MiB 248 / 231 / 237, 938 MiB 617 / 601 / 573; r = 256,
 // 234 MiB 234 / 232 / 218, 938 MiB 671 / 667 / 654; the same under all of them at r = 16.
-static int choose_wpolicy(const flora_matrix_t* mats, int count, int r, const flora_update_t* u, int wbf16)
+//
+// The unfactored rule passes over the second moment V twice, and the last-level cache can carry what
+// the first pass has written to the second: in sets that do not fit it as a whole, the first pass leaves V there
+// (read and written plainly; above the cache's size written with the hint), and the second, which takes the table from
+// its end, where V has been written last, reads and writes everything with the hint.  us as before / so: T5-small step
+// r = 32 217 / 201, r = 64 197 / 188, GPT-2 base r = 16 313 / 290; 8, 16 and 24 matrices of GPT-2 XL (V of 246, 492, 738 MB) r = 16
+// 235 / 211, 453 / 428, 673 / 650, r = 64 231 / 217, 442 / 430, 654 / 649, r = 256 344 / 329, 544 / 536, 767 / 768, with bf16 weights at
+// r = 128 248 / 243, 441 / 420, 635 / 613; but 36 (1.1 GB) r = 64 963 / 974, r = 256 1127 / 1156.
+struct CachePolicy {
+    int first = 0;      // the unfactored rule's first pass
+    int last = 0;       // the pass that writes the weights
+    int reverse = 0;    // ... which takes the table from its end
+};
+static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, const flora_update_t* u, int wbf16)
 {
-    if (g_tune.update_wpolicy) return g_tune.update_wpolicy - 1;
+    CachePolicy c;
+    if (g_tune.update_wpolicy) {
+        c.first = c.last = g_tune.update_wpolicy - 1;
+        return c;
+    }
+    const bool unfactored = u->rule == FLORA_RULE_UNFACTORED;
+    double elems = 0.0;
+    for (int l = 0; l < count; ++l) elems += (double)mats[l].n * (double)mats[l].m;
+    const double bytes = elems * ((wbf16 ? 2.0 : 4.0) + (unfactored ? 4.0 : 0.0)), v_mib = elems * 4.0 / (1024.0 * 1024.0);
+    // a caller that spreads one optimizer step over several calls says how large the whole set is
+    const double mib = std::max(bytes / (1024.0 * 1024.0), (double)u->step_weight_mib);
+    if (unfactored && mib > 192.0 && v_mib <= 768.0) {
+        c.first = v_mib <= 256.0 ? 0 : 2;
+        c.last = 3;
+        c.reverse = 1;
+        return c;
+    }
     // bf16 weights: a wave's piece of a row is half a 128-byte line, and the two halves meet in the
     // caches only with plain accesses (GPT-2 XL, 2.8 GiB of bf16 weights: update 1.90 ms plain, 1.91
     // with streamed writes, 2.04 with both)
-    if (wbf16) return 0;
-    double bytes = 0.0;
-    const double per = (wbf16 ? 2.0 : 4.0) + (u->rule == FLORA_RULE_UNFACTORED ? 4.0 : 0.0);
-    for (int l = 0; l < count; ++l) bytes += per * (double)mats[l].n * (double)mats[l].m;
-    // a caller that spreads one optimizer step over several calls says how large the whole set is
-    const double mib = std::max(bytes / (1024.0 * 1024.0), (double)u->step_weight_mib);
-    if (mib <= 192.0) return 0;
-    if (mib <= (r == 128 ? 400.0 : 300.0) && r != 256) return 2;
-    return 3;
+    if (wbf16 || mib <= 192.0) return c;
+    c.first = c.last = mib <= (r == 128 ? 400.0 : 300.0) && r != 256 ? 2 : 3;
+    return c;
 }
 
 static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16, const flora_update_t* u,
-                        int wpolicy, bool use_next, hipStream_t s, bool dry)
+                        const CachePolicy& wpolicy, bool use_next, hipStream_t s, bool dry)
 {
     const bool factored = u->rule == FLORA_RULE_FACTORED, unfactored = u->rule == FLORA_RULE_UNFACTORED;
     const bool scaled = (factored || unfactored) && u->scale_parameter != 0;
@@ -1411,11 +1434,11 @@ static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16,
     if (st != FLORA_OK || dry) return st;
     const MatDev* dm = p->cur_mats;
     if (u->rule == FLORA_RULE_SGD) {
-        DecompressParams dp{u->alpha, u->lr * u->alpha, 0.f, 0.f, wpolicy};
+        DecompressParams dp{u->alpha, u->lr * u->alpha, 0.f, 0.f, wpolicy.last, 0};
         st = run_decompress(p, sa, r, kModeSgd, wbf16, dp, s);
         if (st != FLORA_OK) return st;
     } else {
-        DecompressParams dp{u->alpha, u->lr, u->beta2, u->eps1, wpolicy};
+        DecompressParams dp{u->alpha, u->lr, u->beta2, u->eps1, 0, 0};
         const int gram = p->route == Plan::kGram ? 1 : 0;
         if (gram) {
             // row and column sums of Gt^2 as quadratic forms in A^T A and S^T S, then the clipping
@@ -1440,11 +1463,14 @@ static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16,
                 if (st != FLORA_OK) return st;
             }
         } else {
+            dp.wpolicy = wpolicy.first;
             st = run_decompress(p, sa, r, kModeFull1, 0, dp, s);
             if (st != FLORA_OK) return st;
         }
         // clip factor from the partial sums of U^2; parameter scale from the caller's sum of W^2
         FLORA_HIP(launch_rms_finalize(dm, count, u->clip_d, scaled ? 1 : 0, u->eps2, gram, s));
+        dp.wpolicy = wpolicy.last;
+        dp.reverse = wpolicy.reverse;
         st = run_decompress(p, sa, r, factored ? kModeFactored : kModeFull2, wbf16, dp, s);
         if (st != FLORA_OK) return st;
         // the update pass left per-workgroup sums of the new W^2
@@ -1614,7 +1640,7 @@ int flora_apply_update(const flora_matrix_t* mats, int count, int r, flora_dtype
     if (st != FLORA_OK) return st;
     std::lock_guard<std::mutex> guard(g_lock);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
-    const int wpolicy = choose_wpolicy(mats, count, r, u, weight_dtype == FLORA_BF16);
+    const CachePolicy wpolicy = choose_wpolicy(mats, count, r, u, weight_dtype == FLORA_BF16);
     return run_call(s, [&](bool dry) {
         FLORA_FOR_CHUNKS(count, c0, cn) {
             const int st2 = update_chunk(mats + c0, cn, r, weight_dtype == FLORA_BF16, u, wpolicy, false, s, dry);
@@ -1635,7 +1661,7 @@ int flora_fused_step(const flora_matrix_t* mats, int count, int r, flora_dtype_t
     std::lock_guard<std::mutex> guard(g_lock);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const bool next = do_transfer != 0;
-    const int wpolicy = choose_wpolicy(mats, count, r, u, weight_dtype == FLORA_BF16);
+    const CachePolicy wpolicy = choose_wpolicy(mats, count, r, u, weight_dtype == FLORA_BF16);
     return run_call(s, [&](bool dry) {
         FLORA_FOR_CHUNKS(count, c0, cn) {
             int st2 = FLORA_OK;

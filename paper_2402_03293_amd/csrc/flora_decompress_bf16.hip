@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void decompress_bf16_kernel(const MatDev* __re
     __shared__ __attribute__((aligned(16))) uint16_t ldsS[2][32][LDS_ROW];
     __shared__ float lds_red[4][32];
 
-    const WorkItem it = items[blockIdx.x];
+    const WorkItem it = items[MODE == kModeFull2 && p.reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x];
     const MatDev& M = mats[it.mat];
     const long long n = M.n, m = M.m;
     const int tid = threadIdx.x;
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(512, (vec_waves<R, MODE, OT>())) void decompress_bf
     __shared__ float lds_row[2][8][32];   // kModeStats: per-wave row sums of a block, double buffered
     __shared__ float lds_fin[8];
 
-    const WorkItem it = items[blockIdx.x];
+    const WorkItem it = items[MODE == kModeFull2 && p.reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x];
     const MatDev& M = mats[it.mat];
     const long long n = M.n, m = M.m;
     const float* __restrict__ state = M.state;

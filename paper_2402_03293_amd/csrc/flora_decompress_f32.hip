@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __res
     constexpr int H = R / 2;   // rank entries per lane
     __shared__ float lds_red[4][32];
 
-    const WorkItem it = items[blockIdx.x];
+    const WorkItem it = items[MODE == kModeFull2 && p.reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x];
     const MatDev& M = mats[it.mat];
     const long long n = M.n, m = M.m;
     const int tid = threadIdx.x;

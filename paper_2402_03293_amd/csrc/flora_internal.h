@@ -72,6 +72,7 @@ struct DecompressParams {
     float eps1;    // kModeFull1: added to Gt^2
     int wpolicy;   // update passes: bit 0 weights / second moment read with the non-temporal hint,
                    // bit 1 written with it (chosen from the size of the set, see choose_wpolicy)
+    int reverse;   // kModeFull2: workgroups take the table from its end
 };
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;

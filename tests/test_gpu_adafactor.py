@@ -384,6 +384,27 @@ def test_update_cache_policies_give_the_same_bits(n, m, r, wdt, rule):
         assert torch.equal(W, out[0])
 
 
+# the unfactored rule's second pass takes the table from its end in sets above 192 MiB (a set's share of such a
+# step here): the same bits, whichever order
+@pytest.mark.parametrize("r,wdt", [(16, "f32"), (32, "bf16"), (64, "f32"), (256, "bf16")])
+@pytest.mark.parametrize("shapes", [[(130, 260), (33, 520), (257, 64)], [(97, 1001), (64, 35)]])
+def test_unfactored_second_pass_from_the_end(shapes, r, wdt):
+    dt = torch.float32 if wdt == "f32" else torch.bfloat16
+    W0 = [rand(s, 300 + i).to(dt).contiguous() for i, s in enumerate(shapes)]
+    S = [rand((n, r), 310 + i) for i, (n, _) in enumerate(shapes)]
+    out = []
+    for mib in (0.0, 193.0):
+        W, V = [w.clone() for w in W0], [torch.full(s, 0.5, device=DEV) for s in shapes]
+        sq = [torch.ones(1, device=DEV) for _ in shapes]
+        mats = flora.matrices(shapes, weights=W, states=S, second_moments=V, weight_sumsqs=sq, seeds=[7, 8, 9][:len(shapes)])
+        flora.apply_update(mats, r, flora.F32 if wdt == "f32" else flora.BF16,
+                           flora.unfactored_update(1e-2, 1.0, 0.5, 1e-30, 1.0, step_weight_mib=mib))
+        sync()
+        out.append(W + V + sq)
+    assert all(torch.equal(x, y) for x, y in zip(*out))
+    assert not torch.equal(out[0][0], W0[0])
+
+
 # ------------------------------------------- the factored rule through Gram matrices
 # Row sums, column sums and the clipping sum of the rule as quadratic forms in A^T A, S^T S and
 # A^T diag(1/K) A (ranks >= 64), against the oracle, and against the passes over the decompressed
