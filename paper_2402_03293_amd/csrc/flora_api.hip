@@ -84,7 +84,8 @@ struct Plan {
     int mt = 1;                         // bf16 compress: rows per workgroup = 128 * mt
     int combine = 0;                    // bf16 compress: shared columns are added by a launch of their own
     int any_rows = 0;                   // bf16 compress: some rows of G do not start on 16-byte boundaries
-    int vec = 0;                        // decompress: the 16-byte-per-lane bf16 kernel (256-column workgroups)
+    int vec = 0;                        // decompress: the 16-byte-per-lane bf16 kernels (256-column workgroups); 2: bf16
+                                        // rows start on 16-byte boundaries too
     int kc = 0;                         // fp32 compress: columns per part (0: whole rows)
     int kg = 2;                         // fp32 compress: column groups per workgroup
     int lean = 0;                       // 1, 2: launch shapes of less and of least memory (see Arena)
@@ -149,7 +150,8 @@ struct Tuning {
     int compress_splitk_cols = 0;   // wide bf16 compress: columns per part when a row block's columns are shared
     int compress_combine = 0;       // wide bf16 compress, shared columns: 0 choose, 1 added by the last to arrive, 2 by a launch
     int decompress_rows = 0;        // decompress / update: rows per workgroup, a multiple of 32
-    int decompress_vec = -1;        // bf16 decompress: -1 choose, 0 scalar kernel, 1 vector kernel when aligned
+    int decompress_vec = -1;        // bf16 decompress: -1 choose, 0 scalar kernel, 1 vector kernel when aligned, 2 also the
+                                    // kernel for whole lines of bf16 weights whatever the size of the set
     int update_wpolicy = 0;         // update passes: 0 choose; 1 + (bit 0 stream reads of W, bit 1 stream writes)
     int factored_gram = 0;          // factored rule at ranks >= 64: 0 choose; 1 reduction passes over the n x m
                                     // product; 2 quadratic forms in r x r Gram matrices
@@ -583,6 +585,11 @@ void build_decompress_items(Plan& p)
     int vec = rank_bf16(p.r) && (g_tune.decompress_vec != 0);
     for (const MatDev& M : p.host_mats) vec = vec && (M.m % 4) == 0 && M.m <= (1LL << 23);
     p.vec = vec;
+    if (vec) {
+        p.vec = 2;
+        for (const MatDev& M : p.host_mats)
+            if (M.m % 8 != 0) p.vec = 1;
+    }
     const int cols = vec ? kDecompressColsVec : kDecompressCols;
     // (the vector kernel addresses a workgroup's state rows with 32-bit byte offsets)
     const int rows_per_wg = std::min(choose_decompress_rows(p.host_mats, cols, p.r, p.kind == kKindFactored, p.route == Plan::kPasses, p.lean > 0), vec ? (1 << 20) : 0x7fffffe0);
@@ -1312,7 +1319,8 @@ static int run_decompress(Plan* p, const SeedArgs& sa, int r, int mode, int out_
 {
     const MatDev* dm = p->cur_mats;
     const WorkItem* di = p->d_items;
-    if (rank_bf16(r)) FLORA_HIP(launch_decompress_bf16(dm, di, (int)p->items.size(), sa, r, mode, out_bf16, p->vec, dp, s));
+    const int vec = p->vec == 2 && !dp.lines ? 1 : p->vec;
+    if (rank_bf16(r)) FLORA_HIP(launch_decompress_bf16(dm, di, (int)p->items.size(), sa, r, mode, out_bf16, vec, dp, s));
     else FLORA_HIP(launch_decompress_f32(dm, di, (int)p->items.size(), sa, r, mode, out_bf16, dp, s));
     return FLORA_OK;
 }
@@ -1381,10 +1389,12 @@ struct CachePolicy {
     int first = 0;      // the unfactored rule's first pass
     int last = 0;       // the pass that writes the weights
     int reverse = 0;    // ... which takes the table from its end
+    int lines = 0;      // ... whose waves move whole lines of bf16 weights where rows start on 16-byte boundaries
 };
 static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, const flora_update_t* u, int wbf16)
 {
     CachePolicy c;
+    c.lines = g_tune.decompress_vec == 2;
     if (g_tune.update_wpolicy) {
         c.first = c.last = g_tune.update_wpolicy - 1;
         return c;
@@ -1401,10 +1411,27 @@ static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, 
         c.reverse = 1;
         return c;
     }
-    // bf16 weights: a wave's piece of a row is half a 128-byte line, and the two halves meet in the
-    // caches only with plain accesses (GPT-2 XL, 2.8 GiB of bf16 weights: update 1.90 ms plain, 1.91
-    // with streamed writes, 2.04 with both)
-    if (wbf16 || mib <= 192.0) return c;
+    if (wbf16) {
+        // In the kernel that takes bf16 weights of any width a wave's piece of a row is half a 128-byte line, and the
+        // two halves meet in the caches only with plain accesses (GPT-2 XL, 2.8 GiB: update 1.90 ms plain, 2.04
+        // streamed both ways).  The kernel for whole lines regenerates twice the entries of A per lane, so it wants
+        // launches of many rounds; streamed it gains where rows end on line boundaries.  Update in us, that kernel / whole
+        // lines plain / streamed, at r = 64, 128, 256 (MiB of weights):
+        //   GPT-2 base (162)             74 / 73 / 78        71 / 71 / 79        101 / 113 / 107
+        //   40 x 3 of ragged rows (300)  174 / 162 / 169     183 / 160 / 223     232 / 199 / 219
+        //   GPT-2 XL, 24 matrices (352)  183 / 174 / 171     186 / 166 / 158     234 / 210 / 199
+        //   all of it (2812)             1426 / 1393 / 1359  1361 / 1234 / 1170  1689 / 1513 / 1472
+        // and under the factored rule at r = 64 (sums included) 8 matrices of T5-3B (112) 98 / 95 / 98, GPT-2 base
+        // 123 / 113 / 117, ragged rows 271 / 227 / 253, GPT-2 XL 1708 / 1430 / 1343; at higher ranks it gains nothing there.
+        const double own = elems * 2.0 / (1024.0 * 1024.0);
+        if (own >= (u->rule == FLORA_RULE_SGD ? 256.0 : 128.0) && (u->rule == FLORA_RULE_SGD || (u->rule == FLORA_RULE_FACTORED && r == 64)))
+            c.lines = 1;
+        bool whole = !unfactored;
+        for (int l = 0; l < count; ++l) whole = whole && mats[l].m % 64 == 0 && mats[l].m <= (1LL << 23);
+        if (c.lines && whole && own >= 256.0) c.first = c.last = 3;
+        return c;
+    }
+    if (mib <= 192.0) return c;
     c.first = c.last = mib <= (r == 128 ? 400.0 : 300.0) && r != 256 ? 2 : 3;
     return c;
 }
@@ -1434,7 +1461,7 @@ static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16,
     if (st != FLORA_OK || dry) return st;
     const MatDev* dm = p->cur_mats;
     if (u->rule == FLORA_RULE_SGD) {
-        DecompressParams dp{u->alpha, u->lr * u->alpha, 0.f, 0.f, wpolicy.last, 0};
+        DecompressParams dp{u->alpha, u->lr * u->alpha, 0.f, 0.f, wpolicy.last, 0, wpolicy.lines};
         st = run_decompress(p, sa, r, kModeSgd, wbf16, dp, s);
         if (st != FLORA_OK) return st;
     } else {
@@ -1471,6 +1498,7 @@ static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16,
         FLORA_HIP(launch_rms_finalize(dm, count, u->clip_d, scaled ? 1 : 0, u->eps2, gram, s));
         dp.wpolicy = wpolicy.last;
         dp.reverse = wpolicy.reverse;
+        dp.lines = wpolicy.lines;
         st = run_decompress(p, sa, r, factored ? kModeFactored : kModeFull2, wbf16, dp, s);
         if (st != FLORA_OK) return st;
         // the update pass left per-workgroup sums of the new W^2
@@ -1872,8 +1900,8 @@ int flora_set_tuning(const char* name, int value)
         if (!pow2_124 && value != 8 && value != 16 && value != 32) return FLORA_ERR_INVALID;
         g_tune.compress_bf16_mt = value;
     } else if (std::strcmp(name, "decompress_vec") == 0) {
-        if (value < 0 || value > 2) return FLORA_ERR_INVALID;
-        g_tune.decompress_vec = value == 0 ? -1 : value - 1;     // 0 default, 1 scalar, 2 vector
+        if (value < 0 || value > 3) return FLORA_ERR_INVALID;
+        g_tune.decompress_vec = value == 0 ? -1 : value - 1;     // 0 default, 1 scalar, 2 vector, 3 whole lines of bf16
     } else if (std::strcmp(name, "update_wpolicy") == 0) {
         if (value < 0 || value > 4) return FLORA_ERR_INVALID;
         g_tune.update_wpolicy = value;

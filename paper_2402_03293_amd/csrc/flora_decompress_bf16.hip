@@ -540,6 +540,212 @@ __global__ __launch_bounds__(512, (vec_waves<R, MODE, OT>())) void decompress_bf
     }
 }
 
+// ---------------------------------------------------------------------------
+// Variant for the update of bf16 weights whose rows start on 16-byte boundaries (m % 8 == 0), in
+// large sets (see choose_wpolicy): a wave owns 64 columns, so that its piece of a row is a whole 128-byte
+// line again, eight columns (16 bytes) per lane, and the block of the state is read from LDS once per 64
+// columns instead of 32.  Four waves, 256 columns per workgroup: workgroups without a common barrier share a
+// compute unit, and one multiplies while another stores.  The products are taken on
+// v_mfma_f32_32x32x16_bf16 (lane = row of W, 16 registers = 32 of its columns).  What bounds the kernel above on bf16
+// weights is its own instructions and LDS passes per 32 rows, and half-line accesses that cannot be streamed: GPT-2 XL
+// update 1426 / 1361 / 1689 us at r = 64 / 128 / 256, so 1359 / 1170 / 1472 (5.9 GB of weights: 4.3 / 5.0 / 4.0 TB/s).
+template <int R, int MODE, int WP>
+__global__ __launch_bounds__(256, R == 256 ? 2 : 3) void decompress_bf16_line_kernel(const MatDev* __restrict__ mats,
+                                                                                     const WorkItem* __restrict__ items,
+                                                                                     const SeedArgs seeds, DecompressParams p)
+{
+    constexpr int S = R / 16;          // MFMA steps along the rank axis
+    constexpr int LDS_ROW = R + 8;     // padded row (bf16 elements)
+    constexpr int F4 = R / 32;         // float4 loads per thread for one 32 x R block
+    constexpr int PD = R >= 128 ? 2 : 3;         // blocks of old weights in flight or in use
+    constexpr int TROW = 68;           // padded row of a wave's 32 x 64 staging tile (floats)
+    __shared__ __attribute__((aligned(16))) uint16_t ldsS[2][32][LDS_ROW];
+    __shared__ __attribute__((aligned(16))) float ldsT[4][32][TROW];
+    __shared__ __attribute__((aligned(16))) float lds_k[MODE == kModeFactored ? 256 : 4];    // factors of the columns
+    __shared__ float lds_fin[4];
+
+    const WorkItem it = items[blockIdx.x];
+    const MatDev& M = mats[it.mat];
+    const long long n = M.n, m = M.m;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ln = lane & 31, g = lane >> 5;
+    const int er = lane >> 3;                    // epilogue: rows er + 8 pp, pp < 4, of a block, columns c0 .. c0 + 7
+    const uint32_t c0 = (uint32_t)it.col0 + 64u * wave + 8u * (lane & 7);
+    const bool cok = c0 < (uint32_t)m;           // (m % 8 == 0: all eight or none)
+    const float cgen = neg2_ln2_over(R);
+    const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
+    const long long row_end = ((long long)it.row0 + it.rows < n) ? (long long)it.row0 + it.rows : n;
+
+    // Resources end at the last valid row of this workgroup's block: rows past it read as zero and their
+    // stores are dropped.  A resource for each access of a lane, so that all of them take one offset register.
+    auto fetch = [&](v4f (&dst)[F4], long long rb) {
+        const long long bytes = (row_end - rb) * (R * 4);
+        const char* base = reinterpret_cast<const char*>(M.state) + (rb < n ? rb : 0) * (R * 4);
+#pragma unroll
+        for (int i = 0; i < F4; ++i) dst[i] = buf_load_f4(make_rsrc(base + 4096 * i, bytes - 4096 * i), 16u * (uint32_t)tid);
+    };
+    auto stash = [&](const v4f (&src)[F4], int buf) {
+#pragma unroll
+        for (int i = 0; i < F4; ++i) {
+            const int f = tid + 256 * i;
+            const uint2 pk = make_uint2(pack_bf16x2(src[i].x, src[i].y), pack_bf16x2(src[i].z, src[i].w));
+            *reinterpret_cast<uint2*>(&ldsS[buf][f / (R / 4)][4 * (f % (R / 4))]) = pk;
+        }
+    };
+    constexpr bool ld_stream = (WP & 1) != 0, st_stream = (WP & 2) != 0;
+    uint16_t* const weight = reinterpret_cast<uint16_t*>(M.weight);
+    auto wrsrc = [&](long long rb) -> rsrc_t {           // eight rows from rb on
+        long long rows = row_end - rb;
+        rows = rows < 0 ? 0 : (rows > 8 ? 8 : rows);
+        return make_rsrc(weight + (rb < n ? rb : 0) * m, rows * m * 2);
+    };
+    const uint32_t woff = cok ? ((uint32_t)er * (uint32_t)m + c0) * 2u : kOob;
+    struct Pre {
+        v4u w[4];
+    };
+    auto pre_fetch = [&](Pre& pre, long long rb) {
+#pragma unroll
+        for (int pp = 0; pp < 4; ++pp) pre.w[pp] = buf_load_u4<ld_stream>(wrsrc(rb + 8 * pp), woff);
+    };
+
+    v4f stage[F4];
+    Pre pre[PD];                       // blocks rb, rb + 32, ...
+    fetch(stage, it.row0);
+#pragma unroll
+    for (int d = 0; d + 1 < PD; ++d) pre_fetch(pre[d], (long long)it.row0 + 32 * d);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // A operand: this lane's column of both 32-wide tiles, r / 2 entries each.  Generated in a loop, through
+    // lane-private slots in the staging tile: 64 quads in straight-line code would be 32 KB of it.
+    bf16x8 areg[2 * S];                // [2 s + jt]
+    {
+        long long j[2];
+#pragma unroll
+        for (int jt = 0; jt < 2; ++jt) {
+            j[jt] = (long long)it.col0 + 64 * wave + 32 * jt + ln;
+            if (j[jt] > m - 1) j[jt] = m - 1;            // clamped: columns past m are never stored
+        }
+        uint4* const slot = reinterpret_cast<uint4*>(&ldsT[wave][0][0]) + lane;
+        constexpr int CH = 8;                            // slots that the tile holds
+        static_assert(CH * 64 * 16 <= 32 * TROW * 4 && (2 * S) % CH == 0, "slots within the tile");
+#pragma unroll
+        for (int c = 0; c < 2 * S; c += CH) {
+#pragma unroll 1
+            for (int i = 0; i < CH; i += 2) {
+                const uint32_t q = (uint32_t)(2 * (c + i) + 2 * g);
+#pragma unroll
+                for (int jt = 0; jt < 2; ++jt) {
+                    const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)j[jt], q, cgen);
+                    const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)j[jt], q + 1, cgen);
+                    slot[64 * (i + jt)] = make_uint4(pack_bf16x2(z0.z[0], z0.z[1]), pack_bf16x2(z0.z[2], z0.z[3]),
+                                                     pack_bf16x2(z1.z[0], z1.z[1]), pack_bf16x2(z1.z[2], z1.z[3]));
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < CH; ++i) areg[c + i] = __builtin_bit_cast(bf16x8, slot[64 * i]);
+        }
+    }
+
+    float total = 0.f;
+    if (MODE == kModeFactored) {       // one column per thread
+        const float meanR = ldg(M.scal), clip = ldg(M.scal + 1), ps = ldg(M.scal + 2);
+        const long long j = (long long)it.col0 + tid;
+        lds_k[MODE == kModeFactored ? tid : 0] =
+            j < m ? p.coef * p.alpha * clip * ps * sqrtf(meanR) * rsqrtf(ldg(M.col_stat + j)) : 0.f;
+    }
+    stash(stage, 0);
+    __syncthreads();
+
+    int buf = 0;
+    for (long long rb = it.row0; rb < row_end; rb += 32) {
+        fetch(stage, rb + 32);                           // (past the end: nothing is fetched)
+        pre_fetch(pre[PD - 1], rb + 32 * (PD - 1));
+        float rs[4];
+        if (MODE == kModeFactored) {
+#pragma unroll
+            for (int pp = 0; pp < 4; ++pp) {
+                const long long row = rb + er + 8 * pp;
+                rs[pp] = ldg(M.row_stat + (row < n ? row : n - 1));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+
+        f32x16 acc[2];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = 0.f;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&ldsS[buf][ln][16 * s + 8 * g]);
+#pragma unroll
+            for (int jt = 0; jt < 2; ++jt) acc[jt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(areg[2 * s + jt], bv, acc[jt], 0, 0, 0);
+        }
+
+        // acc[jt][4 q + v] = (state A^T)[rb + ln, 64 wave + 32 jt + 8 q + 4 g + v], turned round in the wave's own tile
+#pragma unroll
+        for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4*>(&ldsT[wave][ln][32 * jt + 8 * q + 4 * g]) =
+                    f32x4{acc[jt][4 * q], acc[jt][4 * q + 1], acc[jt][4 * q + 2], acc[jt][4 * q + 3]};
+#pragma unroll
+        for (int pp = 0; pp < 4; ++pp) {
+            const v4f* at = reinterpret_cast<const v4f*>(&ldsT[wave][er + 8 * pp][8 * (lane & 7)]);
+            const v4f lo = at[0], hi = at[1];
+            const float a[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+            float c[8];                // what the gradient is scaled by
+            if (MODE == kModeFactored) {
+                const v4f* k = reinterpret_cast<const v4f*>(&lds_k[MODE == kModeFactored ? 64 * wave + 8 * (lane & 7) : 0]);
+                const float ri = rsqrtf(rs[pp]);
+#pragma unroll
+                for (int h = 0; h < 8; ++h) c[h] = k[h / 4][h % 4] * ri;
+            }
+            v4u out;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const uint32_t w = pre[0].w[pp][h];
+                out[h] = pack_bf16x2(__uint_as_float(w << 16) - (MODE == kModeFactored ? c[2 * h] : p.coef) * a[2 * h],
+                                     __uint_as_float(w & 0xffff0000u) - (MODE == kModeFactored ? c[2 * h + 1] : p.coef) * a[2 * h + 1]);
+                if (MODE == kModeFactored) {
+                    // sum of the new W^2 as stored (rows past the end and columns past m add exact zeros:
+                    // their old weights read as zero, their rows of the state or their factors are zero)
+                    const float w0 = __uint_as_float(out[h] << 16), w1 = __uint_as_float(out[h] & 0xffff0000u);
+                    total = __builtin_fmaf(w0, w0, total);
+                    total = __builtin_fmaf(w1, w1, total);
+                }
+            }
+            buf_store_u4<st_stream>(wrsrc(rb + 8 * pp), woff, out);
+        }
+
+        stash(stage, buf ^ 1);
+#pragma unroll
+        for (int d = 0; d + 1 < PD; ++d) pre[d] = pre[d + 1];
+        __syncthreads();
+        buf ^= 1;
+    }
+
+    if (MODE == kModeFactored) {
+        float t = total;
+#pragma unroll
+        for (int d = 32; d > 0; d /= 2) t += __shfl_xor(t, d);
+        if (lane == 0) lds_fin[wave] = t;
+        __syncthreads();
+        if (tid == 0) M.itempart[it.part] = (lds_fin[0] + lds_fin[1]) + (lds_fin[2] + lds_fin[3]);
+    }
+}
+
+template <int R, int MODE>
+hipError_t launch_line(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, DecompressParams p, hipStream_t s)
+{
+    const dim3 grid((unsigned)nitems), block(256);
+#define FLORA_LINE(WP) hipLaunchKernelGGL((decompress_bf16_line_kernel<R, MODE, WP>), grid, block, 0, s, mats, items, seeds, p)
+    if ((p.wpolicy & 3) == 3) FLORA_LINE(3);
+    else FLORA_LINE(0);
+#undef FLORA_LINE
+    return hipGetLastError();
+}
+
 template <int R, int MODE, typename OT>
 hipError_t launch_vec(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, DecompressParams p,
                       hipStream_t s)
@@ -615,6 +821,11 @@ hipError_t launch_r(const MatDev* mats, const WorkItem* items, int nitems, const
     // modes that read or write the n x m array whose element type the caller chose (out, or W)
     const bool typed = mode == kModeOut || mode == kModeSgd || mode == kModeFactored || mode == kModeFull2;
     if (vec) {
+        if (vec == 2 && out_is_bf16) {
+            if (mode == kModeSgd) return launch_line<R, kModeSgd>(mats, items, nitems, seeds, p, s);
+            if constexpr (R == 64)
+                if (mode == kModeFactored) return launch_line<R, kModeFactored>(mats, items, nitems, seeds, p, s);
+        }
         if (typed && out_is_bf16) return launch_mode_vec<R, uint16_t>(mats, items, nitems, seeds, mode, p, s);
         return launch_mode_vec<R, float>(mats, items, nitems, seeds, mode, p, s);
     }
@@ -624,7 +835,8 @@ hipError_t launch_r(const MatDev* mats, const WorkItem* items, int nitems, const
 
 }  // namespace
 
-// vec: every matrix of the launch has m % 4 == 0 (rows of W / out start on 16-byte boundaries)
+// vec: every matrix of the launch has m % 4 == 0 (fp32 rows of W / out start on 16-byte boundaries); 2: m % 8 == 0
+// (bf16 rows do too)
 hipError_t launch_decompress_bf16(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds,
                                  int r, int mode, int out_is_bf16, int vec, DecompressParams p, hipStream_t s)
 {

@@ -73,6 +73,7 @@ struct DecompressParams {
     int wpolicy;   // update passes: bit 0 weights / second moment read with the non-temporal hint,
                    // bit 1 written with it (chosen from the size of the set, see choose_wpolicy)
     int reverse;   // kModeFull2: workgroups take the table from its end
+    int lines;     // kModeSgd, kModeFactored, bf16 weights: whole lines per wave (see choose_wpolicy)
 };
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
@@ -155,6 +156,12 @@ __device__ __forceinline__ void buf_store_u2(rsrc_t r, uint32_t off, v2u v)
 {
     if (STREAM) __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, 2);
     else __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, 0);
+}
+template <bool STREAM>
+__device__ __forceinline__ void buf_store_u4(rsrc_t r, uint32_t off, v4u v)
+{
+    if (STREAM) __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, 2);
+    else __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, 0);
 }
 __device__ __forceinline__ float buf_load_f(rsrc_t r, uint32_t off)
 {

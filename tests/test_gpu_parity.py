@@ -657,6 +657,41 @@ def test_apply_update_factored(n, m, r, clip_d, beta2):
     assert rel_fro(to64(W) - to64(W0), Wr - to64(W0)) < update_bar(r, Wr, to64(W0))
 
 
+# the update kernel for whole lines of bf16 weights: edges of its 32-row blocks and 64-column waves, one and several
+# workgroups per row, one and several row blocks.  The result is rounded to bf16 (2^-9 of a value at most).
+@pytest.mark.parametrize("rows", [0, 64])
+@pytest.mark.parametrize("n,m,r", [(33, 8, 64), (300, 520, 64), (257, 264, 128), (96, 1096, 128), (65, 72, 256), (200, 1024, 256)])
+def test_update_of_whole_bf16_lines(n, m, r, rows):
+    seed = 7100 + n + r
+    S = rand((n, r), seed)
+    W0 = rand((n, m), seed + 1).to(torch.bfloat16)
+    R0 = (rand((n,), seed + 2).abs() + 0.1).contiguous()
+    K0 = (rand((m,), seed + 3).abs() + 0.1).contiguous()
+    lr, alpha, eps1, beta2, clip_d = 0.5, 0.5, 1e-30, 0.8, 0.3
+    guard = torch.full((n + 2, m), 7.0, device=DEV, dtype=torch.bfloat16)
+    Ws, Wf, R, K = guard[1:n + 1], W0.clone(), R0.clone(), K0.clone()
+    Ws.copy_(W0)
+    ss = torch.zeros(4, device=DEV)
+    flora.set_tuning("decompress_vec", 3)
+    flora.set_tuning("decompress_rows", rows)
+    try:
+        flora.apply_update(flora.matrices([(n, m)], weights=[Ws], states=[S], seeds=[seed]), r, flora.BF16,
+                           flora.sgd_update(lr, alpha))
+        flora.apply_update(flora.matrices([(n, m)], weights=[Wf], states=[S], row_stats=[R], col_stats=[K],
+                                          seeds=[seed], weight_sumsqs=[ss]), r, flora.BF16,
+                           flora.factored_update(lr, alpha, beta2, eps1, clip_d))
+        sync()
+    finally:
+        flora.set_tuning("decompress_vec", 0)
+        flora.set_tuning("decompress_rows", 0)
+    Gt = oracle.decompress(to64(S), m, seed, alpha=alpha)
+    assert rel_fro(to64(Ws), oracle.sgd(to64(W0), Gt, lr)) < TOL_BF16 + 2.0 ** -9
+    assert float((guard[0] - 7).abs().max()) == 0 and float((guard[-1] - 7).abs().max()) == 0
+    Wr, _, _ = oracle.factored_update(to64(W0), Gt, to64(R0), to64(K0), beta2, eps1, clip_d, lr)
+    assert rel_fro(to64(Wf), Wr) < TOL_BF16 + 2.0 ** -9
+    assert float(ss[0]) == pytest.approx(float((to64(Wf) ** 2).sum()), rel=1e-5)
+
+
 # both bf16 decompress kernels (4-byte and 16-byte accesses per lane), with one and with several
 # row blocks per matrix (which changes how the column statistics are combined), every mode
 @pytest.mark.parametrize("vec", [1, 2])
