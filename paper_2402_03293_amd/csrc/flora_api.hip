@@ -1770,7 +1770,7 @@ int64_t flora_debug_work_items(int kind, const flora_matrix_t* mats, int count, 
     }
     const std::vector<WorkItem>& items = (kind == 2) ? p.items2 : p.items;
     if (info) {
-        info[0] = p.mt; info[1] = p.vec; info[2] = p.kc;
+        info[0] = p.mt; info[1] = p.vec != 0; info[2] = p.kc;
         info[3] = (int64_t)p.ws_floats; info[4] = (int64_t)p.ws_counters;
     }
     if (out)
