@@ -697,8 +697,8 @@ void build_gram_items(Plan& p)
 {
     // Pieces of the long index: the largest that still give the chip 384 workgroups (the sums of a launch
     // over a few matrices otherwise run on a workgroup per matrix: 16 GPT-2 base matrices at r = 128, the
-    // two Gram kernels 45 + 73 us in pieces of 3072), as far as memory allows: a piece holds r^2 floats,
-    // and all of them no more than pieces of 3072 and the partial sums that the passes would leave
+    // two Gram kernels 45 + 73 us in pieces of 3072), as far as memory allows: a piece holds r^2 floats at
+    // r = 64 and the upper triangle's tiles above, and all of them no more than whole r x r pieces of 3072 and the partial sums that the passes would leave
     // (24 matrices of T5-3B at r = 256, whose state is 96 MiB: 52 MiB; without the limit 473), or than the
     // state itself up to 32 MiB (not in a lean plan, see Arena).
     auto pieces = [&](bool rows, long long most, long long least) {
@@ -729,7 +729,7 @@ void build_gram_items(Plan& p)
         size_t need = sizeof(WorkItem) * p.items.size(), by_m = 0, by_n = 0;
         for (const MatDev& M : p.host_mats) {
             const size_t gm = pieces_of(M.m, chunk_m), gn = pieces_of(M.n, chunk_n);
-            need += std::max(2 * gm, gn) * rr + 1024 +         // (1024: padding, and partial sums of workgroups)
+            need += std::max(2 * gm, gn) * gram_piece_floats(p.r) * 4 + 1024 +         // (1024: padding, and partial sums of workgroups)
                     sizeof(WorkItem) * (gm + gn + pieces_of(M.n, kQuadformRows) + pieces_of(M.m, cols) + 2 * pieces_of(M.n, 128));
             by_m += 2 * gm; by_n += gn;
         }
@@ -793,7 +793,7 @@ AdafactorShare adafactor_share(const MatDev& M, Plan::Route route, int r)
     a.item = round_up((size_t)std::max(M.nitems, M.item0) * 4, 256);
     if (route == Plan::kGram) {
         a.bf16 = round_up((size_t)r * r * 2, 256);
-        a.pieces = round_up((size_t)std::max(2 * M.gchunks_m, M.gchunks_n) * r * r * 4, 256);
+        a.pieces = round_up((size_t)std::max(2 * M.gchunks_m, M.gchunks_n) * gram_piece_floats(r) * 4, 256);
         a.row = round_up((size_t)M.item0 * 4, 256);
     } else if (route == Plan::kPasses) {
         a.row = round_up((size_t)M.ncolchunks * M.n * 4, 256);

@@ -210,8 +210,7 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
 // 16 waves, so that four share a SIMD and one wave's generator chains run in the shadow of the
 // others'; v_mfma_f32_32x32x16_bf16 tiles; only the tiles on or above the diagonal of the
 // symmetric results are computed (36 of 64 at r = 256), consecutive ones to a wave (they mostly
-// share an operand), every SIMD multiplying the same number of them; a tile off the diagonal is
-// also stored as its mirror image.
+// share an operand), every SIMD multiplying the same number of them, and only they are stored.
 // MODE 0: P alone (no clipping asked for); 1: P and P'; 2: Q = S^T S, the tiles being rows of the
 // state, fetched one tile ahead and rounded to bf16 on their way into LDS.
 template <int R>
@@ -234,12 +233,9 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
     static_assert(R >= 128, "ranks 128 and 256");
     typedef UpperTiles<R> UT;
     constexpr int TW = (UT::COUNT + WAVES - 1) / WAVES;   // tiles per wave
-    constexpr int OWNERS = UT::COUNT < WAVES ? UT::COUNT : WAVES;
     constexpr bool PAIR = MODE == 1;
     constexpr int NC = PAIR ? 2 : 1;                       // copies of a tile: plain, scaled
-    constexpr size_t kTileBytes = sizeof(uint16_t) * 2 * NC * R * kGLd, kTurnBytes = sizeof(float) * OWNERS * 32 * 33;
-    __shared__ __attribute__((aligned(16))) unsigned char lds_raw[kTileBytes > kTurnBytes ? kTileBytes : kTurnBytes];
-    uint16_t (*ldsX)[NC][R][kGLd] = reinterpret_cast<uint16_t (*)[NC][R][kGLd]>(lds_raw);   // [buffer][copy][k][t]
+    __shared__ __attribute__((aligned(16))) uint16_t ldsX[2][NC][R][kGLd];                 // [buffer][copy][k][t]
 
     const WorkItem it = items[blockIdx.x];
     const MatDev& M = mats[it.mat];
@@ -386,38 +382,25 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
         __syncthreads();
     }
 
-    // D layout of a 32 x 32 tile: lane holds column ln and rows 8 (v / 4) + 4 g + v % 4.  A tile off
-    // the diagonal is also stored as its mirror image, turned round in a piece of LDS that belongs
-    // to the wave alone (the tiles of X are done with), so that both stores write whole lines.
-    float* turn = reinterpret_cast<float*>(lds_raw) + wave * (32 * 33);     // (only waves that own tiles touch it)
+    // D layout of a 32 x 32 tile: lane holds column ln and rows 8 (v / 4) + 4 g + v % 4.  A partial is the tiles of
+    // the upper triangle one after another, 4 KB each.
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         // (partials: those of P over chunks of m, then those of P'; or those of Q over chunks of n, combined before)
         const int part0 = c ? M.gchunks_m : 0;
-        float* part = M.grampart + (size_t)(part0 + it.part) * R * R;
+        float* part = M.grampart + (size_t)(part0 + it.part) * gram_piece_floats(R);
 #pragma unroll
-        for (int w = 0; w < TW; ++w) {
+        for (int w = 0; w < TW; ++w)
             if (own[w]) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int k1 = 8 * (v / 4) + 4 * g + (v % 4);
-                    stg(part + (32 * ti[w] + k1) * R + 32 * tj[w] + ln, acc[c][w][v]);
-                    if (ti[w] != tj[w]) turn[ln * 33 + k1] = acc[c][w][v];
-                }
-                if (ti[w] != tj[w]) {
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) {
-                        const int k2 = 2 * v + g;                       // row of the mirror image; ln runs along it
-                        stg(part + (32 * tj[w] + k2) * R + 32 * ti[w] + ln, turn[k2 * 33 + ln]);
-                    }
-                }
+                for (int v = 0; v < 16; ++v) stg(part + (wave + WAVES * w) * 1024 + (8 * (v / 4) + 4 * g + (v % 4)) * 32 + ln, acc[c][w][v]);
             }
-        }
     }
 }
 
 // B <- sum over the chunks of their partials, in chunk order; stored as bf16 with the columns of
-// every 32-block in the order the quadratic-form kernels contract them.  which 0: P (chunks of m), 1: Q
+// every 32-block in the order the quadratic-form kernels contract them (rank 64: both partials and results are
+// whole).  which 0: P (chunks of m), 1: Q
 // (chunks of n), 2: P' (chunks of m; it is kept right behind Q); 0 and 2 together as blockIdx.z = 0, 1
 template <int R>
 __global__ __launch_bounds__(256) void combine_gram_kernel(const MatDev* __restrict__ mats, int first)
@@ -441,10 +424,53 @@ __global__ __launch_bounds__(256) void combine_gram_kernel(const MatDev* __restr
     for (; c < nch; ++c) s += ldg4(src + (size_t)c * R * R);
     uint16_t* B = which == 0 ? M.gramP : (which == 1 ? M.gramQ : M.gramQ + R * R);
     const int k2 = idx / R, k1 = idx % R;                       // k1 % 4 == 0: the four stay together
-    // (Q at ranks >= 128 is read by quadform_cols_kernel, everything else in the other order)
-    const int pos = (k1 & ~31) + ((which == 1 && R >= 128) ? perm32w(k1 & 31) : perm32(k1 & 31));
+    const int pos = (k1 & ~31) + perm32(k1 & 31);
     const v2u pk = {pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w)};
     *reinterpret_cast<FLORA_GLOBAL v2u*>((FLORA_GLOBAL uint16_t*)(B + k2 * R + pos)) = pk;
+}
+
+// The same from partials that hold the tiles of the upper triangle (0.56 of the matrix at r = 256, 0.63 at r = 128: less
+// traffic, 384 T5-3B matrices' factored update 6139 -> 6045 us, and more pieces in the same memory, the pair kernel on
+// one 1600 x 6400 matrix at r = 256 124 -> 72, on 16 GPT-2 base matrices at r = 128 23 -> 14): a tile per workgroup,
+// written to both of its places.
+template <int R>
+__global__ __launch_bounds__(256) void combine_gram_tiles_kernel(const MatDev* __restrict__ mats, int first)
+{
+    __shared__ float turn[32][33];
+    const MatDev& M = mats[blockIdx.y];
+    const int which = first + 2 * (int)blockIdx.z;
+    const int nch = which == 1 ? M.gchunks_n : M.gchunks_m;
+    const int part0 = which == 2 ? M.gchunks_m : 0;
+    constexpr size_t kPiece = gram_piece_floats(R);
+    const int row = threadIdx.x / 8, col = 4 * (threadIdx.x % 8);
+    const float* src = M.grampart + (size_t)part0 * kPiece + (size_t)blockIdx.x * 1024 + row * 32 + col;
+    v4f s = {0.f, 0.f, 0.f, 0.f};
+    int c = 0;
+    for (; c + 8 <= nch; c += 8) {                              // eight loads in flight
+        v4f p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p[e] = ldg4(src + (size_t)(c + e) * kPiece);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += p[e];
+    }
+    for (; c < nch; ++c) s += ldg4(src + (size_t)c * kPiece);
+    uint16_t* B = which == 0 ? M.gramP : (which == 1 ? M.gramQ : M.gramQ + R * R);
+    int ti, tj;
+    UpperTiles<R>::at(blockIdx.x, ti, tj);
+    // (Q is read by quadform_cols_kernel, the others in the other order; four consecutive entries stay together)
+    auto put = [&](int k2, int k1, v4f x) {
+        const int pos = (k1 & ~31) + (which == 1 ? perm32w(k1 & 31) : perm32(k1 & 31));
+        *reinterpret_cast<FLORA_GLOBAL v2u*>((FLORA_GLOBAL uint16_t*)(B + k2 * R + pos)) =
+            v2u{pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w)};
+    };
+    put(32 * ti + row, 32 * tj + col, s);
+    if (ti == tj) return;
+    turn[row][col] = s.x;
+    turn[row][col + 1] = s.y;
+    turn[row][col + 2] = s.z;
+    turn[row][col + 3] = s.w;
+    __syncthreads();
+    put(32 * tj + row, 32 * ti + col, v4f{turn[col][row], turn[col + 1][row], turn[col + 2][row], turn[col + 3][row]});
 }
 
 // q_i = Z_i B Z_i^T for 16 ZT rows of Z held in operand registers, rows [16 CT0, 16 (CT0 + NCT)) of B in LDS:
@@ -742,7 +768,7 @@ template <int R>
 hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, int count, const SeedArgs& seeds, int src,
                          hipStream_t s)
 {
-    const dim3 grid((unsigned)nitems), block(512), cgrid((unsigned)(R * R / 1024), (unsigned)count);
+    const dim3 grid((unsigned)nitems), block(512);
     bool p = false, q = false, p2 = false;               // which sums this launch produces
     if constexpr (R >= 128) {
         constexpr int PW = R >= 256 ? 8 : 16;           // waves that can hold both sets of accumulators
@@ -755,8 +781,9 @@ hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, 
         if (src == 2) { hipLaunchKernelGGL((gram_kernel<R, 2>), grid, block, 0, s, mats, items, seeds); q = true; }
     }
     if (!p && !q && !p2) return hipErrorInvalidValue;
-    if (p) hipLaunchKernelGGL((combine_gram_kernel<R>), dim3(cgrid.x, cgrid.y, p2 ? 2 : 1), dim3(256), 0, s, mats, 0);
-    if (q) hipLaunchKernelGGL((combine_gram_kernel<R>), cgrid, dim3(256), 0, s, mats, 1);
+    const dim3 cgrid(R >= 128 ? (unsigned)UpperTiles<R>::COUNT : (unsigned)(R * R / 1024), (unsigned)count, p2 ? 2 : 1);
+    if constexpr (R >= 128) hipLaunchKernelGGL((combine_gram_tiles_kernel<R>), cgrid, dim3(256), 0, s, mats, q ? 1 : 0);
+    else hipLaunchKernelGGL((combine_gram_kernel<R>), cgrid, dim3(256), 0, s, mats, q ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -23,7 +23,7 @@ struct MatDev {
     float* scal;        // [4]: mean(R), clip scale, parameter scale max(eps2, RMS(W)) or 1, spare (workspace)
     uint16_t* gramP;    // r x r bf16: A^T A, later A^T diag(1/K) A (factored rule through Gram matrices; workspace)
     uint16_t* gramQ;    // r x r bf16: S^T S (workspace)
-    float* grampart;    // [chunks][r][r] partial Gram matrices of the chunks of n, then of m twice (workspace)
+    float* grampart;    // [chunks][gram_piece_floats(r)] partial Gram matrices of the chunks of n, then of m twice (workspace)
     long long n, m;
     uint32_t seed_lo, seed_hi, seedn_lo, seedn_hi;   // used by the transfer kernels only
     int ncolchunks, nrowblocks;   // decompress tiling of this matrix
@@ -262,6 +262,11 @@ constexpr int kApplyTRowsBig = 64;       // ... ranks 64 and above
 constexpr int kTransferChunk = 1024;     // columns per workgroup of the T kernel, ranks 64 and above
 constexpr int kSumsqBlocks = 256;        // workgroups per matrix, sum of W^2
 constexpr int kGramChunk = 3072;         // long-index entries per workgroup of the Gram sums, at most
+// Floats of a partial Gram matrix: at ranks >= 128 the 32 x 32 tiles on and above the diagonal.
+constexpr __host__ __device__ size_t gram_piece_floats(int r)
+{
+    return r >= 128 ? (size_t)(r / 32) * (r / 32 + 1) / 2 * 1024 : (size_t)r * r;
+}
 constexpr int kQuadformRows = 256;       // rows of S per workgroup of the quadratic forms
 constexpr int kQuadformCols = 1024;      // rows of A per workgroup of the column statistics, at most
 
