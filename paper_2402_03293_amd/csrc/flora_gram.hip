@@ -398,6 +398,158 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
     }
 }
 
+// P (and P') of a launch with few chunks: a workgroup makes the tiles of one pair of blocks of SB ranks, regenerating those
+// ranks only, where gram_sym_kernel would leave most compute units idle beside a chain of up to 48 whole tiles of A.
+// (Blocks take no memory; shorter chunks would.)  16 waves in groups of SB / 16 that take every KG-th tile of
+// the chunk each and whose sums are added in the groups' order.  A block pair generates SB or 2 SB ranks: with SB =
+// 32 / 64 the entries of A are made 9 / 4.8 times at r = 256, 4.8 times with 32 at r = 128.  Blocks of 32 pay while every
+// pair has a compute unit of its own, those of 64 at r = 256 up to two rounds of them.  Factored update, us with whole matrices / blocks of
+// 64 / of 32, by chunks: r = 256 2 chunks 176 / 126 / 109, 5 173 / 132 / 120, 8 187 / 138 / 139, 16 201 / 153 / 170, 24
+// 220 / 171 / 208, 36 207 / 198 / 235, 48 300 / 287 / 345, 88 362 / 393 / 469; r = 128 4 chunks 68 / 67 / 61, 16 78 / 76 / 71, 18 69 /
+// 70 / 64, 32 101 / 99 / 106, 64 123 / 121 / 139, 96 150 / 163 / 175.
+template <int R, int SB, bool PAIR>
+__global__ __launch_bounds__(1024) void gram_block_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items,
+                                                          const SeedArgs seeds)
+{
+    typedef UpperTiles<R> UT;
+    constexpr int GW = SB / 16, KG = 16 / GW, GT = 64 * GW;      // waves of a group, groups, threads of a group
+    constexpr int NB = R / SB, PAIRS = NB * (NB + 1) / 2;        // consecutive workgroups of a chunk
+    constexpr int SBT = SB / 32;                                 // 32-wide tiles of a block each way
+    constexpr bool SPLIT = SB == 32;                             // one tile: wave 0 makes P's, wave 1 P''s
+    constexpr int TW = SPLIT ? 1 : SBT * SBT / GW;               // tiles per wave
+    constexpr int NC = PAIR ? 2 : 1;                             // results
+    constexpr int NA = SPLIT ? 1 : NC;                           // of them in a wave
+    constexpr int ROWS = (2 + (PAIR ? 1 : 0)) * SB;              // first block, second block, second block scaled
+    constexpr int NQ = 8;                                        // quads per thread and tile
+    static_assert(kGT / NQ * (2 * SB / 4) == GT, "a quad of ranks and eight entries per thread");
+    static_assert((KG - 1) * SB * SB * 4 * (SPLIT ? NC : 1) <= KG * ROWS * kGLd * 2, "a result's sums take the place of the tiles");
+    __shared__ __attribute__((aligned(16))) uint16_t lds[KG][ROWS][kGLd];
+
+    const WorkItem it = items[blockIdx.x / PAIRS];
+    const MatDev& M = mats[it.mat];
+    int bi = 0, c = (int)(blockIdx.x % PAIRS);
+    while (c >= NB - bi) { c -= NB - bi; ++bi; }
+    const int bj = bi + c;
+    const bool diag = bi == bj;
+    const int kg = __builtin_amdgcn_readfirstlane((int)threadIdx.x / GT);
+    const int tid = (int)threadIdx.x % GT;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ln = lane & 31, g = lane >> 5;
+    const long long t0 = it.col0, t1 = it.col1;
+    const int ntiles = (int)((t1 - t0 + KG * kGT - 1) / (KG * kGT));         // of each group (zeros beyond the chunk)
+
+    const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
+    const float cgen = neg2_ln2_over(R);
+    const int gen_j = NQ * (tid % (kGT / NQ)), q = tid / (kGT / NQ);         // LDS rows 4 q .. 4 q + 3
+    const bool second = q >= SB / 4;                                         // (a pair on the diagonal needs one block)
+    const bool gen = !(diag && second);
+    const uint32_t gen_q = (uint32_t)(second ? bj * (SB / 4) + q - SB / 4 : bi * (SB / 4) + q);
+    const bool scaled = PAIR && (second || diag);
+    uint32_t pk[NC][NQ / 2][4];
+    auto produce = [&](int tile) {
+        const long long j = t0 + (long long)(tile * KG + kg) * kGT + gen_j;
+        float wt[NQ];
+#pragma unroll
+        for (int e = 0; e < NQ; ++e) {
+            wt[e] = 1.f;
+            if (PAIR) wt[e] = ldg(M.col_stat + ((j + e < t1) ? j + e : t1 - 1));
+        }
+#pragma unroll
+        for (int e = 0; e < NQ; e += 2) {
+            const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)(j + e), gen_q, cgen);
+            const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)(j + e + 1), gen_q, cgen);
+            const float m0 = (j + e < t1) ? 1.f : 0.f, m1 = (j + e + 1 < t1) ? 1.f : 0.f;
+            const float w0 = m0 * __builtin_amdgcn_rcpf(wt[e]), w1 = m1 * __builtin_amdgcn_rcpf(wt[e + 1]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                pk[0][e / 2][i] = pack_bf16x2(m0 * z0.z[i], m1 * z1.z[i]);
+                if (PAIR) pk[NC - 1][e / 2][i] = pack_bf16x2(w0 * z0.z[i], w1 * z1.z[i]);
+            }
+        }
+    };
+    auto stash = [&]() {
+        if (!gen) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            *reinterpret_cast<v4u*>(&lds[kg][4 * q + i][gen_j]) = v4u{pk[0][0][i], pk[0][1][i], pk[0][2][i], pk[0][3][i]};
+            if (scaled)
+                *reinterpret_cast<v4u*>(&lds[kg][PAIR ? (diag ? 2 * SB : SB) + 4 * q + i : 0][gen_j]) =
+                    v4u{pk[NC - 1][0][i], pk[NC - 1][1][i], pk[NC - 1][2][i], pk[NC - 1][3][i]};
+        }
+    };
+
+    f32x16 acc[NA][TW];
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int w = 0; w < TW; ++w)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][w][v] = 0.f;
+    const int brow = diag ? 0 : SB;                // second operand, plain (its scaled rows start at 2 SB)
+
+    if (gen) produce(0);
+    stash();
+    __syncthreads();
+    for (int tile = 0; tile < ntiles; ++tile) {
+#pragma unroll
+        for (int s = 0; s < kGT / 16; ++s)
+#pragma unroll
+            for (int w = 0; w < TW; ++w) {
+                const int ra = SPLIT ? 0 : (wave * TW + w) / SBT, cb = SPLIT ? 0 : (wave * TW + w) % SBT;
+                const int k = 16 * s + 8 * g;
+                const bf16x8 av = *reinterpret_cast<const bf16x8*>(&lds[kg][32 * ra + ln][k]);
+                const int b0 = SPLIT && PAIR && wave == 1 ? 2 * SB : brow;
+                const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&lds[kg][b0 + 32 * cb + ln][k]);
+                acc[0][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[0][w], 0, 0, 0);
+                if (NA == 2) {
+                    const bf16x8 bs = *reinterpret_cast<const bf16x8*>(&lds[kg][(PAIR ? 2 * SB : 0) + 32 * cb + ln][k]);
+                    acc[NA - 1][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bs, acc[NA - 1][w], 0, 0, 0);
+                }
+            }
+        const bool more = tile + 1 < ntiles;
+        if (more && gen) produce(tile + 1);
+        __syncthreads();
+        if (more) {
+            stash();
+            __syncthreads();
+        }
+    }
+
+    // the groups' sums, one result after the other, then the tiles on and above the diagonal
+    float* const sums = reinterpret_cast<float*>(lds);
+    constexpr int kWave = TW * 1024;               // floats of a wave and result
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+        if (a > 0) __syncthreads();
+        if (kg > 0 && wave * kWave < (SPLIT ? NC : 1) * SB * SB) {
+#pragma unroll
+            for (int w = 0; w < TW; ++w)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    sums[((kg - 1) * (SPLIT ? NC : GW) + wave) * kWave + (w * 16 + v) * 64 + lane] = acc[a][w][v];
+        }
+        __syncthreads();
+        if (kg == 0 && !(SPLIT && wave >= NC)) {
+            const int which = SPLIT ? wave : a;
+            float* part = M.grampart + (size_t)((which ? M.gchunks_m : 0) + it.part) * gram_piece_floats(R);
+#pragma unroll
+            for (int w = 0; w < TW; ++w) {
+#pragma unroll
+                for (int k = 1; k < KG; ++k)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v)
+                        acc[a][w][v] += sums[((k - 1) * (SPLIT ? NC : GW) + wave) * kWave + (w * 16 + v) * 64 + lane];
+                const int ti = bi * SBT + (SPLIT ? 0 : (wave * TW + w) / SBT), tj = bj * SBT + (SPLIT ? 0 : (wave * TW + w) % SBT);
+                if (ti > tj) continue;
+                const int idx = ti * UT::NT - ti * (ti - 1) / 2 + tj - ti;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) stg(part + idx * 1024 + (8 * (v / 4) + 4 * g + (v % 4)) * 32 + ln, acc[a][w][v]);
+            }
+        }
+    }
+}
+
 // B <- sum over the chunks of their partials, in chunk order; stored as bf16 with the columns of
 // every 32-block in the order the quadratic-form kernels contract them (rank 64: both partials and results are
 // whole).  which 0: P (chunks of m), 1: Q
@@ -772,8 +924,21 @@ hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, 
     bool p = false, q = false, p2 = false;               // which sums this launch produces
     if constexpr (R >= 128) {
         constexpr int PW = R >= 256 ? 8 : 16;           // waves that can hold both sets of accumulators
-        if (src == 0) { hipLaunchKernelGGL((gram_sym_kernel<R, 0, 16>), grid, dim3(1024), 0, s, mats, items, seeds); p = true; }
-        if (src == 3) { hipLaunchKernelGGL((gram_sym_kernel<R, 1, PW>), grid, dim3(64 * PW), 0, s, mats, items, seeds); p = p2 = true; }
+#define FLORA_GRAM_BLOCKS(SB)                                                                                                     \
+    do {                                                                                                                          \
+        const dim3 bgrid((unsigned)(nitems * (R / SB) * (R / SB + 1) / 2));                                                       \
+        if (src == 0) hipLaunchKernelGGL((gram_block_kernel<R, SB, false>), bgrid, dim3(1024), 0, s, mats, items, seeds);         \
+        else hipLaunchKernelGGL((gram_block_kernel<R, SB, true>), bgrid, dim3(1024), 0, s, mats, items, seeds);                   \
+    } while (0)
+        if (src == 0 || src == 3) {
+            p = true;
+            p2 = src == 3;
+            if (nitems <= (R == 256 ? 7 : 25)) FLORA_GRAM_BLOCKS(32);
+            else if (R == 256 && nitems <= 48) FLORA_GRAM_BLOCKS((R == 256 ? 64 : 32));
+            else if (src == 0) hipLaunchKernelGGL((gram_sym_kernel<R, 0, 16>), grid, dim3(1024), 0, s, mats, items, seeds);
+            else hipLaunchKernelGGL((gram_sym_kernel<R, 1, PW>), grid, dim3(64 * PW), 0, s, mats, items, seeds);
+        }
+#undef FLORA_GRAM_BLOCKS
         if (src == 2) { hipLaunchKernelGGL((gram_sym_kernel<R, 2, 16>), grid, dim3(1024), 0, s, mats, items, seeds); q = true; }
     } else {
         if (src == 0 || src == 3) { hipLaunchKernelGGL((gram_kernel<R, 0>), grid, block, 0, s, mats, items, seeds); p = true; }

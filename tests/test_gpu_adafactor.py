@@ -483,6 +483,18 @@ def test_factored_rule_through_gram_matrices_in_large_pieces(r, clip_d, beta2):
         flora.set_tuning("gram_chunk", 0)
 
 
+# ... and in pieces whose number puts P and P' on blocks of 32 ranks (up to 25 pieces at r = 128, 7 at r = 256), of 64 (up to
+# 48 at r = 256), and on whole matrices: pieces that end within a tile, within a round of the groups' tiles, and of one tile
+@pytest.mark.parametrize("r,chunk", [(128, 512), (128, 1216), (128, 320), (256, 576), (256, 768), (256, 256), (256, 192)])
+@pytest.mark.parametrize("clip_d,beta2", [(1.0, 0.0), (0.0, 0.6)])
+def test_factored_rule_through_blocks_of_gram_matrices(r, chunk, clip_d, beta2):
+    flora.set_tuning("gram_chunk", chunk)
+    try:
+        test_factored_rule_through_gram_matrices(r, clip_d, beta2)
+    finally:
+        flora.set_tuning("gram_chunk", 0)
+
+
 # Column statistics in blocks of 1024 columns: a set with 384 such blocks (several rounds of rows of A per workgroup,
 # the last of a matrix short)
 @pytest.mark.parametrize("r", [64, 128, 256])
