@@ -119,6 +119,7 @@ struct Plan {
     enum Route { kNoSums, kPasses, kGram };
     Route route = kNoSums;
     int n_gm = 0, n_gn = 0, n_qr = 0, n_qc = 0;
+    int qr_rows = kQuadformRows, qc_rows = kQuadformCols;      // rows per workgroup of the two quadratic forms, at most
 };
 
 // Caller-owned workspace (flora_set_workspace).  While one is set every device buffer of a plan
@@ -711,7 +712,21 @@ void build_gram_items(Plan& p)
     };
     long long chunk_m = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(false, kGramChunk, 192);
     long long chunk_n = g_tune.gram_chunk ? g_tune.gram_chunk : pieces(true, kGramChunk, 192);
-    const long long cols = pieces(false, kQuadformCols, p.r >= 128 ? 512 : 256);
+    // Rows of A and of S per workgroup of the quadratic forms: as few as leave no workgroup waiting for a compute
+    // unit, 128 at least at ranks >= 128.  Factored update, us with 512 rows of A and 256 of S / so: one 768 x 3072 matrix at r =
+    // 256 108 / 92, one 1600 x 6400 121 / 104, sixteen 768 x 3072 211 / 194, GPT-2 XL's 16 (256 and 128 rows) 363 / 356; r = 128 61 /
+    // 55, 70 / 62, 121 / 116, and four GPT-2 base blocks 97 / 90.
+    auto fewest = [&](bool rows, long long c) {
+        for (; p.r >= 128 && c > 128; c /= 2) {
+            long long wgs = 0;
+            for (const MatDev& M : p.host_mats) wgs += ((rows ? M.n : M.m) + c / 2 - 1) / (c / 2);
+            if (wgs > 256) break;
+        }
+        return c;
+    };
+    const long long cols = fewest(false, pieces(false, kQuadformCols, p.r >= 128 ? 512 : 256));
+    p.qc_rows = (int)cols;
+    p.qr_rows = (int)fewest(true, kQuadformRows);
     // (work tables included: smaller pieces, and workgroups of fewer rows here and in the compress launch, are more
     // entries)
     const size_t rr = (size_t)p.r * p.r * 4;
@@ -730,7 +745,7 @@ void build_gram_items(Plan& p)
         for (const MatDev& M : p.host_mats) {
             const size_t gm = pieces_of(M.m, chunk_m), gn = pieces_of(M.n, chunk_n);
             need += std::max(2 * gm, gn) * gram_piece_floats(p.r) * 4 + 1024 +         // (1024: padding, and partial sums of workgroups)
-                    sizeof(WorkItem) * (gm + gn + pieces_of(M.n, kQuadformRows) + pieces_of(M.m, cols) + 2 * pieces_of(M.n, 128));
+                    sizeof(WorkItem) * (gm + gn + pieces_of(M.n, p.qr_rows) + pieces_of(M.m, cols) + 2 * pieces_of(M.n, 128));
             by_m += 2 * gm; by_n += gn;
         }
         if (need <= limit) break;
@@ -775,7 +790,7 @@ void build_gram_items(Plan& p)
     p.n_gm = (int)(p.items2.size() - before); before = p.items2.size();
     for (int l : by_n) emit_chunks(l, p.host_mats[(size_t)l].n, p.host_mats[(size_t)l].gchunks_n);
     p.n_gn = (int)(p.items2.size() - before); before = p.items2.size();
-    for (int l : by_n) p.host_mats[(size_t)l].item0 = emit_blocks(l, p.host_mats[(size_t)l].n, kQuadformRows);
+    for (int l : by_n) p.host_mats[(size_t)l].item0 = emit_blocks(l, p.host_mats[(size_t)l].n, p.qr_rows);
     p.n_qr = (int)(p.items2.size() - before); before = p.items2.size();
     for (int l : by_m) (void)emit_blocks(l, p.host_mats[(size_t)l].m, cols);
     p.n_qc = (int)(p.items2.size() - before);
@@ -1478,9 +1493,9 @@ static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16,
             // regeneration of A then yields both A^T A and A^T diag(1 / K) A
             const bool clip = u->clip_d > 0.f;
             FLORA_HIP(launch_gram(dm, gn, p->n_gn, count, sa, r, 2, s));
-            FLORA_HIP(launch_quadform(dm, qc, p->n_qc, sa, r, 1, u->alpha, u->beta2, u->eps1, s));
+            FLORA_HIP(launch_quadform(dm, qc, p->n_qc, p->qc_rows, sa, r, 1, u->alpha, u->beta2, u->eps1, s));
             FLORA_HIP(launch_gram(dm, gm, p->n_gm, count, sa, r, clip ? 3 : 0, s));
-            FLORA_HIP(launch_quadform(dm, qr, p->n_qr, sa, r, clip ? 2 : 0, u->alpha, u->beta2, u->eps1, s));
+            FLORA_HIP(launch_quadform(dm, qr, p->n_qr, p->qr_rows, sa, r, clip ? 2 : 0, u->alpha, u->beta2, u->eps1, s));
         } else if (factored) {
             st = run_decompress(p, sa, r, kModeStats, 0, dp, s);
             if (st != FLORA_OK) return st;

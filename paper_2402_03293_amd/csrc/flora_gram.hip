@@ -669,17 +669,17 @@ __device__ __forceinline__ void quadform_tiles(float (&q)[ZT], const bf16x8 (&zr
 // A workgroup's 256 rows of S stay in operand registers (32 to a wave) while P and then P' pass through LDS, at
 // r = 256 by halves: 68 KB instead of 135, so that two workgroups share a compute unit and one loads while
 // the other multiplies.
-template <int R, bool CLIP>
-__global__ __launch_bounds__(512, R >= 256 ? 4 : 2) void quadform_rows_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items,
+// 128 rows in four waves where that leaves no workgroup without a compute unit: less to do beside the passage of P and P'.
+template <int R, bool CLIP, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, R >= 256 && WAVES == 8 ? 4 : 2) void quadform_rows_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items,
                                                             float alpha, float beta2, float eps1)
 {
     constexpr int S = R / 32;                      // contraction steps
     constexpr int ZT = 2;                          // 16-row tiles of S per wave
     constexpr int KB = R < 128 ? R : 128;          // rows of B in LDS at a time
     constexpr int LDB = R + 8;                     // padded LDS row (bf16 elements)
-    static_assert(8 * 16 * ZT == kQuadformRows, "one round of rows per workgroup");
     __shared__ __attribute__((aligned(16))) uint16_t ldsB[KB][LDB];
-    __shared__ float lds_fin[2][8];
+    __shared__ float lds_fin[2][WAVES];
 
     const WorkItem it = items[blockIdx.x];
     const MatDev& M = mats[it.mat];
@@ -707,7 +707,7 @@ __global__ __launch_bounds__(512, R >= 256 ? 4 : 2) void quadform_rows_kernel(co
 
     auto stage_B = [&](const uint16_t* B) {
 #pragma unroll
-        for (int f0 = 0; f0 < KB * (R / 8); f0 += 512) {
+        for (int f0 = 0; f0 < KB * (R / 8); f0 += 64 * WAVES) {
             const int f = f0 + tid;
             *reinterpret_cast<v4u*>(&ldsB[f / (R / 8)][8 * (f % (R / 8))]) = ldg4(B + (f / (R / 8)) * R + 8 * (f % (R / 8)));
         }
@@ -767,7 +767,7 @@ __global__ __launch_bounds__(512, R >= 256 ? 4 : 2) void quadform_rows_kernel(co
     if (tid == 0) {
         float fr = 0.f, fu = 0.f;
 #pragma unroll
-        for (int w = 0; w < 8; ++w) { fr += lds_fin[0][w]; fu += lds_fin[1][w]; }
+        for (int w = 0; w < WAVES; ++w) { fr += lds_fin[0][w]; fu += lds_fin[1][w]; }
         M.rowpart[it.part] = fr;
         if (CLIP) M.itempart[it.part] = alpha * alpha * fu;
     }
@@ -953,19 +953,32 @@ hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, 
 }
 
 template <int R>
-hipError_t launch_quadform_r(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, int out,
+hipError_t launch_quadform_r(const MatDev* mats, const WorkItem* items, int nitems, int rows, const SeedArgs& seeds, int out,
                              float alpha, float beta2, float eps1, hipStream_t s)
 {
     const dim3 grid((unsigned)nitems);
+    constexpr int kFew = R >= 128 ? 4 : 8;               // (rank 64 always takes 256 rows)
     switch (out) {
-    case 0: hipLaunchKernelGGL((quadform_rows_kernel<R, false>), grid, dim3(512), 0, s, mats, items, alpha, beta2, eps1); break;
-    case 2: hipLaunchKernelGGL((quadform_rows_kernel<R, true>), grid, dim3(512), 0, s, mats, items, alpha, beta2, eps1); break;
+#define FLORA_ROWS(CLIP, W) hipLaunchKernelGGL((quadform_rows_kernel<R, CLIP, W>), grid, dim3(64 * W), 0, s, mats, items, alpha, beta2, eps1)
+#define FLORA_COLS(W) hipLaunchKernelGGL((quadform_cols_kernel<R, W>), grid, dim3(64 * W), 0, s, mats, items, seeds, alpha, beta2, eps1)
+    case 0:
+        if (rows <= 128) FLORA_ROWS(false, kFew);
+        else FLORA_ROWS(false, 8);
+        break;
+    case 2:
+        if (rows <= 128) FLORA_ROWS(true, kFew);
+        else FLORA_ROWS(true, 8);
+        break;
     case 1:
-        if constexpr (R >= 128)
-            hipLaunchKernelGGL((quadform_cols_kernel<R, 16>), grid, dim3(1024), 0, s, mats, items, seeds, alpha, beta2, eps1);
-        else
+        if constexpr (R >= 128) {
+            if (rows <= 128) FLORA_COLS(4);
+            else if (rows <= 256) FLORA_COLS(8);
+            else FLORA_COLS(16);
+        } else
             hipLaunchKernelGGL((quadform_cols_small_kernel<R, 2>), grid, dim3(512), 0, s, mats, items, seeds, alpha, beta2, eps1);
         break;
+#undef FLORA_ROWS
+#undef FLORA_COLS
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -989,15 +1002,15 @@ hipError_t launch_gram(const MatDev* mats, const WorkItem* items, int nitems, in
 }
 
 // out 0: row sums of Gt^2 (Z = S, B = P) into the row statistics, 2: the same and the clipping sum (B = P'),
-// 1: column sums (Z = A, B = Q) into the column statistics
-hipError_t launch_quadform(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, int r, int out,
+// 1: column sums (Z = A, B = Q) into the column statistics; rows: of Z per workgroup, at most
+hipError_t launch_quadform(const MatDev* mats, const WorkItem* items, int nitems, int rows, const SeedArgs& seeds, int r, int out,
                            float alpha, float beta2, float eps1, hipStream_t s)
 {
     if (nitems == 0) return hipSuccess;
     switch (r) {
-    case 64: return launch_quadform_r<64>(mats, items, nitems, seeds, out, alpha, beta2, eps1, s);
-    case 128: return launch_quadform_r<128>(mats, items, nitems, seeds, out, alpha, beta2, eps1, s);
-    case 256: return launch_quadform_r<256>(mats, items, nitems, seeds, out, alpha, beta2, eps1, s);
+    case 64: return launch_quadform_r<64>(mats, items, nitems, rows, seeds, out, alpha, beta2, eps1, s);
+    case 128: return launch_quadform_r<128>(mats, items, nitems, rows, seeds, out, alpha, beta2, eps1, s);
+    case 256: return launch_quadform_r<256>(mats, items, nitems, rows, seeds, out, alpha, beta2, eps1, s);
     default: return hipErrorInvalidValue;
     }
 }

@@ -245,7 +245,7 @@ hipError_t launch_rms_finalize(const MatDev* mats, int count, float clip_d, int 
                                hipStream_t s);
 hipError_t launch_gram(const MatDev* mats, const WorkItem* items, int nitems, int count, const SeedArgs& seeds, int r,
                        int src, hipStream_t s);
-hipError_t launch_quadform(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, int r, int out,
+hipError_t launch_quadform(const MatDev* mats, const WorkItem* items, int nitems, int rows, const SeedArgs& seeds, int r, int out,
                            float alpha, float beta2, float eps1, hipStream_t s);
 hipError_t launch_wsumsq_finalize(const MatDev* mats, int count, hipStream_t s);
 hipError_t launch_weight_sumsq(const MatDev* mats, int count, int weight_is_bf16, float* partials, hipStream_t s);
@@ -267,7 +267,7 @@ constexpr __host__ __device__ size_t gram_piece_floats(int r)
 {
     return r >= 128 ? (size_t)(r / 32) * (r / 32 + 1) / 2 * 1024 : (size_t)r * r;
 }
-constexpr int kQuadformRows = 256;       // rows of S per workgroup of the quadratic forms
+constexpr int kQuadformRows = 256;       // rows of S per workgroup of the quadratic forms, at most
 constexpr int kQuadformCols = 1024;      // rows of A per workgroup of the column statistics, at most
 
 }  // namespace flora
