@@ -698,8 +698,8 @@ void build_gram_items(Plan& p)
 {
     // Pieces of the long index: the largest that still give the chip 384 workgroups (the sums of a launch
     // over a few matrices otherwise run on a workgroup per matrix: 16 GPT-2 base matrices at r = 128, the
-    // two Gram kernels 45 + 73 us in pieces of 3072), as far as memory allows: a piece holds r^2 floats at
-    // r = 64 and the upper triangle's tiles above, and all of them no more than whole r x r pieces of 3072 and the partial sums that the passes would leave
+    // two Gram kernels 45 + 73 us in pieces of 3072), as far as memory allows: a piece holds the upper
+    // triangle's tiles, and all of them no more than whole r x r pieces of 3072 and the partial sums that the passes would leave
     // (24 matrices of T5-3B at r = 256, whose state is 96 MiB: 52 MiB; without the limit 473), or than the
     // state itself up to 32 MiB (not in a lean plan, see Arena).
     auto pieces = [&](bool rows, long long most, long long least) {

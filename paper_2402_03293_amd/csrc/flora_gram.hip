@@ -15,7 +15,8 @@
 // generated rows of A; then ONE further sweep over A yields both P and P'; then the row statistics
 // R and the clipping sum from one read of S.
 //
-// gram_sym_kernel (ranks >= 128) / gram_kernel (rank 64): one workgroup sums X_t X_t^T over a chunk
+// gram_sym_kernel (ranks >= 128) / gram_block_kernel (P and P' of few chunks, and at rank 64) / gram_kernel (Q at rank
+//   64): one workgroup sums X_t X_t^T over a chunk
 //   of the long index t (X_t = row t of A, regenerated, plain and scaled with 1 / K_t; or row t of
 //   S, loaded) into partial r x r matrices; tiles of 64 t are staged in LDS transposed ([k][t],
 //   bf16), both MFMA operands come from there.  combine_gram_kernel adds the chunks' partials in
@@ -49,10 +50,9 @@ __device__ __forceinline__ int perm32(int x) { return 8 * ((x >> 2) & 3) + 4 * (
 // g holds, for step 2 s + (a >> 1) of the contraction, the values x = 8 a + 4 g + v in elements 4 (a & 1) + v.
 __device__ __forceinline__ int perm32w(int x) { return 16 * (x >> 4) + 8 * ((x >> 2) & 1) + 4 * ((x >> 3) & 1) + (x & 3); }
 
-// SRC 0: X = A(seed), 1: X = A(seed) diag(1 / sqrt(K)), 2: X = S (the state, fp32 in memory)
-template <int R, int SRC>
-__global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items,
-                                                   const SeedArgs seeds)
+// Q = S^T S at rank 64
+template <int R>
+__global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items)
 {
     constexpr int NTR = R / 16;                       // 16-row tiles of the result
     constexpr int RT = (NTR >= 8) ? NTR / 8 : 1;      // row tiles per wave
@@ -71,42 +71,7 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
     const int row_tile0 = (NTR >= 8) ? wave * RT : wave % NTR;
     const int col_tile0 = (NTR >= 8) ? 0 : (wave / NTR) * CT;
 
-    // ---- producers: a 64 x R tile of X, transposed, bf16
-    const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
-    const float cgen = neg2_ln2_over(R);
-    constexpr int NQ = R / 32;                        // quads per thread and tile (generated X)
-    constexpr int JG = kGT / NQ;
-    const int gen_j = NQ * (tid % JG);
-    const uint32_t gen_q = (uint32_t)(tid / JG);
-    auto produce_generated = [&](int buf, int tile) {
-        const long long j = t0 + (long long)tile * kGT + gen_j;
-        uint32_t pk[NQ / 2][4];
-        // the weights first (clamped addresses, so that the loads are issued together and are
-        // long back when the first quad is done)
-        float wt[NQ];
-#pragma unroll
-        for (int e = 0; e < NQ; ++e) {
-            wt[e] = 1.f;
-            if (SRC == 1) wt[e] = ldg(M.col_stat + ((j + e < t1) ? j + e : t1 - 1));
-        }
-#pragma unroll
-        for (int e = 0; e < NQ; e += 2) {
-            const Quad z0 = normal_quad(seed_lo, seed_hi, (uint32_t)(j + e), gen_q, cgen);
-            const Quad z1 = normal_quad(seed_lo, seed_hi, (uint32_t)(j + e + 1), gen_q, cgen);
-            float w0 = (SRC == 1) ? rsqrtf(wt[e]) : 1.f, w1 = (SRC == 1) ? rsqrtf(wt[e + 1]) : 1.f;
-            w0 = (j + e < t1) ? w0 : 0.f;
-            w1 = (j + e + 1 < t1) ? w1 : 0.f;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) pk[e / 2][i] = pack_bf16x2(w0 * z0.z[i], w1 * z1.z[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint16_t* dst = &ldsX[buf][4 * gen_q + i][gen_j];
-            if (NQ == 8) *reinterpret_cast<uint4*>(dst) = make_uint4(pk[0][i], pk[NQ / 8][i], pk[NQ / 4][i], pk[NQ / 2 - 1][i]);
-            else if (NQ == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(pk[0][i], pk[NQ / 2 - 1][i]);
-            else *reinterpret_cast<uint32_t*>(dst) = pk[0][i];
-        }
-    };
+    // ---- a 64 x R tile of S, transposed, bf16
     // loaded X: unit = (pair of rows 2 p, 2 p + 1; four columns 4 k4 ..): 8 R units per tile, R / 64
     // per thread; eight consecutive lanes take eight row pairs (consecutive words of an LDS row),
     // the lanes 8 apart the next columns (a whole 128-byte line per row)
@@ -149,22 +114,13 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // Producing the next tile and multiplying the current one are independent within a round, so
-    // the two waves of a SIMD (w and w + 4) take them in opposite orders: while one regenerates on
-    // the vector ALU the other keeps the matrix core busy.
-    const bool produce_first = wave < 4;
     v4f stage[NU][2];
-    if (SRC == 2) {
-        fetch_loaded(stage, 0);
-        stash_loaded(stage, 0);
-        if (ntiles > 1) fetch_loaded(stage, 1);
-    } else {
-        produce_generated(0, 0);
-    }
+    fetch_loaded(stage, 0);
+    stash_loaded(stage, 0);
+    if (ntiles > 1) fetch_loaded(stage, 1);
     __syncthreads();
     for (int tile = 0; tile < ntiles; ++tile) {
         const int buf = tile & 1;
-        if (SRC != 2 && produce_first && tile + 1 < ntiles) produce_generated(buf ^ 1, tile + 1);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             bf16x8 av[RT];
@@ -179,28 +135,27 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
                     acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[rt], bv, acc[rt][ct], 0, 0, 0);
             }
         }
-        if (SRC != 2 && !produce_first && tile + 1 < ntiles) produce_generated(buf ^ 1, tile + 1);
-        if (SRC == 2 && tile + 1 < ntiles) {
+        if (tile + 1 < ntiles) {
             stash_loaded(stage, buf ^ 1);                        // tile + 1, fetched a round ago
             if (tile + 2 < ntiles) fetch_loaded(stage, tile + 2);
         }
         __syncthreads();
     }
 
-    // partial of this chunk: D layout, lane holds column 16 ct + li and rows 4 g + v of each tile
-    // (partials: those of P over chunks of m, then those of P'; or those of Q over chunks of n, combined before)
-    const int part0 = SRC == 1 ? M.gchunks_m : 0;
-    float* part = M.grampart + (size_t)(part0 + it.part) * R * R;
+    // partial of this chunk: D layout, lane holds column 16 ct + li and rows 4 g + v of each tile; kept are the 32 x 32
+    // tiles on and above the diagonal
+    float* part = M.grampart + (size_t)it.part * gram_piece_floats(R);
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < CT; ++ct) {
+            const int ti = (row_tile0 + rt) / 2, tj = (col_tile0 + ct) / 2;
+            if (ti > tj) continue;
+            float* tile = part + (ti * (R / 32) - ti * (ti - 1) / 2 + tj - ti) * 1024;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int k1 = 16 * (row_tile0 + rt) + 4 * g + v;
-                const int k2 = 16 * (col_tile0 + ct) + li;
-                stg(part + k1 * R + k2, acc[rt][ct][v]);
-            }
+            for (int v = 0; v < 4; ++v)
+                stg(tile + (16 * ((row_tile0 + rt) & 1) + 4 * g + v) * 32 + 16 * ((col_tile0 + ct) & 1) + li, acc[rt][ct][v]);
+        }
 }
 
 // P = A^T A and P' = A^T diag(1 / K) A from ONE regeneration of A, at ranks >= 128.  The vector
@@ -398,7 +353,9 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
     }
 }
 
-// P (and P') of a launch with few chunks: a workgroup makes the tiles of one pair of blocks of SB ranks, regenerating those
+// P (and P') of a launch with few chunks, and of every launch at rank 64, where the one block is the whole matrix (P and P' used to
+// take a sweep over A each: factored update, us before / after, one 768 x 3072 matrix 55 / 45, one 1600 x 6400 65 / 57, GPT-2
+// base 175 / 172, 24 of 768 x 3072 127 / 119; with blocks of 32 48, 58, 205, 133): a workgroup makes the tiles of one pair of blocks of SB ranks, regenerating those
 // ranks only, where gram_sym_kernel would leave most compute units idle beside a chain of up to 48 whole tiles of A.
 // (Blocks take no memory; shorter chunks would.)  16 waves in groups of SB / 16 that take every KG-th tile of
 // the chunk each and whose sums are added in the groups' order.  A block pair generates SB or 2 SB ranks: with SB =
@@ -419,9 +376,10 @@ __global__ __launch_bounds__(1024) void gram_block_kernel(const MatDev* __restri
     constexpr int TW = SPLIT ? 1 : SBT * SBT / GW;               // tiles per wave
     constexpr int NC = PAIR ? 2 : 1;                             // results
     constexpr int NA = SPLIT ? 1 : NC;                           // of them in a wave
-    constexpr int ROWS = (2 + (PAIR ? 1 : 0)) * SB;              // first block, second block, second block scaled
-    constexpr int NQ = 8;                                        // quads per thread and tile
-    static_assert(kGT / NQ * (2 * SB / 4) == GT, "a quad of ranks and eight entries per thread");
+    constexpr int SCALED = SB == R ? SB : 2 * SB;                // first row of the second block's scaled copy (SB == R: of the only one's)
+    constexpr int ROWS = (SB == R || !PAIR ? 2 : 3) * SB;        // first block, second block, second block scaled
+    constexpr int NQ = SB == R ? 4 : 8;                          // quads per thread and tile
+    static_assert(kGT / NQ * ((SB == R ? 1 : 2) * SB / 4) == GT, "a quad of ranks and NQ entries per thread");
     static_assert((KG - 1) * SB * SB * 4 * (SPLIT ? NC : 1) <= KG * ROWS * kGLd * 2, "a result's sums take the place of the tiles");
     __shared__ __attribute__((aligned(16))) uint16_t lds[KG][ROWS][kGLd];
 
@@ -472,10 +430,13 @@ __global__ __launch_bounds__(1024) void gram_block_kernel(const MatDev* __restri
         if (!gen) return;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            *reinterpret_cast<v4u*>(&lds[kg][4 * q + i][gen_j]) = v4u{pk[0][0][i], pk[0][1][i], pk[0][2][i], pk[0][3][i]};
-            if (scaled)
-                *reinterpret_cast<v4u*>(&lds[kg][PAIR ? (diag ? 2 * SB : SB) + 4 * q + i : 0][gen_j]) =
-                    v4u{pk[NC - 1][0][i], pk[NC - 1][1][i], pk[NC - 1][2][i], pk[NC - 1][3][i]};
+            auto put = [&](int row, const uint32_t (&x)[NQ / 2][4]) {
+                uint16_t* at = &lds[kg][row][gen_j];
+                if constexpr (NQ == 8) *reinterpret_cast<v4u*>(at) = v4u{x[0][i], x[1][i], x[2][i], x[3][i]};
+                else *reinterpret_cast<v2u*>(at) = v2u{x[0][i], x[1][i]};
+            };
+            put(4 * q + i, pk[0]);
+            if (scaled) put(PAIR ? (diag ? SCALED : SCALED - SB) + 4 * q + i : 0, pk[NC - 1]);
         }
     };
 
@@ -486,7 +447,7 @@ __global__ __launch_bounds__(1024) void gram_block_kernel(const MatDev* __restri
         for (int w = 0; w < TW; ++w)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][w][v] = 0.f;
-    const int brow = diag ? 0 : SB;                // second operand, plain (its scaled rows start at 2 SB)
+    const int brow = diag ? 0 : SB;                // second operand, plain
 
     if (gen) produce(0);
     stash();
@@ -499,11 +460,11 @@ __global__ __launch_bounds__(1024) void gram_block_kernel(const MatDev* __restri
                 const int ra = SPLIT ? 0 : (wave * TW + w) / SBT, cb = SPLIT ? 0 : (wave * TW + w) % SBT;
                 const int k = 16 * s + 8 * g;
                 const bf16x8 av = *reinterpret_cast<const bf16x8*>(&lds[kg][32 * ra + ln][k]);
-                const int b0 = SPLIT && PAIR && wave == 1 ? 2 * SB : brow;
+                const int b0 = SPLIT && PAIR && wave == 1 ? SCALED : brow;
                 const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&lds[kg][b0 + 32 * cb + ln][k]);
                 acc[0][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[0][w], 0, 0, 0);
                 if (NA == 2) {
-                    const bf16x8 bs = *reinterpret_cast<const bf16x8*>(&lds[kg][(PAIR ? 2 * SB : 0) + 32 * cb + ln][k]);
+                    const bf16x8 bs = *reinterpret_cast<const bf16x8*>(&lds[kg][(PAIR ? SCALED : 0) + 32 * cb + ln][k]);
                     acc[NA - 1][w] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bs, acc[NA - 1][w], 0, 0, 0);
                 }
             }
@@ -551,42 +512,14 @@ __global__ __launch_bounds__(1024) void gram_block_kernel(const MatDev* __restri
 }
 
 // B <- sum over the chunks of their partials, in chunk order; stored as bf16 with the columns of
-// every 32-block in the order the quadratic-form kernels contract them (rank 64: both partials and results are
-// whole).  which 0: P (chunks of m), 1: Q
-// (chunks of n), 2: P' (chunks of m; it is kept right behind Q); 0 and 2 together as blockIdx.z = 0, 1
-template <int R>
-__global__ __launch_bounds__(256) void combine_gram_kernel(const MatDev* __restrict__ mats, int first)
-{
-    const MatDev& M = mats[blockIdx.y];
-    const int which = first + 2 * (int)blockIdx.z;
-    const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;       // four consecutive k1 of one row k2
-    if (idx >= R * R) return;
-    const int nch = which == 1 ? M.gchunks_n : M.gchunks_m;
-    const int part0 = which == 2 ? M.gchunks_m : 0;
-    const float* src = M.grampart + (size_t)part0 * R * R + idx;
-    v4f s = {0.f, 0.f, 0.f, 0.f};
-    int c = 0;
-    for (; c + 8 <= nch; c += 8) {                              // eight loads in flight
-        v4f p[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] = ldg4(src + (size_t)(c + e) * R * R);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += p[e];
-    }
-    for (; c < nch; ++c) s += ldg4(src + (size_t)c * R * R);
-    uint16_t* B = which == 0 ? M.gramP : (which == 1 ? M.gramQ : M.gramQ + R * R);
-    const int k2 = idx / R, k1 = idx % R;                       // k1 % 4 == 0: the four stay together
-    const int pos = (k1 & ~31) + perm32(k1 & 31);
-    const v2u pk = {pack_bf16x2(s.x, s.y), pack_bf16x2(s.z, s.w)};
-    *reinterpret_cast<FLORA_GLOBAL v2u*>((FLORA_GLOBAL uint16_t*)(B + k2 * R + pos)) = pk;
-}
-
-// The same from partials that hold the tiles of the upper triangle (0.56 of the matrix at r = 256, 0.63 at r = 128: less
+// every 32-block in the order the quadratic-form kernels contract them.  which 0: P (chunks of m), 1: Q
+// (chunks of n), 2: P' (chunks of m; it is kept right behind Q); 0 and 2 together as blockIdx.z = 0, 1.
+// Partials hold the tiles of the upper triangle (0.56 of the matrix at r = 256, 0.63 at r = 128, 0.75 at r = 64: less
 // traffic, 384 T5-3B matrices' factored update 6139 -> 6045 us, and more pieces in the same memory, the pair kernel on
 // one 1600 x 6400 matrix at r = 256 124 -> 72, on 16 GPT-2 base matrices at r = 128 23 -> 14): a tile per workgroup,
 // written to both of its places.
 template <int R>
-__global__ __launch_bounds__(256) void combine_gram_tiles_kernel(const MatDev* __restrict__ mats, int first)
+__global__ __launch_bounds__(256) void combine_gram_kernel(const MatDev* __restrict__ mats, int first)
 {
     __shared__ float turn[32][33];
     const MatDev& M = mats[blockIdx.y];
@@ -609,9 +542,9 @@ __global__ __launch_bounds__(256) void combine_gram_tiles_kernel(const MatDev* _
     uint16_t* B = which == 0 ? M.gramP : (which == 1 ? M.gramQ : M.gramQ + R * R);
     int ti, tj;
     UpperTiles<R>::at(blockIdx.x, ti, tj);
-    // (Q is read by quadform_cols_kernel, the others in the other order; four consecutive entries stay together)
+    // (Q at ranks >= 128 is read by quadform_cols_kernel, all else in the other order; four consecutive entries stay together)
     auto put = [&](int k2, int k1, v4f x) {
-        const int pos = (k1 & ~31) + (which == 1 ? perm32w(k1 & 31) : perm32(k1 & 31));
+        const int pos = (k1 & ~31) + (which == 1 && R >= 128 ? perm32w(k1 & 31) : perm32(k1 & 31));
         *reinterpret_cast<FLORA_GLOBAL v2u*>((FLORA_GLOBAL uint16_t*)(B + k2 * R + pos)) =
             v2u{pack_bf16x2(x.x, x.y), pack_bf16x2(x.z, x.w)};
     };
@@ -922,14 +855,14 @@ hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, 
 {
     const dim3 grid((unsigned)nitems), block(512);
     bool p = false, q = false, p2 = false;               // which sums this launch produces
-    if constexpr (R >= 128) {
-        constexpr int PW = R >= 256 ? 8 : 16;           // waves that can hold both sets of accumulators
 #define FLORA_GRAM_BLOCKS(SB)                                                                                                     \
     do {                                                                                                                          \
         const dim3 bgrid((unsigned)(nitems * (R / SB) * (R / SB + 1) / 2));                                                       \
         if (src == 0) hipLaunchKernelGGL((gram_block_kernel<R, SB, false>), bgrid, dim3(1024), 0, s, mats, items, seeds);         \
         else hipLaunchKernelGGL((gram_block_kernel<R, SB, true>), bgrid, dim3(1024), 0, s, mats, items, seeds);                   \
     } while (0)
+    if constexpr (R >= 128) {
+        constexpr int PW = R >= 256 ? 8 : 16;           // waves that can hold both sets of accumulators
         if (src == 0 || src == 3) {
             p = true;
             p2 = src == 3;
@@ -938,17 +871,19 @@ hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, 
             else if (src == 0) hipLaunchKernelGGL((gram_sym_kernel<R, 0, 16>), grid, dim3(1024), 0, s, mats, items, seeds);
             else hipLaunchKernelGGL((gram_sym_kernel<R, 1, PW>), grid, dim3(64 * PW), 0, s, mats, items, seeds);
         }
-#undef FLORA_GRAM_BLOCKS
         if (src == 2) { hipLaunchKernelGGL((gram_sym_kernel<R, 2, 16>), grid, dim3(1024), 0, s, mats, items, seeds); q = true; }
     } else {
-        if (src == 0 || src == 3) { hipLaunchKernelGGL((gram_kernel<R, 0>), grid, block, 0, s, mats, items, seeds); p = true; }
-        if (src == 3) { hipLaunchKernelGGL((gram_kernel<R, 1>), grid, block, 0, s, mats, items, seeds); p2 = true; }
-        if (src == 2) { hipLaunchKernelGGL((gram_kernel<R, 2>), grid, block, 0, s, mats, items, seeds); q = true; }
+        if (src == 0 || src == 3) {
+            p = true;
+            p2 = src == 3;
+            FLORA_GRAM_BLOCKS(64);
+        }
+        if (src == 2) { hipLaunchKernelGGL((gram_kernel<R>), grid, block, 0, s, mats, items); q = true; }
     }
+#undef FLORA_GRAM_BLOCKS
     if (!p && !q && !p2) return hipErrorInvalidValue;
-    const dim3 cgrid(R >= 128 ? (unsigned)UpperTiles<R>::COUNT : (unsigned)(R * R / 1024), (unsigned)count, p2 ? 2 : 1);
-    if constexpr (R >= 128) hipLaunchKernelGGL((combine_gram_tiles_kernel<R>), cgrid, dim3(256), 0, s, mats, q ? 1 : 0);
-    else hipLaunchKernelGGL((combine_gram_kernel<R>), cgrid, dim3(256), 0, s, mats, q ? 1 : 0);
+    hipLaunchKernelGGL((combine_gram_kernel<R>), dim3((unsigned)UpperTiles<R>::COUNT, (unsigned)count, p2 ? 2 : 1), dim3(256), 0, s, mats,
+                       q ? 1 : 0);
     return hipGetLastError();
 }
 

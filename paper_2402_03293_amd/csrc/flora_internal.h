@@ -262,11 +262,8 @@ constexpr int kApplyTRowsBig = 64;       // ... ranks 64 and above
 constexpr int kTransferChunk = 1024;     // columns per workgroup of the T kernel, ranks 64 and above
 constexpr int kSumsqBlocks = 256;        // workgroups per matrix, sum of W^2
 constexpr int kGramChunk = 3072;         // long-index entries per workgroup of the Gram sums, at most
-// Floats of a partial Gram matrix: at ranks >= 128 the 32 x 32 tiles on and above the diagonal.
-constexpr __host__ __device__ size_t gram_piece_floats(int r)
-{
-    return r >= 128 ? (size_t)(r / 32) * (r / 32 + 1) / 2 * 1024 : (size_t)r * r;
-}
+// Floats of a partial Gram matrix: the 32 x 32 tiles on and above the diagonal.
+constexpr __host__ __device__ size_t gram_piece_floats(int r) { return (size_t)(r / 32) * (r / 32 + 1) / 2 * 1024; }
 constexpr int kQuadformRows = 256;       // rows of S per workgroup of the quadratic forms, at most
 constexpr int kQuadformCols = 1024;      // rows of A per workgroup of the column statistics, at most
 
