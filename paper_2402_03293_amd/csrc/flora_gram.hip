@@ -162,7 +162,8 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
 // ALU work of the generator is what these sums cost, so both are taken from the same tile: the
 // tile goes to LDS twice, plain and with its long-index entries scaled by 1 / K, and
 // P'[k1][k2] = sum_t X[t][k1] (X[t][k2] / K_t) takes one operand from each copy.
-// 16 waves, so that four share a SIMD and one wave's generator chains run in the shadow of the
+// 16 waves (12 for both sums at r = 256: 36 tiles, three a wave, in 168 registers; with eight waves of up to five 24 matrices of
+// 768 x 3072 285 us instead of 279, GPT-2 base 341 and 337), so that four share a SIMD and one wave's generator chains run in the shadow of the
 // others'; v_mfma_f32_32x32x16_bf16 tiles; only the tiles on or above the diagonal of the
 // symmetric results are computed (36 of 64 at r = 256), consecutive ones to a wave (they mostly
 // share an operand), every SIMD multiplying the same number of them, and only they are stored.
@@ -217,11 +218,12 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
 
     const uint32_t seed_lo = seeds.s[it.mat].x, seed_hi = seeds.s[it.mat].y;
     const float cgen = neg2_ln2_over(R);
-    constexpr int NQ = R / (4 * WAVES);               // quads per thread and tile
-    constexpr int JG = kGT / NQ;
-    const int gen_j = NQ * (tid % JG);
-    const uint32_t gen_q = (uint32_t)(tid / JG);
-    auto produce = [&](int buf, int tile) {
+    constexpr bool kEven = R % (4 * WAVES) == 0;
+    constexpr int NQ = kEven ? R / (4 * WAVES) : 2;   // quads per thread and tile (12 waves: and round)
+    constexpr int JG = kGT / NQ, UNITS = JG * (R / 4);
+    auto produce_unit = [&](int buf, int tile, int unit) {
+        const int gen_j = NQ * (unit % JG);
+        const uint32_t gen_q = (uint32_t)(unit / JG);
         const long long j = t0 + (long long)tile * kGT + gen_j;
         float wt[NQ];
 #pragma unroll
@@ -252,6 +254,14 @@ __global__ __launch_bounds__(64 * WAVES) void gram_sym_kernel(const MatDev* __re
                 else if (NQ == 4) *reinterpret_cast<uint2*>(dst) = make_uint2(pk[c][0][i], pk[c][NQ / 2 - 1][i]);
                 else *reinterpret_cast<uint32_t*>(dst) = pk[c][0][i];
             }
+    };
+    auto produce = [&](int buf, int tile) {
+        if constexpr (kEven) {
+            produce_unit(buf, tile, tid);
+        } else {
+#pragma unroll 1
+            for (int u = tid; u < UNITS; u += 64 * WAVES) produce_unit(buf, tile, u);
+        }
     };
 
     // loaded X (MODE 2): unit = (pair of rows 2 p, 2 p + 1; four columns 4 k4 ..); eight consecutive
@@ -862,7 +872,7 @@ hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, 
         else hipLaunchKernelGGL((gram_block_kernel<R, SB, true>), bgrid, dim3(1024), 0, s, mats, items, seeds);                   \
     } while (0)
     if constexpr (R >= 128) {
-        constexpr int PW = R >= 256 ? 8 : 16;           // waves that can hold both sets of accumulators
+        constexpr int PW = R >= 256 ? 12 : 16;          // waves that can hold both sets of accumulators
         if (src == 0 || src == 3) {
             p = true;
             p2 = src == 3;
