@@ -1340,6 +1340,30 @@ static int run_decompress(Plan* p, const SeedArgs& sa, int r, int mode, int out_
     return FLORA_OK;
 }
 
+// Rows that start and end on 128-byte lines: a store with the non-temporal hint that leaves part of a line to another wave
+// costs a pass of that line over memory.
+static bool whole_lines(const void* base, int64_t m, int elem_bytes)
+{
+    return (reinterpret_cast<uintptr_t>(base) & 127u) == 0 && (m * elem_bytes) % 128 == 0;
+}
+
+// Cache policy of a decompression's output (bit 1: written with the non-temporal hint): from the last-level cache's size
+// on, where rows are whole lines.  us plain / streamed at r = 16, 64, 128, 256: fp32 GPT-2 base (324 MiB) 68 / 68, 81 / 64, 85 / 75,
+// 112 / 84, 24 matrices of GPT-2 XL (703) 142 / 143, 163 / 135, 166 / 149, 203 / 160; bf16 two GPT-2 base (324) 132 / 94,
+// 128 / 110, 121 / 97, 160 / 139, 48 matrices of GPT-2 XL (703) 243 / 199, 267 / 244, 247 / 226, 297 / 272.  Below: fp32 108 MiB 22 / 24
+// at r = 64, bf16 162 MiB 55 / 58.  Rows of any width (251 MiB): 77 / 155.  At ranks <= 32 into fp32 it makes no difference.
+static int choose_out_policy(const flora_matrix_t* mats, int count, int r, void* const* out, int elem_bytes)
+{
+    if (g_tune.update_wpolicy) return (g_tune.update_wpolicy - 1) & 2;
+    if (r <= 32 && elem_bytes == 4) return 0;
+    double bytes = 0.0;
+    for (int l = 0; l < count; ++l) {
+        if (!whole_lines(out[l], mats[l].m, elem_bytes)) return 0;
+        bytes += (double)mats[l].n * (double)mats[l].m * elem_bytes;
+    }
+    return bytes >= 256.0 * 1024.0 * 1024.0 ? 2 : 0;
+}
+
 static int decompress_chunk(const flora_matrix_t* mats, int count, int r, float alpha, void* const* out,
                             flora_dtype_t out_dtype, hipStream_t s, bool dry)
 {
@@ -1354,7 +1378,7 @@ static int decompress_chunk(const flora_matrix_t* mats, int count, int r, float 
     Plan* p = nullptr;
     int st = get_plan(kKindDecompress, out_dtype == FLORA_BF16 ? 1 : 0, r, md, s, &p, dry);
     if (st != FLORA_OK || dry) return st;
-    DecompressParams dp{alpha, 0.f, 0.f, 0.f, 0, 0};
+    DecompressParams dp{alpha, 0.f, 0.f, 0.f, choose_out_policy(mats, count, r, out, out_dtype == FLORA_BF16 ? 2 : 4), 0, 0};
     return run_decompress(p, sa, r, kModeOut, out_dtype == FLORA_BF16, dp, s);
 }
 
@@ -1442,7 +1466,7 @@ static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, 
         if (own >= (u->rule == FLORA_RULE_SGD ? 256.0 : 128.0) && (u->rule == FLORA_RULE_SGD || (u->rule == FLORA_RULE_FACTORED && r == 64)))
             c.lines = 1;
         bool whole = !unfactored;
-        for (int l = 0; l < count; ++l) whole = whole && mats[l].m % 64 == 0 && mats[l].m <= (1LL << 23);
+        for (int l = 0; l < count; ++l) whole = whole && whole_lines(mats[l].weight, mats[l].m, 2) && mats[l].m <= (1LL << 23);
         if (c.lines && whole && own >= 256.0) c.first = c.last = 3;
         return c;
     }

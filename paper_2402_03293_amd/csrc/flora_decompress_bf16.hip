@@ -403,10 +403,10 @@ __global__ __launch_bounds__(512, (vec_waves<R, MODE, OT>())) void decompress_bf
             for (int pp = 0; pp < 4; ++pp) {
                 const v4f a4 = gt[pp];
                 if (sizeof(OT) == 4) {
-                    buf_store_f4(rw, woff(pp), v4f{p.alpha * a4.x, p.alpha * a4.y, p.alpha * a4.z, p.alpha * a4.w});
+                    buf_store_f4<st_stream>(rw, woff(pp), v4f{p.alpha * a4.x, p.alpha * a4.y, p.alpha * a4.z, p.alpha * a4.w});
                 } else {
                     const v2u pk = {pack_bf16x2(p.alpha * a4.x, p.alpha * a4.y), pack_bf16x2(p.alpha * a4.z, p.alpha * a4.w)};
-                    buf_store_u2(rw, woff(pp), pk);
+                    buf_store_u2<st_stream>(rw, woff(pp), pk);
                 }
             }
         } else if (MODE == kModeSgd) {
@@ -760,6 +760,9 @@ hipError_t launch_vec(const MatDev* mats, const WorkItem* items, int nitems, con
         case 3: FLORA_VEC(3); break;
         default: FLORA_VEC(0); break;
         }
+    } else if constexpr (MODE == kModeOut) {
+        if (p.wpolicy & 2) FLORA_VEC(2);
+        else FLORA_VEC(0);
     } else FLORA_VEC(0);
 #undef FLORA_VEC
     return hipGetLastError();
@@ -793,6 +796,9 @@ hipError_t launch_one(const MatDev* mats, const WorkItem* items, int nitems, con
         case 3: FLORA_DEC(3); break;
         default: FLORA_DEC(0); break;
         }
+    } else if constexpr (MODE == kModeOut) {
+        if (p.wpolicy & 2) FLORA_DEC(2);
+        else FLORA_DEC(0);
     } else FLORA_DEC(0);
 #undef FLORA_DEC
     return hipGetLastError();

@@ -100,6 +100,9 @@ hipError_t launch_one(const MatDev* mats, const WorkItem* items, int nitems, con
         case 3: FLORA_DEC(3); break;
         default: FLORA_DEC(0); break;
         }
+    } else if constexpr (MODE == kModeOut) {
+        if (p.wpolicy & 2) FLORA_DEC(2);
+        else FLORA_DEC(0);
     } else FLORA_DEC(0);
 #undef FLORA_DEC
     return hipGetLastError();

@@ -150,7 +150,7 @@ __device__ __forceinline__ void epilogue_tile(const f32x16& acc, const TilePre<M
         const rsrc_t r = tile_rsrc(reinterpret_cast<OT*>(M.out), M.m, rb, row_end);
         const uint32_t at = tile_lane<OT>(m32, j32, jok);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) buf_store_bits<OT, false>(r, at + tile_step<OT>(m32, v), to_bits<OT>(p.alpha * acc[v]));
+        for (int v = 0; v < 16; ++v) buf_store_bits<OT, (WP & 2) != 0>(r, at + tile_step<OT>(m32, v), to_bits<OT>(p.alpha * acc[v]));
     } else if constexpr (Moves<MODE>::w) {
         const rsrc_t r = tile_rsrc(reinterpret_cast<OT*>(M.weight), M.m, rb, row_end);
         const uint32_t at = tile_lane<OT>(m32, j32, jok);

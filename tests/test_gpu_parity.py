@@ -657,6 +657,26 @@ def test_apply_update_factored(n, m, r, clip_d, beta2):
     assert rel_fro(to64(W) - to64(W0), Wr - to64(W0)) < update_bar(r, Wr, to64(W0))
 
 
+# a decompression writes the same bits with and without the non-temporal hint, in every kernel: ranks <= 32, 4 and 16
+# bytes per lane, rows on and off line boundaries
+@pytest.mark.parametrize("n,m,r", [(70, 96, 16), (70, 101, 32), (70, 192, 64), (65, 101, 64), (70, 128, 128), (33, 260, 256)])
+def test_decompress_streamed_output(n, m, r):
+    S = rand((n, r), 7200 + r)
+    for dtype, fd in ((torch.float32, flora.F32), (torch.bfloat16, flora.BF16)):
+        outs = []
+        for policy in (1, 3):
+            out = torch.full((n, m), float("nan"), device=DEV, dtype=dtype)
+            flora.set_tuning("update_wpolicy", policy)
+            try:
+                flora.decompress(flora.matrices([(n, m)], states=[S], seeds=[r]), r, 0.5, [out], fd)
+                sync()
+            finally:
+                flora.set_tuning("update_wpolicy", 0)
+            outs.append(out)
+        assert torch.equal(outs[0], outs[1])
+        assert rel_fro(to64(outs[0]), oracle.decompress(to64(S), m, r, alpha=0.5)) < (TOL_BF16 if r >= 64 or fd == flora.BF16 else tol_for(r))
+
+
 # the update kernel for whole lines of bf16 weights: edges of its 32-row blocks and 64-column waves, one and several
 # workgroups per row, one and several row blocks.  The result is rounded to bf16 (2^-9 of a value at most).
 @pytest.mark.parametrize("rows", [0, 64])
