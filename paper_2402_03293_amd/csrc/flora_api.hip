@@ -1444,6 +1444,17 @@ static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, 
     const double bytes = elems * ((wbf16 ? 2.0 : 4.0) + (unfactored ? 4.0 : 0.0)), v_mib = elems * 4.0 / (1024.0 * 1024.0);
     // a caller that spreads one optimizer step over several calls says how large the whole set is
     const double mib = std::max(bytes / (1024.0 * 1024.0), (double)u->step_weight_mib);
+    // Rows that do not end on lines: the hint makes two waves' parts of a line two passes over memory.  Sets with a tenth or more of
+    // such weights take plain accesses: 24 each of 1100 x 1003, 257 x 2051, 770 x 3001 and 2000 x 777 in fp32 (503 MiB), us streamed as below
+    // / plain at r = 16, 64, 256: plain update 491 / 248, 369 / 225, 448 / 275, unfactored 873 / 599, 723 / 567, 847 / 705; half
+    // of them 129 / 120, 118 / 108, 231 / 159, and 416 / 310, 353 / 296, 451 / 406; with rows of 16-byte multiples 445 / 244 at r = 16.
+    if (!wbf16 || unfactored) {
+        double cut = 0.0;
+        for (int l = 0; l < count; ++l)
+            if (!whole_lines(mats[l].weight, mats[l].m, wbf16 ? 2 : 4) || (unfactored && !whole_lines(mats[l].second_moment, mats[l].m, 4)))
+                cut += (double)mats[l].n * (double)mats[l].m;
+        if (cut >= 0.1 * elems) return c;
+    }
     if (unfactored && mib > 192.0 && v_mib <= 768.0) {
         c.first = v_mib <= 256.0 ? 0 : 2;
         c.last = 3;
