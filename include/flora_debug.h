@@ -66,12 +66,13 @@ int flora_debug_compute_loop(int kind, int iters, void* sink, double* work_out, 
  * launch of their own), "decompress_rows" (a multiple of 32: rows per workgroup in the
  * decompress / update kernels), "decompress_vec" (1: always the 4-byte-per-lane kernel at
  * ranks >= 64, 2: the 16-byte-per-lane kernel whenever every m is a multiple of 4, which is
- * also the default), "factored_gram" (the factored rule at ranks >= 64: 1 reduction passes over the decompressed
+ * also the default, 3: and its form for whole lines of bf16 weights whatever the size of the set), "factored_gram" (the factored rule at ranks >= 64: 1 reduction passes over the decompressed
  * gradient, 2 quadratic forms in r x r Gram matrices; by default whichever is less arithmetic for the
  * set), "gram_chunk" (a multiple of 64: entries of m or n per workgroup of the Gram sums),
  * "update_wpolicy" (the update passes: 1 plain
- * accesses to the weights, 2 reads with the non-temporal hint, 3 writes with it, 4 both; by
- * default chosen from the size of the call's weights against the 256 MB last-level cache: a
+ * accesses to the weights, 2 reads with the non-temporal hint, 3 writes with it, 4 both, and 3 and 4
+ * the same for the output of a decompression; by default chosen from the size of the call's weights against the
+ * 256 MB last-level cache and from whether rows are whole 128-byte lines: a
  * caller that updates a large model a few matrices per call may want 4).  Results never depend
  * on these beyond summation order.
  * Unknown name or value: FLORA_ERR_INVALID.  Drops the cached descriptor tables. */
