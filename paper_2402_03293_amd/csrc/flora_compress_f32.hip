@@ -251,14 +251,14 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
 #pragma unroll
         for (int u = 0; u < kPF - 1; ++u) load_tile_fast(st[u], u);
         gen_tile(0, 0);
-        // (the round after a single one is multiplied too, by zeros: finite values in the other buffer then, not
-        // whatever LDS held before, which may be NaN)
-        if (fast_rounds == 1)
-            for (int idx = tg; idx < RP * kLda; idx += 256) ldsA[kg][1][idx / kLda][idx % kLda] = 0.f;
         __syncthreads();
         // The body is free of branches around memory operations (a round past the end loads
         // nothing, multiplies zeros and skips only the generator): the compiler can then
         // follow the outstanding loads around the loop and waits for the oldest stage alone.
+        // The round after a single one takes the one buffer that was generated: what LDS held before may be
+        // NaN, which zeros do not undo.  (Zeros stored in the other buffer instead, 256 x 256 at r = 8: 5.0 us
+        // a launch as here, 5.3.)
+        const int second = fast_rounds > 1 ? 1 : 0;
         for (int base = 0; base < fast_rounds; base += kPF) {
 #pragma unroll
             for (int u = 0; u < kPF; ++u) {
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
                 const int buf = i & 1;
                 load_tile_fast(st[(u + kPF - 1) % kPF], i + kPF - 1);
                 if (i + 1 < fast_rounds) gen_tile(buf ^ 1, i + 1);
-                mfma_tile(st[u], buf, true);
+                mfma_tile(st[u], buf & second, true);
                 __syncthreads();
             }
         }
