@@ -34,6 +34,14 @@ int64_t flora_debug_work_items(int kind, const flora_matrix_t* mats, int count, 
  * flora_status_t on bad arguments. */
 int64_t flora_debug_plan_bytes(int plan_kind, const flora_matrix_t* mats, int count, int r, flora_dtype_t grad_dtype);
 
+/* Test hook, host only: how the update passes of this call would access the weights and the second
+ * moment.  out (4 int64): the policy of the unfactored rule's first pass and of the pass that writes
+ * the weights (bit 0: reads with the non-temporal hint, bit 1: writes with it), 1 if the latter takes
+ * its table from the end, 1 if it takes the kernel for whole lines of bf16 weights where rows start on
+ * 16-byte boundaries.  Only alignments and sizes are looked at: pointers may be NULL. */
+int flora_debug_access_policy(const flora_matrix_t* mats, int count, int r, flora_dtype_t weight_dtype,
+                              const flora_update_t* u, int64_t* out);
+
 /* Measurement hook: a plain device-to-device copy kernel of `bytes` bytes (a multiple of 16;
  * both DEVICE pointers 16-byte aligned, not overlapping).  Profiler byte counters for the
  * hot-path kernels are scaled by what they read for this copy of known size. */

@@ -1433,7 +1433,8 @@ struct CachePolicy {
 static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, const flora_update_t* u, int wbf16)
 {
     CachePolicy c;
-    c.lines = g_tune.decompress_vec == 2;
+    const bool line_kernel = rank_bf16(r) && g_tune.decompress_vec != 0;     // (there is none at ranks <= 32)
+    c.lines = line_kernel && g_tune.decompress_vec == 2;
     if (g_tune.update_wpolicy) {
         c.first = c.last = g_tune.update_wpolicy - 1;
         return c;
@@ -1473,8 +1474,11 @@ static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, 
         //   all of it (2812)             1426 / 1393 / 1359  1361 / 1234 / 1170  1689 / 1513 / 1472
         // and under the factored rule at r = 64 (sums included) 8 matrices of T5-3B (112) 98 / 95 / 98, GPT-2 base
         // 123 / 113 / 117, ragged rows 271 / 227 / 253, GPT-2 XL 1708 / 1430 / 1343; at higher ranks it gains nothing there.
+        // Ranks <= 32 have the first kernel only.  Plain / streamed at r = 8, 16, 32: 24 matrices of GPT-2 XL 160 / 184,
+        // 170 / 194, 216 / 225, all of it 1263 / 1495, 1335 / 1565, 1660 / 1779.
         const double own = elems * 2.0 / (1024.0 * 1024.0);
-        if (own >= (u->rule == FLORA_RULE_SGD ? 256.0 : 128.0) && (u->rule == FLORA_RULE_SGD || (u->rule == FLORA_RULE_FACTORED && r == 64)))
+        if (line_kernel && own >= (u->rule == FLORA_RULE_SGD ? 256.0 : 128.0) &&
+            (u->rule == FLORA_RULE_SGD || (u->rule == FLORA_RULE_FACTORED && r == 64)))
             c.lines = 1;
         bool whole = !unfactored;
         for (int l = 0; l < count; ++l) whole = whole && whole_lines(mats[l].weight, mats[l].m, 2) && mats[l].m <= (1LL << 23);
@@ -1831,6 +1835,19 @@ int64_t flora_debug_work_items(int kind, const flora_matrix_t* mats, int count, 
             o[6] = w.col1; o[7] = w.part; o[8] = w.nparts; o[9] = w.cidx; o[10] = w.poff; o[11] = 0;
         }
     return (int64_t)items.size();
+}
+
+int flora_debug_access_policy(const flora_matrix_t* mats, int count, int r, flora_dtype_t weight_dtype,
+                              const flora_update_t* u, int64_t* out)
+{
+    if (count < 0 || (count > 0 && !mats) || !u || !out || !dtype_ok((int)weight_dtype)) return FLORA_ERR_INVALID;
+    if (!rank_f32(r) && !rank_bf16(r)) return FLORA_ERR_UNSUPPORTED;
+    for (int l = 0; l < count; ++l)
+        if (mats[l].n < 1 || mats[l].m < 1 || mats[l].m > (1LL << 24)) return FLORA_ERR_INVALID;
+    std::lock_guard<std::mutex> guard(g_lock);
+    const CachePolicy c = choose_wpolicy(mats, count, r, u, weight_dtype == FLORA_BF16);
+    out[0] = c.first; out[1] = c.last; out[2] = c.reverse; out[3] = c.lines;
+    return FLORA_OK;
 }
 
 int flora_debug_copy(const void* src, void* dst, size_t bytes, void* hip_stream)

@@ -107,6 +107,8 @@ def lib():
         L.flora_debug_generate.restype = ci
         L.flora_debug_work_items.argtypes = [ci, MP, ci, ci, ci, vp, ctypes.c_int64, vp]
         L.flora_debug_work_items.restype = ctypes.c_int64
+        L.flora_debug_access_policy.argtypes = [MP, ci, ci, ci, ctypes.POINTER(Update), vp]
+        L.flora_debug_access_policy.restype = ci
         L.flora_debug_copy.argtypes = [vp, vp, ctypes.c_size_t, vp]
         L.flora_debug_copy.restype = ci
         L.flora_debug_read.argtypes = [vp, ctypes.c_size_t, ci, ctypes.c_size_t, ci, vp, vp]
@@ -145,7 +147,7 @@ EXPORTS = [
     "flora_fused_step", "flora_weight_sumsq", "flora_adafactor_schedule", "flora_debug_generate",
     "flora_debug_work_items", "flora_debug_copy", "flora_debug_read", "flora_debug_compute_loop", "flora_derive_seed", "flora_derive_seeds",
     "flora_workspace_bytes", "flora_set_workspace", "flora_set_tuning", "flora_momentum_transfer_static",
-    "flora_debug_plan_bytes",
+    "flora_debug_plan_bytes", "flora_debug_access_policy",
     "flora_last_device_error", "flora_status_string", "flora_shutdown", "flora_version",
 ]
 
@@ -259,6 +261,14 @@ def debug_work_items(kind: int, shapes, r: int, grad_dtype: int = F32):
     out = np.zeros((int(n), 12), dtype=np.int64)
     lib().flora_debug_work_items(kind, mats, len(mats), r, grad_dtype, out.ctypes.data, int(n), info.ctypes.data)
     return out, info
+
+
+def debug_access_policy(mats, r: int, weight_dtype: int, update: Update):
+    """(first, last, reverse, lines): see flora_debug_access_policy (host only, no GPU)."""
+    out = (ctypes.c_int64 * 4)()
+    _check(lib().flora_debug_access_policy(mats, len(mats), r, weight_dtype, ctypes.byref(update), out),
+           "flora_debug_access_policy")
+    return tuple(out)
 
 
 def debug_copy(src, dst, nbytes: int, stream=None):

@@ -197,3 +197,20 @@ def test_fp32_compress_pieces_by_how_much_they_would_cut():
         for r in (8, 16, 32):
             _, info = check_compress(shapes, r, flora.BF16)
             assert int(info[2]) == kc, (shapes[0], len(shapes), r)
+
+
+def test_bf16_updates_are_streamed_by_the_kernel_of_whole_lines_only():
+    """bf16 weights: the hint where a wave moves whole 128-byte lines, which ranks <= 32 and the 4-byte-per-lane
+    kernel never do, and from 256 MiB on."""
+    xl = workloads.workload(5).shapes
+    sgd = flora.sgd_update(1e-3)
+    for r in RANKS:
+        whole = r >= 64
+        assert flora.debug_access_policy(flora.matrices(xl), r, flora.BF16, sgd) == ((3, 3, 0, 1) if whole else (0, 0, 0, 0))
+        assert flora.debug_access_policy(flora.matrices(xl[:8]), r, flora.BF16, sgd) == (0, 0, 0, 0)
+        assert flora.debug_access_policy(flora.matrices([(n, m + 8) for n, m in xl]), r, flora.BF16, sgd) == (0, 0, 0, int(whole))
+        try:
+            flora.set_tuning("decompress_vec", 1)          # 4 bytes per lane
+            assert flora.debug_access_policy(flora.matrices(xl), r, flora.BF16, sgd) == (0, 0, 0, 0)
+        finally:
+            flora.set_tuning("decompress_vec", 0)
