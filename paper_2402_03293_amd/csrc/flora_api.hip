@@ -1456,7 +1456,11 @@ static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, 
                 cut += (double)mats[l].n * (double)mats[l].m;
         if (cut >= 0.1 * elems) return c;
     }
-    if (unfactored && mib > 192.0 && v_mib <= 768.0) {
+    // (bf16 weights up to 256 MiB with V take plain accesses: 20 matrices of GPT-2 base or 40 of 1024 x 1024, 202 and 240 MiB, three
+    // sets in turn, us so / plain: r = 8, 16, 32 110 / 110, 114 / 114, 126 / 126, and 126 / 125, 131 / 130, 148 / 148; r = 64, 128, 256 136 / 134, 151 /
+    // 147, 159 / 152, and 145 / 141, 159 / 156, 187 / 193; on the same arrays over and over up to 18 % less plain.  283 MiB 148 / 150 at r = 8,
+    // 159 / 159, 172 / 175, 181 / 186 at r = 64, 128, 256; 405 MiB 208 / 225 and 231 / 251, 260 / 277, 327 / 355.)
+    if (unfactored && mib > (wbf16 ? 256.0 : 192.0) && v_mib <= 768.0) {
         c.first = v_mib <= 256.0 ? 0 : 2;
         c.last = 3;
         c.reverse = 1;

@@ -214,3 +214,19 @@ def test_bf16_updates_are_streamed_by_the_kernel_of_whole_lines_only():
             assert flora.debug_access_policy(flora.matrices(xl), r, flora.BF16, sgd) == (0, 0, 0, 0)
         finally:
             flora.set_tuning("decompress_vec", 0)
+
+
+def test_unfactored_policy_by_what_w_and_v_take():
+    """The unfactored rule's plan for the last-level cache: from 192 MiB of W and V on, with bf16 weights from 256 MiB,
+    to 768 MiB of V; V stays in the cache as a whole up to 256 MiB."""
+    u = flora.unfactored_update(1e-3, 1.0, 0.9, 1e-30, 1.0)
+    for count, f32, bf16 in ((24, (0, 0, 0, 0), (0, 0, 0, 0)),           # 192 and 144 MiB
+                             (25, (0, 3, 1, 0), (0, 0, 0, 0)),           # 200, 150
+                             (42, (0, 3, 1, 0), (0, 0, 0, 0)),           # 336, 252
+                             (43, (0, 3, 1, 0), (0, 3, 1, 0)),           # 344, 258
+                             (65, (2, 3, 1, 0), (2, 3, 1, 0)),           # V of 260 MiB
+                             (192, (2, 3, 1, 0), (2, 3, 1, 0))):         # V of 768 MiB
+        mats = flora.matrices([(1024, 1024)] * count)
+        for r in RANKS:
+            assert flora.debug_access_policy(mats, r, flora.F32, u) == f32, (count, r)
+            assert flora.debug_access_policy(mats, r, flora.BF16, u) == bf16, (count, r)
