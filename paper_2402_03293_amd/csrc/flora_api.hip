@@ -1347,6 +1347,20 @@ static bool whole_lines(const void* base, int64_t m, int elem_bytes)
     return (reinterpret_cast<uintptr_t>(base) & 127u) == 0 && (m * elem_bytes) % 128 == 0;
 }
 
+// A set counts as one of cut rows where a tenth or more of its elements are in rows off line boundaries (whole(l): those
+// of matrix l are not).
+template <typename F>
+static bool cut_rows(const flora_matrix_t* mats, int count, F&& whole)
+{
+    double cut = 0.0, all = 0.0;
+    for (int l = 0; l < count; ++l) {
+        const double elems = (double)mats[l].n * (double)mats[l].m;
+        all += elems;
+        if (!whole(l)) cut += elems;
+    }
+    return cut >= 0.1 * all;
+}
+
 // Cache policy of a decompression's output (bit 1: written with the non-temporal hint): from the last-level cache's size
 // on, where rows are whole lines.  us plain / streamed at r = 16, 64, 128, 256: fp32 GPT-2 base (324 MiB) 68 / 68, 81 / 64, 85 / 75,
 // 112 / 84, 24 matrices of GPT-2 XL (703) 142 / 143, 163 / 135, 166 / 149, 203 / 160; bf16 two GPT-2 base (324) 132 / 94,
@@ -1378,7 +1392,9 @@ static int decompress_chunk(const flora_matrix_t* mats, int count, int r, float 
     Plan* p = nullptr;
     int st = get_plan(kKindDecompress, out_dtype == FLORA_BF16 ? 1 : 0, r, md, s, &p, dry);
     if (st != FLORA_OK || dry) return st;
-    DecompressParams dp{alpha, 0.f, 0.f, 0.f, choose_out_policy(mats, count, r, out, out_dtype == FLORA_BF16 ? 2 : 4), 0, 0};
+    const int elem_bytes = out_dtype == FLORA_BF16 ? 2 : 4;
+    DecompressParams dp{alpha, 0.f, 0.f, 0.f, choose_out_policy(mats, count, r, out, elem_bytes), 0, 0,
+                        cut_rows(mats, count, [&](int l) { return whole_lines(out[l], mats[l].m, elem_bytes); })};
     return run_decompress(p, sa, r, kModeOut, out_dtype == FLORA_BF16, dp, s);
 }
 
@@ -1429,12 +1445,15 @@ struct CachePolicy {
     int last = 0;       // the pass that writes the weights
     int reverse = 0;    // ... which takes the table from its end
     int lines = 0;      // ... whose waves move whole lines of bf16 weights where rows start on 16-byte boundaries
+    int cut = 0;        // the weights' rows end off line boundaries
 };
 static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, const flora_update_t* u, int wbf16)
 {
     CachePolicy c;
     const bool line_kernel = rank_bf16(r) && g_tune.decompress_vec != 0;     // (there is none at ranks <= 32)
     c.lines = line_kernel && g_tune.decompress_vec == 2;
+    auto whole_w = [&](int l) { return whole_lines(mats[l].weight, mats[l].m, wbf16 ? 2 : 4); };
+    c.cut = cut_rows(mats, count, whole_w);
     if (g_tune.update_wpolicy) {
         c.first = c.last = g_tune.update_wpolicy - 1;
         return c;
@@ -1449,13 +1468,9 @@ static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, 
     // such weights take plain accesses: 24 each of 1100 x 1003, 257 x 2051, 770 x 3001 and 2000 x 777 in fp32 (503 MiB), us streamed as below
     // / plain at r = 16, 64, 256: plain update 491 / 248, 369 / 225, 448 / 275, unfactored 873 / 599, 723 / 567, 847 / 705; half
     // of them 129 / 120, 118 / 108, 231 / 159, and 416 / 310, 353 / 296, 451 / 406; with rows of 16-byte multiples 445 / 244 at r = 16.
-    if (!wbf16 || unfactored) {
-        double cut = 0.0;
-        for (int l = 0; l < count; ++l)
-            if (!whole_lines(mats[l].weight, mats[l].m, wbf16 ? 2 : 4) || (unfactored && !whole_lines(mats[l].second_moment, mats[l].m, 4)))
-                cut += (double)mats[l].n * (double)mats[l].m;
-        if (cut >= 0.1 * elems) return c;
-    }
+    if (unfactored ? cut_rows(mats, count, [&](int l) { return whole_w(l) && whole_lines(mats[l].second_moment, mats[l].m, 4); })
+                   : !wbf16 && c.cut)
+        return c;
     // (bf16 weights up to 256 MiB with V take plain accesses: 20 matrices of GPT-2 base or 40 of 1024 x 1024, 202 and 240 MiB, three
     // sets in turn, us so / plain: r = 8, 16, 32 110 / 110, 114 / 114, 126 / 126, and 126 / 125, 131 / 130, 148 / 148; r = 64, 128, 256 136 / 134, 151 /
     // 147, 159 / 152, and 145 / 141, 159 / 156, 187 / 193; on the same arrays over and over up to 18 % less plain.  283 MiB 148 / 150 at r = 8,
@@ -1519,11 +1534,11 @@ static int update_chunk(const flora_matrix_t* mats, int count, int r, int wbf16,
     if (st != FLORA_OK || dry) return st;
     const MatDev* dm = p->cur_mats;
     if (u->rule == FLORA_RULE_SGD) {
-        DecompressParams dp{u->alpha, u->lr * u->alpha, 0.f, 0.f, wpolicy.last, 0, wpolicy.lines};
+        DecompressParams dp{u->alpha, u->lr * u->alpha, 0.f, 0.f, wpolicy.last, 0, wpolicy.lines, wpolicy.cut};
         st = run_decompress(p, sa, r, kModeSgd, wbf16, dp, s);
         if (st != FLORA_OK) return st;
     } else {
-        DecompressParams dp{u->alpha, u->lr, u->beta2, u->eps1, 0, 0};
+        DecompressParams dp{u->alpha, u->lr, u->beta2, u->eps1, 0, 0, 0, 0};
         const int gram = p->route == Plan::kGram ? 1 : 0;
         if (gram) {
             // row and column sums of Gt^2 as quadratic forms in A^T A and S^T S, then the clipping

@@ -74,6 +74,7 @@ struct DecompressParams {
                    // bit 1 written with it (chosen from the size of the set, see choose_wpolicy)
     int reverse;   // kModeFull2: workgroups take the table from its end
     int lines;     // kModeSgd, kModeFactored, bf16 weights: whole lines per wave (see choose_wpolicy)
+    int cut;       // kModeOut, kModeSgd: rows of the output or the weights end off line boundaries (see cut_rows)
 };
 
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;

@@ -657,6 +657,46 @@ def test_apply_update_factored(n, m, r, clip_d, beta2):
     assert rel_fro(to64(W) - to64(W0), Wr - to64(W0)) < update_bar(r, Wr, to64(W0))
 
 
+# the passes that write n x m arrays at ranks <= 32: one row tile (nothing to fetch ahead), its edges, two and several, in
+# row blocks of one and of two tiles; rows on and off line boundaries (launches of fewer workgroups per compute unit)
+@pytest.mark.parametrize("rows", [32, 64])
+@pytest.mark.parametrize("m", [128, 131])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 64, 65, 130])
+@pytest.mark.parametrize("r", [8, 16, 32])
+def test_written_tiles_at_small_ranks(r, n, m, rows):
+    seed = 7300 + 10 * n + r
+    S, W0, V0 = rand((n, r), seed), rand((n, m), seed + 1, scale=0.1), (rand((n, m), seed + 2).abs() + 0.1).contiguous()
+    guard = torch.full((4, n + 2, m), 7.0, device=DEV)
+    out, Ws, Wu, V = (guard[i, 1:n + 1] for i in range(4))
+    if m % 4 == 0:                                # (arrays start on 16-byte boundaries)
+        Ws.copy_(W0), Wu.copy_(W0), V.copy_(V0)
+    else:
+        out, Ws, Wu, V, guard = torch.empty_like(W0), W0.clone(), W0.clone(), V0.clone(), None
+    Wb = W0.to(torch.bfloat16)
+    Wb0 = Wb.clone()
+    lr, alpha, beta2, eps1 = 0.5, 0.5, 0.8, 1e-30
+    one = lambda **kw: flora.matrices([(n, m)], states=[S], seeds=[seed], **kw)
+    flora.set_tuning("decompress_rows", rows)
+    try:
+        flora.decompress(one(), r, alpha, [out], flora.F32)
+        flora.apply_update(one(weights=[Ws]), r, flora.F32, flora.sgd_update(lr, alpha))
+        flora.apply_update(one(weights=[Wb]), r, flora.BF16, flora.sgd_update(lr, alpha))
+        flora.apply_update(one(weights=[Wu], second_moments=[V]), r, flora.F32, flora.unfactored_update(lr, alpha, beta2, eps1, 1.0))
+        sync()
+    finally:
+        flora.set_tuning("decompress_rows", 0)
+    Gt = oracle.decompress(to64(S), m, seed, alpha=alpha)
+    assert rel_fro(to64(out), Gt) < TOL_F32
+    Wr = oracle.sgd(to64(W0), Gt, lr)
+    assert rel_fro(to64(Ws) - to64(W0), Wr - to64(W0)) < update_bar(r, Wr, to64(W0))
+    assert rel_fro(to64(Wb), oracle.sgd(to64(Wb0), Gt, lr)) < 2.0 ** -9       # one rounding of the result
+    Wr, Vr = oracle.adafactor_step(to64(W0), Gt, V=to64(V0), beta2=beta2, eps1=eps1, clip_d=1.0, step=lr, scale_parameter=False)
+    assert rel_fro(to64(V), Vr) < TOL_F32
+    assert rel_fro(to64(Wu) - to64(W0), Wr - to64(W0)) < update_bar(r, Wr, to64(W0))
+    if guard is not None:
+        assert float((guard[:, 0] - 7).abs().max()) == 0 and float((guard[:, -1] - 7).abs().max()) == 0
+
+
 # a decompression writes the same bits with and without the non-temporal hint, in every kernel: ranks <= 32, 4 and 16
 # bytes per lane, rows on and off line boundaries
 @pytest.mark.parametrize("n,m,r", [(70, 96, 16), (70, 101, 32), (70, 192, 64), (65, 101, 64), (70, 128, 128), (33, 260, 256)])
