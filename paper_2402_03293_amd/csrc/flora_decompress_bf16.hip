@@ -788,7 +788,13 @@ template <int R, int MODE, typename OT>
 hipError_t launch_one(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds, DecompressParams p, hipStream_t s)
 {
     const dim3 grid((unsigned)nitems), block(256);
-#define FLORA_DEC(WP) hipLaunchKernelGGL((decompress_bf16_kernel<R, MODE, OT, WP>), grid, block, 0, s, mats, items, seeds, p)
+    // Plain update of fp32 weights with rows off line boundaries (DecompressParams::cut), rank 128, launches of four and more workgroups per
+    // compute unit: two of them at a time instead of three, for the reason given at the ranks <= 32.  us three / two, sets of
+    // ragged rows in turn: 62 MiB 27.2 / 28.8 (not taken there), 125 MiB 69.8 / 66.6, 251 MiB 135 / 128, 413 MiB 221 / 201, 503 MiB 285 / 254.  (r =
+    // 64 222 / 219 at 503 MiB, and decompression loses: 185 / 200.)
+    constexpr bool kFew = R == 128 && MODE == kModeSgd && sizeof(OT) == 4;
+    const unsigned lds = kFew && p.cut && nitems >= 1024 ? 44000u : 0u;
+#define FLORA_DEC(WP) hipLaunchKernelGGL((decompress_bf16_kernel<R, MODE, OT, WP>), grid, block, lds, s, mats, items, seeds, p)
     if constexpr (Moves<MODE>::w || Moves<MODE>::v) {
         switch (p.wpolicy & 3) {
         case 1: FLORA_DEC(1); break;
