@@ -1366,6 +1366,7 @@ static bool cut_rows(const flora_matrix_t* mats, int count, F&& whole)
 // 112 / 84, 24 matrices of GPT-2 XL (703) 142 / 143, 163 / 135, 166 / 149, 203 / 160; bf16 two GPT-2 base (324) 132 / 94,
 // 128 / 110, 121 / 97, 160 / 139, 48 matrices of GPT-2 XL (703) 243 / 199, 267 / 244, 247 / 226, 297 / 272.  Below: fp32 108 MiB 22 / 24
 // at r = 64, bf16 162 MiB 55 / 58.  Rows of any width (251 MiB): 77 / 155.  At ranks <= 32 into fp32 it makes no difference.
+// (Asked once per call: 500 matrices of 512 x 512 at r = 256, of which 448 fit a launch, 175 us with the last 52 plain, 160 streamed.)
 static int choose_out_policy(const flora_matrix_t* mats, int count, int r, void* const* out, int elem_bytes)
 {
     if (g_tune.update_wpolicy) return (g_tune.update_wpolicy - 1) & 2;
@@ -1379,7 +1380,7 @@ static int choose_out_policy(const flora_matrix_t* mats, int count, int r, void*
 }
 
 static int decompress_chunk(const flora_matrix_t* mats, int count, int r, float alpha, void* const* out,
-                            flora_dtype_t out_dtype, hipStream_t s, bool dry)
+                            flora_dtype_t out_dtype, int wpolicy, int cut, hipStream_t s, bool dry)
 {
     std::vector<MatDev> md((size_t)count);
     for (int l = 0; l < count; ++l) {
@@ -1392,9 +1393,7 @@ static int decompress_chunk(const flora_matrix_t* mats, int count, int r, float 
     Plan* p = nullptr;
     int st = get_plan(kKindDecompress, out_dtype == FLORA_BF16 ? 1 : 0, r, md, s, &p, dry);
     if (st != FLORA_OK || dry) return st;
-    const int elem_bytes = out_dtype == FLORA_BF16 ? 2 : 4;
-    DecompressParams dp{alpha, 0.f, 0.f, 0.f, choose_out_policy(mats, count, r, out, elem_bytes), 0, 0,
-                        cut_rows(mats, count, [&](int l) { return whole_lines(out[l], mats[l].m, elem_bytes); })};
+    DecompressParams dp{alpha, 0.f, 0.f, 0.f, wpolicy, 0, 0, cut};
     return run_decompress(p, sa, r, kModeOut, out_dtype == FLORA_BF16, dp, s);
 }
 
@@ -1691,9 +1690,12 @@ int flora_decompress(const flora_matrix_t* mats, int count, int r, float alpha, 
         if (!out[l] || !aligned16(out[l]) || out[l] == (void*)mats[l].state) return FLORA_ERR_INVALID;
     std::lock_guard<std::mutex> guard(g_lock);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    const int elem_bytes = out_dtype == FLORA_BF16 ? 2 : 4;
+    const int wpolicy = choose_out_policy(mats, count, r, out, elem_bytes);
+    const int cut = cut_rows(mats, count, [&](int l) { return whole_lines(out[l], mats[l].m, elem_bytes); });
     return run_call(s, [&](bool dry) {
         FLORA_FOR_CHUNKS(count, c0, cn) {
-            const int st2 = decompress_chunk(mats + c0, cn, r, alpha, out + c0, out_dtype, s, dry);
+            const int st2 = decompress_chunk(mats + c0, cn, r, alpha, out + c0, out_dtype, wpolicy, cut, s, dry);
             if (st2 != FLORA_OK) return st2;
         }
         return (int)FLORA_OK;
