@@ -384,21 +384,22 @@ def test_update_cache_policies_give_the_same_bits(n, m, r, wdt, rule):
         assert torch.equal(W, out[0])
 
 
-# the unfactored rule's second pass takes the table from its end in sets above 192 MiB (a set's share of such a
-# step here): the same bits, whichever order
+# the unfactored rule's second pass takes the table from its end in sets above 192 MiB, 256 with bf16 weights (a set's share of
+# such a step here), unless a tenth or more of the elements are in rows off line boundaries: the same bits, whichever order
 @pytest.mark.parametrize("r,wdt", [(16, "f32"), (32, "bf16"), (64, "f32"), (256, "bf16")])
-@pytest.mark.parametrize("shapes", [[(130, 260), (33, 520), (257, 64)], [(97, 1001), (64, 35)]])
-def test_unfactored_second_pass_from_the_end(shapes, r, wdt):
-    dt = torch.float32 if wdt == "f32" else torch.bfloat16
+@pytest.mark.parametrize("shapes,reverse", [([(130, 256), (33, 512), (257, 64), (5, 35)], 1), ([(97, 1001), (64, 35)], 0)])
+def test_unfactored_second_pass_from_the_end(shapes, reverse, r, wdt):
+    dt, fd = (torch.float32, flora.F32) if wdt == "f32" else (torch.bfloat16, flora.BF16)
     W0 = [rand(s, 300 + i).to(dt).contiguous() for i, s in enumerate(shapes)]
     S = [rand((n, r), 310 + i) for i, (n, _) in enumerate(shapes)]
     out = []
-    for mib in (0.0, 193.0):
+    for mib, policy in ((0.0, (0, 0, 0, 0)), (257.0, (0, 3, 1, 0) if reverse else (0, 0, 0, 0))):
         W, V = [w.clone() for w in W0], [torch.full(s, 0.5, device=DEV) for s in shapes]
         sq = [torch.ones(1, device=DEV) for _ in shapes]
-        mats = flora.matrices(shapes, weights=W, states=S, second_moments=V, weight_sumsqs=sq, seeds=[7, 8, 9][:len(shapes)])
-        flora.apply_update(mats, r, flora.F32 if wdt == "f32" else flora.BF16,
-                           flora.unfactored_update(1e-2, 1.0, 0.5, 1e-30, 1.0, step_weight_mib=mib))
+        mats = flora.matrices(shapes, weights=W, states=S, second_moments=V, weight_sumsqs=sq, seeds=[7, 8, 9, 10][:len(shapes)])
+        u = flora.unfactored_update(1e-2, 1.0, 0.5, 1e-30, 1.0, step_weight_mib=mib)
+        assert flora.debug_access_policy(mats, r, fd, u) == policy
+        flora.apply_update(mats, r, fd, u)
         sync()
         out.append(W + V + sq)
     assert all(torch.equal(x, y) for x, y in zip(*out))
@@ -484,8 +485,9 @@ def test_factored_rule_through_gram_matrices_in_large_pieces(r, clip_d, beta2):
 
 
 # ... and in pieces whose number puts P and P' on blocks of 32 ranks (up to 25 pieces at r = 128, 7 at r = 256), of 64 (up to
-# 48 at r = 256), and on whole matrices: pieces that end within a tile, within a round of the groups' tiles, and of one tile
-@pytest.mark.parametrize("r,chunk", [(128, 512), (128, 1216), (128, 320), (256, 576), (256, 768), (256, 256), (256, 192)])
+# 48 at r = 256), and on whole matrices (29 pieces of 320 at r = 128, 69 of 128 at r = 256): pieces that end within a tile,
+# within a round of the groups' tiles, and of one tile
+@pytest.mark.parametrize("r,chunk", [(128, 512), (128, 1216), (128, 320), (256, 576), (256, 768), (256, 256), (256, 192), (256, 128)])
 @pytest.mark.parametrize("clip_d,beta2", [(1.0, 0.0), (0.0, 0.6)])
 def test_factored_rule_through_blocks_of_gram_matrices(r, chunk, clip_d, beta2):
     flora.set_tuning("gram_chunk", chunk)

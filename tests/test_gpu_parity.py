@@ -206,12 +206,6 @@ def test_compress_f32_pieces(r, count, n, m):
             assert rel_fro(to64(states[l]), oracle.compress(to64(Gs[l]), r, seeds[l])) < TOL_F32
 
 
-# rows of G that start anywhere (odd widths, widths that are no multiple of 8, fp32 gradients) in the
-# wide kernel: widths around a tile of 64 columns and around the pieces of a load, row counts around a
-# wave's and a workgroup's, whole rows and shared columns.  The matrix lies between NaNs: whatever a
-# load fetches beside its row must not reach the result.  Bar: one rounded operand (A; with fp32
-# gradients G is compared as the kernel rounds it), about 2^-9 / sqrt(3) = 1.1e-3 on a large matrix;
-# the smallest have a handful of terms per entry, hence 6e-3 as for the other launch shapes.
 # matrices of one tile of columns: the round after it multiplies zeros, and whatever the other LDS buffer holds must
 # not turn them into NaN (a decompression of NaNs leaves its operands in every compute unit's LDS)
 @pytest.mark.parametrize("gdt", [torch.float32, torch.bfloat16])
@@ -226,6 +220,12 @@ def test_compress_f32_one_tile_after_nans(n, m, r, gdt):
         assert rel_fro(to64(C), oracle.compress(to64(G), r, 3)) < TOL_F32
 
 
+# rows of G that start anywhere (odd widths, widths that are no multiple of 8, fp32 gradients) in the
+# wide kernel: widths around a tile of 64 columns and around the pieces of a load, row counts around a
+# wave's and a workgroup's, whole rows and shared columns.  The matrix lies between NaNs: whatever a
+# load fetches beside its row must not reach the result.  Bar: one rounded operand (A; with fp32
+# gradients G is compared as the kernel rounds it), about 2^-9 / sqrt(3) = 1.1e-3 on a large matrix;
+# the smallest have a handful of terms per entry, hence 6e-3 as for the other launch shapes.
 @pytest.mark.parametrize("combine", [1, 2])       # shared columns added by the last part to arrive, or by a launch
 @pytest.mark.parametrize("mt,kc", [(8, 0), (16, 64), (32, 0), (32, 192)])
 @pytest.mark.parametrize("gdt", ["f32", "bf16"])
@@ -740,7 +740,8 @@ def test_decompress_streamed_output(n, m, r):
 
 
 # the update kernel for whole lines of bf16 weights: edges of its 32-row blocks and 64-column waves, one and several
-# workgroups per row, one and several row blocks.  The result is rounded to bf16 (2^-9 of a value at most).
+# workgroups per row, one and several row blocks, with plain accesses and with the streamed ones of large sets of whole
+# lines (the same bits).  The result is rounded to bf16 (2^-9 of a value at most).
 @pytest.mark.parametrize("rows", [0, 64])
 @pytest.mark.parametrize("n,m,r", [(33, 8, 64), (300, 520, 64), (257, 264, 128), (96, 1096, 128), (65, 72, 256), (200, 1024, 256)])
 def test_update_of_whole_bf16_lines(n, m, r, rows):
@@ -750,22 +751,29 @@ def test_update_of_whole_bf16_lines(n, m, r, rows):
     R0 = (rand((n,), seed + 2).abs() + 0.1).contiguous()
     K0 = (rand((m,), seed + 3).abs() + 0.1).contiguous()
     lr, alpha, eps1, beta2, clip_d = 0.5, 0.5, 1e-30, 0.8, 0.3
-    guard = torch.full((n + 2, m), 7.0, device=DEV, dtype=torch.bfloat16)
-    Ws, Wf, R, K = guard[1:n + 1], W0.clone(), R0.clone(), K0.clone()
-    Ws.copy_(W0)
-    ss = torch.zeros(4, device=DEV)
+    got = []
     flora.set_tuning("decompress_vec", 3)
     flora.set_tuning("decompress_rows", rows)
     try:
-        flora.apply_update(flora.matrices([(n, m)], weights=[Ws], states=[S], seeds=[seed]), r, flora.BF16,
-                           flora.sgd_update(lr, alpha))
-        flora.apply_update(flora.matrices([(n, m)], weights=[Wf], states=[S], row_stats=[R], col_stats=[K],
-                                          seeds=[seed], weight_sumsqs=[ss]), r, flora.BF16,
-                           flora.factored_update(lr, alpha, beta2, eps1, clip_d))
-        sync()
+        for policy in (1, 4):
+            flora.set_tuning("update_wpolicy", policy)
+            guard = torch.full((n + 2, m), 7.0, device=DEV, dtype=torch.bfloat16)
+            Ws, Wf, R, K = guard[1:n + 1], W0.clone(), R0.clone(), K0.clone()
+            Ws.copy_(W0)
+            ss = torch.zeros(4, device=DEV)
+            mats = flora.matrices([(n, m)], weights=[Ws], states=[S], seeds=[seed])
+            assert flora.debug_access_policy(mats, r, flora.BF16, flora.sgd_update(lr, alpha)) == (policy - 1, policy - 1, 0, 1)
+            flora.apply_update(mats, r, flora.BF16, flora.sgd_update(lr, alpha))
+            flora.apply_update(flora.matrices([(n, m)], weights=[Wf], states=[S], row_stats=[R], col_stats=[K],
+                                              seeds=[seed], weight_sumsqs=[ss]), r, flora.BF16,
+                               flora.factored_update(lr, alpha, beta2, eps1, clip_d))
+            sync()
+            got.append((guard, Wf, R, K, ss))
     finally:
         flora.set_tuning("decompress_vec", 0)
         flora.set_tuning("decompress_rows", 0)
+        flora.set_tuning("update_wpolicy", 0)
+    assert all(torch.equal(x, y) for x, y in zip(*got))
     Gt = oracle.decompress(to64(S), m, seed, alpha=alpha)
     assert rel_fro(to64(Ws), oracle.sgd(to64(W0), Gt, lr)) < TOL_BF16 + 2.0 ** -9
     assert float((guard[0] - 7).abs().max()) == 0 and float((guard[-1] - 7).abs().max()) == 0
