@@ -17,8 +17,8 @@ extern "C" {
 /* Test hook, host only (touches no GPU): the table of workgroups the library would launch for
  * this set of shapes.  kind 0: flora_compress, 1: flora_decompress and the update passes,
  * 2: the state <- state T pass of the transfer, 3: its T = A^T A' pass (ranks 64 and above; a
- * workgroup takes columns [first column, end column) of chunk `part` and slab `rank slice` of
- * the rows of T), 4: flora_compress_mapped with a map other than the identity.  Returns the number of workgroups (or a
+ * launch takes columns [first column, end column) of chunk `part` from the first entry of each chunk and
+ * decides itself which blocks of T a workgroup makes; `rank slice` counts slabs of 128 rows of T), 4: flora_compress_mapped with a map other than the identity.  Returns the number of workgroups (or a
  * negative flora_status_t) and writes up to `cap` of them to `out`, 12 int64 each:
  * matrix, first row, rows, first column, rank slice (compress) or column chunk (decompress),
  * row-block index, end column, part, number of parts, arrival counter, offset of the partial
@@ -74,7 +74,8 @@ int flora_debug_compute_loop(int kind, int iters, void* sink, double* work_out, 
  * launch of their own), "decompress_rows" (a multiple of 32: rows per workgroup in the
  * decompress / update kernels), "decompress_vec" (1: always the 4-byte-per-lane kernel at
  * ranks >= 64, 2: the 16-byte-per-lane kernel whenever every m is a multiple of 4, which is
- * also the default, 3: and its form for whole lines of bf16 weights whatever the size of the set), "factored_gram" (the factored rule at ranks >= 64: 1 reduction passes over the decompressed
+ * also the default, 3: and its form for whole lines of bf16 weights whatever the size of the set; that one knows two
+ * access policies only, both streamed (4) and plain (any other)), "factored_gram" (the factored rule at ranks >= 64: 1 reduction passes over the decompressed
  * gradient, 2 quadratic forms in r x r Gram matrices; by default whichever is less arithmetic for the
  * set), "gram_chunk" (a multiple of 64: entries of m or n per workgroup of the Gram sums),
  * "update_wpolicy" (the update passes: 1 plain

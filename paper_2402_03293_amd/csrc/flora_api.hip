@@ -655,7 +655,8 @@ void build_apply_T_items(Plan& p)
 }
 
 // T = A_old^T A_new at ranks 64 and above: (matrix, chunk of 1024 columns, slab of up to 128 rows
-// of T); ncolchunks of the matrix = its number of chunks (the partials the combine pass adds).
+// of T); ncolchunks of the matrix = its number of chunks (the partials the combine pass adds).  The launch chooses
+// blocks of T by its number of chunks and reads the first entry of each (the others keep the table's published form).
 void build_transfer_T_items(Plan& p)
 {
     if (p.r < 64) return;

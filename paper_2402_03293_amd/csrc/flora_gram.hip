@@ -50,14 +50,11 @@ __device__ __forceinline__ int perm32(int x) { return 8 * ((x >> 2) & 3) + 4 * (
 // g holds, for step 2 s + (a >> 1) of the contraction, the values x = 8 a + 4 g + v in elements 4 (a & 1) + v.
 __device__ __forceinline__ int perm32w(int x) { return 16 * (x >> 4) + 8 * ((x >> 2) & 1) + 4 * ((x >> 3) & 1) + (x & 3); }
 
-// Q = S^T S at rank 64
-template <int R>
+// Q = S^T S at rank 64: a wave makes two of the sixteen 16 x 16 tiles
 __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ mats, const WorkItem* __restrict__ items)
 {
-    constexpr int NTR = R / 16;                       // 16-row tiles of the result
-    constexpr int RT = (NTR >= 8) ? NTR / 8 : 1;      // row tiles per wave
-    constexpr int NH = (NTR >= 8) ? 1 : 8 / NTR;      // waves that share a row tile split the columns
-    constexpr int CT = NTR / NH;                      // column tiles per wave
+    constexpr int R = 64;
+    constexpr int CT = 2;                             // column tiles per wave
     __shared__ __attribute__((aligned(16))) uint16_t ldsX[2][R][kGLd];
 
     const WorkItem it = items[blockIdx.x];
@@ -68,76 +65,51 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
     const int li = lane & 15, g = lane >> 4;
     const long long t0 = it.col0, t1 = it.col1;       // this chunk of the long index
     const int ntiles = (int)((t1 - t0 + kGT - 1) / kGT);
-    const int row_tile0 = (NTR >= 8) ? wave * RT : wave % NTR;
-    const int col_tile0 = (NTR >= 8) ? 0 : (wave / NTR) * CT;
+    const int row_tile = wave % 4, col_tile0 = (wave / 4) * CT;
 
     // ---- a 64 x R tile of S, transposed, bf16
-    // loaded X: unit = (pair of rows 2 p, 2 p + 1; four columns 4 k4 ..): 8 R units per tile, R / 64
-    // per thread; eight consecutive lanes take eight row pairs (consecutive words of an LDS row),
-    // the lanes 8 apart the next columns (a whole 128-byte line per row)
-    constexpr int NU = R / 64;
-    // (fetched one tile ahead of being stashed, so that the loads are in flight while the
-    // current tile multiplies; rows past the chunk read through a resource that ends there)
+    // unit = (pair of rows 2 p, 2 p + 1; four columns 4 k4 ..), one per thread; eight consecutive lanes take
+    // eight row pairs (consecutive words of an LDS row), the lanes 8 apart the next columns (a whole 128-byte line
+    // per row).  Fetched one tile ahead of being stashed, so that the loads are in flight while the
+    // current tile multiplies; rows past the chunk read through a resource that ends there.
     const long long chunk_rows = t1 - t0;
-    const rsrc_t srs = make_rsrc(M.state + t0 * R, chunk_rows * (long long)R * 4 < 0x7fffffffLL ? chunk_rows * R * 4 : 0x7fffffffLL);
-    auto fetch_loaded = [&](v4f (&st)[NU][2], int tile) {
-#pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int flat = tid + 512 * u;
-            const int rest = flat >> 3;
-            const int k4 = rest % (R / 4);
-            const int p = (rest / (R / 4)) * 8 + (flat & 7);
-            const long long ra = (long long)tile * kGT + 2 * p;       // relative to the chunk
-            const uint32_t off = (uint32_t)((ra * R + 4 * k4) * 4);
-            st[u][0] = (ra < chunk_rows) ? buf_load_f4(srs, off) : v4f{0.f, 0.f, 0.f, 0.f};
-            st[u][1] = (ra + 1 < chunk_rows) ? buf_load_f4(srs, off + (uint32_t)(R * 4)) : v4f{0.f, 0.f, 0.f, 0.f};
-        }
+    const rsrc_t srs = make_rsrc(M.state + t0 * R, chunk_rows * R * 4);
+    const int k4 = (tid >> 3) % (R / 4), p = ((tid >> 3) / (R / 4)) * 8 + (tid & 7);
+    auto fetch = [&](v4f (&st)[2], int tile) {
+        const long long ra = (long long)tile * kGT + 2 * p;           // relative to the chunk
+        const uint32_t off = (uint32_t)((ra * R + 4 * k4) * 4);
+        st[0] = (ra < chunk_rows) ? buf_load_f4(srs, off) : v4f{0.f, 0.f, 0.f, 0.f};
+        st[1] = (ra + 1 < chunk_rows) ? buf_load_f4(srs, off + (uint32_t)(R * 4)) : v4f{0.f, 0.f, 0.f, 0.f};
     };
-    auto stash_loaded = [&](const v4f (&st)[NU][2], int buf) {
+    auto stash = [&](const v4f (&st)[2], int buf) {
 #pragma unroll
-        for (int u = 0; u < NU; ++u) {
-            const int flat = tid + 512 * u;
-            const int rest = flat >> 3;
-            const int k4 = rest % (R / 4);
-            const int p = (rest / (R / 4)) * 8 + (flat & 7);
-            const v4f a = st[u][0], b = st[u][1];
-            *reinterpret_cast<uint32_t*>(&ldsX[buf][4 * k4 + 0][2 * p]) = pack_bf16x2(a.x, b.x);
-            *reinterpret_cast<uint32_t*>(&ldsX[buf][4 * k4 + 1][2 * p]) = pack_bf16x2(a.y, b.y);
-            *reinterpret_cast<uint32_t*>(&ldsX[buf][4 * k4 + 2][2 * p]) = pack_bf16x2(a.z, b.z);
-            *reinterpret_cast<uint32_t*>(&ldsX[buf][4 * k4 + 3][2 * p]) = pack_bf16x2(a.w, b.w);
-        }
+        for (int e = 0; e < 4; ++e)
+            *reinterpret_cast<uint32_t*>(&ldsX[buf][4 * k4 + e][2 * p]) = pack_bf16x2(st[0][e], st[1][e]);
     };
 
-    f32x4 acc[RT][CT];
+    f32x4 acc[CT];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    v4f stage[NU][2];
-    fetch_loaded(stage, 0);
-    stash_loaded(stage, 0);
-    if (ntiles > 1) fetch_loaded(stage, 1);
+    v4f stage[2];
+    fetch(stage, 0);
+    stash(stage, 0);
+    if (ntiles > 1) fetch(stage, 1);
     __syncthreads();
     for (int tile = 0; tile < ntiles; ++tile) {
         const int buf = tile & 1;
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            bf16x8 av[RT];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt)
-                av[rt] = *reinterpret_cast<const bf16x8*>(&ldsX[buf][16 * (row_tile0 + rt) + li][32 * s + 8 * g]);
+            const bf16x8 av = *reinterpret_cast<const bf16x8*>(&ldsX[buf][16 * row_tile + li][32 * s + 8 * g]);
 #pragma unroll
             for (int ct = 0; ct < CT; ++ct) {
                 const bf16x8 bv = *reinterpret_cast<const bf16x8*>(&ldsX[buf][16 * (col_tile0 + ct) + li][32 * s + 8 * g]);
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-                    acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[rt], bv, acc[rt][ct], 0, 0, 0);
+                acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[ct], 0, 0, 0);
             }
         }
         if (tile + 1 < ntiles) {
-            stash_loaded(stage, buf ^ 1);                        // tile + 1, fetched a round ago
-            if (tile + 2 < ntiles) fetch_loaded(stage, tile + 2);
+            stash(stage, buf ^ 1);                               // tile + 1, fetched a round ago
+            if (tile + 2 < ntiles) fetch(stage, tile + 2);
         }
         __syncthreads();
     }
@@ -145,17 +117,13 @@ __global__ __launch_bounds__(512) void gram_kernel(const MatDev* __restrict__ ma
     // partial of this chunk: D layout, lane holds column 16 ct + li and rows 4 g + v of each tile; kept are the 32 x 32
     // tiles on and above the diagonal
     float* part = M.grampart + (size_t)it.part * gram_piece_floats(R);
+    const int ti = row_tile / 2, tj = col_tile0 / 2;
+    if (ti > tj) return;
+    float* tile = part + (ti * (R / 32) - ti * (ti - 1) / 2 + tj - ti) * 1024;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            const int ti = (row_tile0 + rt) / 2, tj = (col_tile0 + ct) / 2;
-            if (ti > tj) continue;
-            float* tile = part + (ti * (R / 32) - ti * (ti - 1) / 2 + tj - ti) * 1024;
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                stg(tile + (16 * ((row_tile0 + rt) & 1) + 4 * g + v) * 32 + 16 * ((col_tile0 + ct) & 1) + li, acc[rt][ct][v]);
-        }
+        for (int v = 0; v < 4; ++v) stg(tile + (16 * (row_tile & 1) + 4 * g + v) * 32 + 16 * ct + li, acc[ct][v]);
 }
 
 // P = A^T A and P' = A^T diag(1 / K) A from ONE regeneration of A, at ranks >= 128.  The vector
@@ -863,7 +831,7 @@ template <int R>
 hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, int count, const SeedArgs& seeds, int src,
                          hipStream_t s)
 {
-    const dim3 grid((unsigned)nitems), block(512);
+    const dim3 grid((unsigned)nitems);
     bool p = false, q = false, p2 = false;               // which sums this launch produces
 #define FLORA_GRAM_BLOCKS(SB)                                                                                                     \
     do {                                                                                                                          \
@@ -888,7 +856,7 @@ hipError_t launch_gram_r(const MatDev* mats, const WorkItem* items, int nitems, 
             p2 = src == 3;
             FLORA_GRAM_BLOCKS(64);
         }
-        if (src == 2) { hipLaunchKernelGGL((gram_kernel<R>), grid, block, 0, s, mats, items); q = true; }
+        if (src == 2) { hipLaunchKernelGGL(gram_kernel, grid, dim3(512), 0, s, mats, items); q = true; }
     }
 #undef FLORA_GRAM_BLOCKS
     if (!p && !q && !p2) return hipErrorInvalidValue;
@@ -902,17 +870,18 @@ hipError_t launch_quadform_r(const MatDev* mats, const WorkItem* items, int nite
                              float alpha, float beta2, float eps1, hipStream_t s)
 {
     const dim3 grid((unsigned)nitems);
-    constexpr int kFew = R >= 128 ? 4 : 8;               // (rank 64 always takes 256 rows)
+    const bool few = R >= 128 && rows <= 128;            // (rank 64 always takes 256 rows)
     switch (out) {
 #define FLORA_ROWS(CLIP, W) hipLaunchKernelGGL((quadform_rows_kernel<R, CLIP, W>), grid, dim3(64 * W), 0, s, mats, items, alpha, beta2, eps1)
 #define FLORA_COLS(W) hipLaunchKernelGGL((quadform_cols_kernel<R, W>), grid, dim3(64 * W), 0, s, mats, items, seeds, alpha, beta2, eps1)
     case 0:
-        if (rows <= 128) FLORA_ROWS(false, kFew);
-        else FLORA_ROWS(false, 8);
-        break;
     case 2:
-        if (rows <= 128) FLORA_ROWS(true, kFew);
-        else FLORA_ROWS(true, 8);
+        if constexpr (R >= 128) {
+            if (few && out == 0) FLORA_ROWS(false, 4);
+            if (few && out == 2) FLORA_ROWS(true, 4);
+        }
+        if (!few && out == 0) FLORA_ROWS(false, 8);
+        if (!few && out == 2) FLORA_ROWS(true, 8);
         break;
     case 1:
         if constexpr (R >= 128) {
