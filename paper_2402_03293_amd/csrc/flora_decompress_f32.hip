@@ -13,8 +13,6 @@
 // them while the wave walks down the rows 32 at a time.  The state rows are
 // the A operand (lane = row, same half of the rank axis).  No LDS and no
 // barrier is needed for the product itself.
-#include <type_traits>
-
 #include "flora_gen.hip.h"
 #include "flora_internal.h"
 #include "flora_epilogue.hip.h"
@@ -23,7 +21,10 @@ namespace flora {
 
 namespace {
 
-// WP: cache policy of the n x m arrays the pass moves (DecompressParams::wpolicy), see flora_epilogue.hip.h.
+// WP: cache policy of the n x m arrays the pass moves (DecompressParams::wpolicy), see flora_epilogue.hip.h; with kCut a
+// decompression into rows off line boundaries.
+constexpr int kCut = 4;
+
 template <int R, int MODE, typename OT, int WP>
 __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __restrict__ mats,
                                                              const WorkItem* __restrict__ items,
@@ -73,39 +74,36 @@ __global__ __launch_bounds__(256) void decompress_f32_kernel(const MatDev* __res
 
     // A pass that writes an n x m array keeps its waves in step (a barrier that waits for no memory): neighbours write
     // the two parts of a line that rows off line boundaries leave between them, and the caches join parts that
-    // arrive together.  A pass that reads one too takes its last tile apart, without a next tile to fetch: 16 or 32 loads that
-    // would find nothing.  us without both / with, fp32 weights: 503 MiB of ragged rows, update at r = 8, 16, 32 247 / 233,
-    // 248 / 232, 275 / 249, decompression 195 / 169, 182 / 160, 185 / 173; GPT-2 base, update at r = 32 132 / 130; one 256 x 256
-    // at r = 8 3.4 / 3.2.
-    constexpr bool kMoves = Moves<MODE>::w || Moves<MODE>::v, kWrites = kMoves || MODE == kModeOut;
-    auto tile = [&](long long rb, auto more) {
-        constexpr bool kMore = decltype(more)::value;
-        if constexpr (kMore) {
-            load_state(a_nxt, rb + 32);
-            epilogue_fetch<MODE, OT, WP>(pre_nxt, M, rb + 32, row_end, j, jok);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        f32x16 acc;
+    // arrive together.  (A decompression into whole lines goes without, which short launches feel.)  A pass that reads
+    // one too takes its last tile apart, without a next tile to fetch: 16 or 32 loads that would find nothing.  us without
+    // both / with, fp32 weights: 503 MiB of ragged rows, update at r = 8, 16, 32 247 / 233, 248 / 232, 275 / 249,
+    // decompression 195 / 169, 182 / 160, 185 / 173; GPT-2 base, update at r = 32 132 / 130; one 256 x 256 at r = 8
+    // 3.4 / 3.2.
+    constexpr bool kMoves = Moves<MODE>::w || Moves<MODE>::v, kStep = kMoves || (MODE == kModeOut && (WP & kCut) != 0);
+    auto product = [&](f32x16& acc) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
         for (int s = 0; s < H; ++s)
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a_cur[s / 4][s % 4], breg[s], acc, 0, 0, 0);
-
-        epilogue_tile<MODE, OT, WP>(acc, pre_cur, M, it, p, rb, row_end, j, jok, ep, lds_red);
-        if constexpr (kMore) {
-#pragma unroll
-            for (int i = 0; i < H / 4; ++i) a_cur[i] = a_nxt[i];
-            pre_cur = pre_nxt;
-            if constexpr (kWrites) __builtin_amdgcn_s_barrier();
-        }
     };
     long long rb = it.row0;
+    for (; kMoves ? rb + 32 < row_end : rb < row_end; rb += 32) {
+        load_state(a_nxt, rb + 32);
+        epilogue_fetch<MODE, OT, WP>(pre_nxt, M, rb + 32, row_end, j, jok);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 acc;
+        product(acc);
+        epilogue_tile<MODE, OT, WP>(acc, pre_cur, M, it, p, rb, row_end, j, jok, ep, lds_red);
+#pragma unroll
+        for (int i = 0; i < H / 4; ++i) a_cur[i] = a_nxt[i];
+        pre_cur = pre_nxt;
+        if constexpr (kStep) __builtin_amdgcn_s_barrier();
+    }
     if constexpr (kMoves) {
-        for (; rb + 32 < row_end; rb += 32) tile(rb, std::true_type{});
-        tile(rb, std::false_type{});
-    } else {
-        for (; rb < row_end; rb += 32) tile(rb, std::true_type{});
+        f32x16 acc;
+        product(acc);
+        epilogue_tile<MODE, OT, WP>(acc, pre_cur, M, it, p, rb, row_end, j, jok, ep, lds_red);
     }
     epilogue_end<MODE>(M, it, j, jok, ep, lds_red);
 }
@@ -119,9 +117,11 @@ hipError_t launch_one(const MatDev* mats, const WorkItem* items, int nitems, con
     // one by one.  Three outputs in turn, us with all / four / three, r = 8 and 16: 125 MiB of ragged rows 39 / 34 / 30 and 39 / 34 / 29,
     // 251 MiB 85 / 66 / 55 and 84 / 62 / 59, 503 MiB 169 / 119 / 131 and 160 / 130 / 144; rows of 16-byte multiples, 305 MiB 99 / 71 / 68 and 95 /
     // 70 / 73; update, r = 8: 64 / 62 / 60, 121 / 118 / 113, 234 / 229 / 216, 142 / 141 / 136 (r = 16: 121 / 121 / 115).  At r = 32 registers leave no more
-    // than that; rows of whole lines want all of them (GPT-2 base decompressed at r = 8 55 / 64).
-    constexpr bool kFew = R <= 16 && sizeof(OT) == 4 && (MODE == kModeOut || MODE == kModeSgd);
-    const unsigned lds = kFew && p.cut ? 40000u : 0u;
+    // than that; rows of whole lines want all of them (GPT-2 base decompressed at r = 8 55 / 64).  Decompressions of fewer than
+    // four workgroups per compute unit, and those into bf16, do not drift and go without both (14 MiB at r = 32 8.1 / 8.3, 305 of bf16
+    // workgroups at r = 16 7.5 / 7.7).
+    const bool cut = p.cut && sizeof(OT) == 4 && (MODE == kModeSgd || (MODE == kModeOut && nitems >= 1024));
+    const unsigned lds = cut && R <= 16 ? 40000u : 0u;
 #define FLORA_DEC(WP) hipLaunchKernelGGL((decompress_f32_kernel<R, MODE, OT, WP>), grid, block, lds, s, mats, items, seeds, p)
     if constexpr (Moves<MODE>::w || Moves<MODE>::v) {
         switch (p.wpolicy & 3) {
@@ -131,8 +131,12 @@ hipError_t launch_one(const MatDev* mats, const WorkItem* items, int nitems, con
         default: FLORA_DEC(0); break;
         }
     } else if constexpr (MODE == kModeOut) {
-        if (p.wpolicy & 2) FLORA_DEC(2);
-        else FLORA_DEC(0);
+        switch ((p.wpolicy & 2) | (cut ? kCut : 0)) {
+        case kCut | 2: FLORA_DEC(sizeof(OT) == 4 ? kCut | 2 : 2); break;
+        case kCut: FLORA_DEC(sizeof(OT) == 4 ? kCut : 0); break;
+        case 2: FLORA_DEC(2); break;
+        default: FLORA_DEC(0); break;
+        }
     } else FLORA_DEC(0);
 #undef FLORA_DEC
     return hipGetLastError();

@@ -697,26 +697,31 @@ def test_written_tiles_at_small_ranks(r, n, m, rows):
         assert float((guard[:, 0] - 7).abs().max()) == 0 and float((guard[:, -1] - 7).abs().max()) == 0
 
 
-# plain updates of fp32 rows off line boundaries at r = 128 in launches on either side of 1024 workgroups (fewer of them per
-# compute unit from there on): the same bits for the same matrices
-def test_update_of_many_ragged_matrices():
-    r, n, m, count = 128, 40, 515, 208
+# fp32 rows off line boundaries in launches on either side of 1024 workgroups, from where on a decompression at ranks <= 32
+# keeps its waves in step and launches take fewer workgroups per compute unit (decompression at ranks <= 16, plain
+# updates at r = 128): the same bits for the same matrices
+@pytest.mark.parametrize("r", [8, 16, 32, 128])
+def test_many_ragged_matrices(r):
+    n, m, count = 40, 515, 208
     assert len(flora.debug_work_items(1, [(n, m)] * count, r)[0]) >= 1024 > len(flora.debug_work_items(1, [(n, m)] * 100, r)[0])
     S, W0 = rand((count, n, r), 7400), rand((count, n, m + 1), 7401)
     W0 = W0.view(count, -1)[:, :n * m].reshape(count, n, m)
-    outs = []
+    got = []
     for step in (count, 100):
-        W = [w.clone() for w in W0]
+        W, out = [w.clone() for w in W0], [torch.full((n, m), float("nan"), device=DEV) for _ in range(count)]
         for l in range(0, count, step):
             part = range(l, min(l + step, count))
-            flora.apply_update(flora.matrices([(n, m)] * len(part), weights=[W[i] for i in part], states=[S[i] for i in part],
-                                              seeds=[50 + i for i in part]), r, flora.F32, flora.sgd_update(0.5, 0.5))
+            mats = flora.matrices([(n, m)] * len(part), weights=[W[i] for i in part], states=[S[i] for i in part], seeds=[50 + i for i in part])
+            flora.apply_update(mats, r, flora.F32, flora.sgd_update(0.5, 0.5))
+            flora.decompress(mats, r, 0.5, [out[i] for i in part], flora.F32)
         sync()
-        outs.append(W)
-    assert all(torch.equal(x, y) for x, y in zip(*outs))
+        got.append(W + out)
+    assert all(torch.equal(x, y) for x, y in zip(*got))
     for i in (0, 101, count - 1):
-        Wr = oracle.sgd(to64(W0[i]), oracle.decompress(to64(S[i]), m, 50 + i, alpha=0.5), 0.5)
-        assert rel_fro(to64(outs[0][i]) - to64(W0[i]), Wr - to64(W0[i])) < update_bar(r, Wr, to64(W0[i]))
+        Gt = oracle.decompress(to64(S[i]), m, 50 + i, alpha=0.5)
+        assert rel_fro(to64(got[0][count + i]), Gt) < tol_for(r)
+        Wr = oracle.sgd(to64(W0[i]), Gt, 0.5)
+        assert rel_fro(to64(got[0][i]) - to64(W0[i]), Wr - to64(W0[i])) < update_bar(r, Wr, to64(W0[i]))
 
 
 # a decompression writes the same bits with and without the non-temporal hint, in every kernel: ranks <= 32, 4 and 16
