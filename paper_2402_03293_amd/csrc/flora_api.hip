@@ -1465,9 +1465,10 @@ static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, 
     // a caller that spreads one optimizer step over several calls says how large the whole set is
     const double mib = std::max(bytes / (1024.0 * 1024.0), (double)u->step_weight_mib);
     // Rows that do not end on lines: the hint makes two waves' parts of a line two passes over memory.  Sets with a tenth or more of
-    // such weights take plain accesses: 24 each of 1100 x 1003, 257 x 2051, 770 x 3001 and 2000 x 777 in fp32 (503 MiB), us streamed as below
-    // / plain at r = 16, 64, 256: plain update 491 / 248, 369 / 225, 448 / 275, unfactored 873 / 599, 723 / 567, 847 / 705; half
-    // of them 129 / 120, 118 / 108, 231 / 159, and 416 / 310, 353 / 296, 451 / 406; with rows of 16-byte multiples 445 / 244 at r = 16.
+    // such weights take plain accesses: 24 each of 1100 x 1003, 257 x 2051, 770 x 3001 and 2000 x 777 in fp32 (503 MiB), us streamed both ways
+    // / writes only / plain at r = 16, 64, 256: plain update 417 / 245 / 232, 372 / 233 / 223, 443 / 286 / 274, unfactored 909 / 634 / 563,
+    // 845 / 631 / 567, 946 / 744 / 703; half of them 207 / 127 / 121, 182 / 114 / 109, 231 / 163 / 157, and 460 / 328 / 295, 432 / 327 / 296,
+    // 504 / 422 / 405; rows of 16-byte multiples (458 MiB) 338 / 223 / 214 at r = 16.
     if (unfactored ? cut_rows(mats, count, [&](int l) { return whole_w(l) && whole_lines(mats[l].second_moment, mats[l].m, 4); })
                    : !wbf16 && c.cut)
         return c;
@@ -1487,10 +1488,11 @@ static CachePolicy choose_wpolicy(const flora_matrix_t* mats, int count, int r, 
         // streamed both ways).  The kernel for whole lines regenerates twice the entries of A per lane, so it wants
         // launches of many rounds; streamed it gains where rows end on line boundaries.  Update in us, that kernel / whole
         // lines plain / streamed, at r = 64, 128, 256 (MiB of weights):
-        //   GPT-2 base (162)             74 / 73 / 78        71 / 71 / 79        101 / 113 / 107
+        //   GPT-2 base (162)             70 / 76 / 82        71 / 74 / 81        104 / 113 / 111
         //   40 x 3 of ragged rows (300)  174 / 162 / 169     183 / 160 / 223     232 / 199 / 219
-        //   GPT-2 XL, 24 matrices (352)  183 / 174 / 171     186 / 166 / 158     234 / 210 / 199
-        //   all of it (2812)             1426 / 1393 / 1359  1361 / 1234 / 1170  1689 / 1513 / 1472
+        //   GPT-2 XL, 24 matrices (352)  181 / 182 / 170     189 / 169 / 162     239 / 213 / 202
+        //   all of it (2812)             1368 / 1369 / 1333  1355 / 1232 / 1174  1671 / 1506 / 1476
+        // (medians of 60 calls in a row; the first ten after a pause take up to 30 % more at r = 64 and 256)
         // and under the factored rule at r = 64 (sums included) 8 matrices of T5-3B (112) 98 / 95 / 98, GPT-2 base
         // 123 / 113 / 117, ragged rows 271 / 227 / 253, GPT-2 XL 1708 / 1430 / 1343; at higher ranks it gains nothing there.
         // Ranks <= 32 have the first kernel only.  Plain / streamed at r = 8, 16, 32: 24 matrices of GPT-2 XL 160 / 184,

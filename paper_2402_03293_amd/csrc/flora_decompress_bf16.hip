@@ -548,7 +548,8 @@ __global__ __launch_bounds__(512, (vec_waves<R, MODE, OT>())) void decompress_bf
 // compute unit, and one multiplies while another stores.  The products are taken on
 // v_mfma_f32_32x32x16_bf16 (lane = row of W, 16 registers = 32 of its columns).  What bounds the kernel above on bf16
 // weights is its own instructions and LDS passes per 32 rows, and half-line accesses that cannot be streamed: GPT-2 XL
-// update 1426 / 1361 / 1689 us at r = 64 / 128 / 256, so 1359 / 1170 / 1472 (5.9 GB of weights: 4.3 / 5.0 / 4.0 TB/s).
+// update 1368 / 1355 / 1671 us at r = 64 / 128 / 256, so 1333 / 1174 / 1476 (5.9 GB of weights: 4.4 / 5.0 / 4.0 TB/s; medians of 60
+// calls in a row).
 template <int R, int MODE, int WP>
 __global__ __launch_bounds__(256, R == 256 ? 2 : 3) void decompress_bf16_line_kernel(const MatDev* __restrict__ mats,
                                                                                      const WorkItem* __restrict__ items,
