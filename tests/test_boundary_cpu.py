@@ -204,6 +204,22 @@ def test_workspace_bytes_is_the_sum_of_the_fused_steps_plans(index, r):
                                                     + twork + 8 * image)
 
 
+# bf16 gradients at r = 32 may take other rows per workgroup than fp32 ones: the stated size covers either, sets of few rows and
+# of rows that are no whole number of 128 among them.
+@pytest.mark.parametrize("r", [16, 32])
+@pytest.mark.parametrize("shapes", [[(64, 2048)] * 300, [(64, 8192)] * 80, [(160, 8192)] * 40, [(320, 4096)] * 40, workloads.workload(5).shapes[:16],
+                                    workloads.workload(5).shapes[:96]])
+def test_workspace_bytes_cover_the_compress_plan_of_either_gradient_type(shapes, r):
+    comp = []
+    for gdt in (flora.F32, flora.BF16):
+        items, info = flora.debug_work_items(0, shapes, r, gdt)
+        work = _round256(4 * int(info[3])) + 4 * int(info[4])
+        comp.append(_round256(48 * len(items)) + _round256(work) + 8 * _round256(184 * len(shapes)))
+        assert flora.debug_plan_bytes(0, shapes, r, gdt) == comp[-1], gdt
+    others = flora.debug_plan_bytes(3, shapes, r) + flora.debug_plan_bytes(2, shapes, r)
+    assert flora.workspace_bytes(flora.matrices(shapes), r) == max(comp) + others
+
+
 def _adafactor_bytes_in_large_pieces(shapes, r, least_rows=256):
     """An Adafactor plan whose row blocks are of 256 rows at least (where that gives enough workgroups), with Gram
     sums in pieces of 3072 beside each other and the passes' partial sums of rows and columns.  least_rows 32: the

@@ -108,6 +108,30 @@ def test_same_bits_with_and_without_a_caller_owned_workspace(r, bf16, shapes):
     assert rel_fro(to64(got[len(shapes) + l]), Mr) < tol_for(r)
 
 
+# bf16 gradients at r = 32 in a set large enough for 128 rows per workgroup, whose partial products take more than the fp32
+# plan's: in exactly the stated workspace the factored rule's sums still come from the row blocks of library memory.
+def test_same_bits_in_the_stated_workspace_with_128_row_blocks():
+    shapes, r = [(320, 4096)] * 40, 32
+    count, gen = len(shapes), torch.Generator(device=DEV).manual_seed(32)
+    rnd = lambda shape: torch.randn(*shape, generator=gen, device=DEV)
+    G = [rnd(s).to(torch.bfloat16) for s in shapes]
+    first = dict(W=[rnd(s) for s in shapes], M=[rnd((n, r)) for n, _ in shapes], R=[rnd((n,)).abs() + 0.5 for n, _ in shapes],
+                 K=[rnd((m,)).abs() + 0.5 for _, m in shapes])
+    need = flora.workspace_bytes(flora.matrices(shapes), r)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    res = []
+    for buf in (None, ws):
+        flora.set_workspace(buf)
+        x = {k: [t.clone() for t in v] for k, v in first.items()}
+        mats = flora.matrices(shapes, grads=G, weights=x["W"], states=x["M"], row_stats=x["R"], col_stats=x["K"],
+                              seeds=list(range(count)), seeds_next=list(range(900, 900 + count)))
+        flora.fused_step(mats, r, flora.BF16, flora.F32, 0.9, 0.1, True, flora.factored_update(1e-2, 1.0, 0.9, 1e-30, 1.0))
+        torch.cuda.synchronize()
+        res.append(x)
+    for k in first:
+        assert all(torch.equal(a, b) for a, b in zip(res[0][k], res[1][k])), k
+
+
 def test_workspace_bytes_is_exact_and_too_small_changes_nothing():
     shapes, r = [(512, 2048), (300, 520)], 256
     x = _inputs(shapes, r, True, 7)
