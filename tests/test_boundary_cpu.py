@@ -220,6 +220,22 @@ def test_workspace_bytes_cover_the_compress_plan_of_either_gradient_type(shapes,
     assert flora.workspace_bytes(flora.matrices(shapes), r) == max(comp) + others
 
 
+# ... and 128 rows per workgroup only where few of them are beyond the matrices: partial products are whole blocks, and half
+# of a workgroup without rows is slower as well.
+def test_128_row_blocks_at_rank_32_hold_little_more_than_64():
+    t5s, gpt, xl = (workloads.workload(i).shapes for i in (2, 3, 5))
+    for shapes, mt in (([(64, 8192)] * 80, 1), ([(64, 2048)] * 300, 1), ([(160, 8192)] * 40, 1), ([(192, 4096)] * 60, 1), ([(64, 4096)] * 400, 1),
+                       ([(64, 8192)] * 60 + [(1024, 4096)], 1), ([(128, 8192)] * 80, 2), ([(320, 4096)] * 40, 2), (t5s, 2), (gpt, 2), (xl, 2), (xl[:16], 2)):
+        _, info = flora.debug_work_items(0, shapes, 32, flora.BF16)
+        assert int(info[0]) == mt, (shapes[0], len(shapes))
+        held = flora.debug_plan_bytes(0, shapes, 32, flora.BF16)
+        try:
+            flora.set_tuning("compress_f32_mt", 1)
+            assert held <= 1.2 * flora.debug_plan_bytes(0, shapes, 32, flora.BF16), (shapes[0], len(shapes))
+        finally:
+            flora.set_tuning("compress_f32_mt", 0)
+
+
 def _adafactor_bytes_in_large_pieces(shapes, r, least_rows=256):
     """An Adafactor plan whose row blocks are of 256 rows at least (where that gives enough workgroups), with Gram
     sums in pieces of 3072 beside each other and the passes' partial sums of rows and columns.  least_rows 32: the

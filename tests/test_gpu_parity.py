@@ -505,6 +505,22 @@ def test_compress_bf16_parts(n, m, count, r):
         assert rel_fro(to64(S[l]), ref) < 2.0 ** -24 * m ** 0.5 + 4e-7, l
 
 
+# ... with 128 rows per workgroup (r = 32): shared columns, and whole rows in one column group; the last block short.
+@pytest.mark.parametrize("n,m,count,kc", [(257, 2048, 80, 512), (65537, 80, 8, 0)])
+def test_compress_bf16_parts_of_128_rows(n, m, count, kc):
+    r = 32
+    _, info = flora.debug_work_items(0, [(n, m)] * count, r, flora.BF16)
+    assert (int(info[0]), int(info[2])) == (2, kc)
+    G = [rand((n, m), 140 + l).to(torch.bfloat16) for l in range(count)]
+    S0 = [rand((n, r), 190 + l) for l in range(count)]
+    S = [x.clone() for x in S0]
+    flora.compress(flora.matrices([(n, m)] * count, grads=G, states=S, seeds=list(range(count))), r, flora.BF16, 0.5, 2.0)
+    sync()
+    for l in (0, count - 1):
+        ref = oracle.compress(to64(G[l]), r, l, state=to64(S0[l]), a=0.5, b=2.0)
+        assert rel_fro(to64(S[l]), ref) < 2.0 ** -24 * m ** 0.5 + 4e-7, l
+
+
 # ... infinities keep the sign of the entry of A that they meet, NaNs and opposite infinities are NaNs, other rows are those of
 # the finite gradient.
 @pytest.mark.parametrize("r,m", [(8, 64), (16, 1024), (32, 640)])
