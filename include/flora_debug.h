@@ -15,8 +15,8 @@ extern "C" {
 #endif
 
 /* Test hook, host only (touches no GPU): the table of workgroups the library would launch for
- * this set of shapes.  kind 0: flora_compress, 1: flora_decompress and the update passes,
- * 2: the state <- state T pass of the transfer, 3: its T = A^T A' pass (ranks 64 and above; a
+ * this set of shapes.  kind 0: flora_compress, 1: flora_decompress and the update passes (grad_dtype: the
+ * type of the n x m rows), 5: the plain update, 2: the state <- state T pass of the transfer, 3: its T = A^T A' pass (ranks 64 and above; a
  * launch takes columns [first column, end column) of chunk `part` from the first entry of each chunk and
  * decides itself which blocks of T a workgroup makes; `rank slice` counts slabs of 128 rows of T), 4: flora_compress_mapped with a map other than the identity.  Returns the number of workgroups (or a
  * negative flora_status_t) and writes up to `cap` of them to `out`, 12 int64 each:

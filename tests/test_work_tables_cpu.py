@@ -70,8 +70,8 @@ def check_compress(shapes, r, gdt):
     return items, info
 
 
-def check_decompress(shapes, r):
-    items, info = flora.debug_work_items(1, shapes, r)
+def check_decompress(shapes, r, dtype=flora.F32, kind=1):
+    items, info = flora.debug_work_items(kind, shapes, r, dtype)
     vec = int(info[1])
     cols = 256 if vec else 128
     c = COLS
@@ -133,6 +133,16 @@ def test_decompress_tables_cover_every_element_once(shapes, r):
                                       ([(33, 252)] * 3, 256), ([(100, 256)] * 300, 128), ([(2304, 1024)] * 40, 64)])
 def test_decompress_tables_by_rounds(shapes, r):
     check_decompress(shapes, r)
+
+
+def test_bf16_rows_at_rank_64_take_128_rows_in_large_launches():
+    """bf16 outputs and weights alike; fp32 ones 64."""
+    gpt, xl = (workloads.workload(i).shapes for i in (3, 5))
+    for shapes in (gpt, gpt * 2, xl[:48], xl, [(1100, 1003)] * 100, [(2304, 1024)] * 40):
+        for kind in (1, 5):
+            for dtype, rows in ((flora.F32, 64), (flora.BF16, 128)):
+                items, _ = check_decompress(shapes, 64, dtype, kind)
+                assert max(it[COLS["rows"]] for it in items) == rows, (shapes[0], len(shapes), kind, dtype)
 
 
 @settings(max_examples=30, deadline=None)
