@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
     // last tile) or belongs to a round past the end (prefetch) is pointed out of range and
     // comes back as zeros.  Matrices with unaligned rows take the plain guarded loop below.
     constexpr int ESZ = (int)sizeof(GT);
-    const int fast_rounds = vec_ok && !parts_ok ? iters : 0;
+    int fast_rounds = vec_ok && !parts_ok ? iters : 0;
     rsrc_t rs[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
@@ -266,36 +266,6 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
         }
     };
 
-    // G tiles are fetched kPF - 1 rounds ahead of their use: a wave's progress is then bound
-    // by the matrix cores and the generator, not by one HBM round trip per tile.  The
-    // prefetch is unconditional (out-of-range rounds read zeros for free), which lets the
-    // compiler wait only for the stage it is about to consume.
-    if (fast_rounds > 0) {
-        v4f st[kPF][MT][4];
-#pragma unroll
-        for (int u = 0; u < kPF - 1; ++u) load_tile_fast(st[u], u);
-        gen_tile(0, 0);
-        __syncthreads();
-        // The body is free of branches around memory operations (a round past the end loads
-        // nothing, multiplies zeros and skips only the generator): the compiler can then
-        // follow the outstanding loads around the loop and waits for the oldest stage alone.
-        // The round after a single one takes the one buffer that was generated: what LDS held before may be
-        // NaN, which zeros do not undo.  (Zeros stored in the other buffer instead, 256 x 256 at r = 8: 5.0 us
-        // a launch as here, 5.3.)
-        const int second = fast_rounds > 1 ? 1 : 0;
-        for (int base = 0; base < fast_rounds; base += kPF) {
-#pragma unroll
-            for (int u = 0; u < kPF; ++u) {
-                const int i = base + u;
-                const int buf = i & 1;
-                load_tile_fast(st[(u + kPF - 1) % kPF], i + kPF - 1);
-                if (i + 1 < fast_rounds) gen_tile(buf ^ 1, i + 1);
-                mfma_tile(st[u], buf & second, true);
-                __syncthreads();
-            }
-        }
-    }
-    int slow_from = fast_rounds;
     // bf16 gradients are exact operands of the bf16 matrix cores and A is the exact sum of three bf16 values (8 significand
     // bits each): three v_mfma_f32_16x16x32_bf16 per 32 columns make the fp32 product that takes eight
     // v_mfma_f32_16x16x4_f32, in a sixth of their time, and round it less often: error against 64 bits at 48 / 520 / 2048 /
@@ -305,8 +275,8 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
     // [part][k][column].  us fp32 / so at r = 8, 16, 32: T5-small 36 / 19, 37 / 20, 48 / 27, GPT-2 base 72 / 38, 74 / 38, 86 / 47,
     // GPT-2 XL 1017 / 476 (6.2 TB/s), 1010 / 507, 1180 / 579, one 1600 x 6400 matrix 17.7 / 12.5, 17.4 / 12.0, 22.8 / 17.2.
     // An infinity in G times the parts of an entry, which may have either sign, would add up to a NaN: where
-    // a sum comes out as not finite (it then has met one, or overflowed) the workgroup starts again below with
-    // fp32 products.
+    // a sum comes out as not finite (it then has met one, or overflowed) the workgroup starts again with the fp32
+    // products below (with one in every workgroup GPT-2 base at r = 8 / 16 / 32 71 / 70 / 92 us, T5-small 46 / 46 / 70).
     if constexpr (kParts) if (parts_ok) {
         typedef uint16_t (*lds_parts_t)[3][RP][kLdp];
         lds_parts_t ldsP = reinterpret_cast<lds_parts_t>(lds_raw) + 2 * kg;
@@ -396,9 +366,8 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) odd = odd || !__builtin_isfinite(acc[mt][nt][v] + acc2[mt][nt][v]);
-        slow_from = iters;
         if (__syncthreads_or(odd)) {
-            slow_from = 0;
+            fast_rounds = iters;
             clear_padding();
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
@@ -406,7 +375,36 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
                 for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = acc2[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
     }
-    for (int i = slow_from; i < iters; ++i) {
+    // G tiles are fetched kPF - 1 rounds ahead of their use: a wave's progress is then bound
+    // by the matrix cores and the generator, not by one HBM round trip per tile.  The
+    // prefetch is unconditional (out-of-range rounds read zeros for free), which lets the
+    // compiler wait only for the stage it is about to consume.
+    if (fast_rounds > 0) {
+        v4f st[kPF][MT][4];
+#pragma unroll
+        for (int u = 0; u < kPF - 1; ++u) load_tile_fast(st[u], u);
+        gen_tile(0, 0);
+        __syncthreads();
+        // The body is free of branches around memory operations (a round past the end loads
+        // nothing, multiplies zeros and skips only the generator): the compiler can then
+        // follow the outstanding loads around the loop and waits for the oldest stage alone.
+        // The round after a single one takes the one buffer that was generated: what LDS held before may be
+        // NaN, which zeros do not undo.  (Zeros stored in the other buffer instead, 256 x 256 at r = 8: 5.0 us
+        // a launch as here, 5.3.)
+        const int second = fast_rounds > 1 ? 1 : 0;
+        for (int base = 0; base < fast_rounds; base += kPF) {
+#pragma unroll
+            for (int u = 0; u < kPF; ++u) {
+                const int i = base + u;
+                const int buf = i & 1;
+                load_tile_fast(st[(u + kPF - 1) % kPF], i + kPF - 1);
+                if (i + 1 < fast_rounds) gen_tile(buf ^ 1, i + 1);
+                mfma_tile(st[u], buf & second, true);
+                __syncthreads();
+            }
+        }
+    }
+    for (int i = vec_ok ? iters : 0; i < iters; ++i) {
         const int tile = kg + KG * i;
         const bool active = tile < ntiles;
         v4f gt[MT][4];

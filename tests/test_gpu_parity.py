@@ -514,9 +514,13 @@ def test_compress_bf16_parts_of_128_rows(n, m, count, kc):
     G = [rand((n, m), 140 + l).to(torch.bfloat16) for l in range(count)]
     S0 = [rand((n, r), 190 + l) for l in range(count)]
     S = [x.clone() for x in S0]
+    G[1][n - 1, m - 1] = float("inf")            # (its workgroup takes fp32 products)
     flora.compress(flora.matrices([(n, m)] * count, grads=G, states=S, seeds=list(range(count))), r, flora.BF16, 0.5, 2.0)
     sync()
-    for l in (0, count - 1):
+    assert np.array_equal(to64(S[1][n - 1]), np.sign(oracle.compress(np.eye(m), r, 1)[m - 1]) * np.inf)
+    G[1][n - 1] = 0
+    S[1][n - 1] = 0.5 * S0[1][n - 1]
+    for l in (0, 1, count - 1):
         ref = oracle.compress(to64(G[l]), r, l, state=to64(S0[l]), a=0.5, b=2.0)
         assert rel_fro(to64(S[l]), ref) < 2.0 ** -24 * m ** 0.5 + 4e-7, l
 
