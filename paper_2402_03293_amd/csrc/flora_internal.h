@@ -238,6 +238,7 @@ hipError_t launch_decompress_f32(const MatDev* mats, const WorkItem* items, int 
                                  int r, int mode, int out_is_bf16, DecompressParams p, hipStream_t s);
 hipError_t launch_decompress_bf16(const MatDev* mats, const WorkItem* items, int nitems, const SeedArgs& seeds,
                                   int r, int mode, int out_is_bf16, int vec, DecompressParams p, hipStream_t s);
+// halves: 0, or the columns of the narrowest matrix where the state times T takes products of two parts
 hipError_t launch_transfer_T(const MatDev* mats, const WorkItem* items, int nitems, int count, int r, int halves, hipStream_t s);
 hipError_t launch_apply_T(const MatDev* mats, const WorkItem* items, int nitems, int r, int halves, float ca, float cb,
                           hipStream_t s);
@@ -261,7 +262,7 @@ constexpr int kDecompressRows = 256;     // rows per workgroup, both decompress 
 constexpr int kApplyTRows = 32;          // rows per workgroup, state <- state T, ranks below 64
 constexpr int kApplyTRowsBig = 64;       // ... ranks 64 and above
 constexpr int kTransferChunk = 1024;     // columns per workgroup of the T kernel, ranks 64 and above
-// Columns from which the transfer takes two-part products (flora_transfer.hip)
+// Columns from which the state times T takes two-part products (flora_transfer.hip)
 constexpr int halves_cols(int r) { return r == 64 ? 2048 : 1024; }
 constexpr int kSumsqBlocks = 256;        // workgroups per matrix, sum of W^2
 constexpr int kGramChunk = 3072;         // long-index entries per workgroup of the Gram sums, at most

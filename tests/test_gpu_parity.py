@@ -712,6 +712,30 @@ def test_transfer_two_part_products(n, m, r, count):
         assert (np.abs(to64(dst[l]) - sums) <= 2.0 ** -23 * (np.abs(to64(D0[l])) + np.abs(ref)) + 8 * bar * norms.reshape(-1, 1)).all(), l
 
 
+# ... wider, and at the widths from which T's own sums take two parts in launches of few chunks (2048 and 2304 columns).
+@pytest.mark.parametrize("n,m,r,count", [(40, 2303, 128, 1), (40, 2304, 128, 1), (70, 2048, 128, 12), (33, 5000, 64, 2), (64, 8192, 256, 1), (35, 20011, 64, 1), (9, 70000, 128, 1)])
+def test_transfer_two_part_products_of_wide_matrices(n, m, r, count):
+    test_transfer_two_part_products(n, m, r, count)
+
+
+# T as a unit state gets it in a launch of few chunks: no further off than sums of three-part products are (1.09, 1.23 and 1.33e-7
+# measured with three parts throughout) and T's second part ends (4.1e-8 in the root mean square), and a twentieth.
+@pytest.mark.parametrize("m,three", [(1024, 1.09e-7), (1600, 1.23e-7), (2048, 1.33e-7)])
+@pytest.mark.parametrize("r", [128, 256])
+def test_transfer_of_a_unit_state_in_short_launches(r, m, three):
+    err = size = 0.0
+    for k in range(4):
+        A = [torch.empty(m, r, device=DEV) for _ in range(2)]
+        for a, seed in zip(A, (77 + k, 1077 + k)):
+            flora.debug_generate(seed, m, r, a)
+        S = torch.eye(r, device=DEV)
+        flora.momentum_transfer(flora.matrices([(r, m)], states=[S], seeds=[77 + k], seeds_next=[1077 + k]), r)
+        sync()
+        T = to64(A[0]).T @ to64(A[1])
+        err, size = err + np.sum((to64(S) - T) ** 2), size + np.sum(T ** 2)
+    assert (err / size) ** 0.5 < 1.05 * (three ** 2 + 4.1e-8 ** 2) ** 0.5
+
+
 # ... and states that are not finite there, as above.
 @pytest.mark.parametrize("r,m", [(64, 2050), (128, 1030), (256, 1030)])
 def test_transfer_two_part_products_of_states_that_are_not_finite(r, m):
