@@ -121,6 +121,15 @@ def test_bf16_compress_tables_of_finer_pieces(shapes, r):
     check_compress(shapes, r, flora.F32)
 
 
+# ... are tried with every number of rows, whatever was the last to be tried with another (us with what was chosen else: 147 / 110,
+# 271 / 195, 123 / 82), and at r = 256 fewer rows of fp32 gradients only where they are ahead by a margin (55 / 41).
+@pytest.mark.parametrize("shapes,r,mt,shared", [([(1664, 1600)] * 47 + [(64, 6976)] * 26, 64, 32, True), ([(980, 67)] * 3 + [(5305, 2145)] * 12 + [(2186, 7856)] * 2, 64, 32, True),
+                                                ([(64, 1792)] * 115 + [(64, 4672)] * 75, 128, 32, True), ([(4488, 5584)], 256, 16, True)])
+def test_finer_pieces_with_every_number_of_rows(shapes, r, mt, shared):
+    _, info = check_compress(shapes, r, flora.F32)
+    assert int(info[0]) == mt and (int(info[3]) > 0) == shared
+
+
 @settings(max_examples=60, deadline=None)
 @given(st.one_of(shape_lists, aligned_shape_lists), st.sampled_from(RANKS))
 def test_decompress_tables_cover_every_element_once(shapes, r):
