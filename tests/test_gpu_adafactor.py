@@ -121,6 +121,40 @@ def test_unfactored_first_step_is_sign_descent_on_the_gpu():
     assert np.array_equal(np.sign(d)[big], -np.sign(Gt)[big])
 
 
+# ------------------------------------------------------- the reduction passes by products of bf16 parts (r = 16)
+# State entries beyond the largest bf16 value have no parts, and tiles with one are multiplied in fp32: statistics and
+# weights come out as of any other state (alpha brings the product back), and an infinity's row and the columns' sums are infinite.
+# No clipping: its sum takes alpha^2, which is below fp32's range here.
+@pytest.mark.parametrize("n,m", [(1, 5), (70, 129), (33, 300)])
+@pytest.mark.parametrize("r", [16, 32])
+def test_factored_passes_of_states_beyond_bf16(n, m, r):
+    seed, alpha, big = 77, 2e-38, sorted({0, n // 2, n - 1})
+    A = oracle.materialise_A(seed, m, r)
+    cols = [int(k) for k in np.argsort(np.abs(A).max(axis=0))[:len(big)]]
+    S = rand((n, r), 5, scale=2e37)
+    for i, k in zip(big, cols):
+        assert np.abs(A[:, k]).max() < 1.0                   # (or the product itself overflows)
+        S[i] = 0
+        S[i, k] = 3.4e38 * (-1) ** i
+    W0, R0, K0 = rand((n, m), 6), rand((n,), 7).abs() + 0.5, rand((m,), 8).abs() + 0.5
+    W, R, K = W0.clone(), R0.clone(), K0.clone()
+    mats = flora.matrices([(n, m)], weights=[W], states=[S], row_stats=[R], col_stats=[K], seeds=[seed])
+    flora.apply_update(mats, r, flora.F32, flora.factored_update(1e-2, alpha, 0.5, 1e-30, 0.0))
+    sync()
+    Wr, Rr, Kr = oracle.factored_update(to64(W0), oracle.decompress(to64(S), m, seed, alpha=alpha), to64(R0), to64(K0), 0.5, 1e-30, 0.0, 1e-2)
+    assert rel_fro(to64(R), Rr) < TOL_F32 and rel_fro(to64(K), Kr) < TOL_F32
+    assert rel_fro(to64(W) - to64(W0), Wr - to64(W0)) < update_bar(r, Wr, to64(W0))
+    # an infinity
+    S[big[-1], cols[-1]] = float("inf")
+    R, K = R0.clone(), K0.clone()
+    mats = flora.matrices([(n, m)], weights=[W.clone()], states=[S], row_stats=[R], col_stats=[K], seeds=[seed])
+    flora.apply_update(mats, r, flora.F32, flora.factored_update(1e-2, alpha, 0.5, 1e-30, 0.0))
+    sync()
+    assert np.isposinf(to64(R)[big[-1]]) and np.isposinf(to64(K)).all()
+    rest = [i for i in range(n) if i != big[-1]]
+    assert rel_fro(to64(R)[rest], Rr[rest]) < TOL_F32
+
+
 # ------------------------------------------------ several steps with the carried scale
 @pytest.mark.parametrize("r,rule", [(16, "factored"), (64, "factored"), (256, "unfactored"), (32, "unfactored")])
 def test_adafactor_steps_with_schedules_and_carried_parameter_scale(r, rule):

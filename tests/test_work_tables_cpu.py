@@ -107,6 +107,14 @@ def test_fp32_compress_tables_cover_every_element_once(shapes, r, gdt):
     check_compress(shapes, r, gdt)
 
 
+# 128 rows per workgroup (bf16 at r = 32): the last block short or a single row, pieces and whole rows.
+@pytest.mark.parametrize("shapes,kc", [([(257, 2048)] * 80, 512), ([(320, 4096)] * 40, 512), ([(65537, 80)] * 8, 0), ([(1281, 1024)] * 30, 1024), (workloads.workload(2).shapes, 1024),
+                                       (workloads.workload(5).shapes, 0)])
+def test_bf16_compress_tables_of_128_rows(shapes, kc):
+    _, info = check_compress(shapes, 32, flora.BF16)
+    assert (int(info[0]), int(info[2])) == (2, kc)
+
+
 @settings(max_examples=60, deadline=None)
 @given(st.one_of(shape_lists, aligned_shape_lists), st.sampled_from([64, 128, 256]))
 def test_bf16_compress_tables_cover_every_element_once(shapes, r):
