@@ -81,7 +81,9 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
     constexpr int RP = NT * 16;
     constexpr int ROWS = 64 * MT;       // rows per workgroup
     // bf16 gradients as they are: three bf16 parts of A on the bf16 matrix cores (see below); squared ones, and rows on
-    // no 8-byte boundary, take the fp32 instruction
+    // no 16-byte boundary, take the fp32 instruction.  (The latter in this kernel too, with the registers and LDS of the parts: 5 waves per SIMD
+    // at r = 16 where 7 would do.  36 timings of sets of such rows, over those of a kernel without parts: 0.88 to 1.06, 1.00 in the mean; sets
+    // in which half or more take parts 0.80 to 1.01.)
     constexpr bool kParts = sizeof(GT) == 2 && MAP == 0;
     constexpr int kF32Bytes = KG * 2 * RP * kLda * 4, kPartsBytes = kParts ? KG * 2 * 3 * RP * kLdp * 2 : 0;
     __shared__ __attribute__((aligned(16))) unsigned char lds_raw[kPartsBytes > kF32Bytes ? kPartsBytes : kF32Bytes];
@@ -268,8 +270,9 @@ __global__ __launch_bounds__(256 * KG) void compress_f32_kernel(const MatDev* __
 
     // bf16 gradients are exact operands of the bf16 matrix cores and A is the exact sum of three bf16 values (8 significand
     // bits each): three v_mfma_f32_16x16x32_bf16 per 32 columns make the fp32 product that takes eight
-    // v_mfma_f32_16x16x4_f32, in a sixth of their time, and round it less often: error against 64 bits at 48 / 520 / 2048 /
-    // 8192 columns 5 / 8 / 10 / 15e-8 (fp32 instructions 10 / 13 / 16 / 18e-8).  The matrix cores and the generator share the
+    // v_mfma_f32_16x16x4_f32, in a sixth of their time, and round it less often: error against 64 bits of one matrix of 48 / 520 / 2048 /
+    // 8192 columns, swept in pieces of 256 or 512, 5 / 8 / 10 / 15e-8 (fp32 instructions 10 / 13 / 16 / 18e-8), of whole rows of 6400 columns at
+    // r = 32 6.2e-7 (7.1e-7).  The matrix cores and the generator share the
     // SIMD, so that time was the launch's.  A tile of 64 columns is fetched 8 rows x 128 bytes per instruction (8 bytes per lane
     // before) and put into operand order with the swap described above; its parts of A lie in LDS as
     // [part][k][column].  us fp32 / so at r = 8, 16, 32: T5-small 36 / 19, 37 / 20, 48 / 27, GPT-2 base 72 / 38, 74 / 38, 86 / 47,
