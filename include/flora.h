@@ -263,7 +263,7 @@ void flora_derive_seeds(uint64_t global_seed, uint64_t first_matrix_id, int coun
  * transfer and an Adafactor rule (its transfer, compress and update plans are resident together).
  * Exact, not a bound: with one 256-byte unit less that call returns FLORA_ERR_INVALID, unless its
  * launches have shapes that hold less (as with fp32 gradients, and rows of G that do not start on
- * 16-byte boundaries, at ranks >= 64): then the call takes those, which are slower and add their
+ * 16-byte boundaries, at ranks >= 64, or large sets of bf16 gradients at r = 32): then the call takes those, which are slower and add their
  * sums in another order.  Only n and m of the descriptors are read.  Host only.  0 for an invalid
  * set or rank.
  *
